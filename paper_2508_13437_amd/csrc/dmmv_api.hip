@@ -568,7 +568,11 @@ static dmmv_status residual_any(Ctx* c) {
         case KIND_CSC: DMMV_TRY(csc_residual(c)); break;
         default:
             if (c->o.residual_mfma) DMMV_TRY(batched_mfma_residual(c));
-            else DMMV_TRY(batched_residual(c));
+            else if (batched_chain_applicable(c)) {
+                DMMV_TRY(batched_chain_residual(c));
+                c->r_valid = true;
+                return DMMV_OK;
+            } else DMMV_TRY(batched_residual(c));
             break;
     }
     DMMV_TRY(refresh_t(c));
