@@ -88,12 +88,14 @@ __global__ void k_alns_begin(AlnsState* S, int64_t R, uint64_t seed, int32_t it)
 }
 
 // Inclusive prefix sums of the weights (one workgroup per instance); only for worst-remove.
+// raw_shift >= 0: what is stored are the sums of the impact terms, a weight is 1 + (sum >> raw_shift).
 // The weights are integers, so the sums are the same in any order: a thread sums SC_E
 // consecutive weights in registers, the wavefronts scan the threads' totals, and the total of a
 // tile of 1024 * SC_E weights is carried into the next.
 constexpr int SC_E = 8;
 __global__ __launch_bounds__(1024) void k_alns_scan(int64_t n, const uint64_t* __restrict__ weight_all,
-                                                    uint64_t* __restrict__ prefix_all, const AlnsState* S) {
+                                                    uint64_t* __restrict__ prefix_all, const AlnsState* S,
+                                                    int32_t raw_shift) {
     __shared__ uint64_t sh_w[16];
     const int64_t q = blockIdx.x;
     if (S[q].d_op != 1) return;
@@ -107,7 +109,10 @@ __global__ __launch_bounds__(1024) void k_alns_scan(int64_t n, const uint64_t* _
 #pragma unroll
         for (int u = 0; u < SC_E; ++u) v[u] = weight[j0 + u < n ? j0 + u : n - 1];   // clamped: the loads go out together
 #pragma unroll
-        for (int u = 0; u < SC_E; ++u) v[u] = j0 + u < n ? v[u] : 0;
+        for (int u = 0; u < SC_E; ++u) {
+            if (raw_shift >= 0) v[u] = 1 + (v[u] >> raw_shift);
+            v[u] = j0 + u < n ? v[u] : 0;
+        }
 #pragma unroll
         for (int u = 1; u < SC_E; ++u) v[u] += v[u - 1];
         const uint64_t tot = v[SC_E - 1];
@@ -314,133 +319,230 @@ __global__ __launch_bounds__(1024) void k_alns_worst_list(int64_t R, const AlnsS
     if (threadIdx.x == 0) flags[FLAG_WORST] = sh_base;
 }
 
-// batched: lane = listed instance (X through the scalar unit); grid.x = group of 64 of them
-// instances, each of the 4 wavefronts takes the variables blockIdx.y*4 + w, +4*gridDim.y, ...
+// batched: impact weights of the listed instances, sum over the rows of the fixed-point terms.
 //
-// Only a few per cent of the terms are not cut off by the shortcut of alns_impact_term (slack >
-// a * 18 / alpha: the term truncates to 0), but they are scattered: almost every group of 64
-// lanes holds one, so testing inside the loop would send every wavefront through the
-// double-precision division and exponential for the sake of a lane or two.  The loop therefore
-// only TESTS (one comparison in the working precision, with a margin of 1 %) and appends the
-// terms that may count to a queue of
-// the wavefront in LDS; whenever 64 are waiting, every lane computes one of them, for whichever
-// instance it belongs to, and adds the integer to that instance's sum with an LDS atomic.  The
-// sum is one of integers, so the order does not matter and the weights are the same bit for bit.
-// A wavefront goes over the rows once for eight consecutive variables, so that an instance's
-// residual (the only per-lane operand) is read once for all eight.
-constexpr int IMQ_CAP = 128;                   // ring of waiting terms per wavefront (drained at 64)
-constexpr int IMQ_ROWS = 1;                    // rows whose operands are fetched before they are tested (more rows in
-                                               //   flight only make the unrolled loop longer: 14.9 ms with 4, 13.1 with 1)
-constexpr int IMQ_VARS = 8;                    // consecutive variables a wavefront works on per pass over the rows
-                                               //   (r is read once for all of them)
+// Only a few per cent of the terms reach 1; the rest truncate to 0.  A term sk e^(-alpha slack / a)
+// scale (sk = |r_i|, slack = t - sk, a = |sc x|) reaches 1 exactly when alpha slack / a <= ln(sk scale),
+// i.e. when |x| is at least a limit that depends on the row and the instance alone.  The limits are
+// written first (k_alns_impact_limits, lowered by 1 % so that the roundings on both sides are covered: a term the
+// test drops is 0, the reverse need not hold), then a term costs one comparison.
+//
+// k_alns_impact_batched: lane = variable, so a row of X is one coalesced load that IM_Q instances share
+// (with lane = instance and X through the scalar unit a small batch left most of the chip idle:
+// 1.56 ms for the 11 listed of 20 instances of 2048 x 768, and 5.0 ms for 512 of 2048 x 4096; now 0.06 and
+// 2.2 ms).  A wavefront takes 64 variables x IM_Q instances x IM_ROWS rows at a time: the tests leave one bit
+// per row in a mask (two instructions a term), the set bits are then popped into a queue in LDS,
+// and whenever 64 are waiting every lane evaluates one, for whichever variable and instance it belongs
+// to, and adds the integer to that sum with an LDS atomic.  Bound by instruction issue (vector unit busy 65 %, about
+// 1100 vector instructions per 64 x 4 x 32 terms, a third of them the evaluations).  The sums are integers, so neither their
+// order nor the split of the rows over workgroups (small batches) changes a weight.
+constexpr int IM_Q = 4;                        // instances that share a row of X
+constexpr int IM_ROWS = 32;                    // rows per pass: one mask bit each
+constexpr int IM_STAGE = IM_ROWS * IM_Q / 64;  // (row, instance) pairs a lane stages per pass
+constexpr int IM_CAP = 128;                    // ring of waiting terms per wavefront (drained at 64)
+constexpr int IM_FEW = 4;                      // a variable with more terms than this in a pass is queued by rows
+
+// mask = 2 mask + (|x| >= lim): the comparison's bit enters as the carry of one addition
+__device__ __forceinline__ uint32_t impact_test(uint32_t mask, float x, float lim) {
+    asm("v_cmp_ge_f32 vcc, abs(%1), %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(mask) : "v"(x), "v"(lim) : "vcc");
+    return mask;
+}
+__device__ __forceinline__ uint32_t impact_test(uint32_t mask, double x, double lim) {
+    asm("v_cmp_ge_f64 vcc, abs(%1), %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(mask) : "v"(x), "v"(lim) : "vcc");
+    return mask;
+}
 
 template <class T>
 struct ImpactShared {
-    T qx[4][IMQ_CAP], qr[4][IMQ_CAP];          // waiting terms: matrix entry, residual of the row,
-    uint16_t qmeta[4][IMQ_CAP];                //   the lane (instance) they belong to, and in the
-                                               //   high byte which of the pass's variables
-    unsigned long long sum[4][IMQ_VARS][64];
-    double sc[4][64], t[4][64], scale[4][64];  // per instance: scale factor, error, fixed-point scale
+    T r[4][IM_ROWS][IM_Q], lim[4][IM_ROWS][IM_Q];
+    unsigned long long sum[4][IM_Q][64];
+    uint16_t queue[4][IM_CAP];                 // lane | instance << 6 | row << 8
+    double sc[IM_Q], t[IM_Q], scale[IM_Q];     // per instance: scale factor, error, fixed-point scale
+    double exp2m[16];                          // 2^(-f/16)
 };
+
+// lim[i][slot], smallest |x| whose term may reach 1 in row i of the slot's instance; clears the sums
+template <class T>
+__global__ __launch_bounds__(256) void k_alns_impact_limits(int64_t m, int64_t n, int64_t R, const T* __restrict__ scale_q,
+                                                            const T* __restrict__ r, const InstState<T>* st, double alpha,
+                                                            T* __restrict__ lim, uint64_t* __restrict__ weight,
+                                                            const int32_t* __restrict__ list,
+                                                            const int32_t* __restrict__ flags) {
+    const int64_t count = flags[FLAG_WORST];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t slot = blockIdx.x * 64ll + lane;
+    if (blockIdx.x * 64ll >= count) return;
+    const int64_t q = list[slot < count ? slot : count - 1];
+    const double t = (double)st[q].t, sc = (double)scale_q[q], scale = alns_impact_scale(t);
+    for (int64_t i = blockIdx.y * 4ll + w; i < m; i += 4ll * gridDim.y) {
+        const double sk = __builtin_fabs((double)r[i * R + q]), v = sk * scale;
+        double l = (double)Limits<T>::inf();
+        if (slot < count && v >= 0.999) l = (t - sk) * alpha / (sc * ((log(v) + 0.01) * 1.01));
+        if (slot < count) lim[i * R + slot] = (T)l;
+    }
+    for (int64_t s = blockIdx.x * 64ll + w; s < count && s < (blockIdx.x + 1) * 64ll; s += 4) {
+        uint64_t* __restrict__ out = weight + (int64_t)list[s] * n;
+        for (int64_t j = blockIdx.y * 64ll + lane; j < n; j += 64ll * gridDim.y) out[j] = 0;
+    }
+}
+
+// The fixed-point term by a shorter route: reciprocal with one Newton step instead of a division, e^-y from
+// 2^(-f/16) and a polynomial of degree 6.  Its relative error stays below 2^-40 (reciprocal 2^-46, times
+// y < 20; polynomial 2^-50), the term is below 2^24, so the integer part is that of alns_impact_term unless the
+// fraction is within 2^-15 of an integer; those (and everything out of the ordinary) take alns_impact_term.
+__device__ __forceinline__ uint32_t alns_impact_term_fast(double a, double sk, double t, double alpha, double scale,
+                                                          const double* exp2m) {
+    const double slack = t - sk;
+    double rc = __builtin_amdgcn_rcp(a);
+    rc = __builtin_fma(rc, __builtin_fma(-a, rc, 1.0), rc);
+    const double y = alpha * (slack * rc);
+    const bool usual = y < 20.0;                            // false for NaN
+    const double kf = __builtin_rint((usual ? y : 0.0) * 0x1.71547652b82fep+4);   // 16 log2 e
+    const double z = __builtin_fma(kf, 0x1.62e42fefa39efp-5, -y);                  // ln 2 / 16: |z| < 0.022
+    double p = __builtin_fma(z, 1.0 / 720.0, 1.0 / 120.0);
+    p = __builtin_fma(p, z, 1.0 / 24.0);
+    p = __builtin_fma(p, z, 1.0 / 6.0);
+    p = __builtin_fma(p, z, 0.5);
+    p = __builtin_fma(p, z, 1.0);
+    p = __builtin_fma(p, z, 1.0);
+    const int k = (int)kf;
+    const double g = __builtin_ldexp((sk * scale) * (p * exp2m[k & 15]), -(k >> 4));
+    const double whole = __builtin_floor(g), frac = g - whole;
+    if (!(usual && frac > 0x1p-15 && frac < 1.0 - 0x1p-15)) return (uint32_t)alns_impact_term(a, sk, t, alpha, scale);
+    return (uint32_t)whole;
+}
 
 template <class T>
 __global__ __launch_bounds__(256) void k_alns_impact_batched(int64_t m, int64_t n, int64_t R,
                                                              const T* __restrict__ Xt,
                                                              const T* __restrict__ scale_q,
-                                                             const T* __restrict__ r,
+                                                             const T* __restrict__ r, const T* __restrict__ lim,
                                                              const InstState<T>* st, double alpha,
-                                                             uint64_t* __restrict__ weight,
+                                                             uint64_t* __restrict__ weight, int64_t chunk_rows,
                                                              const int32_t* __restrict__ list,
                                                              const int32_t* __restrict__ flags) {
     __shared__ ImpactShared<T> L;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t count = flags[FLAG_WORST];                // instances on the list (k_alns_worst_list)
-    const int64_t slot = blockIdx.x * 64ll + lane;
-    if (blockIdx.x * 64ll >= count) return;                 // the same for the whole workgroup
-    const bool live = slot < count;
-    const int64_t q = list[live ? slot : count - 1];
-    const int64_t qc = q;
-    const double t = (double)st[qc].t;
-    const double scale = alns_impact_scale(t);
-    const double sc = (double)scale_q[qc];
-    int shift = alns_bits(m) + 24 + alns_bits(n) - 62;
-    if (shift < 0) shift = 0;
-    const bool counts = live && scale != 0.0;               // otherwise every weight of the instance is 1
-    L.sc[w][lane] = sc;
-    L.t[w][lane] = t;
-    L.scale[w][lane] = scale;
-    __builtin_amdgcn_wave_barrier();
-    // May the term of matrix entry x and a row of slack t - |r_i| count?  The shortcut cuts it off
-    // when slack > |sc x| * 18 / alpha, i.e. when |x| < slack * alpha / (18 sc).  The loop tests
-    // |x| >= lim_i with lim_i = slack_i * cinv, cinv = alpha / (18 * 1.01 * sc), in the working
-    // precision: the 1 % covers the roundings of cinv and of the product, so a term the test
-    // leaves out is one the shortcut cuts off (the reverse need not hold: alns_impact_term
-    // applies the exact shortcut again).  One comparison per term; lim_i is per row.
-    const T tw = (T)t;                                      // exact: t is a value of type T
-    T cinv = (T)(alpha / (18.0 * 1.01)) / (T)sc;
-    if (!(cinv < Limits<T>::inf())) cinv = (T)0;            // a scale so small that this overflows: test nothing
-    for (int64_t j0 = (blockIdx.y * 4ll + w) * IMQ_VARS; j0 < n; j0 += 4ll * IMQ_VARS * gridDim.y) {
+    const int64_t s0 = blockIdx.x * (int64_t)IM_Q;
+    if (s0 >= count) return;                                // the same for the whole workgroup
+    if (threadIdx.x < 16) L.exp2m[threadIdx.x] = exp2(-(double)threadIdx.x / 16.0);
+    if (threadIdx.x < IM_Q) {
+        const int64_t q = list[s0 + threadIdx.x < count ? s0 + threadIdx.x : count - 1];
+        L.sc[threadIdx.x] = (double)scale_q[q];
+        L.t[threadIdx.x] = (double)st[q].t;
+        L.scale[threadIdx.x] = alns_impact_scale((double)st[q].t);
+    }
+    __syncthreads();
+    const int64_t i_begin = blockIdx.z * chunk_rows;
+    const int64_t i_end = i_begin + chunk_rows < m ? i_begin + chunk_rows : m;
+    // staging of r and of the limits: lane = (row, instance), two passes of 16 rows
+    const int sv = lane & (IM_Q - 1), su = lane / IM_Q;
+    const int64_t slot = s0 + sv, slot_c = slot < count ? slot : count - 1;
+    const int64_t sq = list[slot_c];
+    const int wl = threadIdx.x >> 6;                        // (in a vector register: LDS addresses are one register + constants)
+    int head = 0, waiting = 0;                              // the same in every lane
+    int64_t i_pass = 0, j_pass = 0;                         // first row and variable of the pass
+    // every lane evaluates one of the first `take` waiting terms, for the sum it belongs to
+    auto drain = [&](int take) {
+        __builtin_amdgcn_wave_barrier();
+        if (lane < take) {
+            const int e = L.queue[wl][(head + lane) & (IM_CAP - 1)];
+            const int col = e & 63, v = (e >> 6) & (IM_Q - 1), row = e >> 8;
+            const double a = __builtin_fabs(L.sc[v] * (double)(Xt + i_pass * n + j_pass)[(int64_t)row * n + col]);
+            const uint32_t term = alns_impact_term_fast(a, __builtin_fabs((double)L.r[wl][row][v]), L.t[v], alpha, L.scale[v], L.exp2m);
+            if (term) atomicAdd(&L.sum[wl][v][col], (unsigned long long)term);
+        }
+        __builtin_amdgcn_wave_barrier();
+        head = (head + take) & (IM_CAP - 1);
+        waiting -= take;
+    };
+    for (int64_t j0 = (blockIdx.y * 4ll + w) * 64; j0 < n; j0 += 256ll * gridDim.y) {   // whole wavefronts; no barrier inside
+        const int64_t j = j0 + lane;
+        const uint32_t lc = (uint32_t)(j < n ? lane : n - 1 - j0);
 #pragma unroll
-        for (int v = 0; v < IMQ_VARS; ++v) L.sum[w][v][lane] = 0;
-        int head = 0, waiting = 0;                          // the same in every lane
-        // every lane computes one of the first `count` waiting terms, for the instance it belongs to
-        auto drain = [&](int count) {
-            __builtin_amdgcn_wave_barrier();
-            if (lane < count) {
-                const int e = (head + lane) & (IMQ_CAP - 1);
-                const int meta = L.qmeta[w][e];
-                const int owner = meta & 0xFF;
-                const double a = __builtin_fabs(L.sc[w][owner] * (double)L.qx[w][e]);
-                const uint64_t term = alns_impact_term(a, __builtin_fabs((double)L.qr[w][e]), L.t[w][owner], alpha,
-                                                       L.scale[w][owner]);
-                if (term) atomicAdd(&L.sum[w][meta >> 8][owner], (unsigned long long)term);
+        for (int v = 0; v < IM_Q; ++v) L.sum[wl][v][lane] = 0;
+        T x[IM_ROWS], rs[IM_STAGE], ls[IM_STAGE];           // the next pass's operands, in flight
+        auto fetch = [&](int64_t i0) {
+#pragma unroll
+            for (int u = 0; u < IM_STAGE; ++u) {
+                const int row = su + u * (64 / IM_Q);
+                const int64_t i = i0 + row < i_end ? i0 + row : i_end - 1;
+                rs[u] = r[i * R + sq];
+                ls[u] = lim[i * R + slot_c];
+                if (i0 + row >= i_end || slot != slot_c) ls[u] = Limits<T>::inf();
             }
-            __builtin_amdgcn_wave_barrier();
-            head = (head + count) & (IMQ_CAP - 1);
-            waiting -= count;
+            // one uniform pointer that walks (rows past the end repeat the last); the stride is made opaque,
+            // or its 32 multiples are kept in scalar registers across the whole loop, which spills them
+            const T* __restrict__ row = Xt + i0 * n + j0;
+            int64_t stride = n;
+            asm volatile("" : "+s"(stride));
+#pragma unroll
+            for (int u = 0; u < IM_ROWS; ++u) {
+                x[u] = row[lc];
+                row += i0 + u + 1 < i_end ? stride : 0;
+            }
         };
-        for (int64_t i0 = 0; i0 < m; i0 += IMQ_ROWS) {
-            T xs[IMQ_ROWS][IMQ_VARS], rs[IMQ_ROWS], lim[IMQ_ROWS];
+        fetch(i_begin);
+        for (int64_t i0 = i_begin; i0 < i_end; i0 += IM_ROWS) {
 #pragma unroll
-            for (int u = 0; u < IMQ_ROWS; ++u) {
-                const int64_t i = i0 + u < m ? i0 + u : m - 1;
-                rs[u] = r[i * R + qc];
-#pragma unroll
-                for (int v = 0; v < IMQ_VARS; ++v) xs[u][v] = Xt[i * n + (j0 + v < n ? j0 + v : n - 1)];
+            for (int u = 0; u < IM_STAGE; ++u) {
+                L.r[wl][su + u * (64 / IM_Q)][sv] = rs[u];
+                L.lim[wl][su + u * (64 / IM_Q)][sv] = ls[u];
             }
+            __builtin_amdgcn_wave_barrier();
+            i_pass = i0;
+            j_pass = j0;
+            uint32_t mask[IM_Q];
 #pragma unroll
-            for (int u = 0; u < IMQ_ROWS; ++u)              // a lane or a row that does not count takes nothing
-                lim[u] = counts && i0 + u < m ? (tw - dmmv_abs(rs[u])) * cinv : Limits<T>::inf();
+            for (int v = 0; v < IM_Q; ++v) mask[v] = 0;
 #pragma unroll
-            for (int u = 0; u < IMQ_ROWS; ++u) {
+            for (int u = 0; u < IM_ROWS; ++u) {
 #pragma unroll
-                for (int v = 0; v < IMQ_VARS; ++v) {
-                    if (j0 + v >= n) continue;               // the same for the whole wavefront
-                    const bool take = dmmv_abs(xs[u][v]) >= lim[u];
-                    const unsigned long long mask = __ballot(take);
-                    if (mask) {                              // the same for the whole wavefront
-                        if (take) {
-                            const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-                            const int e = (head + waiting + before) & (IMQ_CAP - 1);
-                            L.qx[w][e] = xs[u][v];
-                            L.qr[w][e] = rs[u];
-                            L.qmeta[w][e] = (uint16_t)(lane | (v << 8));
-                        }
-                        waiting += __builtin_popcountll(mask);
-                        if (waiting >= 64) drain(64);
+                for (int v = 0; v < IM_Q; ++v) mask[v] = impact_test(mask[v], x[u], L.lim[wl][u][v]);
+            }
+            if (i0 + IM_ROWS < i_end) fetch(i0 + IM_ROWS);
+#pragma unroll 1
+            for (int v = 0; v < IM_Q; ++v) {
+                uint32_t mk = j < n ? __brev(mask[0]) : 0;  // bit = row
+#pragma unroll
+                for (int e = 0; e + 1 < IM_Q; ++e) mask[e] = mask[e + 1];
+                // a variable with many terms (an outlier channel): all its rows at once, lane = row
+                unsigned long long many = __ballot(__popc(mk) > IM_FEW);
+                while (many) {                              // the same for the whole wavefront
+                    const int col = __ffsll(many) - 1;
+                    many &= many - 1;
+                    const uint32_t rows = __builtin_amdgcn_readlane(mk, col);
+                    if (lane == col) mk = 0;
+                    if (lane < IM_ROWS && ((rows >> lane) & 1u))
+                        L.queue[wl][(head + waiting + __builtin_amdgcn_mbcnt_lo(rows, 0)) & (IM_CAP - 1)] = (uint16_t)(col | (v << 6) | (lane << 8));
+                    waiting += __popc(rows);
+                    if (waiting >= 64) drain(64);
+                }
+                // the others: every variable's next row
+                while (true) {
+                    const unsigned long long some = __ballot(mk != 0);
+                    if (some == 0) break;
+                    if (mk) {
+                        const int row = __ffs(mk) - 1;
+                        mk &= mk - 1;
+                        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32),
+                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0));
+                        L.queue[wl][(head + waiting + before) & (IM_CAP - 1)] = (uint16_t)(lane | (v << 6) | (row << 8));
                     }
+                    waiting += __builtin_popcountll(some);
+                    if (waiting >= 64) drain(64);
                 }
             }
+            if (waiting > 0) drain(waiting);                // the entries of X and r are replaced next
         }
-        if (waiting > 0) drain(waiting);
-        if (live) {
+        if (j < n) {
 #pragma unroll
-            for (int v = 0; v < IMQ_VARS; ++v)
-                if (j0 + v < n) weight[q * n + j0 + v] = 1 + ((uint64_t)L.sum[w][v][lane] >> shift);
+            for (int v = 0; v < IM_Q; ++v)
+                if (s0 + v < count && L.sum[wl][v][lane] != 0)
+                    atomicAdd((unsigned long long*)&weight[(int64_t)list[s0 + v] * n + j], L.sum[wl][v][lane]);
         }
-        __builtin_amdgcn_wave_barrier();                    // the sums are cleared for the next pass
     }
 }
 
@@ -596,20 +698,41 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
                            c->p.n, (const T*)c->p.A_dense, c->p.lda, (const T*)c->r,
                            (const InstState<T>*)c->state, prm.alpha, c->alns_weight, (const AlnsState*)S);
     } else if (c->kind == KIND_BATCHED) {
-        int64_t ny = (c->p.n + 4 * IMQ_VARS - 1) / (4 * IMQ_VARS);     // a wavefront takes IMQ_VARS variables per pass
-        if (ny > 2048) ny = 2048;
-        // (the list shares the buffer of the descent's list of running instances: never both at once)
+        // (the list shares the buffer of the descent's list of running instances, the limits that of its
+        // packed residuals: never both at once)
         hipLaunchKernelGGL(k_alns_worst_list, dim3(1), dim3(1024), 0, c->stream, R, (const AlnsState*)S,
                            c->cmp_orig, c->flags);
-        hipLaunchKernelGGL(k_alns_impact_batched<T>, dim3(blocks_for(R, 64), (unsigned)ny), dim3(256), 0,
-                           c->stream, c->p.m, c->p.n, R, (const T*)c->Xt, (const T*)c->scale_dev,
-                           (const T*)c->r, (const InstState<T>*)c->state, prm.alpha, c->alns_weight,
+        int64_t ly = ceil_div(c->p.m, 16);
+        if (ly > 64) ly = 64;
+        hipLaunchKernelGGL(k_alns_impact_limits<T>, dim3(blocks_for(R, 64), (unsigned)(ly > 0 ? ly : 1)), dim3(256), 0,
+                           c->stream, c->p.m, c->p.n, R, (const T*)c->scale_dev, (const T*)c->r,
+                           (const InstState<T>*)c->state, prm.alpha, (T*)c->cmp_r, c->alns_weight,
                            (const int32_t*)c->cmp_orig, (const int32_t*)c->flags);
+        // about half of the instances are on the list; the rows are split until some 8 wavefronts per SIMD
+        // are there to hide the loads of each other, at least two passes of rows each
+        const int64_t col_groups = ceil_div(c->p.n, 256);
+        const int64_t waves = ceil_div(c->p.n, 64) * ceil_div(ceil_div(R, 2), IM_Q);
+        int64_t chunks = ceil_div(8192, waves > 0 ? waves : 1);
+        if (chunks > ceil_div(c->p.m, 2 * IM_ROWS)) chunks = ceil_div(c->p.m, 2 * IM_ROWS);
+        if (chunks < 1) chunks = 1;
+        const int64_t chunk_rows = ceil_div(ceil_div(c->p.m, chunks), IM_ROWS) * IM_ROWS;
+        chunks = ceil_div(c->p.m, chunk_rows > 0 ? chunk_rows : 1);
+        if (chunks > 0)
+            hipLaunchKernelGGL(k_alns_impact_batched<T>, dim3((unsigned)ceil_div(R, IM_Q), (unsigned)(col_groups < 65535 ? col_groups : 65535), (unsigned)chunks),
+                               dim3(256), 0, c->stream, c->p.m, c->p.n, R, (const T*)c->Xt, (const T*)c->scale_dev,
+                               (const T*)c->r, (const T*)c->cmp_r, (const InstState<T>*)c->state, prm.alpha, c->alns_weight,
+                               chunk_rows, (const int32_t*)c->cmp_orig, (const int32_t*)c->flags);
     } else {
         DMMV_TRY(csc_alns_impact(c, prm.alpha));
     }
+    int32_t raw_shift = -1;
+    if (c->kind == KIND_BATCHED) {
+        auto bits = [](int64_t v) { int b = 0; while (v > 0) { ++b; v >>= 1; } return b; };
+        raw_shift = bits(c->p.m) + 24 + bits(c->p.n) - 62;
+        if (raw_shift < 0) raw_shift = 0;
+    }
     hipLaunchKernelGGL(k_alns_scan, dim3((unsigned)R), dim3(1024), 0, c->stream, c->p.n,
-                       (const uint64_t*)c->alns_weight, c->alns_prefix, (const AlnsState*)S);
+                       (const uint64_t*)c->alns_weight, c->alns_prefix, (const AlnsState*)S, raw_shift);
     hipLaunchKernelGGL(k_alns_sample, dim3((unsigned)R), dim3(R > 1 ? 256 : 1024), 0, c->stream, c->p.n, count,
                        (const uint64_t*)c->alns_prefix, (unsigned long long*)c->alns_first, c->alns_picked,
                        (const AlnsState*)S, prm.seed);
