@@ -631,7 +631,7 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
         if (pruned_batch) return batched_descent_pruned(c, iters, iters, trace, trace_t);
         // a small dense instance too; the wait between its workgroups is bounded and reports here
         if (iters > 0 && dense_persistent_applicable(c)) {
-            DMMV_TRY(dense_descent_persistent(c, iters, trace, trace_t));
+            DMMV_TRY(dense_descent_persistent(c, iters, iters, trace, trace_t));
             int32_t raw = 0;
             const dmmv_status one = check_device_errors(c, &raw);
             // An automatic choice must not add a way to fail: if the workgroups could not all be
@@ -689,12 +689,14 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
     const dmmv_options saved = c->o;
     c->o.radius = prm.ls_radius;
     c->o.keep_going = 0;
-    dmmv_status st = [&]() -> dmmv_status {
+    auto run = [&](bool one_launch) -> dmmv_status {
         DMMV_TRY(alns_start(c, prm.l2_guard != 0));
         for (int32_t it = 0; it < prm.iters; ++it) {
             DMMV_TRY(alns_destroy_repair(c, prm, it, (int32_t)count));
             if (batched_pruned_applicable(c)) {
                 DMMV_TRY(batched_descent_pruned(c, prm.ls_moves, prm.ls_moves, nullptr, nullptr));
+            } else if (one_launch) {
+                DMMV_TRY(dense_descent_persistent(c, prm.ls_moves, prm.ls_moves, nullptr, nullptr));
             } else {
                 for (int32_t mv = 0; mv < prm.ls_moves; ++mv) DMMV_TRY(loop_step(c, prm.ls_moves, nullptr, nullptr));
             }
@@ -705,8 +707,24 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
             }
             DMMV_TRY(alns_finish_iteration(c, prm, trace, trace_t));
         }
-        DMMV_TRY(alns_export(c, t_best_out));
-        return DMMV_OK;
+        return alns_export(c, t_best_out);
+    };
+    // A small dense instance: all moves of a local search in one launch.  Its workgroups wait for one another;
+    // should the device be shared with a kernel that keeps some from starting, the wait ends and an
+    // error bit is raised, and the same run is made again from the saved starting point with a launch per
+    // step.  (The arg-min records of that loop, 16 bytes per variable and more, are free meanwhile.)
+    const bool one_launch = prm.ls_moves > 0 && !batched_pruned_applicable(c) && dense_persistent_applicable(c);
+    dmmv_status st = [&]() -> dmmv_status {
+        if (!one_launch) return run(false);
+        const size_t xbytes = (size_t)c->p.n * sizeof(int32_t);
+        DMMV_HIP_CHECK(hipMemcpyAsync(c->partials, c->kidx, xbytes, hipMemcpyDeviceToDevice, c->stream));
+        DMMV_TRY(run(true));
+        int32_t raw = 0;
+        const dmmv_status one = check_device_errors(c, &raw);
+        if (one == DMMV_OK || raw != ERRBIT_WAIT_LIMIT) return one;
+        DMMV_HIP_CHECK(hipMemcpyAsync(c->kidx, c->partials, xbytes, hipMemcpyDeviceToDevice, c->stream));
+        DMMV_TRY(residual_any(c));
+        return run(false);
     }();
     c->o = saved;
     DMMV_TRY(st);

@@ -267,7 +267,8 @@ dmmv_status batched_compact_end(Ctx* c);
 size_t dense_persistent_exchange_bytes();
 bool dense_persistent_fits(const dmmv_problem& p);
 bool dense_persistent_applicable(const Ctx* c);
-dmmv_status dense_descent_persistent(Ctx* c, int32_t iters, dmmv_move* trace, void* trace_t);
+// (at most `steps` iterations)
+dmmv_status dense_descent_persistent(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t);
 
 // options.prune on a batch: `steps` iterations of the descent for every instance in one launch,
 // same moves as evaluation + selection + apply (an instance stops at its local optimum)

@@ -22,6 +22,8 @@
 // device be shared with another kernel that keeps some of them from starting, the wait ends
 // after options.wait_limit polls: the kernel raises an error flag, every workgroup leaves, and
 // dmmv_solve returns DMMV_ERR_STATE.
+#include <type_traits>
+
 #include "dmmv_common.h"
 
 namespace dmmv {
@@ -108,6 +110,69 @@ __device__ __forceinline__ uint64_t score_bits(float s) { return (uint64_t)__flo
 __device__ __forceinline__ void score_from(uint64_t b, double& s) { s = __longlong_as_double((long long)b); }
 __device__ __forceinline__ void score_from(uint64_t b, float& s) { s = __uint_as_float((uint32_t)b); }
 
+// ---- the exchange ---------------------------------------------------------------------------
+template <class T>
+__device__ __forceinline__ void dp_publish(uint64_t* rec, int G, int g, int32_t it, T bs, int64_t bc) {
+    const uint64_t tag = (uint64_t)(uint32_t)(it + 1) << 32;
+    uint64_t* slot = rec + ((int64_t)(it & 1) * G + g) * DP_REC_WORDS;
+    const uint64_t sb = score_bits(bs), cb = (uint64_t)bc;
+    __hip_atomic_store(&slot[0], tag | (sb >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&slot[1], tag | (sb & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&slot[2], tag | (cb >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&slot[3], tag | (cb & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One whole wavefront: the smallest of all workgroups' records of iteration `it`, the same in every
+// lane (lane q waits for workgroups q, q + 64, ..).  False when a wait ran into its limit.
+template <class T>
+__device__ __forceinline__ bool dp_collect(const uint64_t* rec, int G, int32_t it, int lane, int32_t wait_limit,
+                                           const int32_t* flags, T& gs, int64_t& gc) {
+    const uint64_t tag = (uint64_t)(uint32_t)(it + 1) << 32;
+    gs = (T)0;
+    gc = -1;
+    uint32_t fail = 0;
+    for (int q = lane; q < G; q += 64) {
+        const uint64_t* slot = rec + ((int64_t)(it & 1) * G + q) * DP_REC_WORDS;
+        // Two reads of the record are kept in flight (loads return in order): a read
+        // samples memory half a round trip after it was issued, so with one read at a
+        // time a record that lands just after the sample costs a whole further round
+        // trip; the second read halves that.
+        const uint64_t hi = 0xffffffff00000000ull;
+        uint64_t a0, a1, a2, a3, b0, b1, b2, b3;
+#define DP_READ(x0, x1, x2, x3)                                                              \
+    x0 = __hip_atomic_load(&slot[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);             \
+    x1 = __hip_atomic_load(&slot[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);             \
+    x2 = __hip_atomic_load(&slot[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);             \
+    x3 = __hip_atomic_load(&slot[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#define DP_THERE(x0, x1, x2, x3) (((x0) & hi) == tag && ((x1) & hi) == tag && ((x2) & hi) == tag && ((x3) & hi) == tag)
+        int32_t polls = 0;
+        bool there = false;
+        DP_READ(a0, a1, a2, a3)
+        do {
+            DP_READ(b0, b1, b2, b3)
+            there = DP_THERE(a0, a1, a2, a3);
+            if (there) break;
+            DP_READ(a0, a1, a2, a3)
+            there = DP_THERE(b0, b1, b2, b3);
+            if (there) { a0 = b0; a1 = b1; a2 = b2; a3 = b3; break; }
+            polls += 2;
+            // somebody else has given up already: no point in waiting out the limit
+            if ((polls & 254) == 254 &&
+                __hip_atomic_load(&flags[FLAG_ERROR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+                polls = wait_limit;
+        } while (polls < wait_limit);
+#undef DP_READ
+#undef DP_THERE
+        if (!there) { fail = 1; break; }
+        T s;
+        score_from((a0 << 32) | (a1 & 0xffffffffull), s);
+        const int64_t c = (int64_t)((a2 << 32) | (a3 & 0xffffffffull));
+        if (rec_less(s, c, gs, gc)) { gs = s; gc = c; }
+    }
+    wave_argmin(gs, gc);
+    return __ballot(fail != 0) == 0ull;
+}
+
 __global__ void k_zero_words(uint32_t* p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
@@ -117,7 +182,7 @@ template <class T, int NWAVES>
 __global__ __launch_bounds__(64 * NWAVES) void k_descent_dense_persistent(
     int64_t m, int64_t n, int32_t nd, const T* __restrict__ A, int64_t lda, const T* __restrict__ D,
     T* r, int32_t* kidx, int32_t radius, const uint8_t* __restrict__ var_mask, InstState<T>* st,
-    int32_t keep_going, int32_t iters, dmmv_move* trace, T* trace_t, int32_t tiles, int32_t upw,
+    int32_t keep_going, int32_t steps, int32_t iters, dmmv_move* trace, T* trace_t, int32_t tiles, int32_t upw,
     int32_t ncols, uint64_t* rec /*[2][G][DP_REC_WORDS]*/, int32_t* flags, int32_t wait_limit) {
     constexpr int KT = DP_KT;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -162,7 +227,7 @@ __global__ __launch_bounds__(64 * NWAVES) void k_descent_dense_persistent(
 #pragma unroll
     for (int q = 0; q < KT; ++q) delta_keep[q] = (T)0;
 
-    for (int32_t it = 0; it < iters && !stopped; ++it) {
+    for (int32_t it = 0; it < steps && !stopped; ++it) {
         // ---- score this wavefront's units ------------------------------------------------
         T ws = (T)0;
         int64_t wc = -1;
@@ -233,8 +298,7 @@ __global__ __launch_bounds__(64 * NWAVES) void k_descent_dense_persistent(
         }
         if (lane == 0) { sh_ws[w] = ws; sh_wc[w] = wc; }
         __syncthreads();
-        // ---- publish this workgroup's record ------------------------------------------------
-        const uint64_t tag = (uint64_t)(uint32_t)(it + 1) << 32;
+        // ---- publish this workgroup's record, read every workgroup's ---------------------------
         if (tid == 0) {
             T bs = (T)0;
             int64_t bc = -1;
@@ -245,58 +309,12 @@ __global__ __launch_bounds__(64 * NWAVES) void k_descent_dense_persistent(
 #pragma unroll
             for (int x = 0; x < NWAVES; ++x)
                 if (rec_less(xs[x], xc[x], bs, bc)) { bs = xs[x]; bc = xc[x]; }
-            uint64_t* slot = rec + ((int64_t)(it & 1) * G + g) * DP_REC_WORDS;
-            const uint64_t sb = score_bits(bs), cb = (uint64_t)bc;
-            __hip_atomic_store(&slot[0], tag | (sb >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&slot[1], tag | (sb & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&slot[2], tag | (cb >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&slot[3], tag | (cb & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            dp_publish(rec, G, g, it, bs, bc);
         }
-        // ---- read every workgroup's record (wavefront 0; lane q takes workgroups q, q + 64, ..)
         if (w == 0) {
-            T gs = (T)0;
-            int64_t gc = -1;
-            uint32_t fail = 0;
-            for (int q = lane; q < G; q += 64) {
-                const uint64_t* slot = rec + ((int64_t)(it & 1) * G + q) * DP_REC_WORDS;
-                // Two reads of the record are kept in flight (loads return in order): a read
-                // samples memory half a round trip after it was issued, so with one read at a
-                // time a record that lands just after the sample costs a whole further round
-                // trip; the second read halves that.
-                const uint64_t hi = 0xffffffff00000000ull;
-                uint64_t a0, a1, a2, a3, b0, b1, b2, b3;
-#define DP_READ(x0, x1, x2, x3)                                                              \
-    x0 = __hip_atomic_load(&slot[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);             \
-    x1 = __hip_atomic_load(&slot[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);             \
-    x2 = __hip_atomic_load(&slot[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);             \
-    x3 = __hip_atomic_load(&slot[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#define DP_THERE(x0, x1, x2, x3) (((x0) & hi) == tag && ((x1) & hi) == tag && ((x2) & hi) == tag && ((x3) & hi) == tag)
-                int32_t polls = 0;
-                bool there = false;
-                DP_READ(a0, a1, a2, a3)
-                do {
-                    DP_READ(b0, b1, b2, b3)
-                    there = DP_THERE(a0, a1, a2, a3);
-                    if (there) break;
-                    DP_READ(a0, a1, a2, a3)
-                    there = DP_THERE(b0, b1, b2, b3);
-                    if (there) { a0 = b0; a1 = b1; a2 = b2; a3 = b3; break; }
-                    polls += 2;
-                    // somebody else has given up already: no point in waiting out the limit
-                    if ((polls & 254) == 254 &&
-                        __hip_atomic_load(&flags[FLAG_ERROR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
-                        polls = wait_limit;
-                } while (polls < wait_limit);
-#undef DP_READ
-#undef DP_THERE
-                if (!there) { fail = 1; break; }
-                T s;
-                score_from((a0 << 32) | (a1 & 0xffffffffull), s);
-                const int64_t c = (int64_t)((a2 << 32) | (a3 & 0xffffffffull));
-                if (rec_less(s, c, gs, gc)) { gs = s; gc = c; }
-            }
-            wave_argmin(gs, gc);
-            fail = __ballot(fail != 0) != 0ull;
+            T gs;
+            int64_t gc;
+            const bool fail = !dp_collect(rec, G, it, lane, wait_limit, flags, gs, gc);
             if (lane == 0) {
                 sh_bs = gs;
                 sh_bc = gc;
@@ -343,8 +361,350 @@ __global__ __launch_bounds__(64 * NWAVES) void k_descent_dense_persistent(
     }
 }
 
+// ---- the same loop for the descent itself (not fixed-work mode) ------------------------------
+// Only strictly improving moves matter there, and a variable has few of them.  For a row i of
+// value r_i the product chain x_i(k) = fma(delta_k, A_ij, r_i) is monotone in k (D ascends, rounding is
+// monotone), so the values with |x_i(k)| < t form an interval; a move that lowers the maximum lies in
+// the intersection of the intervals of any rows.  Per iteration a workgroup
+//   1. keeps one row of largest |r| out of each wavefront's share (the largest of all among them),
+//      found while the last move is applied;
+//   2. finds each of its variables' intervals by bisection on those rows, one lane per (row, bound);
+//   3. scores the values of the interval over all rows, DI_KT at a time.  A longer interval is narrowed first:
+//      the score is quasi-convex in k (a maximum of monotone chains' magnitudes, also as computed), so the
+//      minimum lies between the neighbours of the lowest of DI_KT spaced samples; if a plateau keeps
+//      that from shrinking, every value is scored.
+// What is skipped scores at least t, so the record of an iteration is that of the full table whenever
+// there is an improving move, and the loop stops just the same when there is none.
+// On 4096 x 32 with 1024 levels (fp64) an iteration takes 9.1 us instead of 17.7 (all 1024 levels scored),
+// of which the exchange is about 2 and the rest a chain of reductions; a local search of 8 moves to
+// neighbouring levels on 8016 x 251 (256 levels, fp64) takes 59 us in this launch instead of 320 with
+// two launches per move that score all levels.  On 256 x 64 with 16 levels there is too little to skip
+// (5.3 us against 4.3): the host's model keeps the kernel above there.
+// COOP: all wavefronts score one variable, its rows shared out (tall matrices, few variables);
+// otherwise a wavefront scores a variable by itself.
+constexpr int DI_KT = 8;                  // values scored together
+constexpr int DI_PF = 8;                  // loads of a thread in flight where rows come from memory
+
+struct PlanI {
+    int G = 0, vpw = 0, waves = 0;
+    bool coop = false, cols = false;
+    size_t lds = 0;
+    double est_us = 0;
+};
+
+// Modelled like the plan above: exchange 2 us + 4 ns per workgroup, 1.6 us for the rest of an
+// iteration, per variable its interval (0.3 us up to 64 levels, then 0.14 us per step of the bisection) and 1.5
+// rounds of scoring DI_KT values (one round of one value where only the neighbouring levels are
+// allowed).  Rows that come from memory instead of LDS count three times.
+PlanI make_plan_interval(const dmmv_problem& p, int32_t radius, int cus) {
+    PlanI best;
+    if (p.csr_rowptr || p.R != 1 || p.scale || p.m < 1 || p.n < 1 || p.nd < 1) return best;
+    const size_t w = p.dtype == DMMV_F64 ? 8 : 4;
+    if (p.m > (int64_t)(DP_LDS_LIMIT / w) || p.n > (1 << 20) || p.nd > (1 << 16)) return best;
+    const int gmax = cus < DP_MAX_G ? (cus > 0 ? cus : 1) : DP_MAX_G;
+    for (int waves = 4; waves <= DP_MAX_WAVES; waves *= 2)
+        for (int coop = 0; coop < 2; ++coop) {
+            const int64_t want = coop ? p.n : ceil_div(p.n, waves);
+            const int64_t g0 = want < gmax ? want : gmax;
+            const int64_t vpw = ceil_div(p.n, g0), G = ceil_div(p.n, vpw);
+            const size_t base = (size_t)p.m * w + (size_t)waves * DI_KT * DP_SKEW * w + (size_t)p.nd * w + (size_t)p.n * 4;
+            if (base > DP_LDS_LIMIT) continue;
+            const bool cols = base + (size_t)vpw * p.m * w <= DP_LDS_LIMIT;
+            const double per_64 = waves == 4 ? (w == 8 ? 18.0 : 10.0) : (w == 8 ? 32.0 : 16.0);
+            const double rows = (double)ceil_div(p.m, coop ? 64 * waves : 64);
+            const bool near = radius == 1 || p.nd <= 3;
+            double interval = 0.3;
+            for (int32_t k = radius > 0 && radius < p.nd / 2 ? 2 * radius : p.nd; p.nd > 64 && k > 0; k >>= 1) interval += 0.14;
+            const double round = (coop ? 0.6 : 0.4) * (near ? 1.0 : 1.5) + rows * (near ? 1.0 : 1.5 * DI_KT) * per_64 / 2400.0 * (cols ? 1.0 : 3.0);
+            const double est = 3.6 + 0.004 * (double)G + (double)(coop ? vpw : ceil_div(vpw, waves)) * (interval + round) + 0.0002 * (double)p.m;
+            if (best.G == 0 || est < best.est_us) {
+                best.G = (int)G; best.vpw = (int)vpw; best.waves = waves; best.coop = coop != 0; best.cols = cols;
+                best.lds = base + (cols ? (size_t)vpw * p.m * w : 0);
+                best.est_us = est;
+            }
+        }
+    return best;
+}
+
+template <int CTRL>
+__device__ __forceinline__ int32_t dpp_int(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
+
+template <class T, int NWAVES, bool COOP, bool COLS>
+__global__ __launch_bounds__(64 * NWAVES) void k_descent_dense_interval(
+    int64_t m, int64_t n, int32_t nd, const T* __restrict__ A, int64_t lda, const T* __restrict__ D,
+    T* r, int32_t* kidx, int32_t radius, const uint8_t* __restrict__ var_mask, InstState<T>* st,
+    int32_t steps, int32_t iters, dmmv_move* trace, T* trace_t, int32_t vpw, uint64_t* rec, int32_t* flags,
+    int32_t wait_limit) {
+    constexpr int KT = DI_KT, NT = 64 * NWAVES, ROWS = 2 * NWAVES < 16 ? NWAVES : 8;   // rows the intervals are cut on
+    extern __shared__ __align__(16) unsigned char smem[];
+    T* sh_r = reinterpret_cast<T*>(smem);                   // [m]
+    T* sh_cols = sh_r + m;                                  // [vpw][m] (COLS)
+    T* sh_sc = sh_cols + (COLS ? (int64_t)vpw * m : 0);     // [NWAVES][KT * DP_SKEW]
+    T* sh_D = sh_sc + NWAVES * KT * DP_SKEW;                // [nd]
+    int32_t* sh_kidx = reinterpret_cast<int32_t*>(sh_D + nd);   // [n]
+    __shared__ T sh_ws[NWAVES], sh_red[2][NWAVES][KT], sh_top_r[NWAVES];
+    __shared__ int64_t sh_wc[NWAVES];
+    __shared__ int32_t sh_top[NWAVES];
+    __shared__ T sh_bs;
+    __shared__ int64_t sh_bc;
+    __shared__ int32_t sh_fail;
+
+    const int G = gridDim.x, g = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t j_lo = (int64_t)g * vpw, j_end = j_lo + vpw < n ? j_lo + vpw : n;
+
+    // every pass over the rows of an array in memory keeps DI_PF loads of a thread in flight
+    auto rows_of = [&](const T* src, auto use) {
+        for (int64_t i0 = tid; i0 < m; i0 += DI_PF * NT) {
+            T v[DI_PF];
+#pragma unroll
+            for (int u = 0; u < DI_PF; ++u) v[u] = src[i0 + u * NT < m ? i0 + u * NT : m - 1];
+#pragma unroll
+            for (int u = 0; u < DI_PF; ++u)
+                if (i0 + u * NT < m) use(i0 + u * NT, v[u]);
+        }
+    };
+    if (COLS)
+        for (int64_t j = j_lo; j < j_end; ++j) {
+            T* const dst = sh_cols + (j - j_lo) * m;
+            rows_of(A + lda * j, [&](int64_t i, T v) { dst[i] = v; });
+        }
+    for (int64_t j = tid; j < n; j += NT) sh_kidx[j] = kidx[j];
+    for (int32_t k = tid; k < nd; k += NT) sh_D[k] = D[k];
+    if (tid == 0) sh_fail = 0;
+    T t = st[0].t;
+    int32_t moves = st[0].moves;
+    T last_s = st[0].best_s;
+    bool stopped = st[0].done != 0, failed = false;
+    // the wavefront's row of largest |r| among those its threads hold
+    auto top_row = [&](T bv, int32_t bi) {
+        const T top = wave_max(bv);
+        const unsigned long long has = __ballot(bi >= 0 && bv == top);
+        if (has == 0) { if (lane == 0) { sh_top[w] = -1; sh_top_r[w] = (T)0; } }
+        else if (lane == __builtin_ctzll(has)) { sh_top[w] = bi; sh_top_r[w] = sh_r[bi]; }
+    };
+    {
+        T bv = (T)-1;
+        int32_t bi = -1;
+        rows_of(r, [&](int64_t i, T v) {
+            sh_r[i] = v;
+            if (dmmv_abs(v) > bv) { bv = dmmv_abs(v); bi = (int32_t)i; }
+        });
+        top_row(bv, bi);
+    }
+    __syncthreads();
+
+    int parity = 0;
+    for (int32_t it = 0; it < steps && !stopped; ++it) {
+        T ws = (T)0;
+        int64_t wc = -1;
+        for (int64_t j = j_lo + (COOP ? 0 : w); j < j_end; j += COOP ? 1 : NWAVES) {
+            const int32_t kcur = sh_kidx[j];
+            const T dcur = sh_D[kcur];
+            const T* __restrict__ col = COLS ? sh_cols + (j - j_lo) * m : A + lda * j;
+            int32_t klo = radius > 0 && kcur - radius > 0 ? kcur - radius : 0;
+            int32_t khi = radius > 0 && kcur < nd - 1 - radius ? kcur + radius : nd - 1;
+            if (var_mask && var_mask[j] == 0) continue;      // the same for everyone who scores this variable
+            // ---- the values that bring the top rows below t
+            if (nd <= 64) {                                   // lane = value, no chain of dependent reads
+                const int32_t k = lane;
+                const T delta = step_of(sh_D[k < nd ? k : nd - 1], dcur, (T)1);
+                bool good = k >= klo && k <= khi;
+#pragma unroll
+                for (int u = 0; u < ROWS; ++u) {
+                    const int32_t row = sh_top[u];
+                    const T a = col[row >= 0 ? row : 0], ri = sh_top_r[u];
+                    good = good && (row < 0 || dmmv_abs(dmmv_fma(delta, a, ri)) < t);
+                }
+                const unsigned long long b = __ballot(good);
+                if (b == 0) continue;                         // the same for everyone who scores this variable
+                klo = __builtin_ctzll(b);
+                khi = 63 - __builtin_clzll(b);
+            } else {                                          // lane = (row, bound): bisection
+                const int u = (lane >> 1) % ROWS;
+                const bool upper = (lane & 1) == 0;           // x < t, else x > -t
+                const int32_t row = sh_top[u];
+                const T a = row >= 0 ? col[row] : (T)0, ri = sh_top_r[u];
+                const bool prefix = upper == (a >= (T)0);     // the values that satisfy the bound are the first ones
+                int32_t x = klo, y = khi + 1;                 // first value that breaks (prefix) or satisfies it
+                const int32_t span = khi - klo + 1;
+                for (int32_t s = span; s > 0; s >>= 1) {      // the same number of steps in every lane
+                    if (x < y) {
+                        const int32_t mid = (x + y) >> 1;
+                        const T v = dmmv_fma(step_of(sh_D[mid], dcur, (T)1), a, ri);
+                        const bool good = upper ? v < t : v > -t;
+                        if (good != prefix) y = mid; else x = mid + 1;
+                    }
+                }
+                int32_t lo = !prefix && row >= 0 ? y : klo, hi = prefix && row >= 0 ? y - 1 : khi;
+                int32_t o;
+                o = dpp_int<DPP_QUAD_XOR1>(lo); lo = o > lo ? o : lo;
+                o = dpp_int<DPP_QUAD_XOR2>(lo); lo = o > lo ? o : lo;
+                o = dpp_int<DPP_ROW_HALF_MIRROR>(lo); lo = o > lo ? o : lo;
+                o = dpp_int<DPP_ROW_MIRROR>(lo); lo = o > lo ? o : lo;
+                o = dpp_int<DPP_QUAD_XOR1>(hi); hi = o < hi ? o : hi;
+                o = dpp_int<DPP_QUAD_XOR2>(hi); hi = o < hi ? o : hi;
+                o = dpp_int<DPP_ROW_HALF_MIRROR>(hi); hi = o < hi ? o : hi;
+                o = dpp_int<DPP_ROW_MIRROR>(hi); hi = o < hi ? o : hi;
+                klo = __builtin_amdgcn_readlane(lo, 0);
+                khi = __builtin_amdgcn_readlane(hi, 0);
+            }
+            // scores of the first KE of the values k0, k0 + stride, .. (clamped to khi): lane 8 q + x holds that of
+            // value q (the others infinity)
+            auto score = [&](auto ke, int32_t k0, int32_t stride) -> T {
+                constexpr int KE = decltype(ke)::value;
+                T delta[KE], acc[KE];
+#pragma unroll
+                for (int e = 0; e < KE; ++e) {
+                    const int64_t k = k0 + (int64_t)e * stride;
+                    delta[e] = step_of(sh_D[k < khi ? k : khi], dcur, (T)1);
+                    acc[e] = (T)0;
+                }
+                constexpr int STEP = COOP ? NT : 64, RB = KE == KT ? 2 : 4;
+                for (int64_t i0 = COOP ? tid : lane; i0 < m; i0 += RB * STEP) {
+                    T a[RB], ri[RB];
+#pragma unroll
+                    for (int u = 0; u < RB; ++u) {                      // past the end: a maximum does not mind the repeat
+                        const int64_t i = i0 + u * STEP < m ? i0 + u * STEP : i0;
+                        a[u] = col[i];
+                        ri[u] = sh_r[i];
+                    }
+#pragma unroll
+                    for (int u = 0; u < RB; ++u)
+#pragma unroll
+                        for (int e = 0; e < KE; ++e) acc[e] = dmmv_max(acc[e], dmmv_abs(dmmv_fma(delta[e], a[u], ri[u])));
+                }
+                const int q = lane >> 3, part = lane & 7;
+                T v;
+                if (KE == KT) {
+                    T* sc = sh_sc + w * KT * DP_SKEW;
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int e = 0; e < KE; ++e) sc[e * DP_SKEW + lane] = acc[e];
+                    __builtin_amdgcn_wave_barrier();
+                    v = (T)0;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v = dmmv_max(v, sc[q * DP_SKEW + part * 8 + e]);
+                    __builtin_amdgcn_wave_barrier();
+                    v = dmmv_max(v, dpp_mov<DPP_QUAD_XOR1>(v));
+                    v = dmmv_max(v, dpp_mov<DPP_QUAD_XOR2>(v));
+                    v = dmmv_max(v, dpp_mov<DPP_ROW_HALF_MIRROR>(v));
+                } else {
+                    v = Limits<T>::inf();
+#pragma unroll
+                    for (int e = 0; e < KE; ++e) { const T x = wave_max(acc[e]); if (q == e) v = x; }
+                }
+                if (COOP) {
+                    // (two buffers in turn: nobody writes one again before everyone has passed the next barrier)
+                    if (part == 0) sh_red[parity][w][q] = v;
+                    __syncthreads();
+#pragma unroll
+                    for (int x = 0; x < NWAVES; ++x) v = dmmv_max(v, sh_red[parity][x][q]);
+                    parity ^= 1;
+                }
+                return v;
+            };
+            constexpr std::integral_constant<int, KT> all{};
+            while (klo <= khi) {                              // uniform
+                const int32_t len = khi - klo + 1;
+                if (len <= KT) {
+                    const T v = len == 1 ? score(std::integral_constant<int, 1>{}, klo, 1)
+                                         : len == 2 ? score(std::integral_constant<int, 2>{}, klo, 1) : score(all, klo, 1);
+                    const T cs = (lane >> 3) < len ? v : Limits<T>::inf();
+                    const T smin = wave_min(cs);
+                    const int64_t c = j * (int64_t)nd + klo + (__builtin_ctzll(__ballot(cs == smin)) >> 3);
+                    if (rec_less(smin, c, ws, wc)) { ws = smin; wc = c; }
+                    break;
+                }
+                const int32_t stride = (len + KT - 3) / (KT - 1);     // the last sample is khi, or clamped to it
+                const T v = score(all, klo, stride);
+                const T smin = wave_min(v);
+                const unsigned long long hit = __ballot(v == smin);
+                const int e1 = __builtin_ctzll(hit) >> 3, e2 = (63 - __builtin_clzll(hit)) >> 3;
+                const int64_t after = klo + (int64_t)(e2 + 1) * stride;
+                const int32_t nlo = e1 > 0 ? klo + (e1 - 1) * stride + 1 : klo;
+                const int32_t nhi = e2 + 1 < KT && after <= khi ? (int32_t)after - 1 : khi;
+                if ((nhi - nlo + 1) * 2 > len + stride) {             // a plateau: score every value
+                    const int32_t kend = khi;
+                    for (int32_t k0 = klo; k0 <= kend; k0 += KT) {
+                        const T f = score(all, k0, 1);
+                        const T cs = k0 + (lane >> 3) <= kend ? f : Limits<T>::inf();
+                        const T fmin = wave_min(cs);
+                        const int64_t c = j * (int64_t)nd + k0 + (__builtin_ctzll(__ballot(cs == fmin)) >> 3);
+                        if (rec_less(fmin, c, ws, wc)) { ws = fmin; wc = c; }
+                    }
+                    break;
+                }
+                klo = nlo;
+                khi = nhi;
+            }
+        }
+        if (lane == 0) { sh_ws[w] = ws; sh_wc[w] = wc; }
+        __syncthreads();
+        // ---- one record per workgroup, the smallest of all -----------------------------------
+        if (w == 0) {
+            T bs = lane < NWAVES ? sh_ws[lane] : (T)0;
+            int64_t bc = lane < NWAVES ? sh_wc[lane] : (int64_t)-1;
+            wave_argmin(bs, bc);
+            if (lane == 0) dp_publish(rec, G, g, it, bs, bc);
+            T gs;
+            int64_t gc;
+            const bool fail = !dp_collect(rec, G, it, lane, wait_limit, flags, gs, gc);
+            if (lane == 0) {
+                sh_bs = gs;
+                sh_bc = gc;
+                if (fail) { sh_fail = 1; atomicOr(&flags[FLAG_ERROR], ERRBIT_WAIT_LIMIT); }
+            }
+        }
+        __syncthreads();
+        if (sh_fail) { failed = true; break; }
+        // ---- the same decision in every workgroup ------------------------------------------
+        const T s = sh_bs;
+        const int64_t c = sh_bc;
+        if (c >= 0 && s < t) {
+            last_s = s;
+            const int32_t j = (int32_t)(c / nd), k = (int32_t)(c % nd);
+            const T delta = step_of(sh_D[k], sh_D[sh_kidx[j]], (T)1);
+            if (g == 0 && tid == 0 && moves < iters) {
+                if (trace) { trace[moves].j = j; trace[moves].k = k; }
+                if (trace_t) trace_t[moves] = s;
+            }
+            const T* __restrict__ colg = A + lda * (int64_t)j;
+            T bv = (T)-1;
+            int32_t bi = -1;
+            rows_of(colg, [&](int64_t i, T a) {
+                const T v = dmmv_fma(delta, a, sh_r[i]);
+                sh_r[i] = v;
+                if (dmmv_abs(v) > bv) { bv = dmmv_abs(v); bi = (int32_t)i; }
+            });
+            top_row(bv, bi);
+            __syncthreads();                                  // every thread has read sh_kidx[j]
+            if (tid == 0) sh_kidx[j] = k;
+            t = s;
+            moves += 1;
+        } else {
+            stopped = true;
+        }
+        __syncthreads();
+    }
+    // ---- workgroup 0 hands the state back (after a failed wait the state is not written) ---
+    if (g != 0 || failed) return;
+    for (int64_t i = tid; i < m; i += NT) r[i] = sh_r[i];
+    for (int64_t j = tid; j < n; j += NT) kidx[j] = sh_kidx[j];
+    if (tid == 0) {
+        InstState<T> z = st[0];
+        z.t = t;
+        z.best_s = last_s;
+        z.apply_j = -1; z.apply_k = -1; z.delta = (T)0;
+        z.moves = moves;
+        z.done = stopped ? 1 : 0;
+        st[0] = z;
+    }
+}
+
 template <class T>
-dmmv_status run_t(Ctx* c, const Plan& pl, int32_t iters, dmmv_move* trace, void* trace_t) {
+dmmv_status run_t(Ctx* c, const Plan& pl, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t) {
     // iteration numbers start at 1: cleared records name no iteration
     uint64_t* rec = (uint64_t*)c->persist_exchange;
     const int words = 2 * DP_MAX_G * DP_REC_WORDS * 2;       // as 32-bit words
@@ -354,11 +714,34 @@ dmmv_status run_t(Ctx* c, const Plan& pl, int32_t iters, dmmv_move* trace, void*
     DMMV_TRY(ensure_dynamic_lds((const void*)kernel, (int)DP_LDS_LIMIT));
     hipLaunchKernelGGL(kernel, dim3((unsigned)pl.G), dim3(64 * pl.waves), pl.lds, c->stream,
                        c->p.m, c->p.n, c->p.nd, (const T*)c->p.A_dense, c->p.lda, (const T*)c->D_dev, (T*)c->r,
-                       c->kidx, c->o.radius, c->o.var_mask, (InstState<T>*)c->state, c->o.keep_going, iters, trace,
+                       c->kidx, c->o.radius, c->o.var_mask, (InstState<T>*)c->state, c->o.keep_going, steps, iters, trace,
                        (T*)trace_t, (int32_t)ceil_div(c->p.nd, DP_KT), (int32_t)pl.upw, (int32_t)pl.ncols, rec,
                        c->flags, wait_limit);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
+}
+
+template <class T>
+dmmv_status run_interval_t(Ctx* c, const PlanI& pl, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t) {
+    uint64_t* rec = (uint64_t*)c->persist_exchange;
+    const int words = 2 * DP_MAX_G * DP_REC_WORDS * 2;
+    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)ceil_div(words, 256)), dim3(256), 0, c->stream, (uint32_t*)rec, words);
+    const int32_t wait_limit = c->o.wait_limit > 0 ? c->o.wait_limit : DP_WAIT_DEFAULT;
+    auto launch = [&](auto kernel) -> dmmv_status {
+        DMMV_TRY(ensure_dynamic_lds((const void*)kernel, (int)DP_LDS_LIMIT));
+        hipLaunchKernelGGL(kernel, dim3((unsigned)pl.G), dim3(64 * pl.waves), pl.lds, c->stream, c->p.m, c->p.n, c->p.nd,
+                           (const T*)c->p.A_dense, c->p.lda, (const T*)c->D_dev, (T*)c->r, c->kidx, c->o.radius,
+                           c->o.var_mask, (InstState<T>*)c->state, steps, iters, trace, (T*)trace_t, (int32_t)pl.vpw, rec,
+                           c->flags, wait_limit);
+        DMMV_LAUNCH_CHECK();
+        return DMMV_OK;
+    };
+    auto by_mode = [&](auto waves) -> dmmv_status {
+        constexpr int W = decltype(waves)::value;
+        if (pl.coop) return pl.cols ? launch(k_descent_dense_interval<T, W, true, true>) : launch(k_descent_dense_interval<T, W, true, false>);
+        return pl.cols ? launch(k_descent_dense_interval<T, W, false, true>) : launch(k_descent_dense_interval<T, W, false, false>);
+    };
+    return pl.waves == 8 ? by_mode(std::integral_constant<int, 8>{}) : by_mode(std::integral_constant<int, 4>{});
 }
 
 }  // namespace
@@ -368,24 +751,37 @@ dmmv_status run_t(Ctx* c, const Plan& pl, int32_t iters, dmmv_move* trace, void*
 // (dmmv_create refuses the option otherwise).
 bool dense_persistent_fits(const dmmv_problem& p) { return make_plan(p, DP_MAX_G).G > 0; }
 
+// The descent itself takes the kernel with the shorter modelled iteration: scoring every value (few
+// levels and rows: 256 x 64 with 16 levels 4.3 us against 5.3) or only the intervals that can improve.
+static bool take_interval(const Ctx* c, const Plan& all, const PlanI& some) {
+    return !c->o.keep_going && some.G > 0 && (all.G == 0 || some.est_us < all.est_us);
+}
+
 bool dense_persistent_applicable(const Ctx* c) {
     if (c->kind != KIND_DENSE || c->o.dense_loop == 1 || !c->persist_exchange) return false;
     if (c->o.l2_rule == 1 || c->o.l2_rule == 2) return false;
     if (!c->o.keep_going && (c->o.value_search || c->o.prune)) return false;      // those have loops of their own
-    const Plan pl = make_plan(c->p, device_cus());
-    if (pl.G == 0) return false;
+    const Plan all = make_plan(c->p, device_cus());
+    const PlanI some = make_plan_interval(c->p, c->o.radius, device_cus());
+    const bool interval = take_interval(c, all, some);
+    if (!interval && all.G == 0) return false;
+    const double est_us = interval ? some.est_us : all.est_us;
     if (c->o.dense_loop == 2) return true;
     const double pairs = (double)c->p.m * (double)c->p.n * (double)c->p.nd;
     const double launches_us = DP_LAUNCH_LOOP_US + pairs * (c->p.dtype == DMMV_F64 ? DP_LAUNCH_LOOP_US_PER_PAIR_F64
                                                                                    : DP_LAUNCH_LOOP_US_PER_PAIR_F32);
-    return pl.est_us < launches_us;
+    return est_us < launches_us;
 }
 
-dmmv_status dense_descent_persistent(Ctx* c, int32_t iters, dmmv_move* trace, void* trace_t) {
+dmmv_status dense_descent_persistent(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t) {
     const Plan pl = make_plan(c->p, device_cus());
+    const PlanI some = make_plan_interval(c->p, c->o.radius, device_cus());
+    if (take_interval(c, pl, some))
+        return c->p.dtype == DMMV_F64 ? run_interval_t<double>(c, some, steps, iters, trace, trace_t)
+                                      : run_interval_t<float>(c, some, steps, iters, trace, trace_t);
     if (pl.G == 0) return fail(DMMV_ERR_STATE, "one-launch dense descent: the instance does not fit");
-    return c->p.dtype == DMMV_F64 ? run_t<double>(c, pl, iters, trace, trace_t)
-                                  : run_t<float>(c, pl, iters, trace, trace_t);
+    return c->p.dtype == DMMV_F64 ? run_t<double>(c, pl, steps, iters, trace, trace_t)
+                                  : run_t<float>(c, pl, steps, iters, trace, trace_t);
 }
 
 }  // namespace dmmv

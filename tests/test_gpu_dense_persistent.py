@@ -159,3 +159,67 @@ def test_one_launch_descent_bounded_wait_reports_instead_of_hanging():
     with m.from_instance(inst, DEV, dense_loop=2) as h:
         res = m.dmmv_solve(h, T(x0), 50, trace=True)
         assert int(res.iters_done[0]) == o.iters_done and N(res.max_violation)[0] == o.t
+
+
+# ---- the descent's own one-launch kernel: intervals of the values that can improve -----------------
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("shape", [(255, 700, 5),        # a wavefront per variable, several each
+                                   (256, 33, 64), (64, 257, 9),
+                                   (3000, 20, 300), (513, 5, 4000)])  # long intervals, narrowed by samples
+def test_one_launch_intervals_random(shape, dtype):
+    mm, nn, nd = shape
+    print("one-launch intervals", shape, dtype.__name__, flush=True)
+    inst = random_dense(1900 + mm + nn, mm, nn, nd, dtype=dtype)
+    x0 = np.random.default_rng(nn).choice(inst.D, size=inst.n)
+    o = check(inst, 25, x0=x0)
+    assert o.iters_done >= 1
+    check(inst, 10, x0=x0, radius=1)
+
+
+@pytest.mark.parametrize("shape", [(6000, 520, 3), (9001, 12, 2000)])
+def test_one_launch_intervals_columns_in_memory(shape):
+    """fp64 instances whose columns do not fit beside r in LDS (the automatic choice takes them)."""
+    mm, nn, nd = shape
+    m = dmmv()
+    inst = random_dense(1990 + mm, mm, nn, nd, dtype=np.float64)
+    x0 = np.random.default_rng(nn).choice(inst.D, size=inst.n)
+    o = orc.solve_dense(inst.A, inst.b, inst.D, x0, 8)
+    with m.from_instance(inst, DEV) as h:
+        assert m.dmmv_loop_in_use(h) == 2
+        res = m.dmmv_solve(h, T(x0), 8, trace=True)
+        d = int(res.iters_done[0])
+        assert d == o.iters_done and np.array_equal(N(res.trace)[0, :d, 0], o.trace_j)
+        assert np.array_equal(N(m.dmmv_get_state(h)[1]), o.r)
+
+
+def test_one_launch_intervals_plateaus_and_zero_columns():
+    """Scores that are flat over many values (rows no step can reach, columns of zeros and of one entry):
+    the samples tie and every value of the interval is scored; the lowest index wins."""
+    rng = np.random.default_rng(5)
+    for nd in (40, 300):
+        A = np.zeros((90, 24))
+        A[rng.integers(0, 90, 20), np.arange(20)] = rng.choice([-1.0, 1.0, 2.0], 20)
+        A[:, 20] = rng.integers(-1, 2, 90)
+        b = rng.integers(-30, 31, 90).astype(np.float64)
+        b[:6] = 200.0                                     # a maximum that one or no column touches
+        A[:6, 3] = 1.0
+        inst = random_dense(1, 90, 24, 4)
+        inst.A, inst.b = np.asfortranarray(A), b
+        inst.D = np.arange(nd, dtype=np.float64) - nd // 2
+        check(inst, 20, x0=rng.choice(inst.D, size=24))
+
+
+def test_alns_dense_one_launch_local_search_bounded_wait_runs_again():
+    """With a wait limit of one poll the one-launch local search gives up; the outer loop then runs again from
+    the starting point with a launch per step, and the result is the oracle's either way."""
+    m = dmmv()
+    inst = random_dense(77, 120, 40, 16, dtype=np.float64)
+    o = orc.alns_dense(inst.A, inst.b, inst.D, inst.x0, orc.alns_params(8, ls_moves=5, seed=3, destroy_count=3))
+    for limit in (0, 1):
+        with m.from_instance(inst, DEV, wait_limit=limit) as h:
+            for x0 in (T(inst.x0), None):
+                if x0 is None:
+                    m.dmmv_set_x(h, T(inst.x0))
+                res = m.dmmv_alns(h, x0, 8, ls_moves=5, seed=3, destroy_count=3)
+                assert np.array_equal(N(res.trace_t)[:, 0], o.t) and np.array_equal(N(res.x_best), o.x)
+                assert np.array_equal(N(res.trace)[:, 2], o.moves)
