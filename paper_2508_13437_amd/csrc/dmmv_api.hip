@@ -294,6 +294,28 @@ __global__ void k_maxabs_partial(const T* __restrict__ r, int64_t m, T* __restri
     }
 }
 
+// both stages in one workgroup, for vectors that a single one reads as fast as two launches take
+constexpr int64_t MAXABS_ONE_ROWS = 32768;      // 32 rows per thread
+template <class T>
+__global__ __launch_bounds__(1024) void k_maxabs_one(const T* __restrict__ r, int64_t m, InstState<T>* st) {
+    __shared__ T sh[16];
+    T v = (T)0;
+    for (int64_t i0 = threadIdx.x; i0 < m; i0 += 8 * 1024) {
+        T a[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = r[i0 + u * 1024 < m ? i0 + u * 1024 : m - 1];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v = dmmv_max(v, dmmv_abs(a[u]));
+    }
+    v = wave_max(v);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        v = wave_max(sh[threadIdx.x & 15]);
+        if (threadIdx.x == 0) st[0].t = v;
+    }
+}
+
 template <class T>
 __global__ void k_maxabs_final(const T* __restrict__ red, int nred, InstState<T>* st) {
     T v = (T)0;
@@ -458,6 +480,11 @@ static inline dim3 grid1(int64_t n, int block) { return dim3((unsigned)(n > 0 ? 
 
 template <class T>
 static dmmv_status maxabs_single(Ctx* c) {
+    if (c->p.m <= MAXABS_ONE_ROWS) {
+        hipLaunchKernelGGL(k_maxabs_one<T>, dim3(1), dim3(1024), 0, c->stream, (const T*)c->r, c->p.m, (InstState<T>*)c->state);
+        DMMV_LAUNCH_CHECK();
+        return DMMV_OK;
+    }
     const int nblk = (int)(c->p.m > 0 ? (ceil_div(c->p.m, 1024) < c->red_elems ? ceil_div(c->p.m, 1024) : c->red_elems) : 1);
     hipLaunchKernelGGL(k_maxabs_partial<T>, dim3(nblk), dim3(256), 0, c->stream, (const T*)c->r, c->p.m, (T*)c->red);
     hipLaunchKernelGGL(k_maxabs_final<T>, dim3(1), dim3(256), 0, c->stream, (const T*)c->red, nblk, (InstState<T>*)c->state);
@@ -469,7 +496,7 @@ static dmmv_status maxabs_single(Ctx* c) {
 // (sparse: also rebuilds the reservoir of the rows of largest |r|)
 static dmmv_status refresh_t(Ctx* c) {
     if (c->kind == KIND_BATCHED) return batched_maxabs(c);
-    if (c->kind == KIND_CSC) DMMV_TRY(csc_reservoir(c));
+    if (c->kind == KIND_CSC) return csc_reservoir(c, true);
     return c->p.dtype == DMMV_F64 ? maxabs_single<double>(c) : maxabs_single<float>(c);
 }
 

@@ -237,7 +237,7 @@ dmmv_status l2_after_apply_csc(Ctx* c, int32_t iters, dmmv_move* trace, void* tr
 
 dmmv_status csc_build(Ctx* c);
 dmmv_status csc_residual(Ctx* c);
-dmmv_status csc_reservoir(Ctx* c);      // rebuild the reservoir of largest |r| from r
+dmmv_status csc_reservoir(Ctx* c, bool set_t = false);   // rebuild the reservoir of largest |r| from r (set_t: t too)
 dmmv_status csc_eval(Ctx* c, void* scores_out, bool want_partials, bool honor_done);
 dmmv_status csc_apply(Ctx* c);          // staged move only; caller refreshes t and the reservoir
 dmmv_status csc_select_apply(Ctx* c, int32_t iters, dmmv_move* trace, void* trace_t, bool pruned);

@@ -1,0 +1,37 @@
+"""Residuals of single instances, bitwise against the oracle, at the edges of the kernels' tiles: rows longer and
+shorter than a pass, empty rows, a row count that leaves a wavefront part empty, more levels than LDS
+holds, more columns than a staged tile; and t = max |r| after each."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as orc
+from workloads import random_dense, random_sparse
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def check(inst, want):
+    from paper_2508_13437_amd import dmmv
+    with dmmv.from_instance(inst, DEV) as h:
+        dmmv.dmmv_set_x(h, torch.from_numpy(inst.x0).to(DEV))
+        r = dmmv.dmmv_residual(h).cpu().numpy()
+        t = float(dmmv.dmmv_get_state(h)[2][0])
+    assert np.array_equal(r, want) and t == (np.abs(want).max() if want.size else 0.0)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("m,n,nd,density", [(1, 1, 2, 1.0), (15, 64, 3, 1.0), (17, 65, 3, 1.0), (63, 300, 4, 0.9),
+                                            (65, 129, 1500, 0.5), (200, 500, 3, 0.004), (130, 40, 5, 0.0)])
+def test_csr_residual_tiles(m, n, nd, density, dtype):
+    inst = random_sparse(8100 + m, m, n, nd, density=density, dtype=dtype)
+    check(inst, orc.residual_csr(inst.m, inst.csr_rowptr, inst.csr_col, inst.csr_val, inst.b, inst.D, inst.x0))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("m,n", [(1, 1), (63, 15), (65, 16), (130, 17), (64, 1023), (70, 1025), (33000, 3)])
+def test_dense_residual_tiles(m, n, dtype):
+    inst = random_dense(8200 + m + n, m, n, 5, dtype=dtype)
+    check(inst, orc.residual_dense(inst.A, inst.b, inst.D, inst.x0))
