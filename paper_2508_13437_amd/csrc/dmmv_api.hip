@@ -173,7 +173,10 @@ size_t workspace_layout(const dmmv_problem& p, const dmmv_options& o, Ctx* c, ch
     } else if (batched) {
         c->chunk_cols = batched_chunk_cols(p);
         c->n_partials = ceil_div(p.n, c->chunk_cols);
-        b.take(&c->partials, (size_t)(c->n_partials > 0 ? c->n_partials : 1) * p.R * part_sz);
+        // (records of either evaluation kernel; the one over lists may write a few more for very wide batches)
+        int64_t n_rec = c->n_partials > 0 ? c->n_partials : 1;
+        if (batched_lists_applicable(p, o) && batched_lists_records(p.n, p.R) > n_rec) n_rec = batched_lists_records(p.n, p.R);
+        b.take(&c->partials, (size_t)n_rec * p.R * part_sz);
         b.take(&c->Xt, (size_t)p.m * p.n * esz);
         b.take(&c->Bt, (size_t)p.m * p.R * esz);
         b.take(&c->cmp_r, (size_t)p.m * p.R * esz);
@@ -187,6 +190,18 @@ size_t workspace_layout(const dmmv_problem& p, const dmmv_options& o, Ctx* c, ch
             c->mfma_ldk = mfma_ldk(p.n);
             b.take(&c->Xp, (size_t)3 * p.m * c->mfma_ldk * sizeof(uint16_t));
             b.take(&c->Qt, (size_t)p.R * c->mfma_ldk * sizeof(uint16_t));
+        }
+        // The lists of the evaluation, unless they alone would take the workspace past what
+        // dmmv_solve_static holds (then the kernel that scores all rows works without them).
+        c->use_lists = false;
+        if (batched_lists_applicable(p, o)) {
+            const size_t without = (b.off + 255) / 256 * 256, extra = batched_lists_bytes(p, nullptr, nullptr);
+            if (without > (size_t)DMMV_STATIC_SCRATCH_BYTES || without + extra <= (size_t)DMMV_STATIC_SCRATCH_BYTES) {
+                c->use_lists = true;
+                char* at = nullptr;
+                b.take(&at, extra);
+                batched_lists_bytes(p, &c->lists, at);
+            }
         }
     } else {
         c->n_partials = dense_num_partials(p);
@@ -504,7 +519,7 @@ template <class T>
 static dmmv_status select_t(Ctx* c, dmmv_move* best_out, void* best_score_out) {
     if (c->kind == KIND_BATCHED) {
         hipLaunchKernelGGL(k_select_batched<T>, grid1(c->p.R, 256), dim3(256), 0, c->stream,
-                           (const Partial<T>*)c->partials, c->p.n > 0 ? c->n_partials : 0, c->p.R,
+                           (const Partial<T>*)c->partials, c->p.n == 0 ? 0 : c->use_lists ? batched_lists_records(c->p.n, c->p.R) : c->n_partials, c->p.R,
                            (InstState<T>*)c->state, (const T*)c->D_dev, (const T*)c->scale_dev,
                            (const int32_t*)c->kidx, c->p.nd, c->o.keep_going, best_out,
                            (T*)best_score_out);

@@ -83,6 +83,17 @@ enum { FLAG_ERROR = 0, FLAG_ACTIVE = 1, FLAG_PLANES = 2, FLAG_MAXROW = 3, FLAG_M
 // error bits set by kernels
 enum { ERRBIT_X_NOT_IN_D = 1, ERRBIT_CSR_RANGE = 2, ERRBIT_CSR_DUP = 4, ERRBIT_MOVE_RANGE = 8, ERRBIT_WAIT_LIMIT = 16 };
 
+// batch: rows that decide a score (k_eval_lists)
+struct ListTables {
+    float* rT;            // [R][m] r, instance-major
+    uint16_t* rrow;       // [R][list] rows of largest |r| of an instance, descending
+    float* rval;          //   their r
+    float* rmark;         // [R][marks] largest |r| of what is left before every 16th of them
+    uint16_t* crow;       // [list][n] the same for the columns of X
+    float* cval;
+    float* cmark;         // [marks][n]
+};
+
 struct Ctx {
     dmmv_problem p;
     dmmv_options o;
@@ -129,6 +140,8 @@ struct Ctx {
     void* Xt;             // T[m][n] row-major copy of X
     void* Bt;             // T[m][R]
     int32_t chunk_cols;   // columns per chunk of the fused evaluation (n_partials chunks)
+    bool use_lists;       // the evaluation scores only the rows that can decide a move
+    ListTables lists;
     // ALNS outer loop (per instance; batched handles only with options.alns)
     void* alns_state;         // AlnsState[R]
     int32_t* alns_kidx_cur;   // [n] current (last accepted) solution
@@ -243,6 +256,11 @@ dmmv_status csc_apply(Ctx* c);          // staged move only; caller refreshes t 
 dmmv_status csc_select_apply(Ctx* c, int32_t iters, dmmv_move* trace, void* trace_t, bool pruned);
 dmmv_status csc_eval_pruned(Ctx* c, bool honor_done);   // records of the columns of the worst row only
 
+bool batched_lists_applicable(const dmmv_problem& p, const dmmv_options& o);
+size_t batched_lists_bytes(const dmmv_problem& p, ListTables* t, char* base);
+dmmv_status batched_lists_build(Ctx* c);                // the columns' lists, once per handle
+int64_t batched_lists_records(int64_t n, int64_t R);    // arg-min records per instance
+dmmv_status batched_eval_lists(Ctx* c, void* scores_out, bool want_partials);
 bool batched_eval_mfma_applicable(const dmmv_problem& p);
 int64_t batched_eval_mfma_rt_elems(const dmmv_problem& p);
 dmmv_status batched_eval_mfma_build(Ctx* c);

@@ -1,0 +1,83 @@
+"""Batched evaluation over the rows that can decide a move (fp32, 256 rows and more): score tables, arg-mins and
+descents bitwise against the oracle - lists that suffice, lists that run out (rows all alike, so that every row
+is scored), ties that overflow a list, radius and mask, ragged variables, stopped and packed instances."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as orc
+from workloads import llm_layer, random_batched
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def T(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def check(inst, radius=0, mask=None, samples=4):
+    from paper_2508_13437_amd import dmmv
+    nd = len(inst.D)
+    kw = dict(radius=radius)
+    if mask is not None:
+        kw["var_mask"] = T(mask)
+    with dmmv.from_instance(inst, DEV, **kw) as h:
+        dmmv.dmmv_set_x(h, T(inst.x0))
+        r = dmmv.dmmv_residual(h).cpu().numpy()
+        table = dmmv.dmmv_eval_moves(h).cpu().numpy()
+        best, best_s = dmmv.dmmv_argmin_move(h)
+        best, best_s = best.cpu().numpy(), best_s.cpu().numpy()
+    for q in range(inst.R):
+        c = int(np.argmin(table[q]))
+        assert best_s[q] == table[q, c] and best[q, 0] * nd + best[q, 1] == c, q
+    for q in sorted({0, inst.R - 1, *np.random.default_rng(1).integers(0, inst.R, samples).tolist()}):
+        want = orc.eval_moves_dense(inst.A, inst.D, inst.x0[q], r[q], scale=inst.scale[q], radius=radius,
+                                    var_mask=None if mask is None else mask[q])
+        assert np.array_equal(table[q], np.asarray(want).reshape(-1)), q
+
+
+@pytest.mark.parametrize("m,n,R,nd", [(256, 64, 3, 16), (257, 65, 5, 16), (300, 300, 4, 8), (511, 130, 7, 4),
+                                      (700, 70, 66, 2), (900, 100, 5, 21), (400, 257, 9, 6), (2000, 40, 3, 300)])
+def test_batched_lists_random(m, n, R, nd):
+    check(random_batched(8300 + m, m, n, R, nd))
+
+
+@pytest.mark.parametrize("m,n,R,nd", [(256, 33, 20, 13), (600, 80, 9, 8), (1200, 20, 5, 4)])
+def test_batched_lists_integer_ties(m, n, R, nd):
+    check(random_batched(8400 + m, m, n, R, nd, integer=True))
+
+
+def test_batched_lists_run_out():
+    """Entries of one magnitude whose sign is that of the residual: a step against it lowers every row, so no score
+    reaches the bound and all rows are scored."""
+    rng = np.random.default_rng(3)
+    inst = random_batched(8500, 800, 90, 6, 16)
+    sign = rng.choice(np.float32([-1.0, 1.0]), 800)
+    inst.A[:] = sign[:, None]
+    inst.b[:] = -(1000.0 + rng.uniform(size=inst.b.shape)) * sign[None, :]
+    check(inst)
+    inst.A[:, ::3] = 0.0                                     # columns of equal values: an empty list
+    inst.A[700:, 1::3] = 1e-38
+    check(inst)
+
+
+def test_batched_lists_radius_and_mask():
+    inst = random_batched(8600, 500, 140, 10, 16)
+    mask = (np.random.default_rng(4).uniform(size=(10, 140)) < 0.6).astype(np.uint8)
+    check(inst, radius=2)
+    check(inst, radius=1, mask=mask)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_batched_lists_layer_descent(bits):
+    """A small layer with outlier channels to its local optimum (instances stop at different moves and are packed)."""
+    from paper_2508_13437_amd import dmmv
+    inst = llm_layer(8700 + bits, tokens=330, features=150, rows=70, bits=bits, iters=40)
+    check(inst)
+    with dmmv.from_instance(inst, DEV) as h:
+        res = dmmv.dmmv_solve(h, T(inst.x0), 40, trace=True)
+    o = orc.solve_batched(inst.A, inst.b, inst.D, inst.scale, inst.x0, 40)
+    assert np.array_equal(res.iters_done.cpu().numpy(), o.iters_done)
+    assert np.array_equal(res.x.cpu().numpy(), o.x) and np.array_equal(res.max_violation.cpu().numpy(), o.t)
