@@ -134,7 +134,8 @@ struct Ctx {
     void* res_floor;      // T[1] floor value
     int32_t csc_max_row;  // most stored entries in one row (slots of the pruned evaluation)
     int32_t csc_max_col;  // most entries of one column, the segments' padding included
-    void* prune_part;     // Partial<T>[n] records of the pruned evaluation (options.prune)
+    bool csc_prune;       // the descent scores the columns of the worst row only
+    void* prune_part;     // Partial<T>[csc_max_row at most] records of that
 
     // batched
     void* Xt;             // T[m][n] row-major copy of X
