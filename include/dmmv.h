@@ -142,8 +142,10 @@ typedef struct {
                                 values are scored per variable and the moves applied are the same
                                 as with the full evaluation.  dmmv_eval_moves and
                                 dmmv_argmin_move always score all                                */
-    int32_t batched_eval;    /* batched problems: which kernel scores the moves.  0 or 1 = the
-                                vector-unit kernel (default); 2 = the matrix-core kernel, for fp32
+    int32_t batched_eval;    /* batched problems: which kernel scores the moves.  0 or 1 = on the
+                                vector unit (default; in fp32 with 256 to 16384 rows only the rows that
+                                can decide a score are looked at, same scores); 2 = the matrix-core
+                                kernel over all rows, for fp32
                                 with nd <= 32 (dmmv_create fails with DMMV_ERR_UNSUPPORTED
                                 otherwise; it needs R * m more floats of workspace).  It forms every
                                 fused multiply-add as one element of an outer product with K = 1,
@@ -174,7 +176,9 @@ typedef struct {
                                 evaluation and one of selection + apply per iteration.  2 = all
                                 iterations in ONE launch: a fixed grid of at most 256 workgroups shares
                                 the moves, each keeps r, its columns of A, D and x in LDS, and they
-                                exchange one arg-min record per iteration through memory (needs r, D, x
+                                exchange one arg-min record per iteration through memory (without
+                                keep_going they score only the values of D that can improve where that
+                                is the shorter iteration; needs r, D, x
                                 and one column to fit 156 KiB of LDS; dmmv_create fails with
                                 DMMV_ERR_UNSUPPORTED otherwise).  0 = automatic: 2 when it fits and a model
                                 of both loops says its iteration is the shorter one, else 1.  Same

@@ -339,12 +339,30 @@ size_t batched_lists_bytes(const dmmv_problem& p, ListTables* t, char* base) {
     return off;
 }
 
+// the kernel of a number of levels, as launch(kernel, rot)
+template <class F>
+static dmmv_status with_kernel(int32_t nd, F launch) {
+    if (nd == 16) return launch(k_eval_lists<15, true>, true);
+    if (nd == 8) return launch(k_eval_lists<7, true>, true);
+    if (nd == 4) return launch(k_eval_lists<3, true>, true);
+    if (nd > 8) return launch(k_eval_lists<16, false>, false);
+    if (nd > 4) return launch(k_eval_lists<8, false>, false);
+    return launch(k_eval_lists<4, false>, false);
+}
+
+static size_t eval_lds(const dmmv_problem& p, bool rot, bool table) {
+    return (size_t)(p.m + p.nd) * sizeof(float) + (rot && table ? (size_t)4 * 64 * (p.nd + 1) * sizeof(float) : 0);
+}
+
 dmmv_status batched_lists_build(Ctx* c) {
     const ListTables& t = c->lists;
     hipLaunchKernelGGL(k_list_top, dim3((unsigned)c->p.n), dim3(256), 0, c->stream, c->p.m, c->p.n, (const float*)c->p.A_dense,
                        c->p.lda, t.crow, t.cval, t.cmark, c->p.n, (int64_t)1);
     DMMV_LAUNCH_CHECK();
-    return DMMV_OK;
+    // (here and not at a launch: an evaluation may be captured)
+    return with_kernel(c->p.nd, [&](auto kernel, bool rot) -> dmmv_status {
+        return eval_lds(c->p, rot, true) > 64 * 1024 ? ensure_dynamic_lds((const void*)kernel, 128 * 1024) : DMMV_OK;
+    });
 }
 
 // variables per workgroup: as many as leave some 4096 workgroups, so that staging r is shared
@@ -366,24 +384,16 @@ dmmv_status batched_eval_lists(Ctx* c, void* scores, bool want_partials) {
     hipLaunchKernelGGL(k_list_top, dim3((unsigned)R), dim3(256), 0, c->stream, m, R, (const float*)t.rT, m, t.rrow, t.rval,
                        t.rmark, (int64_t)1, (int64_t)LT_LEN);
     const int32_t groups = list_groups(n, R);
-    auto launch = [&](auto kernel, bool rot) -> dmmv_status {
-        size_t lds = (size_t)(m + c->p.nd) * sizeof(float);
-        if (rot && scores) lds += (size_t)4 * 64 * (c->p.nd + 1) * sizeof(float);
-        DMMV_TRY(ensure_dynamic_lds((const void*)kernel, 128 * 1024));
-        hipLaunchKernelGGL(kernel, dim3((unsigned)R, (unsigned)batched_lists_records(n, R)), dim3(256), lds, c->stream, m, n, R,
+    return with_kernel(c->p.nd, [&](auto kernel, bool rot) -> dmmv_status {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)R, (unsigned)batched_lists_records(n, R)), dim3(256),
+                           eval_lds(c->p, rot, scores != nullptr), c->stream, m, n, R,
                            c->p.nd, groups, (const float*)c->Xt, (const float*)c->D_dev, (const int32_t*)c->kidx,
                            (const float*)c->scale_dev, (const float*)t.rT, t.rrow, t.rval, t.rmark, t.crow, t.cval, t.cmark,
                            c->o.radius, c->o.var_mask, (const InstState<float>*)c->state, (float*)scores,
                            want_partials ? (Partial<float>*)c->partials : nullptr);
         DMMV_LAUNCH_CHECK();
         return DMMV_OK;
-    };
-    if (c->p.nd == 16) return launch(k_eval_lists<15, true>, true);
-    if (c->p.nd == 8) return launch(k_eval_lists<7, true>, true);
-    if (c->p.nd == 4) return launch(k_eval_lists<3, true>, true);
-    if (c->p.nd > 8) return launch(k_eval_lists<16, false>, false);
-    if (c->p.nd > 4) return launch(k_eval_lists<8, false>, false);
-    return launch(k_eval_lists<4, false>, false);
+    });
 }
 
 }  // namespace dmmv
