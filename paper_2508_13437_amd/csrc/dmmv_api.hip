@@ -795,6 +795,9 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
     // error bit is raised, and the same run is made again from the saved starting point with a launch per
     // step.  (The arg-min records of that loop, 16 bytes per variable and more, are free meanwhile.)
     const bool one_launch = prm.ls_moves > 0 && !batched_pruned_applicable(c) && dense_persistent_applicable(c);
+    // (a shorter wait than that of a single descent, some 0.1 s: every outer iteration waits anew, and the way
+    // out is the loop of launches)
+    if (one_launch && c->o.wait_limit == 0) c->o.wait_limit = 1 << 17;
     dmmv_status st = [&]() -> dmmv_status {
         if (!one_launch) return run(false);
         const size_t xbytes = (size_t)c->p.n * sizeof(int32_t);
