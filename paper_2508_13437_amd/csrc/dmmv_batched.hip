@@ -495,7 +495,8 @@ static dmmv_status eval_t(Ctx* c, void* scores, bool want_partials) {
 template <class T>
 static dmmv_status apply_t(Ctx* c, bool t_from_score, int32_t iters, dmmv_move* trace, void* trace_t) {
     const int64_t m = c->p.m, R = c->p.R;
-    const int32_t rows_per_block = 64;
+    // 64 rows a block, more where the rows would take more blocks than a grid's second dimension holds
+    const int32_t rows_per_block = (int32_t)(m > 65535ll * 64 ? ceil_div(m, 65535) : 64);
     dim3 grid((unsigned)ceil_div(R, 64), (unsigned)(m > 0 ? ceil_div(m, rows_per_block) : 1));
     hipLaunchKernelGGL(k_apply_batched<T>, grid, dim3(64), 0, c->stream, m, c->p.n, R,
                        (const T*)c->p.A_dense, c->p.lda, (T*)c->r, c->kidx, (InstState<T>*)c->state,

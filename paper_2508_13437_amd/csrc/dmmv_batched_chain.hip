@@ -143,6 +143,7 @@ __global__ __launch_bounds__(64 * WA * WB) void k_residual_chain(
 bool batched_chain_applicable(const Ctx* c) {
     const int64_t lim = (int64_t)1 << 32;
     return c->kind == KIND_BATCHED && c->p.dtype == DMMV_F32 && !c->cmp_on && c->p.m > 0 && c->p.n > 0 &&
+           c->p.R <= 65535 * 16 &&   // the grid's second dimension, at the smallest tile's 16 instances
            (c->p.lda * (c->p.n - 1) + c->p.m) * 4 < lim && c->p.n * c->p.R * 4 < lim;
 }
 

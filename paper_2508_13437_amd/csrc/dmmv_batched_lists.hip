@@ -317,7 +317,8 @@ __global__ void k_list_transpose(const float* __restrict__ in, int64_t rows, int
 
 // Taken for fp32 batches whose r fits LDS and whose lists are worth sorting.
 bool batched_lists_applicable(const dmmv_problem& p, const dmmv_options& o) {
-    return p.dtype == DMMV_F32 && o.batched_eval != 2 && p.m >= LT_MIN_ROWS && p.m <= LT_MAX_ROWS && p.n > 0 && p.n <= (1 << 23) && p.nd <= 4096;
+    return p.dtype == DMMV_F32 && o.batched_eval != 2 && p.m >= LT_MIN_ROWS && p.m <= LT_MAX_ROWS && p.n > 0 && p.n <= (1 << 23) &&
+           p.R <= (1 << 23) && p.nd <= 4096;   // a workgroup of 256 threads for each column and each instance: under 2^32 threads
 }
 
 size_t batched_lists_bytes(const dmmv_problem& p, ListTables* t, char* base) {
