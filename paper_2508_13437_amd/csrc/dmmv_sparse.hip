@@ -297,7 +297,7 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
                                   int32_t* res_row, int32_t* meta, T* floor_val) {
     if (m <= RES_CAP) {
         // everything fits: the floor admits every row
-        for (int32_t u = threadIdx.x; u < (int32_t)m; u += blockDim.x) { L.v[u] = dmmv_abs(ld_coherent(r + u)); L.r[u] = u; }
+        for (int32_t u = threadIdx.x; u < (int32_t)m; u += blockDim.x) { L.v[u] = row_key(ld_coherent(r + u)); L.r[u] = u; }
         __syncthreads();
         reservoir_publish(L, (int32_t)m, false, res_val, res_row, meta, floor_val);
         if (threadIdx.x == 0) { floor_val[0] = (T)-1; meta[RES_FLOOR_ROW] = INT32_MAX; }
@@ -316,13 +316,13 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
         for (; i + (RES_BATCH - 1) * step < m; i += RES_BATCH * step) {
             T a8[RES_BATCH];
 #pragma unroll
-            for (int e = 0; e < RES_BATCH; ++e) a8[e] = dmmv_abs(ld_coherent(r + i + e * step));
+            for (int e = 0; e < RES_BATCH; ++e) a8[e] = row_key(ld_coherent(r + i + e * step));
 #pragma unroll
             for (int e = 0; e < RES_BATCH; ++e)
                 if (key_before(a8[e], (int32_t)(i + e * step), mv, mr)) { mv = a8[e]; mr = (int32_t)(i + e * step); }
         }
         for (; i < m; i += step) {
-            const T a = dmmv_abs(ld_coherent(r + i));
+            const T a = row_key(ld_coherent(r + i));
             if (key_before(a, (int32_t)i, mv, mr)) { mv = a; mr = (int32_t)i; }
         }
     }
@@ -365,7 +365,7 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
             for (; i + (RES_BATCH - 1) * step < m; i += RES_BATCH * step) {
                 T a8[RES_BATCH];
 #pragma unroll
-                for (int e = 0; e < RES_BATCH; ++e) a8[e] = dmmv_abs(ld_coherent(r + i + e * step));
+                for (int e = 0; e < RES_BATCH; ++e) a8[e] = row_key(ld_coherent(r + i + e * step));
 #pragma unroll
                 for (int e = 0; e < RES_BATCH; ++e)
                     if (!key_before(fv, fr, a8[e], (int32_t)(i + e * step))) {      // key before-or-equal floor
@@ -374,7 +374,7 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
                     }
             }
             for (; i < m; i += step) {
-                const T a = dmmv_abs(ld_coherent(r + i));
+                const T a = row_key(ld_coherent(r + i));
                 if (!key_before(fv, fr, a, (int32_t)i)) {
                     const int32_t pos = atomicAdd(&L.count, 1);
                     if (pos < RES_COLLECT) { L.v[pos] = a; L.r[pos] = (int32_t)i; }
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(SA_BLOCK) void k_select_apply_cscp(
         if (incremental) {
             // pads sit at the end of a segment: give them row INT32_MAX-ish keys past the real ones
             sh_srow[u] = pad ? INT32_MAX : (int32_t)i;
-            sh_sval[u] = dmmv_abs(nv);
+            sh_sval[u] = row_key(nv);
         }
     }
     __syncthreads();

@@ -18,6 +18,12 @@ __device__ __forceinline__ bool key_before(T a1, int32_t r1, T a2, int32_t r2) {
     return (a1 > a2) || (a1 == a2 && r1 < r2);
 }
 
+// |r| of a row as the order above takes it.  A NaN (a residual that overflowed) counts as 0, which is what
+// a maximum that drops it makes of it; as itself it would be neither before nor after any other row, two rows would share
+// a rank and another rank would stay empty.
+template <class T>
+__device__ __forceinline__ T row_key(T r) { return dmmv_max((T)0, dmmv_abs(r)); }
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_mov_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);

@@ -1,12 +1,12 @@
 """Residuals of single instances, bitwise against the oracle, at the edges of the kernels' tiles: rows longer and
 shorter than a pass, empty rows, a row count that leaves a wavefront part empty, more levels than LDS
-holds, more columns than a staged tile; and t = max |r| after each."""
+holds, more columns than a staged tile; and t = max |r| after each, rows of NaN left out of it."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import oracle as orc
-from workloads import random_dense, random_sparse
+from workloads import random_batched, random_dense, random_sparse
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +35,28 @@ def test_csr_residual_tiles(m, n, nd, density, dtype):
 def test_dense_residual_tiles(m, n, dtype):
     inst = random_dense(8200 + m + n, m, n, 5, dtype=dtype)
     check(inst, orc.residual_dense(inst.A, inst.b, inst.D, inst.x0))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("m", [5, 128, 129, 700, 3000])
+def test_max_violation_leaves_nan_rows_out(m, dtype):
+    """A residual with NaN rows (one that overflowed): t is the maximum over the other rows for every storage kind, also
+    when the NaN is the first row, when few rows are left and when none is."""
+    from paper_2508_13437_amd import dmmv
+    rng = np.random.default_rng(m)
+    insts = [random_sparse(8150 + m, m, 60, 3, density=0.2, dtype=dtype), random_dense(8150 + m, m, 6, 3, dtype=dtype),
+             random_batched(8150 + m, m, 6, 2, 4, dtype=dtype)]
+    for inst in insts:
+        R = inst.R if inst.kind == "batched" else 1
+        with dmmv.from_instance(inst, DEV) as h:
+            dmmv.dmmv_set_x(h, torch.from_numpy(inst.x0).to(DEV))
+            for nans in (1, m // 2, m - 1, m):
+                r = rng.standard_normal((R, m)).astype(dtype)
+                r[:, rng.permutation(m)[:nans]] = np.nan
+                if nans > 1:
+                    r[:, 0] = np.nan
+                for _ in range(2):
+                    dmmv.dmmv_set_residual(h, torch.from_numpy(r).to(DEV).reshape(h._rshape()))
+                    t = dmmv.dmmv_get_state(h)[2].cpu().numpy()
+                    want = np.where(np.isnan(r), dtype(0), np.abs(r)).max(1)
+                    assert np.array_equal(t, want), (inst.kind, nans)
