@@ -162,7 +162,7 @@ __global__ void k_cscp_ranges(int64_t n, int32_t P, int32_t gbp, const int32_t* 
 // entries, 246 us in fp64 on 26 765 x 34 969 with 4.1 M).  A wavefront takes RC_ROWS rows: 64 consecutive
 // entries of each are read coalesced, the levels looked up, and (value, level) pairs laid into LDS; then
 // lane = row runs its chain over them while the next 64 entries of every row are in flight.  Entries past a
-// row's end are zeros, which leave the sum alone.  Now 52 us and 32 us.
+// row's end are -0 times +0, which leaves any sum alone, also one of -0.  Now 52 us and 32 us.
 constexpr int RC_ROWS = 16;                    // rows per wavefront (64 would leave small matrices with too few wavefronts)
 constexpr int RC_DCAP = 1024;                  // levels kept in LDS
 
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void k_residual_csr(int64_t m, int64_t nnz, co
         for (int g = 0; g < RC_ROWS; ++g) {
             const bool in = read_lane(e0, g) + at + lane < read_lane(e1, g);
             const T dv = d_lds ? L.D[k[g]] : D[k[g]];
-            L.a[w][g][lane] = in ? va[g] : (T)0;
+            L.a[w][g][lane] = in ? va[g] : -(T)0;
             L.d[w][g][lane] = in ? dv : (T)0;
         }
         if (at + 64 < longest) fetch(at + 64);

@@ -31,6 +31,25 @@ def test_csr_residual_tiles(m, n, nd, density, dtype):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("m,n", [(1, 1), (17, 65), (40, 130)])
+def test_csr_residual_keeps_the_sign_of_zero(m, n, dtype):
+    """Products that underflow to -0: the sum is -0, also where a row is shorter than a pass of 64 entries."""
+    from paper_2508_13437_amd import dmmv
+    inst = random_sparse(8180 + m, m, n, 3, density=1.0, dtype=dtype)
+    tiny = np.finfo(dtype).tiny
+    inst.csr_val[:] = -tiny
+    inst.D = np.array([0.0, tiny, 1.0], dtype)
+    inst.x0[:] = tiny
+    inst.b[:] = 0.0
+    want = orc.residual_csr(inst.m, inst.csr_rowptr, inst.csr_col, inst.csr_val, inst.b, inst.D, inst.x0)
+    with dmmv.from_instance(inst, DEV) as h:
+        dmmv.dmmv_set_x(h, torch.from_numpy(inst.x0).to(DEV))
+        r = dmmv.dmmv_residual(h).cpu().numpy()
+    assert np.signbit(want).all() and not want.any() and not r.any()
+    assert np.signbit(r).all()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("m,n", [(1, 1), (63, 15), (65, 16), (130, 17), (64, 1023), (70, 1025), (33000, 3)])
 def test_dense_residual_tiles(m, n, dtype):
     inst = random_dense(8200 + m + n, m, n, 5, dtype=dtype)
