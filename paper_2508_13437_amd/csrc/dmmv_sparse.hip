@@ -165,6 +165,21 @@ __global__ void k_cscp_ranges(int64_t n, int32_t P, int32_t gbp, const int32_t* 
 // row's end are -0 times +0, which leaves any sum alone, also one of -0.  Now 52 us and 32 us.
 constexpr int RC_ROWS = 16;                    // rows per wavefront (64 would leave small matrices with too few wavefronts)
 constexpr int RC_DCAP = 1024;                  // levels kept in LDS
+constexpr int RC_SHORT = 12;                   // longest row up to which k_residual_csr_short is taken
+
+// Short rows: a lane per row, entry by entry.  In the other kernel a row costs a pass of 64 entries however short it
+// is: dmmv_residual on 300 000 rows takes 112 us with it at 1 as at 12 entries a row (fp64 147 to 151), with this one 80 and
+// 99 (97 and 145); at 16 entries 115 against 125 (152 against 211).
+template <class T>
+__global__ void k_residual_csr_short(int64_t m, const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+                                     const T* __restrict__ val, const T* __restrict__ D, const int32_t* __restrict__ kidx,
+                                     const T* __restrict__ b, T* __restrict__ r) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= m) return;
+    T acc = (T)0;
+    for (int64_t e = rowptr[i]; e < rowptr[i + 1]; ++e) acc = dmmv_fma(val[e], D[kidx[col[e]]], acc);
+    r[i] = dmmv_fma(acc, (T)1, -b[i]);
+}
 
 template <class T>
 struct ResidualShared {
@@ -605,6 +620,13 @@ static dmmv_status build_t(Ctx* c) {
 template <class T>
 static dmmv_status residual_t(Ctx* c) {
     if (c->p.m == 0) return DMMV_OK;
+    if (c->csc_max_row <= RC_SHORT) {
+        hipLaunchKernelGGL(k_residual_csr_short<T>, dim3((unsigned)ceil_div(c->p.m, 256)), dim3(256), 0, c->stream,
+                           c->p.m, c->p.csr_rowptr, c->p.csr_col, (const T*)c->p.csr_val, (const T*)c->D_dev,
+                           (const int32_t*)c->kidx, (const T*)c->p.b, (T*)c->r);
+        DMMV_LAUNCH_CHECK();
+        return DMMV_OK;
+    }
     hipLaunchKernelGGL(k_residual_csr<T>, dim3((unsigned)ceil_div(c->p.m, 4 * RC_ROWS)), dim3(256), 0, c->stream,
                        c->p.m, c->p.nnz, c->p.csr_rowptr, c->p.csr_col, (const T*)c->p.csr_val, (const T*)c->D_dev,
                        c->p.nd, (const int32_t*)c->kidx, (const T*)c->p.b, (T*)c->r);

@@ -31,6 +31,20 @@ def test_csr_residual_tiles(m, n, nd, density, dtype):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("m,longest", [(1, 1), (255, 12), (257, 12), (300, 13), (600, 1)])
+def test_csr_residual_short_rows(m, longest, dtype):
+    """Rows of 0 to `longest` entries, on both sides of the length up to which a lane takes a whole row."""
+    inst = random_sparse(8160 + m, m, 40, 4, density=1.0, dtype=dtype)
+    rng = np.random.default_rng(m)
+    lens = rng.integers(0, longest + 1, m)
+    lens[m // 2] = longest
+    at = np.concatenate([inst.csr_rowptr[i] + np.sort(rng.choice(40, lens[i], replace=False)) for i in range(m)]).astype(int)
+    inst.csr_col, inst.csr_val = inst.csr_col[at].copy(), inst.csr_val[at].copy()
+    inst.csr_rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    check(inst, orc.residual_csr(inst.m, inst.csr_rowptr, inst.csr_col, inst.csr_val, inst.b, inst.D, inst.x0))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("m,n", [(1, 1), (17, 65), (40, 130)])
 def test_csr_residual_keeps_the_sign_of_zero(m, n, dtype):
     """Products that underflow to -0: the sum is -0, also where a row is shorter than a pass of 64 entries."""
