@@ -441,9 +441,12 @@ __global__ void k_argmin_table(const T* __restrict__ scores, int64_t ntab, int32
     }
 }
 
-// The same for a single instance's table in two stages, the first over many workgroups (one workgroup read
-// 105 000 fp64 scores in 37 us).
+// The same for a single instance's table in two stages, the first over many workgroups: 6.4 to 7.6 us (by the card)
+// whatever the size up to 200 000 scores, a second launch among them.  One workgroup takes 4.2 / 5.9 / 7.1 / 8.1 us for
+// 12 000 / 24 000 / 32 000 / 40 000 scores (fp64 4.4 / 6.1 / 7.0 / 8.3) and 17 for 100 000, so it keeps the tables up to
+// ARGMIN_STAGES.
 constexpr int ARGMIN_BLOCKS = 256;
+constexpr int64_t ARGMIN_STAGES = 36000;
 template <class T>
 __global__ __launch_bounds__(256) void k_argmin_table_part(const T* __restrict__ scores, int64_t ntab, Partial<T>* __restrict__ part) {
     __shared__ T sh_s[4];
@@ -1116,14 +1119,13 @@ dmmv_status dmmv_argmin_move(dmmv_handle h, const void* scores, dmmv_move* best,
     }
     if (scores) {
         const int64_t ntab = h->p.n * (int64_t)h->p.nd;
-        // a single instance's table of more than a workgroup's few passes: two stages, whose records take the
-        // evaluation's place (idle between calls)
+        // a large table of a single instance: two stages, whose records take the evaluation's place (idle between calls)
         int64_t blocks = ceil_div(ntab, 1024);
         if (blocks > ARGMIN_BLOCKS) blocks = ARGMIN_BLOCKS;
         if (blocks > h->n_partials) blocks = h->n_partials;
         auto run = [&](auto zero) {
             using T = decltype(zero);
-            if (h->kind != KIND_BATCHED && ntab > 8192 && blocks > 1) {
+            if (h->kind != KIND_BATCHED && ntab > ARGMIN_STAGES && blocks > 1) {
                 hipLaunchKernelGGL(k_argmin_table_part<T>, dim3((unsigned)blocks), dim3(256), 0, h->stream, (const T*)scores, ntab, (Partial<T>*)h->partials);
                 hipLaunchKernelGGL(k_argmin_records<T>, dim3(1), dim3(256), 0, h->stream, (const Partial<T>*)h->partials, (int)blocks, h->p.nd, best, (T*)best_score);
             } else {

@@ -12,7 +12,7 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
-@pytest.mark.parametrize("n,nd", [(64, 128), (91, 91), (1025, 8), (300, 999), (4000, 300)])
+@pytest.mark.parametrize("n,nd", [(64, 128), (91, 91), (1025, 8), (360, 100), (18001, 2), (5143, 7), (300, 999), (4000, 300)])
 def test_argmin_of_a_given_table(n, nd, dtype):
     from paper_2508_13437_amd import dmmv
     inst = random_dense(8800 + n, 3, n, nd, dtype=dtype)
