@@ -187,7 +187,10 @@ __global__ __launch_bounds__(256) void k_residual_batched_tiled(
 // per-instance max |r|: lane = instance, the rows split over workgroups and their wavefronts, the maxima
 // joined through memory (|r| >= 0: the bit patterns order like the values).  One workgroup per 64 instances
 // walked its 2048 rows one at a time: 39 us for 500 instances, now 9 with the clearing launch.
+// Few rows (ONE): a single workgroup per 64 instances after all, sixteen wavefronts with eight rows in flight
+// each, which stores its maxima: no clearing launch.
 constexpr int MB_ROWS = 128;                               // rows per workgroup (32 per wavefront)
+constexpr int64_t MB_ONE_ROWS = 512;                       // up to four passes of a wavefront in one workgroup
 template <class T>
 __global__ void k_clear_t(int64_t R, InstState<T>* st) {
     const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -197,19 +200,21 @@ __device__ __forceinline__ void raise_to(float* p, float v) { atomicMax(reinterp
 __device__ __forceinline__ void raise_to(double* p, double v) {
     atomicMax(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v));
 }
-template <class T>
-__global__ __launch_bounds__(256) void k_maxabs_batched(int64_t m, int64_t R, const T* __restrict__ r,
-                                                        InstState<T>* st) {
-    __shared__ T sh[4][64];
+template <class T, bool ONE>
+__global__ __launch_bounds__(ONE ? 1024 : 256) void k_maxabs_batched(int64_t m, int64_t R, const T* __restrict__ r,
+                                                                     InstState<T>* st) {
+    constexpr int WAVES = ONE ? 16 : 4;
+    __shared__ T sh[WAVES][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t q = blockIdx.x * 64ll + lane;
     const int64_t qc = q < R ? q : R - 1;
+    const int64_t rows = ONE ? m : MB_ROWS;                // per workgroup and pass
     T v = (T)0;
-    for (int64_t b0 = blockIdx.y * (int64_t)MB_ROWS; b0 < m; b0 += (int64_t)gridDim.y * MB_ROWS)
-        for (int64_t i0 = b0 + w; i0 < b0 + MB_ROWS && i0 < m; i0 += 4 * 8) {
+    for (int64_t b0 = blockIdx.y * rows; b0 < m; b0 += gridDim.y * rows)
+        for (int64_t i0 = b0 + w; i0 < b0 + rows && i0 < m; i0 += WAVES * 8) {
             T a[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = r[(i0 + 4 * u < m ? i0 + 4 * u : i0) * R + qc];
+            for (int u = 0; u < 8; ++u) a[u] = r[(i0 + WAVES * u < m ? i0 + WAVES * u : i0) * R + qc];
 #pragma unroll
             for (int u = 0; u < 8; ++u) v = dmmv_max(v, dmmv_abs(a[u]));
         }
@@ -217,8 +222,9 @@ __global__ __launch_bounds__(256) void k_maxabs_batched(int64_t m, int64_t R, co
     __syncthreads();
     if (w == 0 && q < R) {
 #pragma unroll
-        for (int ww = 1; ww < 4; ++ww) v = dmmv_max(v, sh[ww][lane]);
-        raise_to(&st[q].t, v);
+        for (int ww = 1; ww < WAVES; ++ww) v = dmmv_max(v, sh[ww][lane]);
+        if (ONE) st[q].t = v;
+        else raise_to(&st[q].t, v);
     }
 }
 
@@ -454,12 +460,17 @@ static dmmv_status residual_t(Ctx* c) {
 
 template <class T>
 static dmmv_status maxabs_t(Ctx* c) {
+    if (c->p.m <= MB_ONE_ROWS) {
+        hipLaunchKernelGGL((k_maxabs_batched<T, true>), dim3((unsigned)ceil_div(c->p.R, 64)), dim3(1024), 0, c->stream, c->p.m,
+                           c->p.R, (const T*)c->r, (InstState<T>*)c->state);
+        DMMV_LAUNCH_CHECK();
+        return DMMV_OK;
+    }
     int64_t rows = ceil_div(c->p.m, MB_ROWS);
     if (rows > 65535) rows = 65535;
     hipLaunchKernelGGL(k_clear_t<T>, dim3((unsigned)ceil_div(c->p.R, 256)), dim3(256), 0, c->stream, c->p.R, (InstState<T>*)c->state);
-    if (rows > 0)
-        hipLaunchKernelGGL(k_maxabs_batched<T>, dim3((unsigned)ceil_div(c->p.R, 64), (unsigned)rows), dim3(256), 0, c->stream,
-                           c->p.m, c->p.R, (const T*)c->r, (InstState<T>*)c->state);
+    hipLaunchKernelGGL((k_maxabs_batched<T, false>), dim3((unsigned)ceil_div(c->p.R, 64), (unsigned)rows), dim3(256), 0, c->stream,
+                       c->p.m, c->p.R, (const T*)c->r, (InstState<T>*)c->state);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
 }

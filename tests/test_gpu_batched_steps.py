@@ -31,7 +31,7 @@ def test_argmin_of_given_tables(n, nd, dtype):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
-@pytest.mark.parametrize("m,R", [(1, 2), (7, 65), (63, 3), (65, 64), (127, 4), (129, 130), (200, 5), (1025, 3)])
+@pytest.mark.parametrize("m,R", [(1, 2), (7, 65), (63, 3), (65, 64), (127, 4), (129, 130), (200, 5), (511, 70), (512, 2), (513, 66), (1025, 3)])
 def test_apply_and_max_violation(m, R, dtype):
     """Integer data: every product and sum is exact in any order, so the residual has one value."""
     from paper_2508_13437_amd import dmmv
