@@ -273,15 +273,23 @@ def cold_eval_ms(h, device: str, reps: int = 8):
 
 
 def descent_timing(inst, device: str, x0, iters: int) -> dict:
-    """The real descent (stops at the local optimum) with default options and with options.prune; both
-    score only the columns that touch the row of largest |r| (where no row is long) and apply the
-    moves of the full evaluation: an EFFECTIVE rate, reported apart from the full-table moves/s."""
+    """The real descent (stops at the local optimum) with every move scored (options.sparse_eval names the
+    kernels: 2, or 1 where the matrix has too many row partitions for it), with default options and with
+    options.prune, which scores only the columns that touch the row of largest |r| (the default does the same where
+    rows and columns are short) and applies the moves of the full evaluation: an EFFECTIVE rate, reported apart from the
+    full-table moves/s."""
     import torch
     from paper_2508_13437_amd import dmmv
 
     res = {}
-    for key, opt in (("default", {}), ("pruned", {"prune": True})):
-        with dmmv.from_instance(inst, device, poll_every=64, **opt) as h:
+    for key, opt in (("full", {"sparse_eval": 2}), ("default", {}), ("pruned", {"prune": True})):
+        try:
+            handle = dmmv.from_instance(inst, device, poll_every=64, **opt)
+        except dmmv.DmmvError as e:
+            if e.status != -8:                          # anything but "not implemented for this matrix"
+                raise
+            handle = dmmv.from_instance(inst, device, poll_every=64, sparse_eval=1)
+        with handle as h:
             dmmv.dmmv_solve(h, x0, iters)
             torch.cuda.synchronize()
             t0 = time.perf_counter()

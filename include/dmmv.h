@@ -117,8 +117,9 @@ typedef struct {
                                 with an entry in the row of largest |r_i|: a move that leaves
                                 that row alone cannot lower the maximum, so the moves applied are
                                 the same as with the full evaluation and an iteration costs far
-                                less (done also with 0 when no row holds more than an eighth of the
-                                variables).  Batches of instances: 1 = the descent bounds every move
+                                less.  With 0 and sparse_eval = 0 this is done where it is the shorter
+                                iteration: no row holds more than an eighth of the variables and no
+                                column is long for a wavefront of its own.  Batches of instances: 1 = the descent bounds every move
                                 from below by its score on 16 rows of large |r_i| (a maximum over
                                 some rows never exceeds the maximum over all) and scores over all
                                 rows only the moves, in ascending order of bound, that can still

@@ -32,6 +32,12 @@ dmmv_status dmmv_time_l2(dmmv_handle h, int32_t reps, float* ms_out);
  * answers 2).  HOST query, no GPU work. */
 int32_t dmmv_loop_in_use(dmmv_handle h);
 
+/* How the descent scores an iteration on this handle with the neighbourhood `radius` (that of the handle's
+ * options for dmmv_solve, ls_radius for dmmv_alns): 1 = every move, 2 = pruned (sparse: the columns of the
+ * row of largest |r|; batches and small dense instances: by lower bounds), 3 = options.value_search.
+ * 0 = no handle, or radius < 0.  HOST query, no GPU work. */
+int32_t dmmv_scoring_in_use(dmmv_handle h, int32_t radius);
+
 #ifdef __cplusplus
 }
 #endif

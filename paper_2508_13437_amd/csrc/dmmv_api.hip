@@ -938,13 +938,25 @@ static dmmv_status ctx_setup(dmmv_ctx* c, const dmmv_problem* problem, const dmm
         DMMV_HIP_CHECK(hipMemcpyAsync(&c->csc_max_col, &c->flags[FLAG_MAXCOL], sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
         DMMV_HIP_CHECK(hipStreamSynchronize(c->stream));
         if (c->csc_max_row > c->p.n) c->csc_max_row = (int32_t)c->p.n;   // duplicates are an error anyway
-        // The descent scores the columns of the worst row only (options.prune) also unasked where no row holds
-        // more than an eighth of the variables: it then reads at most about that share of the matrix, if less
-        // evenly than the full evaluation (5.2 us against 21.8 on 65 340 x 65 536, 360 entries in the longest row).  Its
-        // records, 16 bytes per entry of that row, then fit the two-kernel evaluation's table of at
-        // least 8 bytes per variable, which is idle meanwhile.
+        // The descent scores the columns of the worst row only (options.prune) also unasked, unless sparse_eval names the
+        // kernels.  One wavefront then takes a whole column, so the longest column sets the time, where the full evaluation
+        // gives a column eight lanes (two-kernel form: per partition) and needs the whole matrix.  Hence: no row
+        // longer than an eighth of the variables, and one of
+        // - no column longer than CSC_PRUNE_COL.  us per move, worst row's columns against all, 2 to 64 levels: tomography of
+        //   65 340 x 65 536 (228 entries a column) 12.4 against 30; 4000 x 400 (528) fp64 17 to 44 against 24 to 80; 12 000 x
+        //   1200 (1056) fp64, the closest, 36 to 82 against 41 to 117;
+        // - the full evaluation is the one-kernel form, whose eight lanes take the column through all partitions:
+        //   200 000 x 800 (24 000) 275 against 870; 60 000 x 30 000 (2148) 64 against 167; one full column among short ones,
+        //   20 000 x 4000, 555 against 641;
+        // - the matrix holds CSC_PRUNE_SHARE times its longest column: 150 000 x 65 000 (1543) fp64 90 against 314,
+        //   16 000 x 16 000 (2036) fp64 61 against 90.
+        // Elsewhere the full evaluation is the faster one or close to it (fp64, 200 000 x 800 159 against 355; 65 000 x 4000 of 6443
+        // entries 98 against 123; 33 000 x 2000 of 3323 57 against 62; 33 000 x 2000 of 1099 47 against 44).
+        // The records, 16 bytes per entry of the longest row, fit the two-kernel evaluation's table of at least 8 bytes
+        // per variable, which is idle meanwhile.
         c->csc_prune = o.prune != 0;
-        if (!c->csc_prune && c->csc_max_row > 0 && (int64_t)c->csc_max_row * 8 <= c->p.n) {
+        if (!c->csc_prune && o.sparse_eval == 0 && c->csc_max_row > 0 && (int64_t)c->csc_max_row * 8 <= c->p.n &&
+            (c->csc_max_col <= CSC_PRUNE_COL || c->csc_fused || (int64_t)c->csc_max_col * CSC_PRUNE_SHARE <= c->p.nnz)) {
             c->csc_prune = true;
             c->prune_part = c->part_scores;
         }
@@ -1240,6 +1252,16 @@ dmmv_status dmmv_swap_move(dmmv_handle h, int32_t k_eps, int32_t apply, dmmv_swa
 int32_t dmmv_loop_in_use(dmmv_handle h) {
     if (!h) return 0;
     return (batched_pruned_applicable(h) || dense_persistent_applicable(h)) ? 2 : 1;
+}
+
+int32_t dmmv_scoring_in_use(dmmv_handle h, int32_t radius) {
+    if (!h || radius < 0) return 0;
+    Ctx c = *h;
+    c.o.radius = radius;
+    if (c.o.l2_rule == 1 || c.o.l2_rule == 2 || c.p.n == 0) return 1;
+    if (batched_pruned_applicable(&c)) return 2;
+    if (c.kind == KIND_CSC) return c.csc_prune && !c.o.keep_going ? 2 : 1;
+    return c.kind == KIND_DENSE && c.o.value_search && !c.o.keep_going ? 3 : 1;
 }
 
 dmmv_status dmmv_time_eval(dmmv_handle h, int32_t reps, float* ms_out) {

@@ -205,6 +205,10 @@ static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // columns per workgroup of the sparse finalize kernel (one arg-min record each)
 constexpr int CSC_FIN_BLOCK = 256;
+// longest column (padding included) up to which the descent scores the worst row's columns only unasked, and the
+// number of longest columns the matrix must hold where one is longer (the measurements are at the rule)
+constexpr int CSC_PRUNE_COL = 1024;
+constexpr int CSC_PRUNE_SHARE = 8192;
 // bytes of LDS a sparse evaluation workgroup may use for its partition of r
 // (64 KiB: two workgroups share a compute unit's 160 KiB, so one can stage while the other
 // streams)

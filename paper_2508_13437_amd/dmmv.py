@@ -28,7 +28,7 @@ EXPORTS = ("dmmv_workspace_bytes", "dmmv_create", "dmmv_destroy", "dmmv_set_x",
            "dmmv_set_residual", "dmmv_residual", "dmmv_eval_moves", "dmmv_argmin_move",
            "dmmv_apply_move", "dmmv_get_state", "dmmv_solve", "dmmv_solve_static", "dmmv_alns", "dmmv_swap_move",
            "dmmv_l2_changes",
-           "dmmv_time_eval", "dmmv_time_l2", "dmmv_loop_in_use",
+           "dmmv_time_eval", "dmmv_time_l2", "dmmv_loop_in_use", "dmmv_scoring_in_use",
            "dmmv_last_error",
            "dmmv_version")
 
@@ -100,6 +100,8 @@ def load() -> C.CDLL:
     lib.dmmv_swap_move.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
     lib.dmmv_loop_in_use.restype = C.c_int32
     lib.dmmv_loop_in_use.argtypes = [C.c_void_p]
+    lib.dmmv_scoring_in_use.restype = C.c_int32
+    lib.dmmv_scoring_in_use.argtypes = [C.c_void_p, C.c_int32]
     lib.dmmv_time_eval.restype = C.c_int
     lib.dmmv_time_eval.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_float)]
     lib.dmmv_time_l2.restype = C.c_int
@@ -435,6 +437,11 @@ def dmmv_swap_move(h: Handle, k_eps: int = 0, apply: bool = True) -> SwapResult:
 
 def dmmv_loop_in_use(h: Handle) -> int:
     return int(load().dmmv_loop_in_use(h._h))
+
+
+def dmmv_scoring_in_use(h: Handle, radius: int = 0) -> int:
+    """How the descent scores an iteration (include/dmmv_bench.h)."""
+    return int(load().dmmv_scoring_in_use(h._h, C.c_int32(radius)))
 
 
 def dmmv_time_eval(h: Handle, reps: int) -> float:

@@ -60,9 +60,13 @@ def test_tomography_whole_descent(prune):
     inst = config(3)
     o = tomography_oracle()
     assert 100 < o.iters_done < inst.iters            # a real local optimum, well past any prefix
-    with m.from_instance(inst, DEV, prune=prune) as h:
+    # (named kernels score every move; with the default options the descent prunes on this matrix unasked)
+    with m.from_instance(inst, DEV, **(dict(prune=True) if prune else dict(sparse_eval=2))) as h:
+        assert m.dmmv_scoring_in_use(h) == (2 if prune else 1)
         res = m.dmmv_solve(h, T(inst.x0), inst.iters, trace=True)
         x, r, t = m.dmmv_get_state(h)
+    with m.from_instance(inst, DEV) as h:
+        assert m.dmmv_scoring_in_use(h) == 2
     d = int(res.iters_done[0])
     assert d == o.iters_done
     tr = N(res.trace)[0]
