@@ -5,14 +5,22 @@
 // |X_ij|; after the first p of both, every row not met yet has |r_i| <= a and |X_ij| <= c, so its value is
 // at most fma(|delta|, c, a) - as computed, rounding is monotone - and once the running maximum of every
 // value of D has reached that bound the maximum is final (the threshold algorithm for top-1 queries
-// of Fagin, Lotem and Naor, PODS 2001).  The result is the exact score, bit for bit; a tile whose lists
-// run out is scored over all rows.
+// of Fagin, Lotem and Naor, PODS 2001).  The result is the exact score, bit for bit; a tile that the lists do not
+// decide is scored over all rows.
 // On activations with heavy tails some 50 of 2048 rows decide a tile at a rounded start and 150 at a local
 // optimum.  The kernel that scores all rows (k_eval_batched) is bound by the vector unit's multiply-adds, and
 // with an instance per lane it cannot skip rows: 18.3 ms for 4096 instances of 2048 x 4096 with 16
 // levels, 2.8 ms for 500, 0.37 ms for 20 of 2048 x 768 with 8; this one, its two launches before it
 // included, 0.95, 0.20 and 0.05 ms.  Bound by the vector unit still (about 27 instructions per row and 15
-// values); three wavefronts per SIMD (160 registers: 33 spill at four).
+// values); three wavefronts per SIMD (165 registers: 33 spill at four).
+// Whether the lists decide depends on the data, so what they may cost is bounded: a tile walks at most a quarter of m of
+// either (half of the rows in all), and after an eighth it looks whether the bound at that point is within reach of the
+// maxima it has; if not, it goes to all rows at once.  The walk over all rows uses a uniform pointer: 2.0 times as fast as
+// with an address computed per row.  Worst case, rows all alike and every move lowering all of them (us; all rows with
+// an instance per lane, then this kernel): 2048 x 2048, 256 instances, 16 levels 1026 and 732; 1024 x 1024, 256, 4 levels 109 and
+// 96; 300 x 2048, 256, 16 levels 153 and 152.  Only on batches that fill the chip by themselves is something lost there: 1024 x
+// 2048, 2000 instances, 16 / 8 / 4 levels 2415 / 1133 / 494 and 2609 / 1390 / 892, against 381 / 209 / 141 at a local optimum on
+// heavy-tailed and 381 / 206 / 140 on uniform data.
 //
 // Per handle: the LT_LEN rows of largest |X_ij| of every column (k_list_top on the columns of X).
 // Per evaluation: r transposed to [instance][row], the LT_LEN rows of largest |r| of every instance
@@ -147,7 +155,7 @@ __global__ __launch_bounds__(256, KT == 15 ? 3 : 4) void k_eval_lists(
     const float* __restrict__ D, const int32_t* __restrict__ kidx, const float* __restrict__ scale,
     const float* __restrict__ rT, const uint16_t* __restrict__ rrow, const float* __restrict__ rval,
     const float* __restrict__ rmark, const uint16_t* __restrict__ crow, const float* __restrict__ cval,
-    const float* __restrict__ cmark, int32_t radius, const uint8_t* __restrict__ var_mask,
+    const float* __restrict__ cmark, int32_t look, int32_t most, int32_t radius, const uint8_t* __restrict__ var_mask,
     const InstState<float>* __restrict__ st, float* __restrict__ scores, Partial<float>* __restrict__ part) {
     extern __shared__ __align__(16) unsigned char smem[];
     float* sh_r = reinterpret_cast<float*>(smem);           // [m]
@@ -200,7 +208,7 @@ __global__ __launch_bounds__(256, KT == 15 ? 3 : 4) void k_eval_lists(
                     acc[v] = 0.0f;
                 }
                 bool final = false;
-                for (int32_t p = 0; p < LT_LEN && !final; p += LT_STEP) {
+                for (int32_t p = 0; p < most && !final; p += LT_STEP) {
                     // the next rows of the column's list and of the instance's, all loads first
                     float x[LT_STEP], cx[LT_STEP], cr[LT_STEP];
                     uint16_t ci[LT_STEP];
@@ -241,20 +249,36 @@ __global__ __launch_bounds__(256, KT == 15 ? 3 : 4) void k_eval_lists(
 #pragma unroll
                     for (int v = 0; v < KT; ++v) ok = ok && acc[v] >= dmmv_fma(dmmv_abs(delta[v]), c, a);
                     final = __ballot(!ok) == 0ull;
+                    if (p + LT_STEP == look && !final) {    // is the bound after `most` rows within reach?
+                        const float ce = (cmark + (int64_t)(most / LT_STEP) * n + j0)[lc], ae = sh_mark[most / LT_STEP];
+                        ok = true;
+#pragma unroll
+                        for (int v = 0; v < KT; ++v) ok = ok && acc[v] >= dmmv_fma(dmmv_abs(delta[v]), ce, ae);
+                        if (__ballot(!ok) != 0ull) break;
+                    }
                 }
-                if (!final) {                               // the lists ran out: all rows
-                    for (int64_t i0 = 0; i0 < m; i0 += LT_STEP) {
+                if (!final) {                               // the lists do not decide: all rows
+                    const float* __restrict__ xp = Xt + j0;     // (uniform pointer and stride as above)
+                    int64_t stride = n;
+                    asm volatile("" : "+s"(stride));
+                    int64_t i0 = 0;
+                    for (; i0 + LT_STEP <= m; i0 += LT_STEP) {
                         float x[LT_STEP];
 #pragma unroll
-                        for (int u = 0; u < LT_STEP; ++u) x[u] = (Xt + (i0 + u < m ? i0 + u : m - 1) * n + j0)[lc];
+                        for (int u = 0; u < LT_STEP; ++u) { x[u] = xp[lc]; xp += stride; }
 #pragma unroll
                         for (int u = 0; u < LT_STEP; u += 2) {
-                            const float r0 = sh_r[i0 + u < m ? i0 + u : m - 1], r1 = sh_r[i0 + u + 1 < m ? i0 + u + 1 : m - 1];
+                            const float r0 = sh_r[i0 + u], r1 = sh_r[i0 + u + 1];
 #pragma unroll
                             for (int v = 0; v < KT; ++v)
                                 acc[v] = dmmv_max(dmmv_max(acc[v], dmmv_abs(dmmv_fma(delta[v], x[u], r0))),
                                                   dmmv_abs(dmmv_fma(delta[v], x[u + 1], r1)));
                         }
+                    }
+                    for (; i0 < m; ++i0, xp += stride) {
+                        const float x = xp[lc], ri = sh_r[i0];
+#pragma unroll
+                        for (int v = 0; v < KT; ++v) acc[v] = dmmv_max(acc[v], dmmv_abs(dmmv_fma(delta[v], x, ri)));
                     }
                 }
                 float* out = sh_out + (w * 64 + lane) * (nd + 1);
@@ -377,6 +401,12 @@ static int32_t list_groups(int64_t n, int64_t R) {
 
 int64_t batched_lists_records(int64_t n, int64_t R) { return ceil_div(ceil_div(n, 256), list_groups(n, R)); }
 
+// a `part`-th of the rows in whole steps, one at least and the list's length at most
+static int32_t list_limit(int64_t m, int64_t part) {
+    const int64_t rows = m / part / LT_STEP * LT_STEP;
+    return (int32_t)(rows < LT_STEP ? LT_STEP : rows > LT_LEN ? LT_LEN : rows);
+}
+
 dmmv_status batched_eval_lists(Ctx* c, void* scores, bool want_partials) {
     const ListTables& t = c->lists;
     const int64_t m = c->p.m, n = c->p.n, R = c->p.R;
@@ -385,12 +415,13 @@ dmmv_status batched_eval_lists(Ctx* c, void* scores, bool want_partials) {
     hipLaunchKernelGGL(k_list_top, dim3((unsigned)R), dim3(256), 0, c->stream, m, R, (const float*)t.rT, m, t.rrow, t.rval,
                        t.rmark, (int64_t)1, (int64_t)LT_LEN);
     const int32_t groups = list_groups(n, R);
+    const int32_t most = list_limit(m, 4), look = list_limit(m, 8);
     return with_kernel(c->p.nd, [&](auto kernel, bool rot) -> dmmv_status {
         hipLaunchKernelGGL(kernel, dim3((unsigned)R, (unsigned)batched_lists_records(n, R)), dim3(256),
                            eval_lds(c->p, rot, scores != nullptr), c->stream, m, n, R,
                            c->p.nd, groups, (const float*)c->Xt, (const float*)c->D_dev, (const int32_t*)c->kidx,
                            (const float*)c->scale_dev, (const float*)t.rT, t.rrow, t.rval, t.rmark, t.crow, t.cval, t.cmark,
-                           c->o.radius, c->o.var_mask, (const InstState<float>*)c->state, (float*)scores,
+                           look, most, c->o.radius, c->o.var_mask, (const InstState<float>*)c->state, (float*)scores,
                            want_partials ? (Partial<float>*)c->partials : nullptr);
         DMMV_LAUNCH_CHECK();
         return DMMV_OK;

@@ -1,6 +1,7 @@
 """Batched evaluation over the rows that can decide a move (fp32, 256 rows and more): score tables, arg-mins and
 descents bitwise against the oracle - lists that suffice, lists that run out (rows all alike, so that every row
-is scored), ties that overflow a list, radius and mask, ragged variables, stopped and packed instances."""
+is scored), lists given up after a first look, ties that overflow a list, radius and mask, ragged variables, stopped and
+packed instances, the largest number of rows, several groups of variables in a workgroup."""
 import numpy as np
 import pytest
 import torch
@@ -61,6 +62,41 @@ def test_batched_lists_run_out():
     inst.A[:, ::3] = 0.0                                     # columns of equal values: an empty list
     inst.A[700:, 1::3] = 1e-38
     check(inst)
+
+
+@pytest.mark.parametrize("m", [256, 300, 511, 512, 1040, 2100])
+def test_batched_lists_given_up(m):
+    """Entries of mixed size with the residual's sign: the bound after the rows that may be walked stays out of reach, for
+    some variables only (the others are of mixed sign), so neighbouring tiles are decided by lists and by all rows."""
+    rng = np.random.default_rng(m)
+    inst = random_batched(8520 + m, m, 200, 5, 8)
+    sign = rng.choice(np.float32([-1.0, 1.0]), m)
+    inst.A[:, 60:140] = sign[:, None] * np.abs(inst.A[:, 60:140])
+    inst.b[:] = -(1000.0 + rng.uniform(size=inst.b.shape) * 20) * sign[None, :]
+    check(inst)
+
+
+@pytest.mark.parametrize("m,nd", [(16384, 16), (16385, 16), (16384, 5), (16384, 4)])
+def test_batched_lists_most_rows(m, nd):
+    """The last number of rows whose r fits in LDS (with the score table's scratch beside it), and one more."""
+    check(random_batched(8540 + m + nd, m, 70, 3, nd), samples=1)
+
+
+def test_batched_lists_several_groups_and_packing():
+    """Two groups of 256 variables per workgroup with a ragged last one, fewer arg-min records than groups; the descent
+    packs the running instances, after which a workgroup takes one group."""
+    from paper_2508_13437_amd import dmmv
+    inst = random_batched(8560, 256, 2049, 1000, 4)
+    check(inst)
+    with dmmv.from_instance(inst, DEV) as h:
+        res = dmmv.dmmv_solve(h, T(inst.x0), 300, trace=True)
+    done = res.iters_done.cpu().numpy()
+    few, many = int(np.argmin(done)), int(np.argmax(done))
+    assert np.sort(done)[300] + 16 < done[many]              # a quarter had stopped at a polling point before the end
+    sel = np.array(sorted({few, many, 0, 499, 999}))
+    o = orc.solve_batched(inst.A, inst.b[sel], inst.D, inst.scale[sel], inst.x0[sel], 300)
+    assert np.array_equal(done[sel], o.iters_done)
+    assert np.array_equal(res.x.cpu().numpy()[sel], o.x) and np.array_equal(res.max_violation.cpu().numpy()[sel], o.t)
 
 
 def test_batched_lists_radius_and_mask():
