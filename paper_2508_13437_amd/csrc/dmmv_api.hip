@@ -193,14 +193,18 @@ size_t workspace_layout(const dmmv_problem& p, const dmmv_options& o, Ctx* c, ch
         }
         // The lists of the evaluation, unless they alone would take the workspace past what
         // dmmv_solve_static holds (then the kernel that scores all rows works without them).
-        c->use_lists = false;
+        // A handle whose descents are pruned never looks at them there: r transposed goes to the buffer of the packed
+        // residuals, which such a handle does not pack, and the columns are sorted by the first evaluation, if any.
+        c->use_lists = c->lists_ready = false;
+        c->lists_late = batched_pruned_asked(p, o);
+        c->lists.rT = reinterpret_cast<float*>(c->cmp_r);
         if (batched_lists_applicable(p, o)) {
-            const size_t without = (b.off + 255) / 256 * 256, extra = batched_lists_bytes(p, nullptr, nullptr);
+            const size_t without = (b.off + 255) / 256 * 256, extra = batched_lists_bytes(p, c->lists_late, nullptr, nullptr);
             if (without > (size_t)DMMV_STATIC_SCRATCH_BYTES || without + extra <= (size_t)DMMV_STATIC_SCRATCH_BYTES) {
                 c->use_lists = true;
                 char* at = nullptr;
                 b.take(&at, extra);
-                batched_lists_bytes(p, &c->lists, at);
+                batched_lists_bytes(p, c->lists_late, &c->lists, at);
             }
         }
     } else {
@@ -569,7 +573,7 @@ template <class T>
 static dmmv_status select_t(Ctx* c, dmmv_move* best_out, void* best_score_out) {
     if (c->kind == KIND_BATCHED) {
         hipLaunchKernelGGL(k_select_batched<T>, grid1(c->p.R, 256), dim3(256), 0, c->stream,
-                           (const Partial<T>*)c->partials, c->p.n == 0 ? 0 : c->use_lists ? batched_lists_records(c->p.n, c->p.R) : c->n_partials, c->p.R,
+                           (const Partial<T>*)c->partials, c->p.n == 0 ? 0 : batched_lists_in_use(c) ? batched_lists_records(c->p.n, c->p.R) : c->n_partials, c->p.R,
                            (InstState<T>*)c->state, (const T*)c->D_dev, (const T*)c->scale_dev,
                            (const int32_t*)c->kidx, c->p.nd, c->o.keep_going, best_out,
                            (T*)best_score_out);

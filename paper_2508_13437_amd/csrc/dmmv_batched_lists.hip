@@ -22,7 +22,8 @@
 // 2048, 2000 instances, 16 / 8 / 4 levels 2415 / 1133 / 494 and 2609 / 1390 / 892, against 381 / 209 / 141 at a local optimum on
 // heavy-tailed and 381 / 206 / 140 on uniform data.
 //
-// Per handle: the LT_LEN rows of largest |X_ij| of every column (k_list_top on the columns of X).
+// Per handle: the LT_LEN rows of largest |X_ij| of every column (k_list_top on the columns of X), at create, or at the
+// first evaluation where the descents are pruned and never come here.
 // Per evaluation: r transposed to [instance][row], the LT_LEN rows of largest |r| of every instance
 // (k_list_top on those), then k_eval_lists: a workgroup holds one instance's r in LDS, lane = variable,
 // the instance's rows are uniform (X read along its row-major copy), the column's rows are gathered
@@ -345,7 +346,7 @@ bool batched_lists_applicable(const dmmv_problem& p, const dmmv_options& o) {
            p.R <= (1 << 23) && p.nd <= 4096;   // a workgroup of 256 threads for each column and each instance: under 2^32 threads
 }
 
-size_t batched_lists_bytes(const dmmv_problem& p, ListTables* t, char* base) {
+size_t batched_lists_bytes(const dmmv_problem& p, bool late, ListTables* t, char* base) {
     size_t off = 0;
     auto take = [&](auto** out, size_t bytes) {
         off = (off + 255) / 256 * 256;
@@ -354,7 +355,7 @@ size_t batched_lists_bytes(const dmmv_problem& p, ListTables* t, char* base) {
     };
     ListTables dummy;
     if (!t) t = &dummy;
-    take(&t->rT, (size_t)p.R * p.m * sizeof(float));
+    if (!late) take(&t->rT, (size_t)p.R * p.m * sizeof(float));
     take(&t->rval, (size_t)p.R * LT_LEN * sizeof(float));
     take(&t->rmark, (size_t)p.R * LT_MARKS * sizeof(float));
     take(&t->cval, (size_t)p.n * LT_LEN * sizeof(float));
@@ -379,11 +380,31 @@ static size_t eval_lds(const dmmv_problem& p, bool rot, bool table) {
     return (size_t)(p.m + p.nd) * sizeof(float) + (rot && table ? (size_t)4 * 64 * (p.nd + 1) * sizeof(float) : 0);
 }
 
-dmmv_status batched_lists_build(Ctx* c) {
+static dmmv_status build_lists(Ctx* c) {
     const ListTables& t = c->lists;
     hipLaunchKernelGGL(k_list_top, dim3((unsigned)c->p.n), dim3(256), 0, c->stream, c->p.m, c->p.n, (const float*)c->p.A_dense,
                        c->p.lda, t.crow, t.cval, t.cmark, c->p.n, (int64_t)1);
     DMMV_LAUNCH_CHECK();
+    c->lists_ready = true;
+    return DMMV_OK;
+}
+
+bool batched_lists_in_use(const Ctx* c) { return c->use_lists && c->lists_ready; }
+
+// The columns' lists of a handle that was created without them.  Not inside a capture: the captured sort would run at a
+// replay, perhaps after an eager call that relied on it; such a call scores all rows.
+dmmv_status batched_lists_first_use(Ctx* c) {
+    if (c->lists_ready) return DMMV_OK;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capturing) != hipSuccess) {
+        (void)hipGetLastError();
+        return DMMV_OK;
+    }
+    return capturing == hipStreamCaptureStatusNone ? build_lists(c) : DMMV_OK;
+}
+
+dmmv_status batched_lists_prepare(Ctx* c) {
+    if (!c->lists_late) DMMV_TRY(build_lists(c));
     // (here and not at a launch: an evaluation may be captured)
     return with_kernel(c->p.nd, [&](auto kernel, bool rot) -> dmmv_status {
         return eval_lds(c->p, rot, true) > 64 * 1024 ? ensure_dynamic_lds((const void*)kernel, 128 * 1024) : DMMV_OK;

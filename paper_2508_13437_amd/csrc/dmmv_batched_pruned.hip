@@ -369,6 +369,15 @@ dmmv_status descent_t(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, vo
 
 }  // namespace
 
+static bool bp_fits(int64_t m, int64_t n, int32_t nd, int64_t R, size_t esz) {
+    return n > 0 && R <= INT32_MAX && m <= BP_MAX_ROWS && bp_lds_bytes(m, n, nd, esz) <= BP_LDS_LIMIT;
+}
+
+bool batched_pruned_asked(const dmmv_problem& p, const dmmv_options& o) {
+    return !p.csr_rowptr && (p.R > 1 || p.scale) && o.prune && !o.keep_going && o.l2_rule != 1 && o.l2_rule != 2 &&
+           bp_fits(p.m, p.n, p.nd, p.R, p.dtype == DMMV_F64 ? 8 : 4);
+}
+
 bool batched_pruned_applicable(const Ctx* c) {
     // a batch, or a dense single instance (a batch of one: r [m][1], x [n][1], scale 1, with the
     // row-major copy of A that dmmv_create makes for options.prune)
@@ -380,10 +389,7 @@ bool batched_pruned_applicable(const Ctx* c) {
     const bool kind_ok = c->kind == KIND_BATCHED || small_dense;
     if (!kind_ok || !c->o.prune || c->o.keep_going || c->cmp_on) return false;
     if (c->o.l2_rule == 1 || c->o.l2_rule == 2) return false;      // a bound on the score alone does not order (score, l2 change)
-    const int64_t m = c->p.m, n = c->p.n;
-    if (n <= 0 || c->p.R > INT32_MAX) return false;
-    if (m > BP_MAX_ROWS) return false;
-    return bp_lds_bytes(m, n, c->p.nd, c->esz) <= BP_LDS_LIMIT;
+    return bp_fits(c->p.m, c->p.n, c->p.nd, c->p.R, c->esz);
 }
 
 dmmv_status batched_descent_pruned(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t) {

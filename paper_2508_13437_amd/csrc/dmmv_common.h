@@ -142,6 +142,8 @@ struct Ctx {
     void* Bt;             // T[m][R]
     int32_t chunk_cols;   // columns per chunk of the fused evaluation (n_partials chunks)
     bool use_lists;       // the evaluation scores only the rows that can decide a move
+    bool lists_late;      //   the columns' lists are made by the first evaluation, not at create
+    bool lists_ready;     //   they are there
     ListTables lists;
     // ALNS outer loop (per instance; batched handles only with options.alns)
     void* alns_state;         // AlnsState[R]
@@ -262,8 +264,11 @@ dmmv_status csc_select_apply(Ctx* c, int32_t iters, dmmv_move* trace, void* trac
 dmmv_status csc_eval_pruned(Ctx* c, bool honor_done);   // records of the columns of the worst row only
 
 bool batched_lists_applicable(const dmmv_problem& p, const dmmv_options& o);
-size_t batched_lists_bytes(const dmmv_problem& p, ListTables* t, char* base);
-dmmv_status batched_lists_build(Ctx* c);                // the columns' lists, once per handle
+// bytes of the lists; `late` (the first evaluation makes the columns' lists): without room for rT, which t keeps
+size_t batched_lists_bytes(const dmmv_problem& p, bool late, ListTables* t, char* base);
+dmmv_status batched_lists_prepare(Ctx* c);              // at create: kernel attributes, the columns' lists unless late
+bool batched_lists_in_use(const Ctx* c);
+dmmv_status batched_lists_first_use(Ctx* c);
 int64_t batched_lists_records(int64_t n, int64_t R);    // arg-min records per instance
 dmmv_status batched_eval_lists(Ctx* c, void* scores_out, bool want_partials);
 bool batched_eval_mfma_applicable(const dmmv_problem& p);
@@ -296,6 +301,7 @@ dmmv_status dense_descent_persistent(Ctx* c, int32_t steps, int32_t iters, dmmv_
 // options.prune on a batch: `steps` iterations of the descent for every instance in one launch,
 // same moves as evaluation + selection + apply (an instance stops at its local optimum)
 bool batched_pruned_applicable(const Ctx* c);
+bool batched_pruned_asked(const dmmv_problem& p, const dmmv_options& o);   // every descent of such a batch is pruned
 dmmv_status batched_descent_pruned(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t);
 
 // ----------------------------------------------------------------------------------------

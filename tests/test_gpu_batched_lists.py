@@ -117,3 +117,48 @@ def test_batched_lists_layer_descent(bits):
     o = orc.solve_batched(inst.A, inst.b, inst.D, inst.scale, inst.x0, 40)
     assert np.array_equal(res.iters_done.cpu().numpy(), o.iters_done)
     assert np.array_equal(res.x.cpu().numpy(), o.x) and np.array_equal(res.max_violation.cpu().numpy(), o.t)
+
+
+def test_batched_lists_of_a_pruned_handle():
+    """A handle whose descents are pruned holds no r transposed of its own and sorts the columns at its first evaluation, not
+    at create; a first evaluation inside a graph capture scores all rows.  Same tables and moves throughout, whatever the
+    descent or the outer loop has left in the buffers in between."""
+    from paper_2508_13437_amd import dmmv
+    inst = random_batched(8580, 600, 300, 40, 8)
+    x0 = T(inst.x0)
+    with dmmv.from_instance(inst, DEV, alns=True) as h, dmmv.from_instance(inst, DEV, alns=True, prune=True) as hp:
+        assert h.workspace_bytes - hp.workspace_bytes >= inst.R * inst.m * 4 - 256
+        after = {}
+        for name, hh in (("all", h), ("pruned", hp)):
+            dmmv.dmmv_set_x(hh, x0)
+            dmmv.dmmv_residual(hh)
+            out = []
+            for _ in range(2):
+                out += [dmmv.dmmv_eval_moves(hh), *dmmv.dmmv_argmin_move(hh)]
+            out += [dmmv.dmmv_solve(hh, None, 5).x, dmmv.dmmv_eval_moves(hh)]
+            out += [dmmv.dmmv_alns(hh, None, 2, ls_moves=2, seed=4).x_best, dmmv.dmmv_residual(hh), dmmv.dmmv_eval_moves(hh)]
+            after[name] = [t.cpu().numpy() for t in out]
+    for a, b in zip(after["all"], after["pruned"]):
+        assert np.array_equal(a, b)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with dmmv.from_instance(inst, DEV, prune=True, stream=stream) as h:
+        with torch.cuda.stream(stream):
+            dmmv.dmmv_set_x(h, x0)
+            dmmv.dmmv_residual(h)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            table = dmmv.dmmv_eval_moves(h)
+            best, score = dmmv.dmmv_argmin_move(h)
+        for it in range(3):
+            table.zero_()
+            stream.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(stream):
+                graph.replay()
+            stream.synchronize()
+            assert np.array_equal(table.cpu().numpy(), after["all"][0]), it
+            assert np.array_equal(best.cpu().numpy(), after["all"][1]) and np.array_equal(score.cpu().numpy(), after["all"][2])
+            with torch.cuda.stream(stream):
+                eager = dmmv.dmmv_eval_moves(h)
+            stream.synchronize()
+            assert np.array_equal(eager.cpu().numpy(), after["all"][0]), it
