@@ -34,7 +34,10 @@ int32_t dmmv_loop_in_use(dmmv_handle h);
 
 /* How the descent scores an iteration on this handle with the neighbourhood `radius` (that of the handle's
  * options for dmmv_solve, ls_radius for dmmv_alns): 1 = every move, 2 = pruned (sparse: the columns of the
- * row of largest |r|; batches and small dense instances: by lower bounds), 3 = options.value_search.
+ * row of largest |r|; batches and small dense instances: by lower bounds), 3 = options.value_search,
+ * 4 and more = one launch of a dense instance that scores the interval of values that can improve: 4, + 8 where
+ * all wavefronts of a workgroup share one variable's rows, + 16 where its columns are kept in LDS, + 32 with eight
+ * wavefronts instead of four.
  * 0 = no handle, or radius < 0.  HOST query, no GPU work. */
 int32_t dmmv_scoring_in_use(dmmv_handle h, int32_t radius);
 

@@ -1265,7 +1265,10 @@ int32_t dmmv_scoring_in_use(dmmv_handle h, int32_t radius) {
     if (c.o.l2_rule == 1 || c.o.l2_rule == 2 || c.p.n == 0) return 1;
     if (batched_pruned_applicable(&c)) return 2;
     if (c.kind == KIND_CSC) return c.csc_prune && !c.o.keep_going ? 2 : 1;
-    return c.kind == KIND_DENSE && c.o.value_search && !c.o.keep_going ? 3 : 1;
+    if (c.kind != KIND_DENSE) return 1;
+    if (c.o.value_search && !c.o.keep_going) return 3;
+    const int32_t interval = dense_interval_in_use(&c);
+    return interval ? interval : 1;
 }
 
 dmmv_status dmmv_time_eval(dmmv_handle h, int32_t reps, float* ms_out) {

@@ -295,6 +295,7 @@ dmmv_status batched_compact_end(Ctx* c);
 size_t dense_persistent_exchange_bytes();
 bool dense_persistent_fits(const dmmv_problem& p);
 bool dense_persistent_applicable(const Ctx* c);
+int32_t dense_interval_in_use(const Ctx* c);   // the code of dmmv_scoring_in_use, 0 = another kernel
 // (at most `steps` iterations)
 dmmv_status dense_descent_persistent(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t);
 

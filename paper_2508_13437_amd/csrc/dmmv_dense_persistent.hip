@@ -384,12 +384,14 @@ __global__ __launch_bounds__(64 * NWAVES) void k_descent_dense_persistent(
 // otherwise a wavefront scores a variable by itself.
 constexpr int DI_KT = 8;                  // values scored together
 constexpr int DI_PF = 8;                  // loads of a thread in flight where rows come from memory
+constexpr double DI_COOP_US = 0.6;        // more for rounds that all wavefronts share (a barrier each), not near levels only
 
 struct PlanI {
     int G = 0, vpw = 0, waves = 0;
     bool coop = false, cols = false;
     size_t lds = 0;
     double est_us = 0;
+    double more_us = 0;   // what the choice between the two kernels counts on top
 };
 
 // Modelled like the plan above: exchange 2 us + 4 ns per workgroup, 1.6 us for the rest of an
@@ -421,6 +423,7 @@ PlanI make_plan_interval(const dmmv_problem& p, int32_t radius, int cus) {
                 best.G = (int)G; best.vpw = (int)vpw; best.waves = waves; best.coop = coop != 0; best.cols = cols;
                 best.lds = base + (cols ? (size_t)vpw * p.m * w : 0);
                 best.est_us = est;
+                best.more_us = coop && !near ? DI_COOP_US : 0.0;
             }
         }
     return best;
@@ -752,9 +755,13 @@ dmmv_status run_interval_t(Ctx* c, const PlanI& pl, int32_t steps, int32_t iters
 bool dense_persistent_fits(const dmmv_problem& p) { return make_plan(p, DP_MAX_G).G > 0; }
 
 // The descent itself takes the kernel with the shorter modelled iteration: scoring every value (few
-// levels and rows: 256 x 64 with 16 levels 4.3 us against 5.3) or only the intervals that can improve.
+// levels and rows: 256 x 64 with 16 levels 4.3 us against 5.3) or only the intervals that can improve.  Where the two come
+// close, the barriers of rounds that the wavefronts share decide: 1024 x 64 with 16 levels in fp64 takes 7.3 us by
+// intervals and 6.0 with every value scored, 5.6 and 5.8 by the model alone.  Of 378 measured choices (66 shapes, both types,
+// random and filter matrices, radius 0, 1 and 2) one is by then the slower one, 2048 x 512 with 64 levels in fp32, 10.8 against
+// 10.5.
 static bool take_interval(const Ctx* c, const Plan& all, const PlanI& some) {
-    return !c->o.keep_going && some.G > 0 && (all.G == 0 || some.est_us < all.est_us);
+    return !c->o.keep_going && some.G > 0 && (all.G == 0 || some.est_us + some.more_us < all.est_us);
 }
 
 bool dense_persistent_applicable(const Ctx* c) {
@@ -771,6 +778,13 @@ bool dense_persistent_applicable(const Ctx* c) {
     const double launches_us = DP_LAUNCH_LOOP_US + pairs * (c->p.dtype == DMMV_F64 ? DP_LAUNCH_LOOP_US_PER_PAIR_F64
                                                                                    : DP_LAUNCH_LOOP_US_PER_PAIR_F32);
     return est_us < launches_us;
+}
+
+int32_t dense_interval_in_use(const Ctx* c) {
+    if (!dense_persistent_applicable(c)) return 0;
+    const PlanI some = make_plan_interval(c->p, c->o.radius, device_cus());
+    if (!take_interval(c, make_plan(c->p, device_cus()), some)) return 0;
+    return 4 | (some.coop ? 8 : 0) | (some.cols ? 16 : 0) | (some.waves == 8 ? 32 : 0);
 }
 
 dmmv_status dense_descent_persistent(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t) {

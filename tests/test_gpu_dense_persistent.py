@@ -162,6 +162,17 @@ def test_one_launch_descent_bounded_wait_reports_instead_of_hanging():
 
 
 # ---- the descent's own one-launch kernel: intervals of the values that can improve -----------------
+@pytest.mark.parametrize("dtype,shape,radius,by_interval", [
+    (np.float64, (1024, 64, 16), 0, False), (np.float64, (1024, 64, 16), 1, True), (np.float64, (256, 64, 16), 0, False),
+    (np.float64, (1110, 34, 14), 0, False), (np.float64, (4096, 32, 1024), 0, True), (np.float32, (3000, 100, 16), 0, True)])
+def test_choice_between_the_one_launch_kernels(dtype, shape, radius, by_interval):
+    """Scoring every value where the intervals' rounds, which all wavefronts share, cost more than they save."""
+    m = dmmv()
+    with m.from_instance(random_dense(1, *shape, dtype=dtype), DEV, radius=radius) as h:
+        assert m.dmmv_loop_in_use(h) == 2
+        assert (m.dmmv_scoring_in_use(h, radius) >= 4) == by_interval
+
+
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("shape", [(255, 700, 5),        # a wavefront per variable, several each
                                    (256, 33, 64), (64, 257, 9),
