@@ -178,6 +178,7 @@ def test_choice_between_the_one_launch_kernels(dtype, shape, radius, by_interval
                                    (256, 33, 64), (64, 257, 9),
                                    (3000, 20, 300), (513, 5, 4000)])  # long intervals, narrowed by samples
 def test_one_launch_intervals_random(shape, dtype):
+    """(Without a radius most of these are taken by the kernel that scores every value.)"""
     mm, nn, nd = shape
     print("one-launch intervals", shape, dtype.__name__, flush=True)
     inst = random_dense(1900 + mm + nn, mm, nn, nd, dtype=dtype)
@@ -187,25 +188,10 @@ def test_one_launch_intervals_random(shape, dtype):
     check(inst, 10, x0=x0, radius=1)
 
 
-@pytest.mark.parametrize("shape", [(6000, 520, 3), (9001, 12, 2000)])
-def test_one_launch_intervals_columns_in_memory(shape):
-    """fp64 instances whose columns do not fit beside r in LDS (the automatic choice takes them)."""
-    mm, nn, nd = shape
-    m = dmmv()
-    inst = random_dense(1990 + mm, mm, nn, nd, dtype=np.float64)
-    x0 = np.random.default_rng(nn).choice(inst.D, size=inst.n)
-    o = orc.solve_dense(inst.A, inst.b, inst.D, x0, 8)
-    with m.from_instance(inst, DEV) as h:
-        assert m.dmmv_loop_in_use(h) == 2
-        res = m.dmmv_solve(h, T(x0), 8, trace=True)
-        d = int(res.iters_done[0])
-        assert d == o.iters_done and np.array_equal(N(res.trace)[0, :d, 0], o.trace_j)
-        assert np.array_equal(N(m.dmmv_get_state(h)[1]), o.r)
-
-
 def test_one_launch_intervals_plateaus_and_zero_columns():
     """Scores that are flat over many values (rows no step can reach, columns of zeros and of one entry):
-    the samples tie and every value of the interval is scored; the lowest index wins."""
+    the samples tie and every value of the interval is scored; the lowest index wins.  (So small an instance is taken
+    by the kernel that scores every value.)"""
     rng = np.random.default_rng(5)
     for nd in (40, 300):
         A = np.zeros((90, 24))
@@ -220,14 +206,146 @@ def test_one_launch_intervals_plateaus_and_zero_columns():
         check(inst, 20, x0=rng.choice(inst.D, size=24))
 
 
-def test_alns_dense_one_launch_local_search_bounded_wait_runs_again():
-    """With a wait limit of one poll the one-launch local search gives up; the outer loop then runs again from
+INTERVAL, SHARED, COLUMNS, EIGHT = 4, 8, 16, 32        # dmmv_scoring_in_use: which of its forms a handle runs
+F32, F64 = np.float32, np.float64
+
+
+def check_interval(inst, iters, x0, form, radius=0, mask=None):
+    """The descent on the kernel form named, against the oracle; options 0 (the automatic choice takes it) and, where the
+    other one-launch kernel fits too, dense_loop = 2."""
+    m = dmmv()
+    kw = {} if mask is None else dict(var_mask=mask)
+    o = orc.solve_dense(inst.A, inst.b, inst.D, x0, iters, radius=radius, **kw)
+    hkw = {} if mask is None else dict(var_mask=T(mask))
+    ran = 0
+    for loop in (0, 2):
+        try:
+            h = m.from_instance(inst, DEV, radius=radius, dense_loop=loop, **hkw)
+        except m.DmmvError as e:
+            assert loop == 2 and e.status == -8
+            continue
+        with h:
+            if loop == 0 and m.dmmv_loop_in_use(h) == 1:
+                continue                                  # close to the loop of launches: only on request
+            assert m.dmmv_scoring_in_use(h, radius) == form, (loop, m.dmmv_scoring_in_use(h, radius), form)
+            ran += 1
+            res = m.dmmv_solve(h, T(x0), iters, trace=True)
+            d = int(res.iters_done[0])
+            tr = N(res.trace)[0]
+            assert d == o.iters_done, (loop, d, o.iters_done)
+            assert np.array_equal(tr[:d, 0], o.trace_j) and np.array_equal(tr[:d, 1], o.trace_k) and np.all(tr[d:] == -1)
+            assert np.array_equal(N(res.trace_t)[0, :d], o.trace_t)
+            x, r, t = m.dmmv_get_state(h)
+            assert np.array_equal(N(x).reshape(-1), o.x) and np.array_equal(N(r), o.r) and N(t)[0] == o.t
+    assert ran >= 1
+    return o
+
+
+FORMS = [  # (form, type, m, n, nd, radius): every form in both types; up to 64 levels (a lane each) and more (bisection)
+    (INTERVAL, F32, 7700, 262, 48, 1), (INTERVAL, F64, 3533, 264, 310, 1),
+    (INTERVAL | EIGHT, F32, 4225, 1032, 26, 1), (INTERVAL | EIGHT, F64, 1743, 1046, 376, 1),
+    (INTERVAL | COLUMNS, F32, 321, 311, 55, 0), (INTERVAL | COLUMNS, F64, 129, 274, 63, 0),
+    (INTERVAL | COLUMNS, F64, 1000, 300, 65, 0), (INTERVAL | COLUMNS, F32, 300, 300, 300, 0), (INTERVAL | COLUMNS, F64, 78, 91, 374, 2),
+    (INTERVAL | COLUMNS | EIGHT, F32, 70, 580, 54, 0), (INTERVAL | COLUMNS | EIGHT, F64, 73, 1041, 18, 0),
+    (INTERVAL | COLUMNS | EIGHT, F64, 100, 700, 300, 0), (INTERVAL | COLUMNS | EIGHT, F32, 67, 163, 333, 2),
+    (INTERVAL | SHARED, F32, 37070, 15, 343, 1), (INTERVAL | SHARED, F64, 16038, 39, 357, 2),
+    (INTERVAL | SHARED | EIGHT, F32, 18712, 46, 391, 2), (INTERVAL | SHARED | EIGHT, F64, 10120, 35, 380, 2),
+    (INTERVAL | SHARED | COLUMNS, F32, 17932, 18, 383, 2), (INTERVAL | SHARED | COLUMNS, F64, 1750, 3, 4, 0),
+    (INTERVAL | SHARED | COLUMNS | EIGHT, F32, 3000, 24, 64, 0), (INTERVAL | SHARED | COLUMNS | EIGHT, F64, 1500, 24, 64, 0),
+    (INTERVAL | SHARED | COLUMNS | EIGHT, F64, 2000, 24, 300, 0), (INTERVAL | SHARED | COLUMNS | EIGHT, F32, 4000, 24, 65, 0),
+]
+
+
+@pytest.mark.parametrize("form,dtype,mm,nn,nd,radius", FORMS)
+def test_one_launch_intervals_forms(form, dtype, mm, nn, nd, radius):
+    """Random instances on each form, without and with a mask."""
+    print("one-launch intervals", form, dtype.__name__, mm, nn, nd, radius, flush=True)
+    inst = random_dense(1900 + mm + nn, mm, nn, nd, dtype=dtype)
+    rng = np.random.default_rng(nn)
+    x0 = rng.choice(inst.D, size=inst.n)
+    o = check_interval(inst, 12, x0, form, radius)
+    assert o.iters_done >= 1
+    check_interval(inst, 6, x0, form, radius, mask=(rng.uniform(size=nn) < 0.5).astype(np.uint8))
+
+
+@pytest.mark.parametrize("form,dtype,mm,nn,nd", [
+    (INTERVAL | COLUMNS, F64, 129, 274, 63), (INTERVAL | COLUMNS, F32, 300, 300, 300), (INTERVAL | COLUMNS | EIGHT, F64, 100, 700, 40),
+    (INTERVAL | COLUMNS | EIGHT, F64, 100, 700, 300), (INTERVAL | SHARED | COLUMNS | EIGHT, F64, 1500, 24, 40),
+    (INTERVAL | SHARED | COLUMNS | EIGHT, F64, 2000, 24, 300), (INTERVAL | SHARED | COLUMNS | EIGHT, F32, 4000, 24, 65)])
+def test_one_launch_intervals_plateaus_ties_and_zero_columns(form, dtype, mm, nn, nd):
+    """Scores that are flat over many values (rows no step can reach, columns of zeros and of one entry): the samples tie and
+    every value of the interval is scored.  Integer data: exact ties between values, variables and workgroups.  The lowest
+    index wins."""
+    rng = np.random.default_rng(nd + mm)
+    inst = random_dense(1, mm, nn, 4, dtype=dtype)
+    inst.D = (np.arange(nd) - nd // 2).astype(dtype)
+    A = np.zeros((mm, nn))
+    k = nn - 4
+    A[rng.integers(0, mm, k), np.arange(k)] = rng.choice([-1.0, 1.0, 2.0], k)
+    A[:, k] = rng.integers(-1, 2, mm)
+    b = rng.integers(-30, 31, mm).astype(np.float64)
+    b[:6] = 200.0                                         # a maximum that one or no column touches
+    A[:6, 3] = 1.0
+    inst.A, inst.b = np.asfortranarray(A.astype(dtype)), b.astype(dtype)
+    check_interval(inst, 15, rng.choice(inst.D, size=nn), form)
+    inst.A = np.asfortranarray(rng.integers(-3, 4, (mm, nn)).astype(dtype))
+    inst.b = rng.integers(-20 * nn, 20 * nn, mm).astype(dtype)
+    o = check_interval(inst, 15, rng.choice(inst.D, size=nn), form)
+    assert o.iters_done >= 1
+
+
+@pytest.mark.parametrize("shape", [(6000, 520, 3), (9001, 12, 2000)])
+def test_one_launch_intervals_columns_in_memory(shape):
+    """fp64 instances whose columns do not fit beside r in LDS (the automatic choice takes them)."""
+    mm, nn, nd = shape
+    m = dmmv()
+    inst = random_dense(1990 + mm, mm, nn, nd, dtype=np.float64)
+    x0 = np.random.default_rng(nn).choice(inst.D, size=inst.n)
+    o = orc.solve_dense(inst.A, inst.b, inst.D, x0, 8)
+    with m.from_instance(inst, DEV) as h:
+        assert m.dmmv_loop_in_use(h) == 2
+        form = m.dmmv_scoring_in_use(h)
+        assert form & INTERVAL and not form & COLUMNS
+        res = m.dmmv_solve(h, T(x0), 8, trace=True)
+        d = int(res.iters_done[0])
+        assert d == o.iters_done and np.array_equal(N(res.trace)[0, :d, 0], o.trace_j)
+        assert np.array_equal(N(m.dmmv_get_state(h)[1]), o.r)
+
+
+@pytest.mark.parametrize("form,shape", [(INTERVAL | COLUMNS, (1024, 64, 16)), (INTERVAL | SHARED | COLUMNS | EIGHT, (1500, 24, 64))])
+def test_one_launch_intervals_bounded_wait(form, shape):
+    """A wait limit of one poll: the descent gives up, with the state of the starting point, or finds every arrival there."""
+    m = dmmv()
+    radius = 1 if not form & SHARED else 0
+    inst = random_dense(34, *shape, dtype=np.float64)
+    x0 = np.random.default_rng(2).choice(inst.D, size=inst.n)
+    o = orc.solve_dense(inst.A, inst.b, inst.D, x0, 20, radius=radius)
+    with m.from_instance(inst, DEV, dense_loop=2, wait_limit=1, radius=radius) as h:
+        assert m.dmmv_scoring_in_use(h, radius) == form
+        try:
+            res = m.dmmv_solve(h, T(x0), 20)
+        except m.DmmvError as e:
+            assert e.status == -7
+            x, r, t = m.dmmv_get_state(h)
+            assert np.array_equal(N(x).reshape(-1), x0)
+            assert np.array_equal(N(r), orc.residual_dense(inst.A, inst.b, inst.D, x0))
+        else:
+            assert int(res.iters_done[0]) == o.iters_done and N(res.max_violation)[0] == o.t
+    with m.from_instance(inst, DEV, wait_limit=1, radius=radius) as h:
+        res = m.dmmv_solve(h, T(x0), 20)
+        assert int(res.iters_done[0]) == o.iters_done and np.array_equal(N(res.x), o.x)
+
+
+@pytest.mark.parametrize("scoring,shape", [(1, (120, 40, 16)), (INTERVAL | COLUMNS, (1024, 64, 16))])
+def test_alns_dense_one_launch_local_search_bounded_wait_runs_again(scoring, shape):
+    """With a wait limit of one poll the one-launch local search (either kernel) gives up; the outer loop then runs again from
     the starting point with a launch per step, and the result is the oracle's either way."""
     m = dmmv()
-    inst = random_dense(77, 120, 40, 16, dtype=np.float64)
+    inst = random_dense(77, *shape, dtype=np.float64)
     o = orc.alns_dense(inst.A, inst.b, inst.D, inst.x0, orc.alns_params(8, ls_moves=5, seed=3, destroy_count=3))
     for limit in (0, 1):
         with m.from_instance(inst, DEV, wait_limit=limit) as h:
+            assert m.dmmv_scoring_in_use(h, 1) == scoring          # the local search's neighbourhood
             for x0 in (T(inst.x0), None):
                 if x0 is None:
                     m.dmmv_set_x(h, T(inst.x0))
