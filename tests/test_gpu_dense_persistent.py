@@ -336,19 +336,20 @@ def test_one_launch_intervals_bounded_wait(form, shape):
         assert int(res.iters_done[0]) == o.iters_done and np.array_equal(N(res.x), o.x)
 
 
+@pytest.mark.parametrize("iters", [8, 256, 300])           # before, at and past the first look at the error bit
 @pytest.mark.parametrize("scoring,shape", [(1, (120, 40, 16)), (INTERVAL | COLUMNS, (1024, 64, 16))])
-def test_alns_dense_one_launch_local_search_bounded_wait_runs_again(scoring, shape):
+def test_alns_dense_one_launch_local_search_bounded_wait_runs_again(scoring, shape, iters):
     """With a wait limit of one poll the one-launch local search (either kernel) gives up; the outer loop then runs again from
     the starting point with a launch per step, and the result is the oracle's either way."""
     m = dmmv()
     inst = random_dense(77, *shape, dtype=np.float64)
-    o = orc.alns_dense(inst.A, inst.b, inst.D, inst.x0, orc.alns_params(8, ls_moves=5, seed=3, destroy_count=3))
+    o = orc.alns_dense(inst.A, inst.b, inst.D, inst.x0, orc.alns_params(iters, ls_moves=5, seed=3, destroy_count=3))
     for limit in (0, 1):
         with m.from_instance(inst, DEV, wait_limit=limit) as h:
             assert m.dmmv_scoring_in_use(h, 1) == scoring          # the local search's neighbourhood
             for x0 in (T(inst.x0), None):
                 if x0 is None:
                     m.dmmv_set_x(h, T(inst.x0))
-                res = m.dmmv_alns(h, x0, 8, ls_moves=5, seed=3, destroy_count=3)
+                res = m.dmmv_alns(h, x0, iters, ls_moves=5, seed=3, destroy_count=3)
                 assert np.array_equal(N(res.trace_t)[:, 0], o.t) and np.array_equal(N(res.x_best), o.x)
                 assert np.array_equal(N(res.trace)[:, 2], o.moves)
