@@ -54,7 +54,10 @@ __device__ __forceinline__ bool bp_better(T s, int64_t c, T bs, int64_t bc) {
 }
 
 // KI: type of a level index in LDS (8 bits when nd <= 256, whose values then lie in LDS too).
-template <class T, class KI>
+// AHEAD: the next block of variables' entries are requested before this one is walked.  With a single block (n <= 256) there
+// is none, and the registers it takes cost a wavefront per SIMD: 60 000 instances of 8 x 8, 30 moves, 1193 us with it
+// and 1043 without (fp64 1927 and 1527).
+template <class T, class KI, bool AHEAD>
 __global__ __launch_bounds__(BP_BLOCK) void k_descent_batched_pruned(
     int64_t m, int64_t n, int32_t nd, int64_t R, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Xt, const T* __restrict__ D, const T* __restrict__ scale,
@@ -170,7 +173,6 @@ __global__ __launch_bounds__(BP_BLOCK) void k_descent_batched_pruned(
         um = __builtin_amdgcn_readfirstlane(um);
         const T r_max = F.top_r[um];
         const T* __restrict__ x_max = Xt + (int64_t)__builtin_amdgcn_readfirstlane(F.top_row[um]) * n;
-        // (the next block of variables' entries are requested before this one is walked)
         T nx[BP_S], nm;
         auto fetch = [&](int64_t j0) {
             const int64_t jc = j0 + lane < n ? j0 + lane : n - 1;
@@ -178,16 +180,17 @@ __global__ __launch_bounds__(BP_BLOCK) void k_descent_batched_pruned(
             for (int u = 0; u < BP_S; ++u) nx[u] = xrow[u][jc];
             nm = x_max[jc];
         };
-        if (tid - lane < n) fetch(tid - lane);
+        if (AHEAD && tid - lane < n) fetch(tid - lane);
         for (int64_t j0 = tid - lane; j0 < n; j0 += BP_BLOCK) {     // whole wavefronts
             const int64_t j = j0 + lane;
             const int64_t jc = j < n ? j : n - 1;
             const int32_t kc = sh_k[jc];
+            if (!AHEAD) fetch(j0);
             T xs[BP_S];
 #pragma unroll
             for (int u = 0; u < BP_S; ++u) xs[u] = nx[u];
             const T xm = nm;
-            if (j0 + BP_BLOCK < n) fetch(j0 + BP_BLOCK);
+            if (AHEAD && j0 + BP_BLOCK < n) fetch(j0 + BP_BLOCK);
             const bool up = r_max > (T)0 ? xm < (T)0 : xm > (T)0;
             bool walk = j < n && xm != (T)0 && (vm ? vm[jc] != 0 : true);
             const T dcur = level(kc);
@@ -363,8 +366,9 @@ dmmv_status descent_t(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, vo
     };
     // (512 or 1024 threads per instance measured slower except for a hundred instances and fewer, where they gain
     // a few per cent: 18.9 and 55 ms against 15.9 on the 4096-instance layer)
-    if (c->p.nd > BP_DCAP) return launch(k_descent_batched_pruned<T, uint16_t>);
-    return launch(k_descent_batched_pruned<T, uint8_t>);
+    const bool ahead = n > BP_BLOCK;
+    if (c->p.nd > BP_DCAP) return ahead ? launch(k_descent_batched_pruned<T, uint16_t, true>) : launch(k_descent_batched_pruned<T, uint16_t, false>);
+    return ahead ? launch(k_descent_batched_pruned<T, uint8_t, true>) : launch(k_descent_batched_pruned<T, uint8_t, false>);
 }
 
 }  // namespace

@@ -22,6 +22,13 @@ def test_pruned_batched_random(shape):
     batched_check(random_batched(9000 + mm, mm, nn, R, nd, dtype=np.float32), 14, prune=True)
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n,nd", [(255, 4), (256, 16), (257, 4), (256, 300), (257, 300)])
+def test_pruned_batched_one_block_of_variables(n, nd, dtype):
+    """Up to 256 variables a workgroup has one block of them and requests no next one."""
+    batched_check(random_batched(9030 + n + nd, 50, n, 5, nd, dtype=dtype), 12, prune=True)
+
+
 def test_pruned_batched_many_levels_and_instances_too_large_for_lds():
     # more than 256 levels: 16-bit level indices in LDS
     batched_check(random_batched(9050, 40, 6, 5, 300, dtype=np.float32), 10, prune=True)
