@@ -188,7 +188,9 @@ typedef struct {
                                 if another kernel keeps some from starting, the wait ends after
                                 wait_limit polls; x, r and the loop state are then untouched, and
                                 dmmv_solve returns DMMV_ERR_STATE (dense_loop = 2) or runs the same
-                                descent with launches (dense_loop = 0).  options.prune and value_search (without
+                                descent with launches (dense_loop = 0).  dmmv_alns takes the moves of a
+                                local search in one launch by the same choice (unless 1) and goes back to
+                                launches if a wait has ended.  options.prune and value_search (without
                                 keep_going) and l2_rule 1 / 2 keep their own loops                    */
     int32_t wait_limit;      /* dense_loop = 2: polls of another workgroup's arrival word before the
                                 kernel gives up; 0 = default (2^22, a few seconds)                    */

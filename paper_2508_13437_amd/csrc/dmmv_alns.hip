@@ -329,8 +329,8 @@ __global__ __launch_bounds__(1024) void k_alns_worst_list(int64_t R, const AlnsS
 //
 // k_alns_impact_batched: lane = variable, so a row of X is one coalesced load that IM_Q instances share
 // (with lane = instance and X through the scalar unit a small batch left most of the chip idle:
-// 1.56 ms for the 11 listed of 20 instances of 2048 x 768, and 5.0 ms for 512 of 2048 x 4096; now 0.06 and
-// 2.2 ms).  A wavefront takes 64 variables x IM_Q instances x IM_ROWS rows at a time: the tests leave one bit
+// 1.56 ms for the listed half of 20 instances of 2048 x 768, and 5.0 ms for that of 1024 of 2048 x 4096; now 0.10 and
+// 2.25 ms, the limits' launch 0.01 and 0.02 more).  A wavefront takes 64 variables x IM_Q instances x IM_ROWS rows at a time: the tests leave one bit
 // per row in a mask (two instructions a term), the set bits are then popped into a queue in LDS,
 // and whenever 64 are waiting every lane evaluates one, for whichever variable and instance it belongs
 // to, and adds the integer to that sum with an LDS atomic.  Bound by instruction issue (vector unit busy 65 %, about

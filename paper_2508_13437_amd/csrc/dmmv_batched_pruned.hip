@@ -18,9 +18,9 @@
 // The result is the arg-min of the full table restricted to strictly improving moves, i.e. the
 // move the full evaluation + selection would apply - found with a few full scores instead of
 // n (nd - 1); a candidate's score is given up as soon as a row puts it above the best one.
-// Bound by the vector unit (25 000 wavefront instructions per instance and iteration on 2048 x 4096 with 16
-// levels, 73 % busy).  All levels of every variable screened and every score finished, the 4096
-// instances of that layer took 22.8 ms to their local optima; now 13.2.  The instance's r (m values) and x (n level indices) live in LDS for the whole
+// Bound by the vector unit (24 200 wavefront instructions per instance and iteration on 2048 x 4096 with 16
+// levels, 74 % busy).  With all levels of every variable screened and every score finished, the 4096
+// instances of that layer took 23.7 ms to their local optima, the residual's 0.57 ms included; now 13.9.  The instance's r (m values) and x (n level indices) live in LDS for the whole
 // launch, so a launch can run any number of iterations without touching the other instances;
 // an instance stops by itself at a local optimum.
 #include "dmmv_common.h"
@@ -364,8 +364,8 @@ dmmv_status descent_t(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, vo
         DMMV_LAUNCH_CHECK();
         return DMMV_OK;
     };
-    // (512 or 1024 threads per instance measured slower except for a hundred instances and fewer, where they gain
-    // a few per cent: 18.9 and 55 ms against 15.9 on the 4096-instance layer)
+    // (512 threads per instance, which then screen 32 rows: 26.8 ms against 14.0 on 4096 instances of 2048 x 4096 and 8.0 against
+    // 5.3 on 1024, but 2.6 against 3.9 on 100 and 2.3 against 3.6 on 20; not taken.  1024 threads: 237 and 66 ms, 16 on 100)
     const bool ahead = n > BP_BLOCK;
     if (c->p.nd > BP_DCAP) return ahead ? launch(k_descent_batched_pruned<T, uint16_t, true>) : launch(k_descent_batched_pruned<T, uint16_t, false>);
     return ahead ? launch(k_descent_batched_pruned<T, uint8_t, true>) : launch(k_descent_batched_pruned<T, uint8_t, false>);
