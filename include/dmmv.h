@@ -185,6 +185,8 @@ typedef struct {
                                 of both loops says its iteration is the shorter one, else 1.  Same
                                 scores, moves, traces and residual either way.  With 2 the workgroups
                                 wait for one another, so all must be resident on the device at once;
+                                calls of one process that would not all have room on it at once take
+                                turns (and with 0 use launches rather than wait for long), and
                                 if another kernel keeps some from starting, the wait ends after
                                 wait_limit polls; x, r and the loop state are then untouched, and
                                 dmmv_solve returns DMMV_ERR_STATE (dense_loop = 2) or runs the same

@@ -726,10 +726,15 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
         // a pruned batch runs all its iterations in one launch; every instance stops by itself
         if (pruned_batch) return batched_descent_pruned(c, iters, iters, trace, trace_t);
         // a small dense instance too; the wait between its workgroups is bounded and reports here
-        if (iters > 0 && dense_persistent_applicable(c)) {
-            DMMV_TRY(dense_descent_persistent(c, iters, iters, trace, trace_t));
+        // (others of the process that leave it no room for long: the loop of launches)
+        OneLaunchClaim claim;
+        const int32_t workgroups = iters > 0 ? dense_persistent_workgroups(c) : 0;
+        if (workgroups > 0 && claim.take(c, workgroups, iters)) {
             int32_t raw = 0;
-            const dmmv_status one = check_device_errors(c, &raw);
+            dmmv_status one = dense_descent_persistent(c, iters, iters, trace, trace_t);
+            if (one == DMMV_OK) one = check_device_errors(c, &raw);
+            else (void)hipStreamSynchronize(c->stream);
+            claim.release();
             // An automatic choice must not add a way to fail: if the workgroups could not all be
             // resident (the device is shared), the attempt has left x, r and the loop state alone,
             // and the loop of launches below does the same descent.
@@ -821,7 +826,9 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
     // step.  (The arg-min records of that loop, 16 bytes per variable and more, are free meanwhile.)  The bit is looked
     // at after ALNS_POLL iterations and whenever their number is four times that of the last look, so that a long run
     // is not finished in vain.
-    const bool one_launch = prm.ls_moves > 0 && !batched_pruned_applicable(c) && dense_persistent_applicable(c);
+    OneLaunchClaim claim;
+    const int32_t workgroups = prm.ls_moves > 0 && !batched_pruned_applicable(c) ? dense_persistent_workgroups(c) : 0;
+    const bool one_launch = workgroups > 0 && claim.take(c, workgroups, (int64_t)prm.iters * prm.ls_moves);
     // (a shorter wait than that of a single descent, some 0.1 s: every outer iteration waits anew, and the way
     // out is the loop of launches)
     if (one_launch && c->o.wait_limit == 0) c->o.wait_limit = 1 << 17;
@@ -830,6 +837,8 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
         const size_t xbytes = (size_t)c->p.n * sizeof(int32_t);
         DMMV_HIP_CHECK(hipMemcpyAsync(c->partials, c->kidx, xbytes, hipMemcpyDeviceToDevice, c->stream));
         const dmmv_status one = run(true);
+        if (one != DMMV_OK && raw == 0) (void)hipStreamSynchronize(c->stream);      // a call failed: nothing was waited for
+        claim.release();
         if (one == DMMV_OK || raw != ERRBIT_WAIT_LIMIT) return one;
         DMMV_HIP_CHECK(hipMemcpyAsync(c->kidx, c->partials, xbytes, hipMemcpyDeviceToDevice, c->stream));
         DMMV_TRY(residual_any(c));

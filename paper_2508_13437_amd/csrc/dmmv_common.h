@@ -294,7 +294,22 @@ dmmv_status batched_compact_end(Ctx* c);
 // that exchange one arg-min record per iteration); same moves as evaluation + selection + apply
 size_t dense_persistent_exchange_bytes();
 bool dense_persistent_fits(const dmmv_problem& p);
-bool dense_persistent_applicable(const Ctx* c);
+int32_t dense_persistent_workgroups(const Ctx* c);      // of the one-launch descent, 0 = it does not apply
+inline bool dense_persistent_applicable(const Ctx* c) { return dense_persistent_workgroups(c) > 0; }
+// The compute units that a one-launch descent of `moves` iterations holds.  take: waits while other one-launch descents of
+// the process hold too many, and returns false if they still do when an automatic choice has waited long enough.  Held until release() or the end of the scope; the stream must have been waited for.
+class OneLaunchClaim {
+public:
+    OneLaunchClaim() = default;
+    OneLaunchClaim(const OneLaunchClaim&) = delete;
+    OneLaunchClaim& operator=(const OneLaunchClaim&) = delete;
+    ~OneLaunchClaim() { release(); }
+    bool take(const Ctx* c, int32_t workgroups, int64_t moves);
+    void release();
+
+private:
+    int dev_ = 0, units_ = 0;
+};
 int32_t dense_interval_in_use(const Ctx* c);   // the code of dmmv_scoring_in_use, 0 = another kernel
 // (at most `steps` iterations)
 dmmv_status dense_descent_persistent(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t);

@@ -19,9 +19,13 @@
 //
 // The exchange is a wait on other workgroups, so all G must be resident at once (G never
 // exceeds the number of compute units, and each needs at most one unit's LDS).  Should the
-// device be shared with another kernel that keeps some of them from starting, the wait ends
+// device be shared with a kernel of another process that keeps some of them from starting, the wait ends
 // after options.wait_limit polls: the kernel raises an error flag, every workgroup leaves, and
 // dmmv_solve returns DMMV_ERR_STATE.
+#include <algorithm>
+#include <chrono>
+#include <condition_variable>
+#include <mutex>
 #include <type_traits>
 
 #include "dmmv_common.h"
@@ -749,6 +753,68 @@ dmmv_status run_interval_t(Ctx* c, const PlanI& pl, int32_t steps, int32_t iters
 
 }  // namespace
 
+// Two of these kernels that are each resident in part would wait for one another until their limits end.  Every launch
+// therefore claims as many of the device's compute units as it has workgroups, from before the launch until the stream has
+// been waited for, and the claims of the process together do not exceed the compute units: a workgroup that is not resident
+// then always finds one that has none of them.  Workgroups are dealt to the 8 XCDs in turn, and what holds for the device
+// has to hold for each XCD, so a claim is rounded up to the same number in all of them.  Kernels that do not wait only
+// delay a start.  With dense_loop = 2 a call waits for its turn, in the order of the calls; an automatic choice waits for as
+// long as the loop of launches would take, at most CLAIM_WAIT_US, and then takes that loop.
+// (Four threads with an instance of 8016 x 251 each, whose grid is 251: 40 moves took 1.1 s a call without the claims and
+// take 4.0 ms with them; one thread, 0.98 ms.)
+namespace {
+constexpr int CLAIM_MAX_DEVICES = 64;
+constexpr int CLAIM_XCDS = 8;
+constexpr double CLAIM_WAIT_US = 5000.0;
+struct Claims {
+    int units = 0;                         // compute units claimed
+    uint64_t next = 0, served = 0;         // the queue of claims that wait
+};
+std::mutex g_claim_mu;
+std::condition_variable g_claim_cv;
+Claims g_claims[CLAIM_MAX_DEVICES];
+}  // namespace
+
+static double launch_loop_us(const Ctx* c) {               // an iteration of the loop of launches, by its model
+    const double pairs = (double)c->p.m * (double)c->p.n * (double)c->p.nd;
+    return DP_LAUNCH_LOOP_US + pairs * (c->p.dtype == DMMV_F64 ? DP_LAUNCH_LOOP_US_PER_PAIR_F64
+                                                               : DP_LAUNCH_LOOP_US_PER_PAIR_F32);
+}
+
+bool OneLaunchClaim::take(const Ctx* c, int32_t workgroups, int64_t moves) {
+    release();
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= CLAIM_MAX_DEVICES) return true;    // not counted
+    const int cus = device_cus();
+    const int need = (int)ceil_div(workgroups, CLAIM_XCDS) * CLAIM_XCDS;
+    std::unique_lock<std::mutex> lock(g_claim_mu);
+    Claims& k = g_claims[dev];
+    auto room = [&] { return k.units == 0 || k.units + need <= cus; };
+    if (c->o.dense_loop == 2) {
+        const uint64_t turn = k.next++;
+        g_claim_cv.wait(lock, [&] { return k.served == turn && room(); });
+        ++k.served;
+        g_claim_cv.notify_all();           // the next one in the queue may fit too
+    } else {
+        const std::chrono::duration<double, std::micro> most(std::min((double)moves * launch_loop_us(c), CLAIM_WAIT_US));
+        if (!g_claim_cv.wait_for(lock, most, [&] { return k.served == k.next && room(); })) return false;
+    }
+    k.units += need;
+    dev_ = dev;
+    units_ = need;
+    return true;
+}
+
+void OneLaunchClaim::release() {
+    if (units_ == 0) return;
+    {
+        std::lock_guard<std::mutex> lock(g_claim_mu);
+        g_claims[dev_].units -= units_;
+    }
+    units_ = 0;
+    g_claim_cv.notify_all();
+}
+
 // options.dense_loop: 0 = one launch when the model says its iteration is shorter than that of
 // the loop of launches, 1 = always a launch per step, 2 = one launch whenever the instance fits
 // (dmmv_create refuses the option otherwise).
@@ -764,20 +830,16 @@ static bool take_interval(const Ctx* c, const Plan& all, const PlanI& some) {
     return !c->o.keep_going && some.G > 0 && (all.G == 0 || some.est_us + some.more_us < all.est_us);
 }
 
-bool dense_persistent_applicable(const Ctx* c) {
-    if (c->kind != KIND_DENSE || c->o.dense_loop == 1 || !c->persist_exchange) return false;
-    if (c->o.l2_rule == 1 || c->o.l2_rule == 2) return false;
-    if (!c->o.keep_going && (c->o.value_search || c->o.prune)) return false;      // those have loops of their own
+int32_t dense_persistent_workgroups(const Ctx* c) {
+    if (c->kind != KIND_DENSE || c->o.dense_loop == 1 || !c->persist_exchange) return 0;
+    if (c->o.l2_rule == 1 || c->o.l2_rule == 2) return 0;
+    if (!c->o.keep_going && (c->o.value_search || c->o.prune)) return 0;      // those have loops of their own
     const Plan all = make_plan(c->p, device_cus());
     const PlanI some = make_plan_interval(c->p, c->o.radius, device_cus());
     const bool interval = take_interval(c, all, some);
-    if (!interval && all.G == 0) return false;
+    const int32_t workgroups = interval ? some.G : all.G;
     const double est_us = interval ? some.est_us : all.est_us;
-    if (c->o.dense_loop == 2) return true;
-    const double pairs = (double)c->p.m * (double)c->p.n * (double)c->p.nd;
-    const double launches_us = DP_LAUNCH_LOOP_US + pairs * (c->p.dtype == DMMV_F64 ? DP_LAUNCH_LOOP_US_PER_PAIR_F64
-                                                                                   : DP_LAUNCH_LOOP_US_PER_PAIR_F32);
-    return est_us < launches_us;
+    return workgroups > 0 && (c->o.dense_loop == 2 || est_us < launch_loop_us(c)) ? workgroups : 0;
 }
 
 int32_t dense_interval_in_use(const Ctx* c) {

@@ -4,6 +4,8 @@ the launch-per-step loop (dense_loop = 1): traces, x, r and the error bit for bi
 Paper, section "GPU Acceleration": the iteration is to run without host-side stepping and
 synchronisation; the moves are those of the single-move descent (Algorithm 2's local search).
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -334,6 +336,50 @@ def test_one_launch_intervals_bounded_wait(form, shape):
     with m.from_instance(inst, DEV, wait_limit=1, radius=radius) as h:
         res = m.dmmv_solve(h, T(x0), 20)
         assert int(res.iters_done[0]) == o.iters_done and np.array_equal(N(res.x), o.x)
+
+
+@pytest.mark.parametrize("loop", [2, 0])
+@pytest.mark.parametrize("shapes", [[(6000, 251, 64)] * 4,              # each takes nearly the whole device
+                                    [(6000, 251, 64), (1024, 64, 16), (300, 20, 16), (4096, 32, 1024)]])
+def test_one_launch_descents_of_several_threads(shapes, loop):
+    """Handles of several threads, each on its own stream: the workgroups of one call do not keep those of another from
+    starting.  None fails with dense_loop = 2, where an ended wait is an error, and all moves are those of a call by itself."""
+    m = dmmv()
+    rng = np.random.default_rng(29)
+    work, errors = [], []
+    for s, (mm, nn, nd) in enumerate(shapes):
+        inst = random_dense(60 + s, mm, nn, nd)
+        x0 = rng.integers(0, nd, nn)
+        o = orc.solve_dense(inst.A, inst.b, inst.D, inst.D[x0], 5)
+        work.append((inst, inst.D[x0], o, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    gate = threading.Barrier(len(work))
+
+    def calls(inst, x0, o, stream):
+        try:
+            with torch.cuda.stream(stream), m.from_instance(inst, DEV, dense_loop=loop, stream=stream) as h:
+                start = T(x0)
+                stream.synchronize()
+                gate.wait(60)
+                first = None
+                for _ in range(6):
+                    res = m.dmmv_solve(h, start, 5)
+                    assert int(res.iters_done[0]) == o.iters_done and N(res.max_violation)[0] == o.t
+                    assert np.array_equal(N(res.x).reshape(-1), o.x)
+                    a = m.dmmv_alns(h, start, 6, ls_moves=4, seed=5)
+                    got = (N(a.x_best).tobytes(), N(a.t_best).tobytes())
+                    first = first or got
+                    assert got == first
+        except BaseException as e:                      # noqa: BLE001 - reported by the test itself
+            gate.abort()
+            errors.append(e)
+
+    threads = [threading.Thread(target=calls, args=w) for w in work]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
 
 
 @pytest.mark.parametrize("iters", [8, 256, 300])           # before, at and past the first look at the error bit
