@@ -276,6 +276,515 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_eval(
     }
 }
 
+// ---- evaluation over sorted variables: grid (R, nb), the same records.
+//
+// The variables are sorted by (level, entry in the row of largest |r|).  For a variable u and a lower level b the
+// step Delta is fixed, so the new residual of that row, fma(Delta, A_v - A_u, r), ascends with A_v also as computed
+// (every rounding is monotone): the partners that keep it within a threshold are a contiguous range of the level's
+// variables, found by bisection on the evaluation itself.  Only pairs of such ranges are looked at.
+// The threshold grows in stages towards t and ends at the best t' found so far: at a rounded start the best swap lowers
+// t by a tenth or a third, which one variable of large entries is needed for, and the ranges hold some hundredth of the
+// pairs (50 000 of 7 million on 2048 x 4096); at a local optimum two thirds, of which the next rows drop most.
+// A unit of work is (64 consecutive variables, level); the wavefronts of a workgroup take units from a counter
+// per stage.  A wavefront is through when a stage it has finished reached the bound: the units of that stage
+// are all taken, and whoever holds one covers it up to the smaller of stage and bound.  A few units hold most
+// pairs (outlier channels sort to the ends of their levels), so what is over SWI_PART is shared.
+// Bound by the latency of its gathers in the slowest instances (three times the pairs of the average one) and, at
+// local optima, by instruction issue; one workgroup of 16 wavefronts a compute unit (73 registers; held to 64
+// they spill, 0.95 ms).  Against the evaluation of all pairs (ms, rounded start / local optimum): 512 instances of
+// 2048 x 4096, 16 levels 12.0 / 15.4 and now 0.87 / 13.5; 20 of them 2.96 / 1.07 and 0.40 / 0.92; 64 of 4096 x 4096, 8
+// levels 17.0 and 0.49; 200 of 700 x 1000 1.40 / 0.96 and 0.19 / 0.60; single instances 2048 x 512, 64 levels, fp64 0.53 and
+// 0.093, 256 x 64 0.067 and 0.064.  Seven filter rows in LDS instead of three: 1.9 / 10.6; two workgroups an instance
+// where one fills the chip: no gain (0.86 / 13.9), 20 instances 0.46 / 1.5 with twice as many.
+template <class T> struct SwapKey;
+template <> struct SwapKey<float> {                        // level 8 bits | entry, as ordered bits, 32 | variable 16
+    uint64_t k;
+    __device__ __forceinline__ void set(uint32_t lev, float y, uint32_t j) {
+        uint32_t b = __float_as_uint(y);
+        b = (b & 0x80000000u) ? ~b : b | 0x80000000u;
+        k = ((uint64_t)lev << 48) | ((uint64_t)b << 16) | j;
+    }
+    __device__ __forceinline__ bool less(const SwapKey& o) const { return k < o.k; }
+    __device__ __forceinline__ uint32_t level() const { return (uint32_t)(k >> 48); }
+    __device__ __forceinline__ uint32_t var() const { return (uint32_t)k & 0xFFFFu; }
+    __device__ __forceinline__ float entry() const {
+        const uint32_t b = (uint32_t)(k >> 16);
+        return __uint_as_float((b & 0x80000000u) ? b ^ 0x80000000u : ~b);
+    }
+};
+template <> struct SwapKey<double> {
+    double y;
+    uint32_t lev, j;
+    __device__ __forceinline__ void set(uint32_t l, double v, uint32_t var) { lev = l; y = v; j = var; }
+    __device__ __forceinline__ bool less(const SwapKey& o) const {
+        return lev != o.lev ? lev < o.lev : y != o.y ? y < o.y : j < o.j;
+    }
+    __device__ __forceinline__ uint32_t level() const { return lev; }
+    __device__ __forceinline__ uint32_t var() const { return j; }
+    __device__ __forceinline__ double entry() const { return y; }
+};
+
+constexpr int SWI_LEVELS = 64;                 // most levels (one byte each, and a lane to look each up)
+constexpr int SWI_NMIN = 64;                   // fewest variables
+constexpr int SWI_NMAX = 8192;                 // most variables
+constexpr int SWI_EACH = SWI_NMAX / SWE_BLOCK; // of them a thread holds
+constexpr int SWI_LROWS = 3;                   // filter rows in LDS at most
+constexpr int SWI_STAGES = 5;
+constexpr int SWI_ROWS = 8;                    // of the others, those tried a lane a pair
+constexpr int SWI_SEEN = 8;                    // rows that pairs have failed at, remembered by a workgroup
+constexpr int SWI_HOT = 4;                     // rows of large |entry| looked up per variable
+constexpr int SWI_PART = 1024;                 // pairs of a unit one wavefront takes at a time
+constexpr int SWI_SHARED = 32;                 // larger units a workgroup can have on its list
+constexpr size_t SWI_LDS_HALF = 78 * 1024;     // dynamic LDS: half a compute unit's if a filter row fits it, else nearly all
+constexpr size_t SWI_LDS_ALL = 152 * 1024;
+
+// what lies in the dynamic LDS of a workgroup (the sort's keys overlap everything)
+struct SwapLds {
+    size_t y, lr, queue, rtop, rows, perm, lev, bytes;
+    int32_t L;
+    bool stage_r;
+};
+static SwapLds swap_lds(int64_t m, int64_t n, int32_t K, size_t esz, size_t key, size_t budget) {
+    SwapLds s;
+    int64_t n2 = 64;
+    while (n2 < n) n2 *= 2;
+    auto up = [](size_t v) { return (v + 15) / 16 * 16; };
+    size_t at = 0;
+    s.queue = at; at = up(at + (size_t)SWE_WAVES * SWE_QCAP * sizeof(uint32_t));
+    s.rtop = at; at = up(at + (size_t)K * esz);
+    s.rows = at; at = up(at + (size_t)K * sizeof(int32_t));
+    s.perm = at; at = up(at + (size_t)n * 2);
+    s.lev = at; at = up(at + (size_t)n);
+    const size_t row = up((size_t)n * esz), rr = up((size_t)m * esz);
+    s.stage_r = at + row + rr <= budget;
+    s.lr = at;
+    if (s.stage_r) at += rr;
+    s.y = at;
+    s.L = 0;
+    while (s.L < SWI_LROWS && s.L < K && at + row <= budget) { at += row; ++s.L; }
+    s.bytes = at > key * (size_t)n2 ? at : key * (size_t)n2;
+    if (s.bytes > budget) s.L = 0;
+    return s;
+}
+
+// rows of large |entry| of every column: the largest of each wavefront's share of the rows.  hot[w * n + j]
+template <class T>
+__global__ __launch_bounds__(64 * SWI_HOT) void k_swap_hot(int64_t m, int64_t n, const T* __restrict__ A, int64_t lda,
+                                                           int32_t* __restrict__ hot, int32_t n_hot) {
+    const int64_t j = blockIdx.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, step = 64 * (blockDim.x >> 6);
+    const T* __restrict__ col = A + j * lda;
+    T s = (T)1;                                            // arg-min of -|entry|
+    int64_t c = -1;
+    for (int64_t i0 = threadIdx.x; i0 < m; i0 += 8 * step) {
+        T a[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = col[i0 + u * step < m ? i0 + u * step : m - 1];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = i0 + u * step;
+            if (i < m && -dmmv_abs(a[u]) < s) { s = -dmmv_abs(a[u]); c = i; }
+        }
+    }
+    wave_argmin(s, c);
+    if (lane == 0 && w < n_hot) hot[w * n + j] = c >= 0 ? (int32_t)c : 0;
+}
+
+template <class T>
+__global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
+    int64_t m, int32_t n, int64_t R, int32_t nd, int32_t nb, int32_t K, SwapLds lds, const T* __restrict__ A,
+    int64_t lda, const T* __restrict__ At, const T* __restrict__ D, const T* __restrict__ scale,
+    const int32_t* __restrict__ kidx, const T* __restrict__ r, const InstState<T>* __restrict__ st,
+    const uint8_t* __restrict__ var_mask, const int32_t* __restrict__ rows_all,
+    const int32_t* __restrict__ hot32, const uint16_t* __restrict__ hot16, int32_t n_hot,
+    const int32_t* __restrict__ skip, T* gbest, Partial<T>* __restrict__ part) {
+    extern __shared__ __align__(16) unsigned char sw_smem[];
+    SwapKey<T>* keys = reinterpret_cast<SwapKey<T>*>(sw_smem);
+    T* y = reinterpret_cast<T*>(sw_smem + lds.y);          // [L][n] filter rows, sorted order
+    T* lr = reinterpret_cast<T*>(sw_smem + lds.lr);        // [m] (stage_r)
+    T* rtop = reinterpret_cast<T*>(sw_smem + lds.rtop);    // [K]
+    int32_t* sh_rows = reinterpret_cast<int32_t*>(sw_smem + lds.rows);
+    uint16_t* perm = reinterpret_cast<uint16_t*>(sw_smem + lds.perm);
+    uint8_t* lev = reinterpret_cast<uint8_t*>(sw_smem + lds.lev);
+    __shared__ T sh_dl[SWI_LEVELS];
+    __shared__ int32_t sh_first[SWI_LEVELS + 1];           // where every level begins
+    __shared__ int32_t sh_unit[SWI_STAGES];
+    __shared__ int32_t sh_big, sh_big_ready[SWI_SHARED], sh_big_unit[SWI_SHARED], sh_big_next[SWI_SHARED], sh_big_parts[SWI_SHARED];
+    __shared__ T sh_big_thr[SWI_SHARED];
+    __shared__ int32_t sh_fail[SWI_SEEN], sh_fails;
+    __shared__ unsigned long long sh_best;
+    __shared__ T sh_s[SWE_WAVES];
+    __shared__ int64_t sh_c[SWE_WAVES];
+
+    const int64_t q = blockIdx.x;
+    const int blk = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Partial<T>* out = part + q * nb + blk;
+    if (skip && skip[q]) {
+        if (tid == 0) { Partial<T> e; e.s = (T)0; e.c = -1; *out = e; }
+        return;
+    }
+    const int32_t* __restrict__ rows_g = rows_all + q * K;
+    const uint8_t* __restrict__ vm = var_mask ? var_mask + q * n : nullptr;
+
+    // ---- sort (bitonic; variables that may not move, and the padding, come last) -----------
+    int32_t n2 = 64;
+    while (n2 < n) n2 *= 2;
+    {
+        const int64_t row = rows_g[0];
+        int32_t kk[SWI_EACH];
+        T yy[SWI_EACH];
+#pragma unroll
+        for (int e = 0; e < SWI_EACH; ++e) {
+            const int32_t j = tid + e * SWE_BLOCK, jc = j < n ? j : n - 1;
+            kk[e] = kidx[(int64_t)jc * R + q];
+            yy[e] = At ? At[row * n + jc] : A[row + jc * lda];
+            if (j >= n || (vm && !vm[jc])) kk[e] = 255;
+        }
+#pragma unroll
+        for (int e = 0; e < SWI_EACH; ++e) {
+            const int32_t j = tid + e * SWE_BLOCK;
+            if (j < n2) { SwapKey<T> key; key.set((uint32_t)kk[e], yy[e], (uint32_t)j); keys[j] = key; }
+        }
+        if (tid < nd) sh_dl[tid] = D[tid];
+        if (tid < SWI_STAGES) sh_unit[tid] = 0;
+        if (tid < SWI_SHARED) { sh_big_ready[tid] = 0; sh_big_next[tid] = 0; }
+        if (tid < SWI_SEEN) sh_fail[tid] = rows_g[0];
+        if (tid == 0) { sh_big = 0; sh_fails = 0; }
+        if (tid == 0) sh_best = order_bits(Limits<T>::inf());
+        __syncthreads();
+        for (int32_t k = 2; k <= n2; k <<= 1) {
+            for (int32_t d = k >> 1; d > 0; d >>= 1) {
+                for (int32_t p = tid; p < n2 >> 1; p += SWE_BLOCK) {
+                    const int32_t a = 2 * p - (p & (d - 1)), b = a + d;
+                    const SwapKey<T> ka = keys[a], kb = keys[b];
+                    if (kb.less(ka) == ((a & k) == 0)) { keys[a] = kb; keys[b] = ka; }
+                }
+                // pairs at most 64 apart stay inside the 128 keys of one wavefront
+                if (d > 64 || (d == 1 && k >= 128)) __syncthreads();
+                else { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); }
+            }
+        }
+        __syncthreads();
+        if (tid <= nd) {                                   // first position of every level
+            int32_t lo = 0, hi = n;
+            while (lo < hi) {
+                const int32_t mid = (lo + hi) >> 1;
+                if ((int32_t)keys[mid].level() < tid) lo = mid + 1; else hi = mid;
+            }
+            sh_first[tid] = lo;
+        }
+        SwapKey<T> mine[SWI_EACH];
+#pragma unroll
+        for (int e = 0; e < SWI_EACH; ++e) if (tid + e * SWE_BLOCK < n) mine[e] = keys[tid + e * SWE_BLOCK];
+        __syncthreads();
+        // the other filter rows: read along the row, then put in order in place
+        for (int l = 1; l < lds.L; ++l) {
+            const int64_t row_l = rows_g[l];
+            for (int32_t j = tid; j < n; j += SWE_BLOCK) y[l * n + j] = At ? At[row_l * n + j] : A[row_l + j * lda];
+        }
+#pragma unroll
+        for (int e = 0; e < SWI_EACH; ++e) {
+            const int32_t p = tid + e * SWE_BLOCK;
+            if (p < n) {
+                perm[p] = (uint16_t)mine[e].var();
+                lev[p] = (uint8_t)mine[e].level();
+                y[p] = mine[e].entry();
+            }
+        }
+        __syncthreads();
+        for (int l = 1; l < lds.L; ++l) {
+            T v[SWI_EACH];
+#pragma unroll
+            for (int e = 0; e < SWI_EACH; ++e) {
+                // (a masked variable's place may hold a padding number: its entries are never looked at)
+                const int32_t p = tid + e * SWE_BLOCK, j = perm[p < n ? p : n - 1];
+                v[e] = y[l * n + (j < n ? j : n - 1)];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < SWI_EACH; ++e)
+                if (tid + e * SWE_BLOCK < n) y[l * n + tid + e * SWE_BLOCK] = v[e];
+        }
+    }
+    for (int l = tid; l < K; l += SWE_BLOCK) {
+        const int32_t row = rows_g[l];
+        sh_rows[l] = row;
+        rtop[l] = r[(int64_t)row * R + q];
+    }
+    if (lds.stage_r)
+        for (int64_t i = tid; i < m; i += SWE_BLOCK) lr[i] = r[i * R + q];
+    __syncthreads();
+
+    uint32_t* queue = reinterpret_cast<uint32_t*>(sw_smem + lds.queue) + w * SWE_QCAP;
+    const T sc = scale[q], t = st[q].t, t_below = value_below(t), r1 = rtop[0];
+    const int32_t nv = __builtin_amdgcn_readfirstlane(sh_first[nd]);      // variables that may move
+    const int32_t groups = (nv + 63) >> 6;
+    T best_t = Limits<T>::inf(), others = Limits<T>::inf();
+    int64_t best_c = -1;                                   // the wavefront's record (uniform)
+    auto bound = [&]() -> T {
+        T shared_t;
+        from_order_bits(__hip_atomic_load(&sh_best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shared_t);
+        return dmmv_min(dmmv_min(best_t, others), shared_t);
+    };
+
+    // The first `cnt` queued pairs, a lane each, on a few rows: more of large |r|, those that pairs failed at before, and
+    // those of the two variables' largest entries (a swap of an outlier channel makes its new maximum there).  Then on
+    // every row, the pair of the smallest error seen so far first, so that what it finds drops most others; and where it
+    // finds nothing, the row it failed at is tried on the others.
+    auto drain = [&](int cnt) {
+        if (gbest) others = __hip_atomic_load(gbest + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool alive = lane < cnt;
+        const uint32_t e = queue[alive ? lane : 0];
+        const int32_t pu = (int32_t)(e >> 16), pv = (int32_t)(e & 0xFFFFu);
+        const int64_t u = perm[pu], v = perm[pv];
+        const T Ds = sc * (sh_dl[lev[pu]] - sh_dl[lev[pv]]);
+        T seen = (T)0;                                     // largest |r'| on the rows tried
+        for (int k = 0; k < lds.L; ++k) seen = dmmv_max(seen, dmmv_abs(dmmv_fma(Ds, y[k * n + pv] - y[k * n + pu], rtop[k])));
+        T thr = dmmv_min(bound(), t_below);
+        alive = alive && seen <= thr;
+        auto r_at = [&](int64_t i) -> T { return lds.stage_r ? lr[i] : r[i * R + q]; };
+        auto a_at = [&](int64_t i, int64_t j) -> T { return At ? At[i * n + j] : A[i + j * lda]; };
+        auto rows4 = [&](int64_t i0, int64_t i1, int64_t i2, int64_t i3) {
+            const T v0 = a_at(i0, v), v1 = a_at(i1, v), v2 = a_at(i2, v), v3 = a_at(i3, v);
+            const T u0 = a_at(i0, u), u1 = a_at(i1, u), u2 = a_at(i2, u), u3 = a_at(i3, u);
+            seen = dmmv_max(seen, dmmv_abs(dmmv_fma(Ds, v0 - u0, r_at(i0))));
+            seen = dmmv_max(seen, dmmv_abs(dmmv_fma(Ds, v1 - u1, r_at(i1))));
+            seen = dmmv_max(seen, dmmv_abs(dmmv_fma(Ds, v2 - u2, r_at(i2))));
+            seen = dmmv_max(seen, dmmv_abs(dmmv_fma(Ds, v3 - u3, r_at(i3))));
+            alive = seen <= thr;
+        };
+        const int l_end = lds.L + SWI_ROWS < K ? lds.L + SWI_ROWS : K;
+        const int tries = l_end - lds.L + SWI_SEEN;        // sh_rows[L .. l_end), then sh_fail
+        for (int l0 = 0; l0 < tries && __any(alive); l0 += 4) {
+            if (alive) {
+                auto row = [&](int l) -> int32_t {
+                    l = l < tries ? l : tries - 1;
+                    return lds.L + l < l_end ? sh_rows[lds.L + l] : sh_fail[lds.L + l - l_end];
+                };
+                rows4(row(l0), row(l0 + 1), row(l0 + 2), row(l0 + 3));
+            }
+        }
+        for (int h = 0; h < n_hot && __any(alive); h += 2) {
+            if (alive) {
+                int32_t row[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const int64_t at = (int64_t)(h + x / 2 < n_hot ? h + x / 2 : h) * n + (x & 1 ? v : u);
+                    row[x] = hot16 ? (int32_t)hot16[at] : hot32[at];
+                }
+                rows4(row[0], row[1], row[2], row[3]);
+            }
+        }
+        while (true) {
+            alive = alive && seen <= thr;
+            if (!__any(alive)) break;
+            const T least = wave_min(alive ? seen : Limits<T>::inf());
+            const int src = __builtin_ctzll(__ballot(alive && seen == least));
+            alive = alive && lane != src;
+            const uint32_t se = (uint32_t)__builtin_amdgcn_readlane((int)e, src);
+            const int32_t su = (int32_t)(se >> 16), sv = (int32_t)(se & 0xFFFFu);
+            const int64_t ju = __builtin_amdgcn_readfirstlane(perm[su]), jv = __builtin_amdgcn_readfirstlane(perm[sv]);
+            const T Dl = sc * (sh_dl[lev[su]] - sh_dl[lev[sv]]);
+            const T* __restrict__ Au = A + ju * lda;
+            const T* __restrict__ Av = A + jv * lda;
+            const T bnd = bound();
+            T val = (T)0, wm = (T)0;
+            int32_t at = 0;                                // the lane's row of val
+            bool ok = true;
+            for (int64_t base = 0; base < m && ok; base += 256) {
+                T a[4], b[4], rr[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const int64_t i = base + x * 64 + lane, ic = i < m ? i : m - 1;
+                    a[x] = Au[ic];
+                    b[x] = Av[ic];
+                    rr[x] = r_at(ic);
+                }
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const T w1 = dmmv_abs(dmmv_fma(Dl, b[x] - a[x], rr[x]));
+                    const int64_t i = base + x * 64 + lane;
+                    if (w1 > val) { val = w1; at = (int32_t)(i < m ? i : m - 1); }
+                }
+                wm = wave_max(val);
+                ok = wm < t && !(wm > bnd);
+            }
+            if (ok) {
+                const int64_t c = ju * n + jv;
+                if (rec_less(wm, c, best_t, best_c)) {
+                    best_t = wm;
+                    best_c = c;
+                    if (lane == 0) {
+                        atomicMin(&sh_best, order_bits(wm));
+                        if (gbest) share_best(gbest + q, wm);
+                    }
+                }
+            } else {
+                const int64_t row = __builtin_amdgcn_readlane(at, __builtin_ctzll(__ballot(val == wm)));
+                if (lane == 0) sh_fail[atomicAdd(&sh_fails, 1) & (SWI_SEEN - 1)] = (int32_t)row;
+                if (alive) seen = dmmv_max(seen, dmmv_abs(dmmv_fma(Ds, a_at(row, v) - a_at(row, u), r_at(row))));
+            }
+            thr = dmmv_min(bound(), t_below);
+        }
+    };
+
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int32_t units = groups * nd;
+    int qn = 0;                                            // queued pairs (uniform)
+    // The pairs of a unit within thr0, by lane: `upto` pairs up to and with this lane's, which are its variable with
+    // positions start + (number of the pair).  Returns how many there are.
+    int32_t upto = 0, start = 0, first_u = 0, first_v = 0;
+    T Ds = (T)0;
+    auto search = [&](int32_t unit, T thr0) -> int32_t {
+        const int32_t b = unit / groups, g = unit % groups;
+        const int32_t s0 = __builtin_amdgcn_readfirstlane(sh_first[b]), len = __builtin_amdgcn_readfirstlane(sh_first[b + 1]) - s0;
+        const int32_t pu = g * 64 + lane, puc = pu < nv ? pu : nv - 1;
+        const int32_t lu = lev[puc];
+        bool on = len > 0 && pu < nv && lu > b;
+        if (!__any(on)) return 0;
+        const T yu = y[puc];
+        Ds = sc * (sh_dl[lu] - sh_dl[b]);
+        auto f = [&](int32_t p) -> T { return dmmv_fma(Ds, y[p] - yu, r1); };
+        const T f0 = f(s0), f1 = f(s0 + len - 1);
+        on = on && f0 <= thr0 && f1 >= -thr0;              // (false where the step is not finite and gives no number)
+        if (!__any(on)) return 0;
+        int32_t hi = len, lo = 0;                          // variables with f <= thr0, and with f < -thr0
+        int32_t top = 1;
+        while (2 * top <= len) top *= 2;
+        if (__any(on && !(f1 <= thr0))) {
+            hi = 0;
+            for (int32_t d = top; d > 0; d >>= 1) {
+                const int32_t p = hi + d;
+                if (p <= len && f(s0 + (p < len ? p : len) - 1) <= thr0) hi = p;
+            }
+        }
+        if (__any(on && !(f0 >= -thr0))) {
+            for (int32_t d = top; d > 0; d >>= 1) {
+                const int32_t p = lo + d;
+                if (p <= len && !(f(s0 + (p < len ? p : len) - 1) >= -thr0)) lo = p;
+            }
+        }
+        const int32_t cnt = on && hi > lo ? hi - lo : 0;
+        upto = cnt;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t v = __shfl_up(upto, off, 64);
+            if (lane >= off) upto += v;
+        }
+        start = s0 + lo - (upto - cnt);
+        first_u = g * 64;
+        first_v = s0;
+        return __builtin_amdgcn_readlane(upto, 63);
+    };
+    // the 64 pairs from x0 of the unit searched last: the filter rows in LDS, what is left goes to the queue
+    auto look = [&](int32_t x0, int32_t x1) {
+        const int32_t x = x0 + lane;
+        int32_t l = 0;                                     // lanes whose pairs all come before pair x
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            const int32_t v = __shfl(upto, l + d - 1, 64);
+            if (v <= x) l += d;
+        }
+        bool alive = x < x1;
+        const int32_t pa = first_u + l, from = __shfl(start, l, 64);
+        const int32_t pb = alive ? from + x : first_v;
+        const T Dp = __shfl(Ds, l, 64);
+        const T thr = dmmv_min(bound(), t_below);
+        const int32_t pac = pa < nv ? pa : nv - 1;
+        for (int k = 1; k < lds.L; ++k) {
+            const T val = dmmv_abs(dmmv_fma(Dp, y[k * n + pb] - y[k * n + pac], rtop[k]));
+            alive = alive & (val <= thr);
+        }
+        const unsigned long long bal = __ballot(alive);
+        if (alive) queue[qn + __popcll(bal & below)] = ((uint32_t)pa << 16) | (uint32_t)pb;
+        qn += __popcll(bal);
+        __builtin_amdgcn_wave_barrier();
+    };
+    // The next pairs of stage s, [x0, x1) of a unit that has been searched: a unit of the stage, or when these are all
+    // taken a part of one on the workgroup's list.  (Its writer comes to the list after writing, so none is left
+    // over; an entry that is not ready yet is its writer's to see to.)
+    int slot = 0;
+    auto next = [&](int s, T reach, int32_t& x0, int32_t& x1) -> bool {
+        while (true) {
+            int32_t id = 0;
+            if (lane == 0) id = atomicAdd(&sh_unit[s], 1);
+            const int64_t unit = blk + (int64_t)nb * __builtin_amdgcn_readfirstlane(id);
+            int32_t u_next, parts = 0, p = 0;
+            T thr0;
+            if (unit < units) {
+                u_next = (int32_t)unit;
+                thr0 = dmmv_min(bound(), reach);
+            } else {
+                if (slot >= SWI_SHARED || slot >= __builtin_amdgcn_readfirstlane(__hip_atomic_load(&sh_big, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) return false;
+                if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&sh_big_ready[slot], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP))) {
+                    parts = __builtin_amdgcn_readfirstlane(sh_big_parts[slot]);
+                    if (lane == 0) p = atomicAdd(&sh_big_next[slot], 1);
+                    p = __builtin_amdgcn_readfirstlane(p);
+                }
+                if (p >= parts) { ++slot; continue; }
+                u_next = __builtin_amdgcn_readfirstlane(sh_big_unit[slot]);
+                thr0 = sh_big_thr[slot];
+            }
+            x0 = 0;
+            x1 = search(u_next, thr0);
+            if (parts > 0) {
+                x0 = p * SWI_PART;
+                x1 = x0 + SWI_PART < x1 ? x0 + SWI_PART : x1;
+            } else if (x1 > SWI_PART) {                    // a large one goes on the list, if there is room
+                int32_t to = 0;
+                if (lane == 0) to = atomicAdd(&sh_big, 1);
+                to = __builtin_amdgcn_readfirstlane(to);
+                if (to < SWI_SHARED) {
+                    if (lane == 0) {
+                        sh_big_unit[to] = u_next;
+                        sh_big_parts[to] = (x1 + SWI_PART - 1) / SWI_PART;
+                        sh_big_thr[to] = thr0;
+                        __hip_atomic_store(&sh_big_ready[to], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    slot = to < slot ? to : slot;
+                    continue;
+                }
+            }
+            if (x0 < x1) return true;
+        }
+    };
+    for (int s = 0; s < SWI_STAGES; ++s) {
+        const T share[SWI_STAGES] = {(T)0.75, (T)0.875, (T)0.9375, (T)0.96875, (T)1};
+        const T reach = dmmv_min(t * share[s], t_below);   // (the last one: t_below)
+        if (gbest) others = __hip_atomic_load(gbest + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (bool more = true; more;) {
+            int32_t x0 = 0, x1 = 0;
+            more = next(s, reach, x0, x1);
+            do {
+                if (x0 < x1) look(x0, x1);
+                x0 += 64;
+                if (qn >= 64 || (!more && qn > 0)) {       // (what is queued when nothing is left to take: at the end)
+                    drain(qn < 64 ? qn : 64);
+                    const uint32_t carry = 64 + lane < qn ? queue[64 + lane] : 0;
+                    __builtin_amdgcn_wave_barrier();
+                    if (64 + lane < qn) queue[lane] = carry;
+                    __builtin_amdgcn_wave_barrier();
+                    qn = qn > 64 ? qn - 64 : 0;
+                }
+            } while (x0 < x1 || (!more && qn > 0));
+        }
+        if (reach >= dmmv_min(bound(), t_below)) break;
+    }
+    if (lane == 0) { sh_s[w] = best_t; sh_c[w] = best_c; }
+    __syncthreads();
+    if (tid == 0) {
+        T bs = sh_s[0];
+        int64_t bc = sh_c[0];
+        for (int x = 1; x < SWE_WAVES; ++x)
+            if (rec_less(sh_s[x], sh_c[x], bs, bc)) { bs = sh_s[x]; bc = sh_c[x]; }
+        Partial<T> p;
+        p.s = bc < 0 ? (T)0 : bs;
+        p.c = bc;
+        *out = p;
+    }
+}
+
 // ---- reduce the records of an instance, report, and carry the swap out.  One workgroup per
 // instance.
 template <class T>
@@ -336,6 +845,15 @@ __global__ void k_swap_clear(int32_t* skip, int64_t R) {
     if (q < R) skip[q] = 0;
 }
 
+// workgroups per instance: two rounds of what the chip holds, each with two units or more for every wavefront
+static int32_t swap_sorted_blocks(int64_t n, int64_t R, int32_t nd, int32_t most) {
+    int64_t nb = ceil_div(512, R);
+    const int64_t units = ceil_div(n, 64) * nd;
+    if (nb > ceil_div(units, 2 * SWE_WAVES)) nb = ceil_div(units, 2 * SWE_WAVES);
+    if (nb > most) nb = most;
+    return (int32_t)(nb < 1 ? 1 : nb);
+}
+
 template <class T>
 dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swap* best, void* best_t) {
     const int64_t m = c->p.m, n = c->p.n, R = c->p.R;
@@ -343,7 +861,7 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
     int32_t K = k_eps > 0 ? k_eps : 100;
     if (K > SWAP_KMAX) K = SWAP_KMAX;
     if ((int64_t)K > m) K = (int32_t)m;
-    const int32_t nb = c->swap_nb;
+    int32_t nb = c->swap_nb;
     int32_t* skip = use_skip ? c->swap_skip : nullptr;
     // A batch's workgroups share the best t' of their instance, so that what one finds prunes the others' pairs
     // (the buffer of the descent's packed scales is free outside a descent's loop).
@@ -356,14 +874,46 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
     if (L > K) L = K;
     used += (size_t)L * n * sizeof(T);
 
+    // Sorted variables where their keys and filter rows fit.  Under 64 variables the sort and one more launch cost more
+    // than they save (100 x 17: 42 us without, 49 with; 256 x 64: 67 and 64).
+    const bool sorted = K > 0 && n >= SWI_NMIN && n <= SWI_NMAX && c->p.nd <= SWI_LEVELS;
+    SwapLds lds = {};
+    if (sorted) {
+        lds = swap_lds(m, n, K, sizeof(T), sizeof(SwapKey<T>), SWI_LDS_HALF);
+        if (lds.L == 0) lds = swap_lds(m, n, K, sizeof(T), sizeof(SwapKey<T>), SWI_LDS_ALL);
+    }
+    if (lds.L > 0) {
+        nb = swap_sorted_blocks(n, R, c->p.nd, c->swap_nb);
+        // (a single instance has two words among the flags, which nothing else looks at)
+        gbest = nb == 1 ? nullptr : c->kind == KIND_BATCHED ? (T*)c->cmp_scale : (T*)(c->flags + FLAG_SWAP_BEST);
+    }
     if (K > 0)
         hipLaunchKernelGGL(k_swap_top<T>, dim3((unsigned)R), dim3(SW_BLOCK), 0, c->stream, m, R, K, (const T*)c->r,
                            (const int32_t*)skip, c->swap_rows, gbest);
-    const dim3 grid((unsigned)R, (unsigned)nb);
+    if (lds.L > 0) {
+        // rows of large entries: from the evaluation's lists where a batch has them, else found now (in the buffer of
+        // the packed instances' levels, or that of the sampling weights: neither is in use during a search)
+        const uint16_t* hot16 = batched_lists_in_use(c) ? c->lists.crow : nullptr;
+        int32_t* hot32 = c->kind == KIND_BATCHED ? c->cmp_kidx : reinterpret_cast<int32_t*>(c->alns_weight);
+        int32_t n_hot = SWI_HOT;
+        if (!hot16) {
+            const int64_t room = c->kind == KIND_BATCHED ? R : 2;
+            if (n_hot > room) n_hot = (int32_t)room;
+            hipLaunchKernelGGL(k_swap_hot<T>, dim3((unsigned)n), dim3(64u * n_hot), 0, c->stream, m, n, (const T*)c->p.A_dense,
+                               c->p.lda, hot32, n_hot);
+        }
+        DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_intervals<T>), (int)SWI_LDS_ALL));
+        hipLaunchKernelGGL(k_swap_intervals<T>, dim3((unsigned)R, (unsigned)nb), dim3(SWE_BLOCK), lds.bytes, c->stream,
+                           m, (int32_t)n, R, c->p.nd, nb, K, lds, (const T*)c->p.A_dense, c->p.lda,
+                           (const T*)(c->kind == KIND_BATCHED ? c->Xt : nullptr), (const T*)c->D_dev,
+                           (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->r,
+                           (const InstState<T>*)c->state, c->o.var_mask, (const int32_t*)c->swap_rows,
+                           (const int32_t*)hot32, hot16, n_hot, (const int32_t*)skip, gbest, (Partial<T>*)c->swap_part);
+    } else {
     DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_eval<T, true>), (int)SW_LDS_BUDGET));
     DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_eval<T, false>), (int)SW_LDS_BUDGET));
 #define DMMV_SWAP_LAUNCH(DV)                                                                               \
-    hipLaunchKernelGGL((k_swap_eval<T, DV>), grid, dim3(SWE_BLOCK), used, c->stream, m, n, R, nb, K,       \
+    hipLaunchKernelGGL((k_swap_eval<T, DV>), dim3((unsigned)R, (unsigned)nb), dim3(SWE_BLOCK), used, c->stream, m, n, R, nb, K,       \
                        (int32_t)L, (const T*)c->p.A_dense, c->p.lda,                                       \
                        (const T*)(c->kind == KIND_BATCHED ? c->Xt : nullptr), (const T*)c->D_dev,          \
                        (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->r,                    \
@@ -372,6 +922,7 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
     if (dvl) DMMV_SWAP_LAUNCH(true);
     else DMMV_SWAP_LAUNCH(false);
 #undef DMMV_SWAP_LAUNCH
+    }
     hipLaunchKernelGGL(k_swap_apply<T>, dim3((unsigned)R), dim3(SW_BLOCK), 0, c->stream, m, n, R, nb, apply,
                        (const T*)c->p.A_dense, c->p.lda, (const T*)c->D_dev, (const T*)c->scale_dev, c->kidx,
                        (T*)c->r, (InstState<T>*)c->state, (const Partial<T>*)c->swap_part, skip,
