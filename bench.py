@@ -456,7 +456,7 @@ def l2_timing(inst, device: str, x0) -> dict:
         torch.cuda.synchronize()
         it_ms = (time.perf_counter() - t0) / 3 * 1e3
     peak = 157.3
-    return {"kernel": "k_l2_g_mfma" if inst.dtype == np.float32 else "k_l2_g_batched", "flops": flops, "ms": ms,
+    return {"kernel": "k_chain_product" if inst.dtype == np.float32 else "k_l2_g_batched", "flops": flops, "ms": ms,
             "TFLOPs": flops / (ms * 1e-3) / 1e12, "peak_TFLOPs_fp32_matrix": peak,
             "frac": flops / (ms * 1e-3) / 1e12 / peak,
             "ms_per_iteration_with_l2_rule": it_ms,

@@ -281,6 +281,8 @@ dmmv_status batched_build_xt(Ctx* c);    // the row-major copy of X only
 dmmv_status batched_residual(Ctx* c);
 bool batched_chain_applicable(const Ctx* c);
 dmmv_status batched_chain_residual(Ctx* c);   // the same residual on the matrix cores (fp32); also sets t = max |r|
+bool batched_chain_l2_applicable(const Ctx* c);
+dmmv_status batched_chain_l2_g(Ctx* c);       // l2_g = X^T r by the same kernel
 dmmv_status batched_eval(Ctx* c, void* scores_out, bool want_partials);
 dmmv_status batched_apply(Ctx* c, bool t_from_score, int32_t iters, dmmv_move* trace, void* trace_t);
 dmmv_status batched_set_x(Ctx* c, const void* x_values);

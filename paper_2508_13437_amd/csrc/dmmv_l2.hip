@@ -12,17 +12,14 @@
 //     c_j = ||a_j||^2 : the same chain with fma(A_ij, A_ij, acc)      (once, at create)
 //     dq(j, k)        = delta * fma(delta, c_j, 2 g_j)
 // For a batch g is the matrix G = X^T R_mat (n x R), a dense contraction: on fp32 batches it runs on
-// the matrix cores in the form that keeps the chain, v_mfma_f32_32x32x1_2b_f32 with K = 1 (one fused
-// multiply-add per element and instruction, rows in ascending order), so G carries the same bits
-// as the chain on the vector unit.
+// the matrix cores in the form that keeps the chain (dmmv_batched_chain.hip), so G carries the same
+// bits as the chain on the vector unit.
 #include "dmmv_common.h"
 #include "dmmv_sparse_common.h"
 
 namespace dmmv {
 
 namespace {
-
-typedef __attribute__((__vector_size__(32 * sizeof(float)))) float floatx32;
 
 // ---- column sums of squares, once per handle ------------------------------------------------
 template <class T>
@@ -97,85 +94,6 @@ __global__ __launch_bounds__(256) void k_l2_g_batched(int64_t m, int64_t n, int6
     }
 }
 
-// Batch, matrix cores (fp32).  One wavefront owns a 128 x 64 tile of G (variables x instances) as
-// four 2 x (32 x 32) accumulators; row i of the contraction is ONE instruction per accumulator:
-//     D = a b^T + C,  a = X[i][64 variables] (lane l: variable l of the tile's half),
-//                     b = r[i][32 instances] (lane l: instance l % 32),
-// each element one fused multiply-add rounded once, so after row i an accumulator holds exactly
-// the chain fma(X_ij, r_iq, .) over the rows 0..i.  Lane l receives, in register v, block v / 16
-// (variables 32 (v / 16) ...), instance l % 32 and variable row 8 ((v % 16) / 4) + 4 (l / 32) + v % 4
-// of the block.  The operands of the next L2_U rows are loaded before the products of the
-// current ones are issued.
-constexpr int L2_U = 6;
-
-__global__ __launch_bounds__(256, 2) void k_l2_g_mfma(int64_t m, int64_t n, int64_t R, const float* __restrict__ Xt,
-                                                      const float* __restrict__ r, float* __restrict__ G) {
-    const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const int64_t j0 = (blockIdx.x * 2ll + (w & 1)) * 128;
-    const int64_t q0 = (blockIdx.y * 2ll + (w >> 1)) * 64;
-    if (j0 >= n || q0 >= R) return;                       // whole wavefronts only
-    // Vector instructions do not overlap with the matrix cores' (measured: every one of them adds
-    // its issue time to the loop), so the loop is written to need none: a row's address is a
-    // uniform pointer (scalar unit) plus an unsigned 32-bit lane offset that never changes, and two sets
-    // of operand registers take turns, so nothing is copied.
-    // (byte offsets inside X and r, 32-bit: the host takes this kernel when both are below 4 GiB)
-    const uint32_t ja = 4u * (uint32_t)(j0 + lane < n ? j0 + lane : n - 1);
-    const uint32_t jb = 4u * (uint32_t)(j0 + 64 + lane < n ? j0 + 64 + lane : n - 1);
-    const uint32_t qa = 4u * (uint32_t)(q0 + (lane & 31) < R ? q0 + (lane & 31) : R - 1);
-    const uint32_t qb = 4u * (uint32_t)(q0 + 32 + (lane & 31) < R ? q0 + 32 + (lane & 31) : R - 1);
-    floatx32 c00, c01, c10, c11;
-#pragma unroll
-    for (int v = 0; v < 32; ++v) { c00[v] = 0.0f; c01[v] = 0.0f; c10[v] = 0.0f; c11[v] = 0.0f; }
-    const int32_t mrows = (int32_t)m;                       // rows are counted on the scalar unit
-    float pa0[L2_U], pa1[L2_U], pb0[L2_U], pb1[L2_U];       // set P
-    float qa0[L2_U], qa1[L2_U], qb0[L2_U], qb1[L2_U];       // set Q
-    // raw buffer loads: address = descriptor base + scalar row offset + lane offset, no vector
-    // instruction involved (a 64-bit global address would cost one vector add per load)
-    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void*)Xt, 0, (int)(uint32_t)(m * n * 4), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc((void*)r, 0, (int)(uint32_t)(m * R * 4), 0x00020000);
-    const uint32_t xstride = (uint32_t)n * 4u, rstride = (uint32_t)R * 4u;
-#define L2_AT(rs, off, soff) __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(off), (int)(soff), 0))
-#define L2_LOAD(A0, A1, B0, B1, I0)                                         \
-    _Pragma("unroll") for (int u = 0; u < L2_U; ++u) {                       \
-        const uint32_t i = (uint32_t)((I0) + u < mrows ? (I0) + u : mrows - 1); \
-        A0[u] = L2_AT(rs_x, ja, i * xstride);                                \
-        A1[u] = L2_AT(rs_x, jb, i * xstride);                                \
-        B0[u] = L2_AT(rs_r, qa, i * rstride);                                \
-        B1[u] = L2_AT(rs_r, qb, i * rstride);                                \
-    }
-#define L2_ROWS(A0, A1, B0, B1, I0)                                                      \
-    _Pragma("unroll") for (int u = 0; u < L2_U; ++u) {                                    \
-        if ((I0) + u < mrows) { /* uniform */                                             \
-            c00 = __builtin_amdgcn_mfma_f32_32x32x1f32(A0[u], B0[u], c00, 0, 0, 0);        \
-            c01 = __builtin_amdgcn_mfma_f32_32x32x1f32(A0[u], B1[u], c01, 0, 0, 0);        \
-            c10 = __builtin_amdgcn_mfma_f32_32x32x1f32(A1[u], B0[u], c10, 0, 0, 0);        \
-            c11 = __builtin_amdgcn_mfma_f32_32x32x1f32(A1[u], B1[u], c11, 0, 0, 0);        \
-        }                                                                                 \
-    }
-    if (mrows > 0) { L2_LOAD(pa0, pa1, pb0, pb1, 0) }
-    for (int32_t i0 = 0; i0 < mrows; i0 += 2 * L2_U) {
-        if (i0 + L2_U < mrows) { L2_LOAD(qa0, qa1, qb0, qb1, i0 + L2_U) }
-        L2_ROWS(pa0, pa1, pb0, pb1, i0)
-        if (i0 + 2 * L2_U < mrows) { L2_LOAD(pa0, pa1, pb0, pb1, i0 + 2 * L2_U) }
-        L2_ROWS(qa0, qa1, qb0, qb1, i0 + L2_U)
-    }
-#undef L2_LOAD
-#undef L2_ROWS
-#undef L2_AT
-    const int half = lane >> 5, col = lane & 31;
-#pragma unroll
-    for (int v = 0; v < 32; ++v) {
-        const int row = 32 * (v / 16) + 8 * ((v % 16) / 4) + 4 * half + v % 4;   // variable inside a 64-wide operand
-        const int64_t jlo = j0 + row, jhi = j0 + 64 + row;
-        const int64_t qlo = q0 + col, qhi = q0 + 32 + col;
-        if (jlo < n && qlo < R) G[jlo * R + qlo] = c00[v];
-        if (jlo < n && qhi < R) G[jlo * R + qhi] = c01[v];
-        if (jhi < n && qlo < R) G[jhi * R + qlo] = c10[v];
-        if (jhi < n && qhi < R) G[jhi * R + qhi] = c11[v];
-    }
-}
-
 // ---- the table dq[q][j*nd + k] -----------------------------------------------------------------
 template <class T>
 __device__ __forceinline__ T l2_change(T delta, T csq, T g) {
@@ -183,17 +101,51 @@ __device__ __forceinline__ T l2_change(T delta, T csq, T g) {
     return delta * dmmv_fma(delta, csq, twog);
 }
 
-// one thread per (instance, variable); g and kidx are [n][R]
+// A workgroup takes LTB_J variables x LTB_Q instances: g and the current values go through LDS, read along
+// the instances ([n][R]) and used along the table's rows, whose LTB_J nd values of an instance are contiguous.
+// (One thread per variable and instance, its nd values written by itself: 242 us for 1376 tables of 4096 x 8, a
+// wavefront's stores 64 tables apart; now 49.)
+constexpr int LTB_J = 64, LTB_Q = 32;
 template <class T>
-__global__ void k_l2_table(int64_t n, int64_t R, int32_t nd, const T* __restrict__ D, const T* __restrict__ scale,
-                           const int32_t* __restrict__ kidx, const T* __restrict__ g, const T* __restrict__ csq,
-                           T* __restrict__ dq) {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= n * R) return;
-    const int64_t q = t % R, j = t / R;
-    const T sc = scale[q], dcur = D[kidx[j * R + q]], gj = g[j * R + q], cj = csq[j];
-    T* __restrict__ out = dq + q * (n * (int64_t)nd) + j * nd;
-    for (int32_t k = 0; k < nd; ++k) out[k] = l2_change(step_of(D[k], dcur, sc), cj, gj);
+__global__ __launch_bounds__(256) void k_l2_table(int64_t n, int64_t R, int32_t nd, const T* __restrict__ D,
+                                                  const T* __restrict__ scale, const int32_t* __restrict__ kidx,
+                                                  const T* __restrict__ g, const T* __restrict__ csq, T* __restrict__ dq) {
+    __shared__ T sh_g[LTB_J][LTB_Q + 1], sh_d[LTB_J][LTB_Q + 1], sh_c[LTB_J];
+    const int64_t j0 = blockIdx.x * (int64_t)LTB_J, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) * LTB_Q;
+    if (q0 >= R) return;
+    const int32_t nj = (int32_t)(n - j0 < LTB_J ? n - j0 : LTB_J), nq = (int32_t)(R - q0 < LTB_Q ? R - q0 : LTB_Q);
+    const int tid = threadIdx.x, lq = tid % LTB_Q;
+    T gv[LTB_J * LTB_Q / 256];
+    int32_t kv[LTB_J * LTB_Q / 256];
+#pragma unroll
+    for (int u = 0; u < LTB_J * LTB_Q / 256; ++u) {
+        const int lj = tid / LTB_Q + u * (256 / LTB_Q);
+        const int64_t at = (j0 + (lj < nj ? lj : nj - 1)) * R + q0 + (lq < nq ? lq : nq - 1);
+        gv[u] = g[at];
+        kv[u] = kidx[at];
+    }
+#pragma unroll
+    for (int u = 0; u < LTB_J * LTB_Q / 256; ++u) {
+        const int lj = tid / LTB_Q + u * (256 / LTB_Q);
+        sh_g[lj][lq] = gv[u];
+        sh_d[lj][lq] = D[kv[u]];
+    }
+    if (tid < LTB_J) sh_c[tid] = csq[j0 + (tid < nj ? tid : nj - 1)];
+    __syncthreads();
+    // a wavefront takes an instance at a time; its lanes walk (variable, value) in table order
+    const int lane = tid & 63, w = tid >> 6;
+    const int32_t step_j = 64 / nd, step_k = 64 % nd;
+    for (int x = w; x < nq; x += 4) {
+        const T sc = scale[q0 + x];
+        T* __restrict__ out = dq + (q0 + x) * (n * (int64_t)nd) + j0 * nd;
+        int32_t j = lane / nd, k = lane % nd;
+        for (int64_t e = lane; j < nj; e += 64) {
+            out[e] = l2_change(step_of(D[k], sh_d[j][x], sc), sh_c[j], sh_g[j][x]);
+            k += step_k;
+            j += step_j;
+            if (k >= nd) { k -= nd; ++j; }
+        }
+    }
 }
 
 // ---- arg-min of a score table with dq as second criterion, one workgroup per instance ----------
@@ -206,7 +158,9 @@ __device__ __forceinline__ bool rec3_less(T s1, T q1, int64_t c1, T s2, T q2, in
     return c1 < c2;
 }
 
-template <class T>
+// ROWS: a thread takes a variable's values one after the other (what depends on the variable is read once, and
+// nothing of a value whose score is above the best so far); else the values are spread over the threads.
+template <class T, bool ROWS>
 __global__ __launch_bounds__(1024) void k_l2_select(int64_t n, int64_t R, int32_t nd, int32_t rule,
                                                     const T* __restrict__ scores, const T* __restrict__ D,
                                                     const T* __restrict__ scale, const int32_t* __restrict__ kidx,
@@ -222,7 +176,23 @@ __global__ __launch_bounds__(1024) void k_l2_select(int64_t n, int64_t R, int32_
     const T* __restrict__ tab = scores + q * (n * (int64_t)nd);
     T bs = (T)0, bq = (T)0;
     int64_t bc = -1;
-    for (int64_t e = threadIdx.x; e < n * (int64_t)nd; e += blockDim.x) {
+    for (int64_t j = threadIdx.x; ROWS && j < n; j += blockDim.x) {
+        const T dcur = D[kidx[j * R + q]], gj = g[j * R + q], cj = csq[j];
+        for (int32_t k0 = 0; k0 < nd; k0 += 8) {
+            T s[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s[u] = tab[j * nd + (k0 + u < nd ? k0 + u : nd - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (k0 + u >= nd || (bc >= 0 && s[u] > bs)) continue;
+                const T dq = l2_change(step_of(D[k0 + u], dcur, sc), cj, gj);
+                const int64_t e = j * nd + k0 + u;
+                if (rule == 2 && !(dq <= (T)0)) continue;
+                if (rec3_less(s[u], dq, e, bs, bq, bc)) { bs = s[u]; bq = dq; bc = e; }
+            }
+        }
+    }
+    for (int64_t e = threadIdx.x; !ROWS && e < n * (int64_t)nd; e += blockDim.x) {
         const int64_t j = e / nd;
         const int32_t k = (int32_t)(e - j * nd);
         const T dq = l2_change(step_of(D[k], D[kidx[j * R + q]], sc), csq[j], g[j * R + q]);
@@ -299,10 +269,8 @@ dmmv_status update_g_t(Ctx* c) {
     } else if (c->kind == KIND_DENSE) {
         hipLaunchKernelGGL(k_l2_g_dense<T>, dim3((unsigned)ceil_div(n, 64)), dim3(64), 0, c->stream, m, n,
                            (const T*)c->p.A_dense, c->p.lda, (const T*)c->r, (T*)c->l2_g);
-    } else if (sizeof(T) == 4 && m * n < (1ll << 30) && m * R < (1ll << 30)) {     // the kernel's 32-bit byte offsets
-        const dim3 grid((unsigned)ceil_div(n, 256), (unsigned)ceil_div(R, 128));
-        hipLaunchKernelGGL(k_l2_g_mfma, grid, dim3(256), 0, c->stream, m, n, R, (const float*)c->Xt, (const float*)c->r,
-                           (float*)c->l2_g);
+    } else if (batched_chain_l2_applicable(c)) {
+        return batched_chain_l2_g(c);
     } else {
         constexpr int TJ = 8;
         const dim3 grid((unsigned)ceil_div(R, 256), (unsigned)ceil_div(n, TJ));
@@ -317,7 +285,8 @@ template <class T>
 dmmv_status table_t(Ctx* c, void* dq_out) {
     const int64_t n = c->p.n, R = c->p.R;
     if (n == 0) return DMMV_OK;
-    hipLaunchKernelGGL(k_l2_table<T>, dim3((unsigned)ceil_div(n * R, 256)), dim3(256), 0, c->stream, n, R, c->p.nd,
+    const int64_t gq = ceil_div(R, LTB_Q), gy = gq < 32768 ? gq : 32768;
+    hipLaunchKernelGGL(k_l2_table<T>, dim3((unsigned)ceil_div(n, LTB_J), (unsigned)gy, (unsigned)ceil_div(gq, gy)), dim3(256), 0, c->stream, n, R, c->p.nd,
                        (const T*)c->D_dev, (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->l2_g,
                        (const T*)c->l2_c, (T*)dq_out);
     DMMV_LAUNCH_CHECK();
@@ -326,7 +295,9 @@ dmmv_status table_t(Ctx* c, void* dq_out) {
 
 template <class T>
 dmmv_status select_t(Ctx* c, const void* scores, int32_t keep_going, dmmv_move* best_out, void* best_score_out) {
-    hipLaunchKernelGGL(k_l2_select<T>, dim3((unsigned)c->p.R), dim3(1024), 0, c->stream, c->p.n, c->p.R, c->p.nd,
+    // (up to 32 values: a wavefront's 64 rows of the table then stay in the cache between the loads of a row)
+    auto kernel = c->p.nd <= 32 ? k_l2_select<T, true> : k_l2_select<T, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)c->p.R), dim3(1024), 0, c->stream, c->p.n, c->p.R, c->p.nd,
                        c->o.l2_rule, (const T*)scores, (const T*)c->D_dev, (const T*)c->scale_dev,
                        (const int32_t*)c->kidx, (const T*)c->l2_g, (const T*)c->l2_c, (InstState<T>*)c->state,
                        keep_going, best_out, (T*)best_score_out);
