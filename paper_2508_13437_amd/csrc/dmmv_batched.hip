@@ -37,31 +37,76 @@ static void launch_transpose(hipStream_t s, const T* in, int64_t rows, int64_t c
     hipLaunchKernelGGL(k_transpose<T>, grid, dim3(32, 8), 0, s, in, rows, cols, ld_in, out, ld_out);
 }
 
-// x values [R][n] -> kidx [n][R]
+// x values [R][n] <-> kidx [n][R], 32 x 32 at a time through LDS so that both are read and written along their rows (an
+// element per thread in the order of one of them took 99 and 57 us for 4096 x 4096 and 19 and 14 for 500 x 4096; now 39 and
+// 27, 9 and 6).
+// Values are looked up in a copy of D in LDS where it fits.
+constexpr int XV_LEVELS = 1024;
 template <class T>
-__global__ void k_values_to_index_batched(const T* __restrict__ x, const T* __restrict__ D,
-                                          int32_t nd, int64_t n, int64_t R,
-                                          int32_t* __restrict__ kidx, int32_t* flags) {
-    int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= n * R) return;
-    const int64_t j = t / R, q = t % R;
-    const T v = x[q * n + j];
-    int32_t lo = 0, hi = nd - 1;
-    while (lo < hi) {
-        int32_t mid = (lo + hi) >> 1;
-        if (D[mid] < v) lo = mid + 1; else hi = mid;
+__global__ __launch_bounds__(256) void k_values_to_index_batched(const T* __restrict__ x, const T* __restrict__ D,
+                                                                 int32_t nd, int64_t n, int64_t R,
+                                                                 int32_t* __restrict__ kidx, int32_t* flags) {
+    __shared__ int32_t tile[32][33];
+    __shared__ T sh_d[XV_LEVELS];
+    const int64_t j0 = blockIdx.x * 32ll, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) * 32;
+    if (q0 >= R) return;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const bool in_lds = nd <= XV_LEVELS;
+    T v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t q = q0 + ty + 8 * u, j = j0 + tx;
+        v[u] = x[(q < R ? q : R - 1) * n + (j < n ? j : n - 1)];
     }
-    if (!(D[lo] == v)) { atomicOr(&flags[FLAG_ERROR], ERRBIT_X_NOT_IN_D); lo = 0; }
-    kidx[t] = lo;
+    for (int32_t k = threadIdx.x; in_lds && k < nd; k += 256) sh_d[k] = D[k];
+    __syncthreads();
+    auto level = [&](int32_t k) -> T { return in_lds ? sh_d[k] : D[k]; };
+    int32_t lo[4] = {0, 0, 0, 0}, hi[4] = {nd - 1, nd - 1, nd - 1, nd - 1};
+    for (int32_t span = nd - 1; span > 0; span >>= 1)       // (as many steps as the widest interval takes)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t mid = (lo[u] + hi[u]) >> 1;
+            if (lo[u] < hi[u]) { if (level(mid) < v[u]) lo[u] = mid + 1; else hi[u] = mid; }
+        }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if (!(level(lo[u]) == v[u])) { atomicOr(&flags[FLAG_ERROR], ERRBIT_X_NOT_IN_D); lo[u] = 0; }
+        tile[ty + 8 * u][tx] = lo[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t j = j0 + ty + 8 * u, q = q0 + tx;
+        if (j < n && q < R) kidx[j * R + q] = tile[tx][ty + 8 * u];
+    }
 }
 
 template <class T>
-__global__ void k_index_to_values_batched(const int32_t* __restrict__ kidx, const T* __restrict__ D,
-                                          int64_t n, int64_t R, T* __restrict__ x) {
-    int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= n * R) return;
-    const int64_t q = t / n, j = t % n;
-    x[t] = D[kidx[j * R + q]];
+__global__ __launch_bounds__(256) void k_index_to_values_batched(const int32_t* __restrict__ kidx, const T* __restrict__ D,
+                                                                 int64_t n, int64_t R, T* __restrict__ x) {
+    __shared__ T tile[32][33];
+    const int64_t j0 = blockIdx.x * 32ll, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) * 32;
+    if (q0 >= R) return;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    int32_t k[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t j = j0 + ty + 8 * u, q = q0 + tx;
+        k[u] = kidx[(j < n ? j : n - 1) * R + (q < R ? q : R - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) tile[ty + 8 * u][tx] = D[k[u]];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t q = q0 + ty + 8 * u, j = j0 + tx;
+        if (j < n && q < R) x[q * n + j] = tile[tx][ty + 8 * u];
+    }
+}
+
+static dim3 values_grid(int64_t n, int64_t R) {
+    const int64_t gq = ceil_div(R, 32), gy = gq < 32768 ? gq : 32768;
+    return dim3((unsigned)ceil_div(n, 32), (unsigned)gy, (unsigned)ceil_div(gq, gy));
 }
 
 // ---- residual -------------------------------------------------------------------------------
@@ -520,7 +565,7 @@ static dmmv_status apply_t(Ctx* c, bool t_from_score, int32_t iters, dmmv_move* 
 template <class T>
 static dmmv_status set_x_t(Ctx* c, const void* x) {
     const int64_t tot = c->p.n * c->p.R;
-    hipLaunchKernelGGL(k_values_to_index_batched<T>, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, c->stream,
+    hipLaunchKernelGGL(k_values_to_index_batched<T>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
                        (const T*)x, (const T*)c->D_dev, c->p.nd, c->p.n, c->p.R, c->kidx, c->flags);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
@@ -529,7 +574,7 @@ static dmmv_status set_x_t(Ctx* c, const void* x) {
 template <class T>
 static dmmv_status get_x_t(Ctx* c, void* x) {
     const int64_t tot = c->p.n * c->p.R;
-    hipLaunchKernelGGL(k_index_to_values_batched<T>, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, c->stream,
+    hipLaunchKernelGGL(k_index_to_values_batched<T>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
                        (const int32_t*)c->kidx, (const T*)c->D_dev, c->p.n, c->p.R, (T*)x);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
@@ -682,10 +727,10 @@ dmmv_status batched_get_x_from(Ctx* c, const int32_t* kidx, void* x) {
     const int64_t tot = c->p.n * c->p.R;
     if (tot == 0) return DMMV_OK;
     if (c->p.dtype == DMMV_F64)
-        hipLaunchKernelGGL(k_index_to_values_batched<double>, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, c->stream,
+        hipLaunchKernelGGL(k_index_to_values_batched<double>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
                            kidx, (const double*)c->D_dev, c->p.n, c->p.R, (double*)x);
     else
-        hipLaunchKernelGGL(k_index_to_values_batched<float>, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, c->stream,
+        hipLaunchKernelGGL(k_index_to_values_batched<float>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
                            kidx, (const float*)c->D_dev, c->p.n, c->p.R, (float*)x);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
