@@ -564,7 +564,6 @@ static dmmv_status apply_t(Ctx* c, bool t_from_score, int32_t iters, dmmv_move* 
 
 template <class T>
 static dmmv_status set_x_t(Ctx* c, const void* x) {
-    const int64_t tot = c->p.n * c->p.R;
     hipLaunchKernelGGL(k_values_to_index_batched<T>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
                        (const T*)x, (const T*)c->D_dev, c->p.nd, c->p.n, c->p.R, c->kidx, c->flags);
     DMMV_LAUNCH_CHECK();
@@ -573,7 +572,6 @@ static dmmv_status set_x_t(Ctx* c, const void* x) {
 
 template <class T>
 static dmmv_status get_x_t(Ctx* c, void* x) {
-    const int64_t tot = c->p.n * c->p.R;
     hipLaunchKernelGGL(k_index_to_values_batched<T>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
                        (const int32_t*)c->kidx, (const T*)c->D_dev, c->p.n, c->p.R, (T*)x);
     DMMV_LAUNCH_CHECK();
