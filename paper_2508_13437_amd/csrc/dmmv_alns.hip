@@ -329,18 +329,20 @@ __global__ __launch_bounds__(1024) void k_alns_worst_list(int64_t R, const AlnsS
 //
 // k_alns_impact_batched: lane = variable, so a row of X is one coalesced load that IM_Q instances share
 // (with lane = instance and X through the scalar unit a small batch left most of the chip idle:
-// 1.56 ms for the listed half of 20 instances of 2048 x 768, and 5.0 ms for that of 1024 of 2048 x 4096; now 0.10 and
-// 2.25 ms, the limits' launch 0.01 and 0.02 more).  A wavefront takes 64 variables x IM_Q instances x IM_ROWS rows at a time: the tests leave one bit
-// per row in a mask (two instructions a term), the set bits are then popped into a queue in LDS,
-// and whenever 64 are waiting every lane evaluates one, for whichever variable and instance it belongs
-// to, and adds the integer to that sum with an LDS atomic.  Bound by instruction issue (vector unit busy 65 %, about
-// 1100 vector instructions per 64 x 4 x 32 terms, a third of them the evaluations).  The sums are integers, so neither their
-// order nor the split of the rows over workgroups (small batches) changes a weight.
+// 1.56 ms for the listed half of 20 instances of 2048 x 768, and 5.0 ms for that of 1024 of 2048 x 4096; now 0.056 and
+// 1.8 ms, the limits' launch 0.01 and 0.02 more).  A wavefront takes 64 variables x IM_Q instances x IM_ROWS rows at a time: the tests leave one bit
+// per row in a mask (two instructions a term), the set bits go to a queue in LDS, a lane's behind those of the lanes before
+// it, and the queue is evaluated two entries a lane, for whichever variable and instance they belong to, the integers
+// added to the sums with LDS atomics.  About 1050 vector instructions per 64 x 4 x 32 terms, a quarter of them the tests
+// and a third the evaluations, the unit 60 % busy.  (One entry a lane: 1.88 ms; the bits popped a variable at a time over
+// the wavefront, with an evaluation whenever 64 were waiting and the whole of the term's arithmetic in it: 2.25.)  The sums are integers, so neither their
+// order nor the split of the rows over workgroups (small batches: one pass each, 0.056 ms against 0.10 with two) changes a weight.
 constexpr int IM_Q = 4;                        // instances that share a row of X
 constexpr int IM_ROWS = 32;                    // rows per pass: one mask bit each
 constexpr int IM_STAGE = IM_ROWS * IM_Q / 64;  // (row, instance) pairs a lane stages per pass
-constexpr int IM_CAP = 128;                    // ring of waiting terms per wavefront (drained at 64)
-constexpr int IM_FEW = 4;                      // a variable with more terms than this in a pass is queued by rows
+constexpr int IM_MOST = 64 * IM_ROWS;          // terms of an instance a pass can have
+constexpr int IM_CAP = IM_MOST + 512;          // queue of a wavefront: evaluated when over 512 are waiting
+constexpr int IM_FEW = 8;                      // a variable with more terms than this in a pass is queued by rows
 
 // mask = 2 mask + (|x| >= lim): the comparison's bit enters as the carry of one addition
 __device__ __forceinline__ uint32_t impact_test(uint32_t mask, float x, float lim) {
@@ -354,12 +356,24 @@ __device__ __forceinline__ uint32_t impact_test(uint32_t mask, double x, double 
 
 template <class T>
 struct ImpactShared {
-    T r[4][IM_ROWS][IM_Q], lim[4][IM_ROWS][IM_Q];
+    double rate[4][IM_ROWS][IM_Q], base[4][IM_ROWS][IM_Q];   // per row and instance: 16 log2(e) alpha (t - sk) / sc, sk scale
+    T lim[4][IM_ROWS][IM_Q];
     unsigned long long sum[4][IM_Q][64];
     uint16_t queue[4][IM_CAP];                 // lane | instance << 6 | row << 8
-    double sc[IM_Q], t[IM_Q], scale[IM_Q];     // per instance: scale factor, error, fixed-point scale
+    double rate_q[IM_Q], t[IM_Q], scale[IM_Q]; // per instance: 16 log2(e) alpha / sc, error, fixed-point scale
     double exp2m[16];                          // 2^(-f/16)
 };
+
+// inclusive sum over the lanes up to this one
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);      // row_shr 1, 2, 4, 8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);      // row_bcast 15, 31
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
+    return v;
+}
 
 // lim[i][slot], smallest |x| whose term may reach 1 in row i of the slot's instance; clears the sums
 template <class T>
@@ -386,34 +400,34 @@ __global__ __launch_bounds__(256) void k_alns_impact_limits(int64_t m, int64_t n
     }
 }
 
-// The fixed-point term by a shorter route: reciprocal with one Newton step instead of a division, e^-y from
-// 2^(-f/16) and a polynomial of degree 6.  Its relative error stays below 2^-40 (reciprocal 2^-46, times
-// y < 20; polynomial 2^-50), the term is below 2^24, so the integer part is that of alns_impact_term unless the
-// fraction is within 2^-15 of an integer; those (and everything out of the ordinary) take alns_impact_term.
-__device__ __forceinline__ uint32_t alns_impact_term_fast(double a, double sk, double t, double alpha, double scale,
-                                                          const double* exp2m) {
-    const double slack = t - sk;
-    double rc = __builtin_amdgcn_rcp(a);
-    rc = __builtin_fma(rc, __builtin_fma(-a, rc, 1.0), rc);
-    const double y = alpha * (slack * rc);
-    const bool usual = y < 20.0;                            // false for NaN
-    const double kf = __builtin_rint((usual ? y : 0.0) * 0x1.71547652b82fep+4);   // 16 log2 e
-    const double z = __builtin_fma(kf, 0x1.62e42fefa39efp-5, -y);                  // ln 2 / 16: |z| < 0.022
-    double p = __builtin_fma(z, 1.0 / 720.0, 1.0 / 120.0);
-    p = __builtin_fma(p, z, 1.0 / 24.0);
-    p = __builtin_fma(p, z, 1.0 / 6.0);
-    p = __builtin_fma(p, z, 0.5);
-    p = __builtin_fma(p, z, 1.0);
+// The fixed-point term by a shorter route: y16 = 16 log2(e) alpha (t - sk) / (sc |x|) with the part of row and instance
+// given (rate) and a reciprocal with one Newton step instead of a division, 2^(-y16 / 16) from 2^(-f/16) and a polynomial
+// of degree 6.  Its relative error stays below 2^-40 (reciprocal 2^-46, rate 2^-50, times y < 20; polynomial 2^-50),
+// the term is below 2^24, so the integer part is that of alns_impact_term unless the
+// fraction is within 2^-15 of an integer; those (and everything out of the ordinary) are left to it: false.
+__device__ __forceinline__ bool alns_impact_term_fast(double x, double rate, double base, const double* exp2m, uint32_t& term) {
+    double rc = __builtin_amdgcn_rcp(x);
+    rc = __builtin_fma(rc, __builtin_fma(-x, rc, 1.0), rc);
+    const double y16 = rate * rc;
+    const bool usual = y16 < 20.0 * 16.0 * 0x1.71547652b82fep+0;      // false for NaN
+    const double kf = __builtin_rint(usual ? y16 : 0.0);
+    const double z = kf - y16;                                        // |z| <= 1/2: powers of (ln 2 / 16) z
+    constexpr double C = 0x1.62e42fefa39efp-5;
+    double p = __builtin_fma(z, C * C * C * C * C * C / 720.0, C * C * C * C * C / 120.0);
+    p = __builtin_fma(p, z, C * C * C * C / 24.0);
+    p = __builtin_fma(p, z, C * C * C / 6.0);
+    p = __builtin_fma(p, z, C * C / 2.0);
+    p = __builtin_fma(p, z, C);
     p = __builtin_fma(p, z, 1.0);
     const int k = (int)kf;
-    const double g = __builtin_ldexp((sk * scale) * (p * exp2m[k & 15]), -(k >> 4));
+    const double g = __builtin_ldexp(base * (p * exp2m[k & 15]), -(k >> 4));
     const double whole = __builtin_floor(g), frac = g - whole;
-    if (!(usual && frac > 0x1p-15 && frac < 1.0 - 0x1p-15)) return (uint32_t)alns_impact_term(a, sk, t, alpha, scale);
-    return (uint32_t)whole;
+    term = (uint32_t)whole;
+    return usual && frac > 0x1p-15 && frac < 1.0 - 0x1p-15;
 }
 
 template <class T>
-__global__ __launch_bounds__(256) void k_alns_impact_batched(int64_t m, int64_t n, int64_t R,
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_batched(int64_t m, int64_t n, int64_t R,
                                                              const T* __restrict__ Xt,
                                                              const T* __restrict__ scale_q,
                                                              const T* __restrict__ r, const T* __restrict__ lim,
@@ -430,7 +444,7 @@ __global__ __launch_bounds__(256) void k_alns_impact_batched(int64_t m, int64_t 
     if (threadIdx.x < 16) L.exp2m[threadIdx.x] = exp2(-(double)threadIdx.x / 16.0);
     if (threadIdx.x < IM_Q) {
         const int64_t q = list[s0 + threadIdx.x < count ? s0 + threadIdx.x : count - 1];
-        L.sc[threadIdx.x] = (double)scale_q[q];
+        L.rate_q[threadIdx.x] = 0x1.71547652b82fep+4 * alpha / (double)scale_q[q];
         L.t[threadIdx.x] = (double)st[q].t;
         L.scale[threadIdx.x] = alns_impact_scale((double)st[q].t);
     }
@@ -442,21 +456,47 @@ __global__ __launch_bounds__(256) void k_alns_impact_batched(int64_t m, int64_t 
     const int64_t slot = s0 + sv, slot_c = slot < count ? slot : count - 1;
     const int64_t sq = list[slot_c];
     const int wl = threadIdx.x >> 6;                        // (in a vector register: LDS addresses are one register + constants)
-    int head = 0, waiting = 0;                              // the same in every lane
-    int64_t i_pass = 0, j_pass = 0;                         // first row and variable of the pass
-    // every lane evaluates one of the first `take` waiting terms, for the sum it belongs to
-    auto drain = [&](int take) {
+    int waiting = 0;                                        // queued terms, the same in every lane
+    // all queued terms of the pass at (i_pass, j_pass), 64 at a time, each for the sum it belongs to
+    auto evaluate = [&](int64_t i_pass, int64_t j_pass) {
         __builtin_amdgcn_wave_barrier();
-        if (lane < take) {
-            const int e = L.queue[wl][(head + lane) & (IM_CAP - 1)];
-            const int col = e & 63, v = (e >> 6) & (IM_Q - 1), row = e >> 8;
-            const double a = __builtin_fabs(L.sc[v] * (double)(Xt + i_pass * n + j_pass)[(int64_t)row * n + col]);
-            const uint32_t term = alns_impact_term_fast(a, __builtin_fabs((double)L.r[wl][row][v]), L.t[v], alpha, L.scale[v], L.exp2m);
-            if (term) atomicAdd(&L.sum[wl][v][col], (unsigned long long)term);
+        const T* __restrict__ at = Xt + i_pass * n + j_pass;
+        // (an entry is column, instance and row from the lowest bit on, which is the order of the tables: its parts are
+        // their indices)
+        const double* rate = &L.rate[wl][0][0];
+        const double* base = &L.base[wl][0][0];
+        unsigned long long* sums = &L.sum[wl][0][0];
+        // two entries a lane at a time, for one's latencies to hide the other's (past the end: the last, not counted)
+        for (int h = 0; h < waiting; h += 128) {
+            uint32_t e[2], term[2];
+            T x[2];
+            bool exact[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int p = h + 64 * u + lane;
+                e[u] = L.queue[wl][p < waiting ? p : waiting - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) x[u] = dmmv_abs(at[(int64_t)(e[u] >> 8) * n + (e[u] & 63u)]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) exact[u] = alns_impact_term_fast((double)x[u], rate[e[u] >> 6], base[e[u] >> 6], L.exp2m, term[u]);
+            if (!(exact[0] && exact[1])) {
+#pragma unroll 1
+                for (int u = 0; u < 2; ++u) {
+                    const uint32_t eu = u ? e[1] : e[0];
+                    const int v = (int)(eu >> 6) & (IM_Q - 1);
+                    const int64_t q = list[s0 + v < count ? s0 + v : count - 1];
+                    const uint32_t whole = (uint32_t)alns_impact_term(__builtin_fabs((double)scale_q[q] * (double)(u ? x[1] : x[0])),
+                                                                      __builtin_fabs((double)r[(i_pass + (int)(eu >> 8)) * R + q]), L.t[v], alpha, L.scale[v]);
+                    if (u) term[1] = whole; else term[0] = whole;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (term[u] && h + 64 * u + lane < waiting) atomicAdd(&sums[e[u] & 255u], (unsigned long long)term[u]);
         }
         __builtin_amdgcn_wave_barrier();
-        head = (head + take) & (IM_CAP - 1);
-        waiting -= take;
+        waiting = 0;
     };
     for (int64_t j0 = (blockIdx.y * 4ll + w) * 64; j0 < n; j0 += 256ll * gridDim.y) {   // whole wavefronts; no barrier inside
         const int64_t j = j0 + lane;
@@ -473,27 +513,29 @@ __global__ __launch_bounds__(256) void k_alns_impact_batched(int64_t m, int64_t 
                 ls[u] = lim[i * R + slot_c];
                 if (i0 + row >= i_end || slot != slot_c) ls[u] = Limits<T>::inf();
             }
-            // one uniform pointer that walks (rows past the end repeat the last); the stride is made opaque,
+            // one uniform pointer that walks; the stride is made opaque,
             // or its 32 multiples are kept in scalar registers across the whole loop, which spills them
             const T* __restrict__ row = Xt + i0 * n + j0;
             int64_t stride = n;
             asm volatile("" : "+s"(stride));
+            if (i0 + IM_ROWS <= i_end) {
 #pragma unroll
-            for (int u = 0; u < IM_ROWS; ++u) {
-                x[u] = row[lc];
-                row += i0 + u + 1 < i_end ? stride : 0;
+                for (int u = 0; u < IM_ROWS; ++u) { x[u] = row[lc]; row += stride; }
+            } else {                                        // (rows past the end repeat the last)
+#pragma unroll
+                for (int u = 0; u < IM_ROWS; ++u) { x[u] = row[lc]; row += i0 + u + 1 < i_end ? stride : 0; }
             }
         };
         fetch(i_begin);
         for (int64_t i0 = i_begin; i0 < i_end; i0 += IM_ROWS) {
 #pragma unroll
             for (int u = 0; u < IM_STAGE; ++u) {
-                L.r[wl][su + u * (64 / IM_Q)][sv] = rs[u];
+                const double sk = __builtin_fabs((double)rs[u]);
+                L.rate[wl][su + u * (64 / IM_Q)][sv] = (L.t[sv] - sk) * L.rate_q[sv];
+                L.base[wl][su + u * (64 / IM_Q)][sv] = sk * L.scale[sv];
                 L.lim[wl][su + u * (64 / IM_Q)][sv] = ls[u];
             }
             __builtin_amdgcn_wave_barrier();
-            i_pass = i0;
-            j_pass = j0;
             uint32_t mask[IM_Q];
 #pragma unroll
             for (int v = 0; v < IM_Q; ++v) mask[v] = 0;
@@ -503,9 +545,14 @@ __global__ __launch_bounds__(256) void k_alns_impact_batched(int64_t m, int64_t 
                 for (int v = 0; v < IM_Q; ++v) mask[v] = impact_test(mask[v], x[u], L.lim[wl][u][v]);
             }
             if (i0 + IM_ROWS < i_end) fetch(i0 + IM_ROWS);
+            // (the entries of X and r are replaced after the pass: the queue is emptied with its last instance)
 #pragma unroll 1
-            for (int v = 0; v < IM_Q; ++v) {
-                uint32_t mk = j < n ? __brev(mask[0]) : 0;  // bit = row
+            for (int v = 0;; ++v) {
+                if (waiting > IM_CAP - IM_MOST || v == IM_Q) {
+                    evaluate(i0, j0);
+                    if (v == IM_Q) break;
+                }
+                uint32_t mk = j < n ? mask[0] : 0;          // highest bit = first row
 #pragma unroll
                 for (int e = 0; e + 1 < IM_Q; ++e) mask[e] = mask[e + 1];
                 // a variable with many terms (an outlier channel): all its rows at once, lane = row
@@ -513,29 +560,24 @@ __global__ __launch_bounds__(256) void k_alns_impact_batched(int64_t m, int64_t 
                 while (many) {                              // the same for the whole wavefront
                     const int col = __ffsll(many) - 1;
                     many &= many - 1;
-                    const uint32_t rows = __builtin_amdgcn_readlane(mk, col);
+                    const uint32_t rows = __brev(__builtin_amdgcn_readlane(mk, col));
                     if (lane == col) mk = 0;
                     if (lane < IM_ROWS && ((rows >> lane) & 1u))
-                        L.queue[wl][(head + waiting + __builtin_amdgcn_mbcnt_lo(rows, 0)) & (IM_CAP - 1)] = (uint16_t)(col | (v << 6) | (lane << 8));
+                        L.queue[wl][waiting + __builtin_amdgcn_mbcnt_lo(rows, 0)] = (uint16_t)(col | (v << 6) | (lane << 8));
                     waiting += __popc(rows);
-                    if (waiting >= 64) drain(64);
                 }
-                // the others: every variable's next row
-                while (true) {
-                    const unsigned long long some = __ballot(mk != 0);
-                    if (some == 0) break;
+                // the others: a lane's rows one after the other, behind those of the lanes before it
+                const uint32_t mine = __popc(mk), upto = wave_scan(mine);
+                int at = waiting + (int)(upto - mine);
+                waiting += (int)__builtin_amdgcn_readlane(upto, 63);
+                while (__ballot(mk != 0) != 0ull) {
                     if (mk) {
-                        const int row = __ffs(mk) - 1;
-                        mk &= mk - 1;
-                        const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32),
-                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0));
-                        L.queue[wl][(head + waiting + before) & (IM_CAP - 1)] = (uint16_t)(lane | (v << 6) | (row << 8));
+                        const int row = __clz(mk);
+                        L.queue[wl][at++] = (uint16_t)(lane | (v << 6) | (row << 8));
+                        mk ^= 0x80000000u >> row;
                     }
-                    waiting += __builtin_popcountll(some);
-                    if (waiting >= 64) drain(64);
                 }
             }
-            if (waiting > 0) drain(waiting);                // the entries of X and r are replaced next
         }
         if (j < n) {
 #pragma unroll
@@ -709,11 +751,11 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
                            (const InstState<T>*)c->state, prm.alpha, (T*)c->cmp_r, c->alns_weight,
                            (const int32_t*)c->cmp_orig, (const int32_t*)c->flags);
         // about half of the instances are on the list; the rows are split until some 8 wavefronts per SIMD
-        // are there to hide the loads of each other, at least two passes of rows each
+        // are there to hide the loads of each other, at least one pass of rows each
         const int64_t col_groups = ceil_div(c->p.n, 256);
         const int64_t waves = ceil_div(c->p.n, 64) * ceil_div(ceil_div(R, 2), IM_Q);
         int64_t chunks = ceil_div(8192, waves > 0 ? waves : 1);
-        if (chunks > ceil_div(c->p.m, 2 * IM_ROWS)) chunks = ceil_div(c->p.m, 2 * IM_ROWS);
+        if (chunks > ceil_div(c->p.m, IM_ROWS)) chunks = ceil_div(c->p.m, IM_ROWS);
         if (chunks < 1) chunks = 1;
         const int64_t chunk_rows = ceil_div(ceil_div(c->p.m, chunks), IM_ROWS) * IM_ROWS;
         chunks = ceil_div(c->p.m, chunk_rows > 0 ? chunk_rows : 1);
