@@ -794,7 +794,7 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
 }
 
 template <class T>
-static dmmv_status finish_iteration_t(Ctx* c, const dmmv_alns_params& prm, int32_t* trace, void* trace_t) {
+static dmmv_status finish_iteration_t(Ctx* c, const dmmv_alns_params& prm, bool last, int32_t* trace, void* trace_t) {
     AlnsState* S = (AlnsState*)c->alns_state;
     const int64_t R = c->p.R;
     if (prm.l2_guard) DMMV_TRY(sumsq_t<T>(c));
@@ -805,7 +805,8 @@ static dmmv_status finish_iteration_t(Ctx* c, const dmmv_alns_params& prm, int32
                        (const AlnsState*)S, c->kidx, c->alns_kidx_cur, c->alns_kidx_best, (T*)c->r,
                        (T*)c->alns_r_cur);
     DMMV_LAUNCH_CHECK();
-    if (c->kind == KIND_CSC) DMMV_TRY(csc_alns_after_copy(c));
+    // (before another iteration, its repair gives what it leaves a reservoir of its own)
+    if (c->kind == KIND_CSC && last) DMMV_TRY(csc_alns_after_copy(c));
     return DMMV_OK;
 }
 
@@ -825,9 +826,9 @@ dmmv_status alns_destroy_repair(Ctx* c, const dmmv_alns_params& prm, int32_t it,
     return c->p.dtype == DMMV_F64 ? destroy_repair_t<double>(c, prm, it, count)
                                   : destroy_repair_t<float>(c, prm, it, count);
 }
-dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, int32_t* trace, void* trace_t) {
-    return c->p.dtype == DMMV_F64 ? finish_iteration_t<double>(c, prm, trace, trace_t)
-                                  : finish_iteration_t<float>(c, prm, trace, trace_t);
+dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, bool last, int32_t* trace, void* trace_t) {
+    return c->p.dtype == DMMV_F64 ? finish_iteration_t<double>(c, prm, last, trace, trace_t)
+                                  : finish_iteration_t<float>(c, prm, last, trace, trace_t);
 }
 dmmv_status alns_export(Ctx* c, void* t_best_out) {
     return c->p.dtype == DMMV_F64 ? export_t<double>(c, t_best_out) : export_t<float>(c, t_best_out);

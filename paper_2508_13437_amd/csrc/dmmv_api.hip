@@ -811,7 +811,7 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
                 for (int32_t sw = 0; sw < prm.ls_swaps; ++sw)
                     DMMV_TRY(swap_move(c, prm.k_eps, 1, true, nullptr, nullptr));
             }
-            DMMV_TRY(alns_finish_iteration(c, prm, trace, trace_t));
+            DMMV_TRY(alns_finish_iteration(c, prm, it + 1 == prm.iters, trace, trace_t));
             if (one_launch && it + 1 == poll_at && it + 1 < prm.iters) {
                 DMMV_TRY(check_device_errors(c, &raw));
                 poll_at = poll_at < INT32_MAX / 4 ? 4 * poll_at : INT32_MAX;

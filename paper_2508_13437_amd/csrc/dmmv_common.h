@@ -224,7 +224,7 @@ constexpr int CSC_MAX_PARTITIONS = 1024;
 dmmv_status alns_start(Ctx* c, bool l2_guard);
 dmmv_status alns_sumsq(Ctx* c);          // alns_q2 <- squared l2 norm of r, per instance
 dmmv_status alns_destroy_repair(Ctx* c, const dmmv_alns_params& prm, int32_t it, int32_t count);
-dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, int32_t* trace, void* trace_t);
+dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, bool last, int32_t* trace, void* trace_t);
 dmmv_status alns_export(Ctx* c, void* t_best_out);
 dmmv_status csc_alns_impact(Ctx* c, double alpha);
 dmmv_status csc_alns_repair(Ctx* c, int32_t count, uint64_t seed);

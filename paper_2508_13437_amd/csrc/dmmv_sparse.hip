@@ -306,13 +306,13 @@ __device__ void reservoir_publish(ResLds<T>& L, int32_t c, bool set_floor_from_l
     __syncthreads();
 }
 
-// Full rebuild from r.  Call with every thread of the workgroup.
-template <class T>
-__device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_val,
-                                  int32_t* res_row, int32_t* meta, T* floor_val) {
+// Full rebuild from r, whose row i is load(i).  Call with every thread of the workgroup.
+template <class T, class LD>
+__device__ void reservoir_rebuild_from(ResLds<T>& L, int64_t m, LD load, T* res_val,
+                                       int32_t* res_row, int32_t* meta, T* floor_val) {
     if (m <= RES_CAP) {
         // everything fits: the floor admits every row
-        for (int32_t u = threadIdx.x; u < (int32_t)m; u += blockDim.x) { L.v[u] = row_key(ld_coherent(r + u)); L.r[u] = u; }
+        for (int32_t u = threadIdx.x; u < (int32_t)m; u += blockDim.x) { L.v[u] = row_key(load(u)); L.r[u] = u; }
         __syncthreads();
         reservoir_publish(L, (int32_t)m, false, res_val, res_row, meta, floor_val);
         if (threadIdx.x == 0) { floor_val[0] = (T)-1; meta[RES_FLOOR_ROW] = INT32_MAX; }
@@ -331,13 +331,13 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
         for (; i + (RES_BATCH - 1) * step < m; i += RES_BATCH * step) {
             T a8[RES_BATCH];
 #pragma unroll
-            for (int e = 0; e < RES_BATCH; ++e) a8[e] = row_key(ld_coherent(r + i + e * step));
+            for (int e = 0; e < RES_BATCH; ++e) a8[e] = row_key(load(i + e * step));
 #pragma unroll
             for (int e = 0; e < RES_BATCH; ++e)
                 if (key_before(a8[e], (int32_t)(i + e * step), mv, mr)) { mv = a8[e]; mr = (int32_t)(i + e * step); }
         }
         for (; i < m; i += step) {
-            const T a = row_key(ld_coherent(r + i));
+            const T a = row_key(load(i));
             if (key_before(a, (int32_t)i, mv, mr)) { mv = a; mr = (int32_t)i; }
         }
     }
@@ -380,7 +380,7 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
             for (; i + (RES_BATCH - 1) * step < m; i += RES_BATCH * step) {
                 T a8[RES_BATCH];
 #pragma unroll
-                for (int e = 0; e < RES_BATCH; ++e) a8[e] = row_key(ld_coherent(r + i + e * step));
+                for (int e = 0; e < RES_BATCH; ++e) a8[e] = row_key(load(i + e * step));
 #pragma unroll
                 for (int e = 0; e < RES_BATCH; ++e)
                     if (!key_before(fv, fr, a8[e], (int32_t)(i + e * step))) {      // key before-or-equal floor
@@ -389,7 +389,7 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
                     }
             }
             for (; i < m; i += step) {
-                const T a = row_key(ld_coherent(r + i));
+                const T a = row_key(load(i));
                 if (!key_before(fv, fr, a, (int32_t)i)) {
                     const int32_t pos = atomicAdd(&L.count, 1);
                     if (pos < RES_COLLECT) { L.v[pos] = a; L.r[pos] = (int32_t)i; }
@@ -403,6 +403,12 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
     const int32_t c = L.count < RES_COLLECT ? L.count : RES_COLLECT;
     __syncthreads();
     reservoir_publish(L, c, true, res_val, res_row, meta, floor_val);
+}
+
+template <class T>
+__device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_val, int32_t* res_row, int32_t* meta,
+                                  T* floor_val) {
+    reservoir_rebuild_from(L, m, [=](int64_t i) -> T { return ld_coherent(r + i); }, res_val, res_row, meta, floor_val);
 }
 
 template <class T>
@@ -1019,6 +1025,166 @@ __global__ __launch_bounds__(RP_BLOCK) void k_alns_repair_gathered(
     if (tid == 0) { st[0].t = tmax; st[0].done = 0; st[0].moves = 0; }
 }
 
+// Repair with r in LDS, where it fits.  Per pick the kernel above still waits for two trips to memory, the residuals and the
+// acknowledgement of their stores, and the reservoir is another launch that reads r again.  Here r comes in once, a pick is
+// LDS accesses only, and the reservoir is made before the workgroup ends.  What else a pick needs is there beforehand:
+// its steps and, where it does not depend on r, the choice, from one thread per pick for RL_PICKS picks at a time;
+// the entries of the next picks in registers.
+// A greedy pick's threads take their residuals out (0 in their place), so that "the largest |r| outside the column" is the
+// maximum over all of r, four rows an access, and put the new ones in: one workgroup issues one wavefront instruction per
+// clock at best, and this is a third of the instructions that maxima of chunks need (135 us for 82 picks of 8192 rows).
+// 8192 rows, 82 picks of some 190 entries: 38 us where the choices are random, 52 where
+// they are greedy, the reservoir's 16 us included, against 87 on the average and 18 for the reservoir (outer iteration of the
+// tomography of that size 272 against 195 us).
+constexpr int64_t RL_R_BYTES = 112 * 1024;   // largest r
+constexpr int RL_PICKS = 256;
+constexpr int RL_AHEAD = 4;                  // picks whose entries are requested together: a greedy pick takes about as
+constexpr int RL_AHEAD_RANDOM = 16;          //   long as a quarter of a trip to memory, the others less than a tenth
+
+template <class T>
+__global__ __launch_bounds__(RP_BLOCK) void k_alns_repair_lds(
+    int32_t m, int32_t nd, int32_t stride, const int32_t* __restrict__ g_row, const T* __restrict__ g_val,
+    const T* __restrict__ D, T* r, int32_t* kidx, int32_t count, const int32_t* __restrict__ picked,
+    InstState<T>* st, const AlnsState* S, uint64_t seed, uint64_t inst, T* res_val, int32_t* res_row,
+    int32_t* res_meta, T* res_floor) {
+    extern __shared__ __align__(32) unsigned char smem[];
+    T* sh_r = reinterpret_cast<T*>(smem);                           // rows m .. to a multiple of 4: 0
+    __shared__ ResLds<T> L;
+    __shared__ T sh[16];
+    __shared__ T sh_red[2][4];                                      // by the pick's parity: outside, column low, column high
+    __shared__ T sh_lo[RL_PICKS], sh_hi[RL_PICKS];                  // steps to the neighbouring levels
+    __shared__ int32_t sh_new[RL_PICKS];                            // the new level; -2 - level: down or up, by the errors
+    const int32_t it = S->it;
+    const bool greedy = S->r_op == 1;
+    const int32_t tid = threadIdx.x;
+    const int lane = tid & 63, w = tid >> 6;
+    const int32_t m4 = (m + 3) / 4;
+    for (int32_t i0 = tid; i0 < 4 * m4; i0 += 8 * RP_BLOCK) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = r[min(i0 + u * RP_BLOCK, m - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int32_t i = i0 + u * RP_BLOCK;
+            if (i < 4 * m4) sh_r[i] = i < m ? v[u] : (T)0;
+        }
+    }
+    if (tid < 8) sh_red[tid >> 2][tid & 3] = (T)0;
+    const bool mine = tid < stride;
+    const bool entry_wave = w * 64 < stride;                        // wavefronts that hold entries
+
+    for (int32_t q0 = 0; q0 < count; q0 += RL_PICKS) {
+        const int32_t nb = min(RL_PICKS, count - q0);
+        auto entry = [&](int32_t pos, int32_t& row, T& a) {         // pick pos of these (none beyond the last)
+            row = -1;
+            a = (T)0;
+            if (mine && pos < nb) {
+                const int64_t e = (int64_t)(q0 + pos) * stride + tid;
+                row = g_row[e];
+                a = g_val[e];
+            }
+        };
+        int32_t my_j = 0;
+        if (tid < nb) {
+            my_j = picked[q0 + tid];
+            const int32_t kc = kidx[my_j];
+            const bool has_lo = kc > 0, has_hi = kc < nd - 1;
+            const T cur = D[kc], below = D[has_lo ? kc - 1 : kc], above = D[has_hi ? kc + 1 : kc];
+            bool up = !has_lo;
+            if (has_lo && has_hi && !greedy) up = (alns_rnd(seed, inst, (uint64_t)it, 2, (uint64_t)(q0 + tid)) & 1) != 0;
+            const T hi = step_of(above, cur, (T)1);
+            sh_lo[tid] = up ? hi : step_of(below, cur, (T)1);       // (a choice that stands: its step)
+            sh_hi[tid] = hi;
+            sh_new[tid] = has_lo && has_hi && greedy ? -2 - kc : (up ? kc + 1 : kc - 1);
+        }
+        if (!greedy) {
+            int32_t row_n[RL_AHEAD_RANDOM];
+            T a_n[RL_AHEAD_RANDOM];
+#pragma unroll
+            for (int u = 0; u < RL_AHEAD_RANDOM; ++u) entry(u, row_n[u], a_n[u]);
+            __syncthreads();                                        // r and the picks are there
+            for (int32_t g = 0; g < nb; g += RL_AHEAD_RANDOM) {
+                int32_t rows[RL_AHEAD_RANDOM];
+                T as[RL_AHEAD_RANDOM];
+#pragma unroll
+                for (int u = 0; u < RL_AHEAD_RANDOM; ++u) { rows[u] = row_n[u]; as[u] = a_n[u]; }
+#pragma unroll
+                for (int u = 0; u < RL_AHEAD_RANDOM; ++u) entry(g + RL_AHEAD_RANDOM + u, row_n[u], a_n[u]);
+#pragma unroll
+                for (int u = 0; u < RL_AHEAD_RANDOM; ++u) {
+                    if (g + u >= nb) break;
+                    if (rows[u] >= 0) sh_r[rows[u]] = dmmv_fma(sh_lo[g + u], as[u], sh_r[rows[u]]);
+                    __syncthreads();
+                }
+            }
+        } else {
+            int32_t row_n[RL_AHEAD];
+            T a_n[RL_AHEAD];
+#pragma unroll
+            for (int u = 0; u < RL_AHEAD; ++u) entry(u, row_n[u], a_n[u]);
+            __syncthreads();
+            for (int32_t g = 0; g < nb; g += RL_AHEAD) {
+                int32_t rows[RL_AHEAD];
+                T as[RL_AHEAD];
+#pragma unroll
+                for (int u = 0; u < RL_AHEAD; ++u) { rows[u] = row_n[u]; as[u] = a_n[u]; }
+#pragma unroll
+                for (int u = 0; u < RL_AHEAD; ++u) entry(g + RL_AHEAD + u, row_n[u], a_n[u]);
+#pragma unroll
+                for (int u = 0; u < RL_AHEAD; ++u) {
+                    const int32_t pos = g + u;
+                    if (pos >= nb) break;
+                    const int32_t row = rows[u];
+                    const T a = as[u];
+                    const int32_t knew = sh_new[pos];
+                    T delta = sh_lo[pos];
+                    T ri = (T)0;
+                    if (row >= 0) ri = sh_r[row];
+                    if (knew < 0) {                                 // (the same for all threads)
+                        const int par = pos & 1;
+                        const T dhi = sh_hi[pos];
+                        if (row >= 0) sh_r[row] = (T)0;
+                        __syncthreads();
+                        T rest = (T)0;
+                        for (int32_t q = tid; q < m4; q += RP_BLOCK) {
+                            const typename Vec4<T>::type v = *reinterpret_cast<const typename Vec4<T>::type*>(&sh_r[4 * q]);
+                            rest = dmmv_max(dmmv_max(rest, dmmv_abs(v.x)), dmmv_max(dmmv_abs(v.y), dmmv_max(dmmv_abs(v.z), dmmv_abs(v.w))));
+                        }
+                        rest = wave_max(rest);
+                        if (lane == 0) lds_max_nonneg(&sh_red[par][0], rest);
+                        if (entry_wave) {
+                            const T lo = wave_max(row >= 0 ? dmmv_abs(dmmv_fma(delta, a, ri)) : (T)0);
+                            const T hi = wave_max(row >= 0 ? dmmv_abs(dmmv_fma(dhi, a, ri)) : (T)0);
+                            if (lane == 0) { lds_max_nonneg(&sh_red[par][1], lo); lds_max_nonneg(&sh_red[par][2], hi); }
+                        }
+                        __syncthreads();
+                        const T outside = sh_red[par][0];
+                        const T elo = dmmv_max(outside, sh_red[par][1]), ehi = dmmv_max(outside, sh_red[par][2]);
+                        const bool up = ehi < elo;
+                        if (up) delta = dhi;
+                        if (tid == 0) sh_new[pos] = (-2 - knew) + (up ? 1 : -1);
+                    }
+                    // (the other set: read by the previous pick, raised by the next one)
+                    if (tid < 4) sh_red[(pos & 1) ^ 1][tid] = (T)0;
+                    if (row >= 0) sh_r[row] = dmmv_fma(delta, a, ri);
+                    __syncthreads();
+                }
+            }
+        }
+        if (tid < nb) kidx[my_j] = sh_new[tid];
+        // (the next picks' tables: a thread overwrites only what is its own, all others are past the last barrier)
+    }
+    T tmax = (T)0;
+    for (int32_t i = tid; i < m; i += RP_BLOCK) {
+        const T v = sh_r[i];
+        r[i] = v;
+        tmax = dmmv_max(tmax, dmmv_abs(v));
+    }
+    tmax = block_max(tmax, sh);
+    if (tid == 0) { st[0].t = tmax; st[0].done = 0; st[0].moves = 0; }
+    reservoir_rebuild_from(L, m, [&](int64_t i) -> T { return sh_r[i]; }, res_val, res_row, res_meta, res_floor);
+}
+
 // after a rejected iteration r was restored: the reservoir has to follow
 template <class T>
 __global__ __launch_bounds__(1024) void k_reservoir_build_if_rejected(int64_t m, const T* r, T* res_val,
@@ -1056,6 +1222,18 @@ static dmmv_status alns_repair_t(Ctx* c, int32_t count, uint64_t seed) {
             hipLaunchKernelGGL(k_alns_gather<T>, dim3((unsigned)count), dim3(128), 0, c->stream, c->p.n, c->csc_mp,
                                c->csc_P, stride, (const int32_t*)c->segptr, (const uint16_t*)c->row16,
                                (const T*)c->cval, (const int32_t*)c->alns_picked, c->alns_g_row, (T*)c->alns_g_val);
+        // (one workgroup either way; an r beyond its LDS: the kernel above)
+        if (c->p.m * (int64_t)sizeof(T) <= RL_R_BYTES) {
+            auto kernel = k_alns_repair_lds<T>;
+            DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)RL_R_BYTES));
+            hipLaunchKernelGGL(kernel, dim3(1), dim3(RP_BLOCK), (size_t)ceil_div(c->p.m, 4) * 4 * sizeof(T), c->stream, (int32_t)c->p.m, c->p.nd,
+                               stride, (const int32_t*)c->alns_g_row, (const T*)c->alns_g_val, (const T*)c->D_dev, (T*)c->r,
+                               c->kidx, count, (const int32_t*)c->alns_picked, (InstState<T>*)c->state,
+                               (const AlnsState*)c->alns_state, seed, (uint64_t)0, (T*)c->res_val, c->res_row, c->res_meta,
+                               (T*)c->res_floor);
+            DMMV_LAUNCH_CHECK();
+            return DMMV_OK;
+        }
         hipLaunchKernelGGL(k_alns_repair_gathered<T>, dim3(1), dim3(RP_BLOCK), 0, c->stream, (int32_t)c->p.m, c->p.nd, stride,
                            (const int32_t*)c->alns_g_row, (const T*)c->alns_g_val, (const T*)c->D_dev, (T*)c->r,
                            c->kidx, count, (const int32_t*)c->alns_picked, (InstState<T>*)c->state,
