@@ -251,7 +251,8 @@ __global__ __launch_bounds__(256) void k_residual_csr(int64_t m, int64_t nnz, co
 //   res_val/res_row [RES_CAP] sorted by key_before; meta[RES_CNT] entries; the reservoir holds
 //   EVERY row whose key is before-or-equal the floor key (floor_val[0], meta[RES_FLOOR_ROW]).
 // =========================================================================================
-constexpr int RES_SEL = 256;     // threads whose strided maxima choose the floor at a rebuild
+constexpr int RES_SEL = 128;     // classes of rows whose maxima choose the floor at a rebuild (256 of them, the 64th: the
+constexpr int RES_TARGET = 56;   //   ranks, all against all, take 5.6 of 9.6 us); the rank that stands for some 74 rows
 constexpr int RES_COLLECT = 1024;
 constexpr int RES_BATCH = 8;     // rows a thread requests before it waits, in the scans of a rebuild (16: slower)
 
@@ -273,26 +274,42 @@ struct ResLds {
     int32_t count;
 };
 
+// How many of the first c entries of L.v/L.r come before (a, row): by `lanes` neighbouring lanes (a power of two), of
+// which this is number `part`; the sum in all of them.  Eight entries per step, so that their LDS reads are in flight
+// together, and several lanes per entry: a lane alone runs at the LDS latency, 4.5 us for 150 entries one at a time, 2 us by
+// eights.
+template <class T>
+__device__ __forceinline__ int32_t res_rank(const ResLds<T>& L, int32_t c, int32_t part, int32_t lanes, T a, int32_t row) {
+    static_assert(RES_COLLECT % 8 == 0, "reads of whole eights");
+    int32_t rank = 0;
+    for (int32_t q = 8 * part; q < c; q += 8 * lanes) {
+        T v8[8];
+        int32_t r8[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { v8[e] = L.v[q + e]; r8[e] = L.r[q + e]; }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rank += q + e < c && key_before(v8[e], r8[e], a, row);
+    }
+    if (lanes > 1) rank += (int32_t)dpp_mov_u32<DPP_QUAD_XOR1>((uint32_t)rank);      // the neighbour, the pair, the half row, the row
+    if (lanes > 2) rank += (int32_t)dpp_mov_u32<DPP_QUAD_XOR2>((uint32_t)rank);
+    if (lanes > 4) rank += (int32_t)dpp_mov_u32<DPP_ROW_HALF_MIRROR>((uint32_t)rank);
+    if (lanes > 8) rank += (int32_t)dpp_mov_u32<DPP_ROW_MIRROR>((uint32_t)rank);
+    return rank;
+}
+
 // rank-sort the first c entries of L.v/L.r, keep the first RES_CAP, publish them
 template <class T>
 __device__ void reservoir_publish(ResLds<T>& L, int32_t c, bool set_floor_from_last, T* res_val,
                                   int32_t* res_row, int32_t* meta, T* floor_val) {
-    for (int32_t u = threadIdx.x; u < c; u += blockDim.x) {
-        const T a = L.v[u];
-        const int32_t row = L.r[u];
-        // eight entries per step, so that their LDS reads are in flight together (one at a time
-        // the loop runs at the LDS latency: 4.5 us for 150 entries)
-        int32_t rank = 0, q = 0;
-        for (; q + 8 <= c; q += 8) {
-            T v8[8];
-            int32_t r8[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { v8[e] = L.v[q + e]; r8[e] = L.r[q + e]; }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) rank += key_before(v8[e], r8[e], a, row);
-        }
-        for (; q < c; ++q) rank += key_before(L.v[q], L.r[q], a, row);
-        if (rank < RES_CAP) { L.ov[rank] = a; L.orow[rank] = row; }
+    int32_t lanes = 1;                                  // per entry
+    while (lanes < 16 && 2 * lanes * c <= (int32_t)blockDim.x) lanes *= 2;
+    const int32_t part = (int32_t)threadIdx.x & (lanes - 1);
+    for (int32_t u0 = 0; u0 < c; u0 += (int32_t)blockDim.x / lanes) {
+        const int32_t u = u0 + (int32_t)threadIdx.x / lanes;
+        const T a = L.v[u < c ? u : 0];
+        const int32_t row = L.r[u < c ? u : 0];
+        const int32_t rank = res_rank(L, c, part, lanes, a, row);
+        if (u < c && part == 0 && rank < RES_CAP) { L.ov[rank] = a; L.orow[rank] = row; }
     }
     __syncthreads();
     const int32_t keep = c < RES_CAP ? c : RES_CAP;
@@ -345,30 +362,33 @@ __device__ void reservoir_rebuild_from(ResLds<T>& L, int64_t m, LD load, T* res_
     L.r[threadIdx.x] = mr;
     __syncthreads();
     if (threadIdx.x < RES_SEL) {
-        for (int32_t o = threadIdx.x + RES_SEL; o < (int32_t)blockDim.x; o += RES_SEL) {
-            const T ov = L.v[o];
-            const int32_t orow = L.r[o];
-            if (key_before(ov, orow, mv, mr)) { mv = ov; mr = orow; }
+        constexpr int MOST = 1024 / RES_SEL;            // (workgroups of 1024 threads at most; all reads in flight)
+        T ov[MOST];
+        int32_t orow[MOST];
+#pragma unroll
+        for (int e = 1; e < MOST; ++e) {
+            const int32_t o = (int32_t)threadIdx.x + e * RES_SEL;
+            ov[e] = L.v[o < (int32_t)blockDim.x ? o : (int32_t)threadIdx.x];
+            orow[e] = L.r[o < (int32_t)blockDim.x ? o : (int32_t)threadIdx.x];
         }
+#pragma unroll
+        for (int e = 1; e < MOST; ++e)
+            if (key_before(ov[e], orow[e], mv, mr)) { mv = ov[e]; mr = orow[e]; }
     }
-    int32_t target = RES_CAP / 2;
+    int32_t target = RES_TARGET;
     for (;;) {
         __syncthreads();
         if (threadIdx.x < RES_SEL) { L.v[threadIdx.x] = mv; L.r[threadIdx.x] = mr; }
         if (threadIdx.x == 0) L.count = 0;
         __syncthreads();
-        if (threadIdx.x < RES_SEL) {
-            int32_t rank = 0;
-            static_assert(RES_SEL % 8 == 0, "ranking loop step");
-            for (int32_t q = 0; q < RES_SEL; q += 8) {
-                T v8[8];
-                int32_t r8[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { v8[e] = L.v[q + e]; r8[e] = L.r[q + e]; }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) rank += key_before(v8[e], r8[e], mv, mr);
-            }
-            if (rank == target - 1) { L.fv = mv; L.fr = mr; }
+        {
+            const int32_t lanes = (int32_t)blockDim.x / RES_SEL < 16 ? (int32_t)blockDim.x / RES_SEL : 16;     // per class
+            const int32_t u = (int32_t)threadIdx.x / lanes, part = (int32_t)threadIdx.x % lanes;
+            const int32_t uc = u < RES_SEL ? u : 0;
+            const T a = L.v[uc];
+            const int32_t row = L.r[uc];
+            const int32_t rank = res_rank(L, RES_SEL, part, lanes, a, row);
+            if (u < RES_SEL && part == 0 && rank == target - 1) { L.fv = a; L.fr = row; }
         }
         __syncthreads();
         const T fv = L.fv;
@@ -465,8 +485,7 @@ __global__ __launch_bounds__(SA_BLOCK) void k_select_apply_cscp(
     __shared__ int64_t sh_c[SA_BLOCK / 64];
     __shared__ int32_t sh_srow[SA_MAXCOL];      // rows changed by the move, ascending
     __shared__ T sh_sval[SA_MAXCOL];            // their new |r|
-    __shared__ int32_t sh_ns, sh_j, sh_k;
-    __shared__ T sh_delta, sh_best;
+    __shared__ int32_t sh_j, sh_k;
     __shared__ int32_t sh_e0[CSC_MAX_PARTITIONS], sh_len[CSC_MAX_PARTITIONS];   // column j's segments
     __shared__ T sh_D[SA_DCAP];                 // the levels, when they fit: requested with the first loads
     // Everything that depends on nothing is fetched together (one memory latency, not one per
@@ -494,40 +513,44 @@ __global__ __launch_bounds__(SA_BLOCK) void k_select_apply_cscp(
     if (threadIdx.x == 0) {
         InstState<T> z = z0;
         int32_t j = -1, k = -1;
-        if (c >= 0) { j = (int32_t)(c / nd); k = (int32_t)(c % nd); }
+        if (c >= 0 && c <= (int64_t)UINT32_MAX) {               // (a 64-bit division is some hundred instructions)
+            j = (int32_t)((uint32_t)c / (uint32_t)nd);
+            k = (int32_t)((uint32_t)c % (uint32_t)nd);
+        } else if (c >= 0) {
+            j = (int32_t)(c / nd);
+            k = (int32_t)(c % nd);
+        }
         const bool improving = c >= 0 && s < z.t;
         z.best_s = s;
         z.apply_j = -1; z.apply_k = -1; z.delta = (T)0;      // applied right here
         sh_j = improving ? j : -1;
         sh_k = k;
-        sh_best = s;
         if (improving) {
-            const int32_t kc = kidx[j];
-            sh_delta = d_lds ? step_of(sh_D[k], sh_D[kc], (T)1) : step_of(D[k], D[kc], (T)1);
             if (z.moves < iters) {
                 if (trace) { trace[z.moves].j = j; trace[z.moves].k = k; }
                 if (trace_t) trace_t[z.moves] = s;
             }
             z.t = s;
             z.moves += 1;
-            kidx[j] = k;
         } else if (!keep_going) {
             z.done = 1;
         }
         st[0] = z;
-        sh_ns = 0;
     }
     __syncthreads();
     const int32_t j = sh_j;
     if (j < 0) return;
-    const T delta = sh_delta;
+    // (the column's segments and its level in one trip; the level is written once all have it)
+    const int32_t kc = kidx[j];
     // ---- rank-1 update of the rows of column j; remember them (ascending by row) ----
     for (int32_t p = threadIdx.x; p < P; p += SA_BLOCK) {
         const int32_t e0 = segptr[(int64_t)p * n + j], e1 = segptr[(int64_t)p * n + j + 1];
         sh_e0[p] = e0;
         sh_len[p] = e1 - e0;
     }
+    const T delta = d_lds ? step_of(sh_D[sh_k], sh_D[kc], (T)1) : step_of(D[sh_k], D[kc], (T)1);
     __syncthreads();
+    if (threadIdx.x == 0) kidx[j] = sh_k;
     int32_t col_len = 0;
     for (int32_t p = 0; p < P; ++p) col_len += sh_len[p];
     const bool incremental = col_len <= SA_MAXCOL && m > RES_CAP;
