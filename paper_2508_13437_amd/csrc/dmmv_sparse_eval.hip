@@ -751,8 +751,9 @@ __global__ __launch_bounds__(64) void k_eval_pruned_csc(
 // and two reservoir rows in registers, so whether a reservoir row is in the column is a
 // comparison across lanes, and what remains is six dependent accesses.
 constexpr int PR_SLOTS = 8;
+constexpr int PR_FEW_SLOTS = 4;
 
-template <class T>
+template <class T, int SLOTS, int KT>
 __global__ __launch_bounds__(64) void k_eval_pruned_csc_reg(
     int64_t m, int64_t n, int32_t nd, int32_t mp, int32_t P, const int64_t* __restrict__ csr_rowptr,
     const int32_t* __restrict__ csr_col, const int32_t* __restrict__ segptr,
@@ -761,7 +762,6 @@ __global__ __launch_bounds__(64) void k_eval_pruned_csc_reg(
     const int32_t* __restrict__ res_row, const int32_t* __restrict__ res_meta, int32_t radius,
     const uint8_t* __restrict__ var_mask, const InstState<T>* __restrict__ st, int32_t honor_done,
     Partial<T>* __restrict__ part) {
-    constexpr int KT = 8;
     static_assert(RES_CAP <= 128, "two reservoir entries per lane");
     const int lane = threadIdx.x;
     // 1: everything that depends on nothing
@@ -787,17 +787,17 @@ __global__ __launch_bounds__(64) void k_eval_pruned_csc_reg(
     }
     // 4: the segment bounds and the current value; a lane's slots are entries lane, lane + 64, ...
     // (up to 64 partitions: lane p fetches the bounds of partition p, all in one trip)
-    const int32_t kcur = __builtin_amdgcn_readfirstlane(kidx[j]);
-    int32_t ent[PR_SLOTS], part_of[PR_SLOTS];
+    // (what is used late is requested here too, and nothing inside a branch: a load there is waited for there)
+    const int32_t kcur_in = kidx[j];
+    const uint8_t ok_in = var_mask ? var_mask[j] : (uint8_t)1;
+    int32_t ent[SLOTS], part_of[SLOTS];
 #pragma unroll
-    for (int u = 0; u < PR_SLOTS; ++u) { ent[u] = -1; part_of[u] = 0; }
+    for (int u = 0; u < SLOTS; ++u) { ent[u] = -1; part_of[u] = 0; }
     {
         const bool by_lane = P <= 64;
-        int32_t my_e0 = 0, my_len = 0;
-        if (by_lane && lane < P) {
-            my_e0 = segptr[(int64_t)lane * n + j];
-            my_len = segptr[(int64_t)lane * n + j + 1] - my_e0;
-        }
+        const int64_t my_seg = (int64_t)(lane < P ? lane : P - 1) * n + j;
+        const int32_t my_e0 = segptr[my_seg];
+        const int32_t my_len = segptr[my_seg + 1] - my_e0;
         int32_t base = 0;
         for (int32_t p = 0; p < P; ++p) {
             int32_t e0, len;
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(64) void k_eval_pruned_csc_reg(
                 len = segptr[(int64_t)p * n + j + 1] - e0;
             }
 #pragma unroll
-            for (int u = 0; u < PR_SLOTS; ++u) {
+            for (int u = 0; u < SLOTS; ++u) {
                 const int32_t t = lane + 64 * u - base;
                 if (t >= 0 && t < len) { ent[u] = e0 + t; part_of[u] = p; }
             }
@@ -817,20 +817,20 @@ __global__ __launch_bounds__(64) void k_eval_pruned_csc_reg(
         }
     }
     // 5: entries, current value of D;  6: residuals
-    int32_t row[PR_SLOTS];
-    T a[PR_SLOTS], ri[PR_SLOTS];
+    int32_t row[SLOTS];
+    T a[SLOTS], ri[SLOTS];
 #pragma unroll
-    for (int u = 0; u < PR_SLOTS; ++u) {
-        row[u] = -1;
-        a[u] = (T)0;
-        if (ent[u] >= 0) {
-            const uint32_t loc = row16[ent[u]];
-            if (loc != (uint32_t)mp) { row[u] = part_of[u] * mp + (int32_t)loc; a[u] = cval[ent[u]]; }
-        }
+    for (int u = 0; u < SLOTS; ++u) {
+        const uint32_t loc = row16[ent[u] >= 0 ? ent[u] : 0];
+        const T v = cval[ent[u] >= 0 ? ent[u] : 0];
+        const bool real = ent[u] >= 0 && loc != (uint32_t)mp;
+        row[u] = real ? part_of[u] * mp + (int32_t)loc : -1;
+        a[u] = real ? v : (T)0;
     }
+    const int32_t kcur = __builtin_amdgcn_readfirstlane(kcur_in);
     const T dcur = d_in_lanes ? read_lane(d_lane, kcur) : D[kcur];
 #pragma unroll
-    for (int u = 0; u < PR_SLOTS; ++u) ri[u] = row[u] >= 0 ? r[row[u]] : (T)0;
+    for (int u = 0; u < SLOTS; ++u) ri[u] = r[row[u] >= 0 ? row[u] : 0];
     // maximum over the rows outside column j: first reservoir row the column does not hold
     T outside = (T)0;
     {
@@ -839,7 +839,7 @@ __global__ __launch_bounds__(64) void k_eval_pruned_csc_reg(
             const int32_t want = q < 64 ? __builtin_amdgcn_readlane(rr0, q) : __builtin_amdgcn_readlane(rr1, q - 64);
             bool hit = false;
 #pragma unroll
-            for (int u = 0; u < PR_SLOTS; ++u) hit = hit || row[u] == want;
+            for (int u = 0; u < SLOTS; ++u) hit = hit || row[u] == want;
             if (!__any(hit)) { first = q; break; }
         }
         if (first >= 0) {
@@ -851,7 +851,7 @@ __global__ __launch_bounds__(64) void k_eval_pruned_csc_reg(
             outside = wave_max(o);
         }
     }
-    const bool var_ok = var_mask ? var_mask[j] != 0 : true;
+    const bool var_ok = ok_in != 0;
     for (int32_t k0 = 0; k0 < nd; k0 += KT) {
         T delta[KT], acc[KT];
 #pragma unroll
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(64) void k_eval_pruned_csc_reg(
             acc[q] = (T)0;
         }
 #pragma unroll
-        for (int u = 0; u < PR_SLOTS; ++u)
+        for (int u = 0; u < SLOTS; ++u)
             if (row[u] >= 0) {
 #pragma unroll
                 for (int q = 0; q < KT; ++q) acc[q] = dmmv_max(acc[q], dmmv_abs(dmmv_fma(delta[q], a[u], ri[u])));
@@ -958,7 +958,12 @@ template <class T>
 static dmmv_status eval_pruned_t(Ctx* c, bool honor_done) {
     if (c->csc_max_row <= 0) return DMMV_OK;       // no stored entry anywhere: nothing can move r
     // short columns: the variant that keeps the column in registers
-    auto kernel = c->csc_max_col <= 64 * PR_SLOTS ? k_eval_pruned_csc_reg<T> : k_eval_pruned_csc<T>;
+    // (half the slots and levels where they do: fewer instructions between the trips; with the loads of a trip outside
+    // branches 5.5 -> 4.9 us a launch on 8192 rows, columns of some 190 entries, four levels)
+    const bool few = c->csc_max_col <= 64 * PR_FEW_SLOTS;
+    auto kernel = c->csc_max_col > 64 * PR_SLOTS ? k_eval_pruned_csc<T>
+                : c->p.nd <= 4 ? (few ? k_eval_pruned_csc_reg<T, PR_FEW_SLOTS, 4> : k_eval_pruned_csc_reg<T, PR_SLOTS, 4>)
+                               : (few ? k_eval_pruned_csc_reg<T, PR_FEW_SLOTS, 8> : k_eval_pruned_csc_reg<T, PR_SLOTS, 8>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)c->csc_max_row), dim3(64), 0, c->stream, c->p.m,
                        c->p.n, c->p.nd, c->csc_mp, c->csc_P, c->p.csr_rowptr, c->p.csr_col,
                        (const int32_t*)c->segptr, (const uint16_t*)c->row16, (const T*)c->cval,
