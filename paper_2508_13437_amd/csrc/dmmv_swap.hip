@@ -743,6 +743,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
                         __hip_atomic_store(&sh_big_ready[to], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                     slot = to < slot ? to : slot;
+                    x1 = 0;                                // (if it is all taken when this wavefront gets there, nothing is left)
                     continue;
                 }
             }
