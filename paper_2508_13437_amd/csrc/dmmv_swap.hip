@@ -332,7 +332,7 @@ constexpr int SWI_LROWS = 3;                   // filter rows in LDS at most
 constexpr int SWI_STAGES = 5;
 constexpr int SWI_ROWS = 8;                    // of the others, those tried a lane a pair
 constexpr int SWI_SEEN = 8;                    // rows that pairs have failed at, remembered by a workgroup
-constexpr int SWI_HOT = 4;                     // rows of large |entry| looked up per variable
+constexpr int SWI_HOT = 4;                     // rows of large |entry| looked up per variable, where they are known
 constexpr int SWI_PART = 1024;                 // pairs of a unit one wavefront takes at a time
 constexpr int SWI_SHARED = 32;                 // larger units a workgroup can have on its list
 constexpr size_t SWI_LDS_HALF = 78 * 1024;     // dynamic LDS: half a compute unit's if a filter row fits it, else nearly all
@@ -367,36 +367,13 @@ static SwapLds swap_lds(int64_t m, int64_t n, int32_t K, size_t esz, size_t key,
     return s;
 }
 
-// rows of large |entry| of every column: the largest of each wavefront's share of the rows.  hot[w * n + j]
-template <class T>
-__global__ __launch_bounds__(64 * SWI_HOT) void k_swap_hot(int64_t m, int64_t n, const T* __restrict__ A, int64_t lda,
-                                                           int32_t* __restrict__ hot, int32_t n_hot) {
-    const int64_t j = blockIdx.x;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, step = 64 * (blockDim.x >> 6);
-    const T* __restrict__ col = A + j * lda;
-    T s = (T)1;                                            // arg-min of -|entry|
-    int64_t c = -1;
-    for (int64_t i0 = threadIdx.x; i0 < m; i0 += 8 * step) {
-        T a[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = col[i0 + u * step < m ? i0 + u * step : m - 1];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int64_t i = i0 + u * step;
-            if (i < m && -dmmv_abs(a[u]) < s) { s = -dmmv_abs(a[u]); c = i; }
-        }
-    }
-    wave_argmin(s, c);
-    if (lane == 0 && w < n_hot) hot[w * n + j] = c >= 0 ? (int32_t)c : 0;
-}
-
 template <class T>
 __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
     int64_t m, int32_t n, int64_t R, int32_t nd, int32_t nb, int32_t K, SwapLds lds, const T* __restrict__ A,
     int64_t lda, const T* __restrict__ At, const T* __restrict__ D, const T* __restrict__ scale,
     const int32_t* __restrict__ kidx, const T* __restrict__ r, const InstState<T>* __restrict__ st,
     const uint8_t* __restrict__ var_mask, const int32_t* __restrict__ rows_all,
-    const int32_t* __restrict__ hot32, const uint16_t* __restrict__ hot16, int32_t n_hot,
+    const uint16_t* __restrict__ hot, int32_t n_hot,
     const int32_t* __restrict__ skip, T* gbest, Partial<T>* __restrict__ part) {
     extern __shared__ __align__(16) unsigned char sw_smem[];
     SwapKey<T>* keys = reinterpret_cast<SwapKey<T>*>(sw_smem);
@@ -571,7 +548,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
                     const int64_t at = (int64_t)(h + x / 2 < n_hot ? h + x / 2 : h) * n + (x & 1 ? v : u);
-                    row[x] = hot16 ? (int32_t)hot16[at] : hot32[at];
+                    row[x] = hot[at];
                 }
                 rows4(row[0], row[1], row[2], row[3]);
             }
@@ -892,24 +869,16 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
         hipLaunchKernelGGL(k_swap_top<T>, dim3((unsigned)R), dim3(SW_BLOCK), 0, c->stream, m, R, K, (const T*)c->r,
                            (const int32_t*)skip, c->swap_rows, gbest);
     if (lds.L > 0) {
-        // rows of large entries: from the evaluation's lists where a batch has them, else found now (in the buffer of
-        // the packed instances' levels, or that of the sampling weights: neither is in use during a search)
-        const uint16_t* hot16 = batched_lists_in_use(c) ? c->lists.crow : nullptr;
-        int32_t* hot32 = c->kind == KIND_BATCHED ? c->cmp_kidx : reinterpret_cast<int32_t*>(c->alns_weight);
-        int32_t n_hot = SWI_HOT;
-        if (!hot16) {
-            const int64_t room = c->kind == KIND_BATCHED ? R : 2;
-            if (n_hot > room) n_hot = (int32_t)room;
-            hipLaunchKernelGGL(k_swap_hot<T>, dim3((unsigned)n), dim3(64u * n_hot), 0, c->stream, m, n, (const T*)c->p.A_dense,
-                               c->p.lda, hot32, n_hot);
-        }
+        // Rows of large entries, where the evaluation's lists of a batch are there.  Looking for them by a pass over A in every
+        // search took longer than it saved: a single instance of 100 000 x 2000 (ms) 0.82 / 1.25, without 0.71 / 0.99.
+        const uint16_t* hot = batched_lists_in_use(c) ? c->lists.crow : nullptr;
         DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_intervals<T>), (int)SWI_LDS_ALL));
         hipLaunchKernelGGL(k_swap_intervals<T>, dim3((unsigned)R, (unsigned)nb), dim3(SWE_BLOCK), lds.bytes, c->stream,
                            m, (int32_t)n, R, c->p.nd, nb, K, lds, (const T*)c->p.A_dense, c->p.lda,
                            (const T*)(c->kind == KIND_BATCHED ? c->Xt : nullptr), (const T*)c->D_dev,
                            (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->r,
                            (const InstState<T>*)c->state, c->o.var_mask, (const int32_t*)c->swap_rows,
-                           (const int32_t*)hot32, hot16, n_hot, (const int32_t*)skip, gbest, (Partial<T>*)c->swap_part);
+                           hot, hot ? SWI_HOT : 0, (const int32_t*)skip, gbest, (Partial<T>*)c->swap_part);
     } else {
     DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_eval<T, true>), (int)SW_LDS_BUDGET));
     DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_eval<T, false>), (int)SW_LDS_BUDGET));
