@@ -282,7 +282,8 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_eval(
 // step Delta is fixed, so the new residual of that row, fma(Delta, A_v - A_u, r), ascends with A_v also as computed
 // (every rounding is monotone): the partners that keep it within a threshold are a contiguous range of the level's
 // variables, found by bisection on the evaluation itself.  Only pairs of such ranges are looked at.
-// The threshold grows in stages towards t and ends at the best t' found so far: at a rounded start the best swap lowers
+// The threshold grows in stages towards t, each of which leaves out the pairs that the one before has looked at (a pair is tested
+// against the best t' found so far, not against its stage: what a stage meets is settled), and ends at the best t' found so far: at a rounded start the best swap lowers
 // t by a tenth or a third, which one variable of large entries is needed for, and the ranges hold some hundredth of the
 // pairs (50 000 of 7 million on 2048 x 4096); at a local optimum two thirds, of which the next rows drop most.
 // A unit of work is (64 consecutive variables, level); the wavefronts of a workgroup take units from a counter
@@ -387,7 +388,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
     __shared__ int32_t sh_first[SWI_LEVELS + 1];           // where every level begins
     __shared__ int32_t sh_unit[SWI_STAGES];
     __shared__ int32_t sh_big, sh_big_ready[SWI_SHARED], sh_big_unit[SWI_SHARED], sh_big_next[SWI_SHARED], sh_big_parts[SWI_SHARED];
-    __shared__ T sh_big_thr[SWI_SHARED];
+    __shared__ T sh_big_thr[SWI_SHARED], sh_big_inner[SWI_SHARED];
     __shared__ int32_t sh_fail[SWI_SEEN], sh_fails;
     __shared__ unsigned long long sh_best;
     __shared__ T sh_s[SWE_WAVES];
@@ -609,11 +610,12 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
     const unsigned long long below = (1ull << lane) - 1ull;
     const int32_t units = groups * nd;
     int qn = 0;                                            // queued pairs (uniform)
-    // The pairs of a unit within thr0, by lane: `upto` pairs up to and with this lane's, which are its variable with
-    // positions start + (number of the pair).  Returns how many there are.
-    int32_t upto = 0, start = 0, first_u = 0, first_v = 0;
+    // The pairs of a unit within thr0 and, from the second stage on, not within `inner`, which the stage before has seen to;
+    // by lane: `upto` pairs up to and with this lane's, which are its variable with positions start + (number of the pair),
+    // from gap_at on `gap` further.  Returns how many there are.
+    int32_t upto = 0, start = 0, gap_at = 0, gap = 0, first_u = 0, first_v = 0;
     T Ds = (T)0;
-    auto search = [&](int32_t unit, T thr0) -> int32_t {
+    auto search = [&](int32_t unit, T thr0, T inner) -> int32_t {
         const int32_t b = unit / groups, g = unit % groups;
         const int32_t s0 = __builtin_amdgcn_readfirstlane(sh_first[b]), len = __builtin_amdgcn_readfirstlane(sh_first[b + 1]) - s0;
         const int32_t pu = g * 64 + lane, puc = pu < nv ? pu : nv - 1;
@@ -626,23 +628,37 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
         const T f0 = f(s0), f1 = f(s0 + len - 1);
         on = on && f0 <= thr0 && f1 >= -thr0;              // (false where the step is not finite and gives no number)
         if (!__any(on)) return 0;
-        int32_t hi = len, lo = 0;                          // variables with f <= thr0, and with f < -thr0
         int32_t top = 1;
         while (2 * top <= len) top *= 2;
-        if (__any(on && !(f1 <= thr0))) {
-            hi = 0;
+        // how many of the level's variables have f <= v, and f < v; a bisection where some lane's are not all of them, or none
+        auto up_to = [&](T v) -> int32_t {
+            if (!__any(on && !(f1 <= v))) return len;
+            int32_t at = 0;
             for (int32_t d = top; d > 0; d >>= 1) {
-                const int32_t p = hi + d;
-                if (p <= len && f(s0 + (p < len ? p : len) - 1) <= thr0) hi = p;
+                const int32_t p = at + d;
+                if (p <= len && f(s0 + (p < len ? p : len) - 1) <= v) at = p;
             }
-        }
-        if (__any(on && !(f0 >= -thr0))) {
+            return at;
+        };
+        auto below_of = [&](T v) -> int32_t {
+            if (!__any(on && !(f0 >= v))) return 0;
+            int32_t at = 0;
             for (int32_t d = top; d > 0; d >>= 1) {
-                const int32_t p = lo + d;
-                if (p <= len && !(f(s0 + (p < len ? p : len) - 1) >= -thr0)) lo = p;
+                const int32_t p = at + d;
+                if (p <= len && !(f(s0 + (p < len ? p : len) - 1) >= v)) at = p;
             }
+            return at;
+        };
+        const int32_t hi = up_to(thr0), lo = below_of(-thr0);
+        int32_t in0 = lo, in1 = lo;
+        if (inner >= (T)0) {                               // (thr0 may have come below `inner`: then nothing is left)
+            in0 = below_of(-inner);
+            in1 = up_to(inner);
+            in0 = in0 > lo ? in0 : lo;
+            in1 = in1 < hi ? in1 : hi;
+            in1 = in1 > in0 ? in1 : in0;
         }
-        const int32_t cnt = on && hi > lo ? hi - lo : 0;
+        const int32_t cnt = on && hi > lo ? hi - lo - (in1 - in0) : 0;
         upto = cnt;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -650,6 +666,8 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
             if (lane >= off) upto += v;
         }
         start = s0 + lo - (upto - cnt);
+        gap_at = s0 + in0;
+        gap = in1 - in0;
         first_u = g * 64;
         first_v = s0;
         return __builtin_amdgcn_readlane(upto, 63);
@@ -664,8 +682,9 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
             if (v <= x) l += d;
         }
         bool alive = x < x1;
-        const int32_t pa = first_u + l, from = __shfl(start, l, 64);
-        const int32_t pb = alive ? from + x : first_v;
+        const int32_t pa = first_u + l, at = __shfl(start, l, 64) + x;
+        const int32_t hole = __shfl(gap_at, l, 64), wide = __shfl(gap, l, 64);
+        const int32_t pb = alive ? at + (at >= hole ? wide : 0) : first_v;
         const T Dp = __shfl(Ds, l, 64);
         const T thr = dmmv_min(bound(), t_below);
         const int32_t pac = pa < nv ? pa : nv - 1;
@@ -682,13 +701,13 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
     // taken a part of one on the workgroup's list.  (Its writer comes to the list after writing, so none is left
     // over; an entry that is not ready yet is its writer's to see to.)
     int slot = 0;
-    auto next = [&](int s, T reach, int32_t& x0, int32_t& x1) -> bool {
+    auto next = [&](int s, T reach, T inner, int32_t& x0, int32_t& x1) -> bool {
         while (true) {
             int32_t id = 0;
             if (lane == 0) id = atomicAdd(&sh_unit[s], 1);
             const int64_t unit = blk + (int64_t)nb * __builtin_amdgcn_readfirstlane(id);
             int32_t u_next, parts = 0, p = 0;
-            T thr0;
+            T thr0, inner0 = inner;
             if (unit < units) {
                 u_next = (int32_t)unit;
                 thr0 = dmmv_min(bound(), reach);
@@ -702,9 +721,10 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
                 if (p >= parts) { ++slot; continue; }
                 u_next = __builtin_amdgcn_readfirstlane(sh_big_unit[slot]);
                 thr0 = sh_big_thr[slot];
+                inner0 = sh_big_inner[slot];
             }
             x0 = 0;
-            x1 = search(u_next, thr0);
+            x1 = search(u_next, thr0, inner0);
             if (parts > 0) {
                 x0 = p * SWI_PART;
                 x1 = x0 + SWI_PART < x1 ? x0 + SWI_PART : x1;
@@ -717,6 +737,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
                         sh_big_unit[to] = u_next;
                         sh_big_parts[to] = (x1 + SWI_PART - 1) / SWI_PART;
                         sh_big_thr[to] = thr0;
+                        sh_big_inner[to] = inner0;
                         __hip_atomic_store(&sh_big_ready[to], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                     slot = to < slot ? to : slot;
@@ -727,13 +748,14 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
             if (x0 < x1) return true;
         }
     };
+    T inner = (T)-1;                                       // (nothing yet)
     for (int s = 0; s < SWI_STAGES; ++s) {
         const T share[SWI_STAGES] = {(T)0.75, (T)0.875, (T)0.9375, (T)0.96875, (T)1};
         const T reach = dmmv_min(t * share[s], t_below);   // (the last one: t_below)
         if (gbest) others = __hip_atomic_load(gbest + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (bool more = true; more;) {
             int32_t x0 = 0, x1 = 0;
-            more = next(s, reach, x0, x1);
+            more = next(s, reach, inner, x0, x1);
             do {
                 if (x0 < x1) look(x0, x1);
                 x0 += 64;
@@ -748,6 +770,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
             } while (x0 < x1 || (!more && qn > 0));
         }
         if (reach >= dmmv_min(bound(), t_below)) break;
+        inner = reach;
     }
     if (lane == 0) { sh_s[w] = best_t; sh_c[w] = best_c; }
     __syncthreads();
