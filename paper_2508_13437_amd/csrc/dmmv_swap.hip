@@ -286,7 +286,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_eval(
 // against the best t' found so far, not against its stage: what a stage meets is settled), and ends at the best t' found so far: at a rounded start the best swap lowers
 // t by a tenth or a third, which one variable of large entries is needed for, and the ranges hold some hundredth of the
 // pairs (50 000 of 7 million on 2048 x 4096); at a local optimum two thirds, of which the next rows drop most.
-// A unit of work is (64 consecutive variables, level); the wavefronts of a workgroup take units from a counter
+// A unit of work is (64 consecutive variables, level), or with `slices` (a power of two) every slices-th of the 64; the wavefronts of a workgroup take units from a counter
 // per stage.  A wavefront is through when a stage it has finished reached the bound: the units of that stage
 // are all taken, and whoever holds one covers it up to the smaller of stage and bound.  A few units hold most
 // pairs (outlier channels sort to the ends of their levels), so what is over SWI_PART is shared.
@@ -335,9 +335,8 @@ constexpr int SWI_ROWS = 8;                    // of the others, those tried a l
 constexpr int SWI_SEEN = 8;                    // rows that pairs have failed at, remembered by a workgroup
 constexpr int SWI_HOT = 4;                     // rows of large |entry| looked up per variable, where they are known
 constexpr int SWI_PART = 1024;                 // pairs of a unit one wavefront takes at a time
-constexpr int SWI_SHARED = 32;                 // larger units a workgroup can have on its list
-constexpr size_t SWI_LDS_HALF = 78 * 1024;     // dynamic LDS: half a compute unit's if a filter row fits it, else nearly all
-constexpr size_t SWI_LDS_ALL = 152 * 1024;
+constexpr int SWI_SHARED = 128;                // larger units a workgroup can have on its list
+constexpr size_t SWI_LDS = 152 * 1024;          // dynamic LDS at most: the registers leave room for one workgroup a compute unit
 
 // what lies in the dynamic LDS of a workgroup (the sort's keys overlap everything)
 struct SwapLds {
@@ -345,7 +344,7 @@ struct SwapLds {
     int32_t L;
     bool stage_r;
 };
-static SwapLds swap_lds(int64_t m, int64_t n, int32_t K, size_t esz, size_t key, size_t budget) {
+static SwapLds swap_lds(int64_t m, int64_t n, int32_t K, size_t esz, size_t key) {
     SwapLds s;
     int64_t n2 = 64;
     while (n2 < n) n2 *= 2;
@@ -357,20 +356,20 @@ static SwapLds swap_lds(int64_t m, int64_t n, int32_t K, size_t esz, size_t key,
     s.perm = at; at = up(at + (size_t)n * 2);
     s.lev = at; at = up(at + (size_t)n);
     const size_t row = up((size_t)n * esz), rr = up((size_t)m * esz);
-    s.stage_r = at + row + rr <= budget;
+    s.stage_r = at + row + rr <= SWI_LDS;
     s.lr = at;
     if (s.stage_r) at += rr;
     s.y = at;
     s.L = 0;
-    while (s.L < SWI_LROWS && s.L < K && at + row <= budget) { at += row; ++s.L; }
+    while (s.L < SWI_LROWS && s.L < K && at + row <= SWI_LDS) { at += row; ++s.L; }
     s.bytes = at > key * (size_t)n2 ? at : key * (size_t)n2;
-    if (s.bytes > budget) s.L = 0;
+    if (s.bytes > SWI_LDS) s.L = 0;
     return s;
 }
 
 template <class T>
 __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
-    int64_t m, int32_t n, int64_t R, int32_t nd, int32_t nb, int32_t K, SwapLds lds, const T* __restrict__ A,
+    int64_t m, int32_t n, int64_t R, int32_t nd, int32_t nb, int32_t slices, int32_t K, SwapLds lds, const T* __restrict__ A,
     int64_t lda, const T* __restrict__ At, const T* __restrict__ D, const T* __restrict__ scale,
     const int32_t* __restrict__ kidx, const T* __restrict__ r, const InstState<T>* __restrict__ st,
     const uint8_t* __restrict__ var_mask, const int32_t* __restrict__ rows_all,
@@ -566,7 +565,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
             const T Dl = sc * (sh_dl[lev[su]] - sh_dl[lev[sv]]);
             const T* __restrict__ Au = A + ju * lda;
             const T* __restrict__ Av = A + jv * lda;
-            const T bnd = bound();
+            if (gbest) others = __hip_atomic_load(gbest + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             T val = (T)0, wm = (T)0;
             int32_t at = 0;                                // the lane's row of val
             bool ok = true;
@@ -586,7 +585,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
                     if (w1 > val) { val = w1; at = (int32_t)(i < m ? i : m - 1); }
                 }
                 wm = wave_max(val);
-                ok = wm < t && !(wm > bnd);
+                ok = wm < t && !(wm > bound());         // (what the others have found meanwhile included)
             }
             if (ok) {
                 const int64_t c = ju * n + jv;
@@ -608,7 +607,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
     };
 
     const unsigned long long below = (1ull << lane) - 1ull;
-    const int32_t units = groups * nd;
+    const int32_t units = groups * nd * slices;
     int qn = 0;                                            // queued pairs (uniform)
     // The pairs of a unit within thr0 and, from the second stage on, not within `inner`, which the stage before has seen to;
     // by lane: `upto` pairs up to and with this lane's, which are its variable with positions start + (number of the pair),
@@ -616,11 +615,11 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
     int32_t upto = 0, start = 0, gap_at = 0, gap = 0, first_u = 0, first_v = 0;
     T Ds = (T)0;
     auto search = [&](int32_t unit, T thr0, T inner) -> int32_t {
-        const int32_t b = unit / groups, g = unit % groups;
+        const int32_t slice = unit & (slices - 1), b = unit / slices / groups, g = unit / slices % groups;
         const int32_t s0 = __builtin_amdgcn_readfirstlane(sh_first[b]), len = __builtin_amdgcn_readfirstlane(sh_first[b + 1]) - s0;
         const int32_t pu = g * 64 + lane, puc = pu < nv ? pu : nv - 1;
         const int32_t lu = lev[puc];
-        bool on = len > 0 && pu < nv && lu > b;
+        bool on = len > 0 && pu < nv && lu > b && (lane & (slices - 1)) == slice;
         if (!__any(on)) return 0;
         const T yu = y[puc];
         Ds = sc * (sh_dl[lu] - sh_dl[b]);
@@ -846,13 +845,23 @@ __global__ void k_swap_clear(int32_t* skip, int64_t R) {
     if (q < R) skip[q] = 0;
 }
 
-// workgroups per instance: two rounds of what the chip holds, each with two units or more for every wavefront
-static int32_t swap_sorted_blocks(int64_t n, int64_t R, int32_t nd, int32_t most) {
-    int64_t nb = ceil_div(512, R);
-    const int64_t units = ceil_div(n, 64) * nd;
-    if (nb > ceil_div(units, 2 * SWE_WAVES)) nb = ceil_div(units, 2 * SWE_WAVES);
+// Workgroups per instance: as many as the chip holds, one a compute unit, as long as each has some pairs (every one of them sorts
+// for itself) - SWI_PAIRS of a single instance.  Several instances get up to four times as many pairs a workgroup: at a rounded
+// start every workgroup has to find a good swap of its own before it learns of the others' (20 of 2048 x 512, 16 levels, 0.12 against
+// 0.14 ms), at a local optimum they are the slower ones (4 of them 0.11 against 0.10).  Slices of units until every
+// wavefront has two, while they hold SWI_SLICE pairs on the average.
+constexpr int64_t SWI_PAIRS = 4096, SWI_SLICE = 256;
+static void swap_sorted_grid(int64_t n, int64_t R, int32_t nd, int32_t most, int32_t* nb_out, int32_t* slices_out) {
+    const int64_t units = ceil_div(n, 64) * nd, pairs = n * n / 2 / nd * (nd - 1);
+    int64_t nb = ceil_div(256, R);
+    const int64_t some = ceil_div(pairs, SWI_PAIRS * (R < 4 ? R : 4));
+    if (nb > some) nb = some;
     if (nb > most) nb = most;
-    return (int32_t)(nb < 1 ? 1 : nb);
+    if (nb < 1) nb = 1;
+    int32_t slices = 1;
+    while (slices < 64 && units * slices < nb * 2 * SWE_WAVES && pairs / (units * slices) > SWI_SLICE) slices *= 2;
+    *nb_out = (int32_t)nb;
+    *slices_out = slices;
 }
 
 template <class T>
@@ -879,12 +888,10 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
     // than they save (100 x 17: 42 us without, 49 with; 256 x 64: 67 and 64).
     const bool sorted = K > 0 && n >= SWI_NMIN && n <= SWI_NMAX && c->p.nd <= SWI_LEVELS;
     SwapLds lds = {};
-    if (sorted) {
-        lds = swap_lds(m, n, K, sizeof(T), sizeof(SwapKey<T>), SWI_LDS_HALF);
-        if (lds.L == 0) lds = swap_lds(m, n, K, sizeof(T), sizeof(SwapKey<T>), SWI_LDS_ALL);
-    }
+    int32_t slices = 1;
+    if (sorted) lds = swap_lds(m, n, K, sizeof(T), sizeof(SwapKey<T>));
     if (lds.L > 0) {
-        nb = swap_sorted_blocks(n, R, c->p.nd, c->swap_nb);
+        swap_sorted_grid(n, R, c->p.nd, c->swap_nb, &nb, &slices);
         // (a single instance has two words among the flags, which nothing else looks at)
         gbest = nb == 1 ? nullptr : c->kind == KIND_BATCHED ? (T*)c->cmp_scale : (T*)(c->flags + FLAG_SWAP_BEST);
     }
@@ -895,9 +902,9 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
         // Rows of large entries, where the evaluation's lists of a batch are there.  Looking for them by a pass over A in every
         // search took longer than it saved: a single instance of 100 000 x 2000 (ms) 0.82 / 1.25, without 0.71 / 0.99.
         const uint16_t* hot = batched_lists_in_use(c) ? c->lists.crow : nullptr;
-        DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_intervals<T>), (int)SWI_LDS_ALL));
+        DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_intervals<T>), (int)SWI_LDS));
         hipLaunchKernelGGL(k_swap_intervals<T>, dim3((unsigned)R, (unsigned)nb), dim3(SWE_BLOCK), lds.bytes, c->stream,
-                           m, (int32_t)n, R, c->p.nd, nb, K, lds, (const T*)c->p.A_dense, c->p.lda,
+                           m, (int32_t)n, R, c->p.nd, nb, slices, K, lds, (const T*)c->p.A_dense, c->p.lda,
                            (const T*)(c->kind == KIND_BATCHED ? c->Xt : nullptr), (const T*)c->D_dev,
                            (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->r,
                            (const InstState<T>*)c->state, c->o.var_mask, (const int32_t*)c->swap_rows,
