@@ -331,7 +331,8 @@ constexpr int SWI_NMAX = 8192;                 // most variables
 constexpr int SWI_EACH = SWI_NMAX / SWE_BLOCK; // of them a thread holds
 constexpr int SWI_LROWS = 3;                   // filter rows in LDS at most
 constexpr int SWI_STAGES = 5;
-constexpr int SWI_ROWS = 8;                    // of the others, those tried a lane a pair
+constexpr int SWI_ROWS = 8;                    // of the others, those tried a lane a pair, and one more for every 1024 rows that a
+                                               // pair left over is evaluated on
 constexpr int SWI_SEEN = 8;                    // rows that pairs have failed at, remembered by a workgroup
 constexpr int SWI_HOT = 4;                     // rows of large |entry| looked up per variable, where they are known
 constexpr int SWI_PART = 1024;                 // pairs of a unit one wavefront takes at a time
@@ -531,7 +532,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
             seen = dmmv_max(seen, dmmv_abs(dmmv_fma(Ds, v3 - u3, r_at(i3))));
             alive = seen <= thr;
         };
-        const int l_end = lds.L + SWI_ROWS < K ? lds.L + SWI_ROWS : K;
+        const int n_rows = SWI_ROWS + (int)min(m >> 10, (int64_t)SWAP_KMAX), l_end = lds.L + n_rows < K ? lds.L + n_rows : K;
         const int tries = l_end - lds.L + SWI_SEEN;        // sh_rows[L .. l_end), then sh_fail
         for (int l0 = 0; l0 < tries && __any(alive); l0 += 4) {
             if (alive) {
