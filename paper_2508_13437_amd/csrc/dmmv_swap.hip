@@ -331,6 +331,7 @@ constexpr int SWI_NMAX = 8192;                 // most variables
 constexpr int SWI_EACH = SWI_NMAX / SWE_BLOCK; // of them a thread holds
 constexpr int SWI_LROWS = 3;                   // filter rows in LDS at most
 constexpr int SWI_STAGES = 5;
+constexpr int64_t SWI_FEW = 1 << 17;           // pairs of an instance up to which two stages are enough
 constexpr int SWI_ROWS = 8;                    // of the others, those tried a lane a pair, and one more for every 1024 rows that a
                                                // pair left over is evaluated on
 constexpr int SWI_SEEN = 8;                    // rows that pairs have failed at, remembered by a workgroup
@@ -370,7 +371,7 @@ static SwapLds swap_lds(int64_t m, int64_t n, int32_t K, size_t esz, size_t key)
 
 template <class T>
 __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
-    int64_t m, int32_t n, int64_t R, int32_t nd, int32_t nb, int32_t slices, int32_t K, SwapLds lds, const T* __restrict__ A,
+    int64_t m, int32_t n, int64_t R, int32_t nd, int32_t nb, int32_t slices, bool few, int32_t K, SwapLds lds, const T* __restrict__ A,
     int64_t lda, const T* __restrict__ At, const T* __restrict__ D, const T* __restrict__ scale,
     const int32_t* __restrict__ kidx, const T* __restrict__ r, const InstState<T>* __restrict__ st,
     const uint8_t* __restrict__ var_mask, const int32_t* __restrict__ rows_all,
@@ -751,6 +752,7 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_intervals(
     T inner = (T)-1;                                       // (nothing yet)
     for (int s = 0; s < SWI_STAGES; ++s) {
         const T share[SWI_STAGES] = {(T)0.75, (T)0.875, (T)0.9375, (T)0.96875, (T)1};
+        if (few && s != 2 && s != SWI_STAGES - 1) continue;
         const T reach = dmmv_min(t * share[s], t_below);   // (the last one: t_below)
         if (gbest) others = __hip_atomic_load(gbest + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (bool more = true; more;) {
@@ -846,6 +848,9 @@ __global__ void k_swap_clear(int32_t* skip, int64_t R) {
     if (q < R) skip[q] = 0;
 }
 
+// pairs of an instance whose variables are spread evenly over the levels
+static int64_t swap_pairs(int64_t n, int32_t nd) { return n * n / 2 * (nd - 1) / nd; }
+
 // Workgroups per instance: as many as the chip holds, one a compute unit, as long as each has some pairs (every one of them sorts
 // for itself) - SWI_PAIRS of a single instance.  Several instances get up to four times as many pairs a workgroup: at a rounded
 // start every workgroup has to find a good swap of its own before it learns of the others' (20 of 2048 x 512, 16 levels, 0.12 against
@@ -853,7 +858,7 @@ __global__ void k_swap_clear(int32_t* skip, int64_t R) {
 // wavefront has two, while they hold SWI_SLICE pairs on the average.
 constexpr int64_t SWI_PAIRS = 4096, SWI_SLICE = 256;
 static void swap_sorted_grid(int64_t n, int64_t R, int32_t nd, int32_t most, int32_t* nb_out, int32_t* slices_out) {
-    const int64_t units = ceil_div(n, 64) * nd, pairs = n * n / 2 / nd * (nd - 1);
+    const int64_t units = ceil_div(n, 64) * nd, pairs = swap_pairs(n, nd);
     int64_t nb = ceil_div(256, R);
     const int64_t some = ceil_div(pairs, SWI_PAIRS * (R < 4 ? R : 4));
     if (nb > some) nb = some;
@@ -905,7 +910,7 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
         const uint16_t* hot = batched_lists_in_use(c) ? c->lists.crow : nullptr;
         DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_intervals<T>), (int)SWI_LDS));
         hipLaunchKernelGGL(k_swap_intervals<T>, dim3((unsigned)R, (unsigned)nb), dim3(SWE_BLOCK), lds.bytes, c->stream,
-                           m, (int32_t)n, R, c->p.nd, nb, slices, K, lds, (const T*)c->p.A_dense, c->p.lda,
+                           m, (int32_t)n, R, c->p.nd, nb, slices, swap_pairs(n, c->p.nd) <= SWI_FEW, K, lds, (const T*)c->p.A_dense, c->p.lda,
                            (const T*)(c->kind == KIND_BATCHED ? c->Xt : nullptr), (const T*)c->D_dev,
                            (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->r,
                            (const InstState<T>*)c->state, c->o.var_mask, (const int32_t*)c->swap_rows,
