@@ -20,7 +20,7 @@
 // row, so that A is read along its columns.  A batch's workgroups share the best t' of their
 // instance through memory, so that a pair one of them has found prunes the others' (512 instances of
 // 2048 x 4096: 18.6 -> 11.9 ms at a rounded start, where good swaps are plenty, 15.8 -> 15.4 at a
-// local optimum; 20 instances 10.7 -> 3.0).
+// local optimum; 20 instances 10.7 -> 3.0; the kernel alone).
 #include "dmmv_common.h"
 
 namespace dmmv {
@@ -55,7 +55,8 @@ __device__ __forceinline__ double value_below(double t) {
 // selection is not needed: every thread takes the largest |r| among its rows i = thread,
 // thread + 256, ... and the 256 maxima are ranked (larger first, lower row first among equal
 // values).  The row of largest |r| always comes first; of the next largest most are there.
-// One workgroup per instance.
+// One workgroup per instance, bound by the latency of its reads of memory and of LDS: eight of either are in flight in a thread
+// (one at a time 24 us on 256 rows and 74 on 100 000, now 13 and 30).
 template <class T>
 __global__ __launch_bounds__(SW_BLOCK) void k_swap_top(int64_t m, int64_t R, int32_t K,
                                                         const T* __restrict__ r,
@@ -68,18 +69,25 @@ __global__ __launch_bounds__(SW_BLOCK) void k_swap_top(int64_t m, int64_t R, int
     if (gbest && threadIdx.x == 0) gbest[q] = Limits<T>::inf();
     T a = (T)-1;                                           // no row: ranks after every real one
     int32_t row = INT32_MAX;
-    for (int64_t i = threadIdx.x; i < m; i += SW_BLOCK) {
-        const T v = dmmv_abs(r[i * R + q]);
-        if (v > a) { a = v; row = (int32_t)i; }
+    for (int64_t i0 = threadIdx.x; i0 < m; i0 += 8 * SW_BLOCK) {
+        T v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = dmmv_abs(r[(i0 + e * SW_BLOCK < m ? i0 + e * SW_BLOCK : m - 1) * R + q]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (i0 + e * SW_BLOCK < m && v[e] > a) { a = v[e]; row = (int32_t)(i0 + e * SW_BLOCK); }
     }
     sh_a[threadIdx.x] = a;
     sh_row[threadIdx.x] = row;
     __syncthreads();
     int32_t rank = 0;
-    for (int x = 0; x < SW_BLOCK; ++x) {
-        const T oa = sh_a[x];
-        const int32_t orow = sh_row[x];
-        rank += (oa > a || (oa == a && orow < row)) ? 1 : 0;
+    for (int x = 0; x < SW_BLOCK; x += 8) {
+        T oa[8];
+        int32_t orow[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { oa[e] = sh_a[x + e]; orow[e] = sh_row[x + e]; }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rank += (oa[e] > a || (oa[e] == a && orow[e] < row)) ? 1 : 0;
     }
     if (row != INT32_MAX && rank < K) rows_all[q * K + rank] = row;
 }
@@ -291,12 +299,14 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_eval(
 // are all taken, and whoever holds one covers it up to the smaller of stage and bound.  A few units hold most
 // pairs (outlier channels sort to the ends of their levels), so what is over SWI_PART is shared.
 // Bound by the latency of its gathers in the slowest instances (three times the pairs of the average one) and, at
-// local optima, by instruction issue; one workgroup of 16 wavefronts a compute unit (73 registers; held to 64
-// they spill, 0.95 ms).  Against the evaluation of all pairs (ms, rounded start / local optimum): 512 instances of
-// 2048 x 4096, 16 levels 12.0 / 15.4 and now 0.87 / 13.5; 20 of them 2.96 / 1.07 and 0.40 / 0.92; 64 of 4096 x 4096, 8
-// levels 17.0 and 0.49; 200 of 700 x 1000 1.40 / 0.96 and 0.19 / 0.60; single instances 2048 x 512, 64 levels, fp64 0.53 and
-// 0.093, 256 x 64 0.067 and 0.064.  Seven filter rows in LDS instead of three: 1.9 / 10.6; two workgroups an instance
-// where one fills the chip: no gain (0.86 / 13.9), 20 instances 0.46 / 1.5 with twice as many.
+// local optima, by instruction issue; one workgroup of 16 wavefronts a compute unit (67 registers, 89 in fp64).
+// A whole search in ms, rounded start / local optimum, by the evaluation of all pairs and by this one:
+//     512 instances of 2048 x 4096, 16 levels  22.6 / 16.6    0.67 / 11.2      one of 2048 x 512, 16 levels      0.36 / 0.089    0.055 / 0.054
+//     20 of them                               9.0 / 1.28     0.19 / 0.91      2048 x 8192, 2 levels             1.98 / 0.54     0.31 / 0.26
+//     64 of 4096 x 4096, 8 levels              29.1 / 2.52    0.33 / 1.51      100 000 x 512, 8 levels           11.9 / 0.122    0.69 / 0.068
+//     200 of 700 x 1000, 8 levels              2.12 / 0.90    0.20 / 0.49      256 x 64, 16 levels               0.070 / 0.041   0.040 / 0.037
+// Slower at a local optimum, in fp64: one of 2048 x 512, 2 levels, 0.054 and 0.065; a batch of four 2048 x 8192, 1.83 and 2.38
+// (two filter rows fit LDS) - with 1.92 and 0.5 at a rounded start.
 template <class T> struct SwapKey;
 template <> struct SwapKey<float> {                        // level 8 bits | entry, as ordered bits, 32 | variable 16
     uint64_t k;
@@ -890,8 +900,8 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
     if (L > K) L = K;
     used += (size_t)L * n * sizeof(T);
 
-    // Sorted variables where their keys and filter rows fit.  Under 64 variables the sort and one more launch cost more
-    // than they save (100 x 17: 42 us without, 49 with; 256 x 64: 67 and 64).
+    // Sorted variables where their keys and filter rows fit.  Under 64 variables the sort costs more than it saves
+    // (100 x 17: 42 us without, 49 with; 256 x 64: 70 and 40).
     const bool sorted = K > 0 && n >= SWI_NMIN && n <= SWI_NMAX && c->p.nd <= SWI_LEVELS;
     SwapLds lds = {};
     int32_t slices = 1;
@@ -916,17 +926,17 @@ dmmv_status swap_t(Ctx* c, int32_t k_eps, int32_t apply, bool use_skip, dmmv_swa
                            (const InstState<T>*)c->state, c->o.var_mask, (const int32_t*)c->swap_rows,
                            hot, hot ? SWI_HOT : 0, (const int32_t*)skip, gbest, (Partial<T>*)c->swap_part);
     } else {
-    DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_eval<T, true>), (int)SW_LDS_BUDGET));
-    DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_eval<T, false>), (int)SW_LDS_BUDGET));
+        DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_eval<T, true>), (int)SW_LDS_BUDGET));
+        DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(&k_swap_eval<T, false>), (int)SW_LDS_BUDGET));
 #define DMMV_SWAP_LAUNCH(DV)                                                                               \
-    hipLaunchKernelGGL((k_swap_eval<T, DV>), dim3((unsigned)R, (unsigned)nb), dim3(SWE_BLOCK), used, c->stream, m, n, R, nb, K,       \
-                       (int32_t)L, (const T*)c->p.A_dense, c->p.lda,                                       \
-                       (const T*)(c->kind == KIND_BATCHED ? c->Xt : nullptr), (const T*)c->D_dev,          \
-                       (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->r,                    \
-                       (const InstState<T>*)c->state, c->o.var_mask, (const int32_t*)c->swap_rows,         \
-                       (const int32_t*)skip, gbest, (Partial<T>*)c->swap_part)
-    if (dvl) DMMV_SWAP_LAUNCH(true);
-    else DMMV_SWAP_LAUNCH(false);
+        hipLaunchKernelGGL((k_swap_eval<T, DV>), dim3((unsigned)R, (unsigned)nb), dim3(SWE_BLOCK), used, c->stream, m, n, R, nb, K,       \
+                           (int32_t)L, (const T*)c->p.A_dense, c->p.lda,                                       \
+                           (const T*)(c->kind == KIND_BATCHED ? c->Xt : nullptr), (const T*)c->D_dev,          \
+                           (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->r,                    \
+                           (const InstState<T>*)c->state, c->o.var_mask, (const int32_t*)c->swap_rows,         \
+                           (const int32_t*)skip, gbest, (Partial<T>*)c->swap_part)
+        if (dvl) DMMV_SWAP_LAUNCH(true);
+        else DMMV_SWAP_LAUNCH(false);
 #undef DMMV_SWAP_LAUNCH
     }
     hipLaunchKernelGGL(k_swap_apply<T>, dim3((unsigned)R), dim3(SW_BLOCK), 0, c->stream, m, n, R, nb, apply,
