@@ -211,8 +211,8 @@ __global__ __launch_bounds__(64 * WA * WB, PER) void k_chain_product(
 template <bool RES>
 static dmmv_status chain_product(Ctx* c, int64_t m, int64_t n, const float* X, int64_t ldx, const float* V, float* out) {
     const int64_t R = c->p.R;
-    auto launch = [&](auto kernel, int64_t rows, int64_t insts, int threads) -> dmmv_status {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(m, rows), (unsigned)ceil_div(R, insts)), dim3(threads), 0, c->stream,
+    auto launch = [&](auto kernel, int64_t rows, int64_t insts, int threads, size_t lds) -> dmmv_status {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(m, rows), (unsigned)ceil_div(R, insts)), dim3(threads), lds, c->stream,
                            m, n, R, X, ldx, V, (const float*)c->scale_dev,
                            (const float*)c->Bt, out, (InstState<float>*)c->state);
         DMMV_LAUNCH_CHECK();
@@ -224,13 +224,20 @@ static dmmv_status chain_product(Ctx* c, int64_t m, int64_t n, const float* X, i
     // wavefront per workgroup 18.  Total at R = 20 / 128 / 500 / 1024 / 4096 of m = 2048 (us): 73 / 78 / 96 / 146 / 512 with
     // the tile taken; before the operands of V shared their registers and the loads went out between the products
     // 95 / 98 / 147 / 201 / 578, and 1610 / 1610 / 1610 / 1744 / 2206 on the vector unit.
+    // A chain of up to 256 columns ends before the deep request queues of the tiles below have paid for their start: 2048 x 64
+    // with 500 instances 11.1 us by this one, 12.4 by the next; 4096 x 128 with 128 11.1 and 12.8.
     const int64_t few = ceil_div(m, 64) * ceil_div(R, 16);
-    if (few <= 512) return launch(k_chain_product<Mfma16, 1, 1, 1, 1, 48, 1, RES>, 64, 16, 64);
+    if (n <= 256 && few <= 1024) return launch(k_chain_product<Mfma16, 1, 1, 1, 1, 16, 1, RES>, 64, 16, 64, 0);
+    if (few <= 512) return launch(k_chain_product<Mfma16, 1, 1, 1, 1, 48, 1, RES>, 64, 16, 64, 0);
     auto rounds = [&](int64_t rows, int64_t insts) { return ceil_div(ceil_div(m, rows) * ceil_div(R, insts), 256); };
     const int64_t t16 = 20 * rounds(64, 64), t32 = 31 * rounds(64, 128), t64 = 59 * rounds(128, 128);
-    if (t16 <= t32 && t16 <= t64) return launch(k_chain_product<Mfma16, 1, 1, 1, 4, 32, 1, RES>, 64, 64, 256);
-    if (t32 <= t64) return launch(k_chain_product<Mfma32, 1, 1, 1, 4, 16, 3, RES>, 64, 128, 256);
-    return launch(k_chain_product<Mfma32, 1, 2, 2, 2, 16, 2, RES>, 128, 128, 256);
+    if (t16 <= t32 && t16 <= t64) return launch(k_chain_product<Mfma16, 1, 1, 1, 4, 32, 1, RES>, 64, 64, 256, 0);
+    // The larger tiles ask for LDS that they do not use, for two workgroups a compute unit: where the registers let three
+    // (G of the 64 x 64 tile) or five in, 1024 workgroups are 768 and then 256 of uneven distribution.  G of 2048 x 4096
+    // with 4096 instances: 644 us with three, 497 with two (64 x 32: 553 with five, 504 with two).
+    constexpr size_t TWO_PER_CU = 56 * 1024;
+    if (t32 <= t64) return launch(k_chain_product<Mfma32, 1, 1, 1, 4, 16, 3, RES>, 64, 128, 256, TWO_PER_CU);
+    return launch(k_chain_product<Mfma32, 1, 2, 2, 2, 16, 2, RES>, 128, 128, 256, TWO_PER_CU);
 }
 
 bool batched_chain_applicable(const Ctx* c) {
