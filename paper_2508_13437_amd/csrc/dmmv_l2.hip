@@ -101,46 +101,63 @@ __device__ __forceinline__ T l2_change(T delta, T csq, T g) {
     return delta * dmmv_fma(delta, csq, twog);
 }
 
-// A workgroup takes LTB_J variables x LTB_Q instances: g and the current values go through LDS, read along
-// the instances ([n][R]) and used along the table's rows, whose LTB_J nd values of an instance are contiguous.
+// A workgroup takes `width` variables x 2^qsh instances (64 x 32, or more variables of fewer instances): g and the current values
+// go through LDS, read along the instances ([n][R]) and used along the table's rows, whose width * nd values of an instance are
+// contiguous.  The host sizes the tile by its values (table_t).
 // (One thread per variable and instance, its nd values written by itself: 242 us for 1376 tables of 4096 x 8, a
 // wavefront's stores 64 tables apart; now 49.)
-constexpr int LTB_J = 64, LTB_Q = 32;
+constexpr int LTB_Q = 32, LTB_AREA = 64 * (LTB_Q + 1), LTB_J = 256, LTB_EACH = 8, LTB_D = 256;
+static constexpr int ltb_pitch(int32_t qsh) { return (1 << qsh) + (qsh > 0); }
+static constexpr int ltb_most(int32_t qsh) {                // variables: what the tile, a thread's registers and sh_c hold
+    int v = LTB_AREA / ltb_pitch(qsh);
+    v = v < LTB_EACH * (256 >> qsh) ? v : LTB_EACH * (256 >> qsh);
+    return v < LTB_J ? v : LTB_J;
+}
 template <class T>
-__global__ __launch_bounds__(256) void k_l2_table(int64_t n, int64_t R, int32_t nd, const T* __restrict__ D,
+__global__ __launch_bounds__(256) void k_l2_table(int64_t n, int64_t R, int32_t nd, int32_t width, int32_t qsh, const T* __restrict__ D,
                                                   const T* __restrict__ scale, const int32_t* __restrict__ kidx,
                                                   const T* __restrict__ g, const T* __restrict__ csq, T* __restrict__ dq) {
-    __shared__ T sh_g[LTB_J][LTB_Q + 1], sh_d[LTB_J][LTB_Q + 1], sh_c[LTB_J];
-    const int64_t j0 = blockIdx.x * (int64_t)LTB_J, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) * LTB_Q;
+    __shared__ T sh_g[LTB_AREA], sh_d[LTB_AREA], sh_c[LTB_J], sh_lev[LTB_D];
+    const int64_t j0 = blockIdx.x * (int64_t)width, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) << qsh;
     if (q0 >= R) return;
-    const int32_t nj = (int32_t)(n - j0 < LTB_J ? n - j0 : LTB_J), nq = (int32_t)(R - q0 < LTB_Q ? R - q0 : LTB_Q);
-    const int tid = threadIdx.x, lq = tid % LTB_Q;
-    T gv[LTB_J * LTB_Q / 256];
-    int32_t kv[LTB_J * LTB_Q / 256];
+    const int32_t nj = (int32_t)(n - j0 < width ? n - j0 : width), nq = (int32_t)(R - q0 < 1 << qsh ? R - q0 : 1 << qsh);
+    const int tid = threadIdx.x, lq = tid & ((1 << qsh) - 1), lj0 = tid >> qsh, step = 256 >> qsh;
+    const int pitch = (1 << qsh) + (qsh > 0);
+    T gv[LTB_EACH];
+    int32_t kv[LTB_EACH];
 #pragma unroll
-    for (int u = 0; u < LTB_J * LTB_Q / 256; ++u) {
-        const int lj = tid / LTB_Q + u * (256 / LTB_Q);
+    for (int u = 0; u < LTB_EACH; ++u) {
+        if (u * step >= width) break;                       // uniform
+        const int lj = lj0 + u * step;
         const int64_t at = (j0 + (lj < nj ? lj : nj - 1)) * R + q0 + (lq < nq ? lq : nq - 1);
         gv[u] = g[at];
         kv[u] = kidx[at];
     }
+    const bool lev_lds = nd <= LTB_D;
+    for (int32_t k = tid; lev_lds && k < nd; k += 256) sh_lev[k] = D[k];
 #pragma unroll
-    for (int u = 0; u < LTB_J * LTB_Q / 256; ++u) {
-        const int lj = tid / LTB_Q + u * (256 / LTB_Q);
-        sh_g[lj][lq] = gv[u];
-        sh_d[lj][lq] = D[kv[u]];
+    for (int u = 0; u < LTB_EACH; ++u) {
+        if (u * step >= width) break;
+        const int lj = lj0 + u * step;
+        if (lj < width) {
+            sh_g[lj * pitch + lq] = gv[u];
+            sh_d[lj * pitch + lq] = D[kv[u]];
+        }
     }
-    if (tid < LTB_J) sh_c[tid] = csq[j0 + (tid < nj ? tid : nj - 1)];
+    for (int32_t lj = tid; lj < width; lj += 256) sh_c[lj] = csq[j0 + (lj < nj ? lj : nj - 1)];
     __syncthreads();
-    // a wavefront takes an instance at a time; its lanes walk (variable, value) in table order
+    // a wavefront takes an instance at a time, or with fewer than four several share one; its lanes walk (variable, value) in
+    // table order
     const int lane = tid & 63, w = tid >> 6;
-    const int32_t step_j = 64 / nd, step_k = 64 % nd;
-    for (int x = w; x < nq; x += 4) {
+    const int share = nq >= 4 ? 1 : nq == 1 ? 4 : 2, jump = 64 * share;
+    const int32_t step_j = jump / nd, step_k = jump % nd;
+    for (int x = w / share; x < nq; x += 4 / share) {
         const T sc = scale[q0 + x];
         T* __restrict__ out = dq + (q0 + x) * (n * (int64_t)nd) + j0 * nd;
-        int32_t j = lane / nd, k = lane % nd;
-        for (int64_t e = lane; j < nj; e += 64) {
-            out[e] = l2_change(step_of(D[k], sh_d[j][x], sc), sh_c[j], sh_g[j][x]);
+        const int32_t e0 = lane + 64 * (w % share);
+        int32_t j = e0 / nd, k = e0 % nd;
+        for (int64_t e = e0; j < nj; e += jump) {
+            out[e] = l2_change(step_of(lev_lds ? sh_lev[k] : D[k], sh_d[j * pitch + x], sc), sh_c[j], sh_g[j * pitch + x]);
             k += step_k;
             j += step_j;
             if (k >= nd) { k -= nd; ++j; }
@@ -285,8 +302,17 @@ template <class T>
 dmmv_status table_t(Ctx* c, void* dq_out) {
     const int64_t n = c->p.n, R = c->p.R;
     if (n == 0) return DMMV_OK;
-    const int64_t gq = ceil_div(R, LTB_Q), gy = gq < 32768 ? gq : 32768;
-    hipLaunchKernelGGL(k_l2_table<T>, dim3((unsigned)ceil_div(n, LTB_J), (unsigned)gy, (unsigned)ceil_div(gq, gy)), dim3(256), 0, c->stream, n, R, c->p.nd,
+    // A workgroup's values: 32768, less where there would be fewer than two workgroups a compute unit (full tiles of 64 x 32
+    // left 500 instances of 64 variables and 16 values to 16 workgroups: 20 us, now 6; 100 of 1000 x 64 values 74 and 12), 512 at least.
+    int32_t qsh = 0;
+    while (1 << qsh < LTB_Q && 1ll << qsh < R) ++qsh;
+    int64_t values = n * R * c->p.nd / 512;
+    values = values < 512 ? 512 : values > 32768 ? 32768 : values;
+    int64_t width = values / ((int64_t)c->p.nd << qsh);
+    width = width < 1 ? 1 : width > ltb_most(qsh) ? ltb_most(qsh) : width;
+    const int64_t gq = ceil_div(R, 1ll << qsh), gy = gq < 32768 ? gq : 32768;
+    hipLaunchKernelGGL(k_l2_table<T>, dim3((unsigned)ceil_div(n, width), (unsigned)gy, (unsigned)ceil_div(gq, gy)), dim3(256), 0, c->stream, n, R, c->p.nd,
+                       (int32_t)width, qsh,
                        (const T*)c->D_dev, (const T*)c->scale_dev, (const int32_t*)c->kidx, (const T*)c->l2_g,
                        (const T*)c->l2_c, (T*)dq_out);
     DMMV_LAUNCH_CHECK();
@@ -295,8 +321,13 @@ dmmv_status table_t(Ctx* c, void* dq_out) {
 
 template <class T>
 dmmv_status select_t(Ctx* c, const void* scores, int32_t keep_going, dmmv_move* best_out, void* best_score_out) {
-    // (up to 32 values: a wavefront's 64 rows of the table then stay in the cache between the loads of a row)
-    auto kernel = c->p.nd <= 32 ? k_l2_select<T, true> : k_l2_select<T, false>;
+    // By rows up to 32 values (a wavefront's 64 rows of the table then stay in the cache between the loads of a row), where there are
+    // variables for a quarter of the threads and four values for each of them, and no more instances than compute units: there it
+    // is latency that counts (us by values / by rows, fp32: one of 500 x 31 16.6 / 13.5; one of 512 x 8 9.8 / 9.2; 100 of 4096 x 8
+    // 42 / 31; 200 of 4096 x 16 73 / 46; 300 of them 82 / 85; 1376 of 4096 x 4 92 / 116; 5000 of 600 x 4 86 / 112; one of 16 x 16
+    // 6.3 / 8.5).
+    const bool by_rows = c->p.nd <= 32 && c->p.n >= 256 && c->p.n * c->p.nd >= 4096 && c->p.R <= 256;
+    auto kernel = by_rows ? k_l2_select<T, true> : k_l2_select<T, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)c->p.R), dim3(1024), 0, c->stream, c->p.n, c->p.R, c->p.nd,
                        c->o.l2_rule, (const T*)scores, (const T*)c->D_dev, (const T*)c->scale_dev,
                        (const int32_t*)c->kidx, (const T*)c->l2_g, (const T*)c->l2_c, (InstState<T>*)c->state,
