@@ -334,14 +334,18 @@ __global__ __launch_bounds__(1024) void k_alns_worst_list(int64_t R, const AlnsS
 // per row in a mask (two instructions a term), the set bits go to a queue in LDS, a lane's behind those of the lanes before
 // it, and the queue is evaluated two entries a lane, for whichever variable and instance they belong to, the integers
 // added to the sums with LDS atomics.  About 1050 vector instructions per 64 x 4 x 32 terms, a quarter of them the tests
-// and a third the evaluations, the unit 60 % busy.  (One entry a lane: 1.88 ms; the bits popped a variable at a time over
-// the wavefront, with an evaluation whenever 64 were waiting and the whole of the term's arithmetic in it: 2.25.)  The sums are integers, so neither their
-// order nor the split of the rows over workgroups (small batches: one pass each, 0.056 ms against 0.10 with two) changes a weight.
+// and a third the evaluations, the unit 60 % busy.  Where most terms of most variables count (no outlier channels, or a small
+// alpha) they are evaluated row by row without the queue: 1000 instances of 700 x 128, normal entries, 239 us with the queue of
+// the kernel before, 275 with this one, 145 without; 5000 of 32 x 100 100, 126 and 45.  (One entry a lane: 1.88 ms; the bits
+// popped a variable at a time over the wavefront, with an evaluation whenever 64 were waiting and the whole of the term's
+// arithmetic in it: 2.25.)  The sums are integers, so neither their order nor the split of the rows over workgroups (small
+// batches: one pass each, 0.056 ms against 0.10 with two) changes a weight.
 constexpr int IM_Q = 4;                        // instances that share a row of X
 constexpr int IM_ROWS = 32;                    // rows per pass: one mask bit each
 constexpr int IM_STAGE = IM_ROWS * IM_Q / 64;  // (row, instance) pairs a lane stages per pass
 constexpr int IM_MOST = 64 * IM_ROWS;          // terms of an instance a pass can have
 constexpr int IM_CAP = IM_MOST + 512;          // queue of a wavefront: evaluated when over 512 are waiting
+constexpr int IM_DENSE = 14;                   // more terms than this in half of the variables: no queue
 constexpr int IM_FEW = 8;                      // a variable with more terms than this in a pass is queued by rows
 
 // mask = 2 mask + (|x| >= lim): the comparison's bit enters as the carry of one addition
@@ -457,7 +461,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
     const int64_t sq = list[slot_c];
     const int wl = threadIdx.x >> 6;                        // (in a vector register: LDS addresses are one register + constants)
     int waiting = 0;                                        // queued terms, the same in every lane
-    // all queued terms of the pass at (i_pass, j_pass), 64 at a time, each for the sum it belongs to
+    // all queued terms of the pass at (i_pass, j_pass), 128 at a time, each for the sum it belongs to
     auto evaluate = [&](int64_t i_pass, int64_t j_pass) {
         __builtin_amdgcn_wave_barrier();
         const T* __restrict__ at = Xt + i_pass * n + j_pass;
@@ -555,6 +559,32 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
                 uint32_t mk = j < n ? mask[0] : 0;          // highest bit = first row
 #pragma unroll
                 for (int e = 0; e + 1 < IM_Q; ++e) mask[e] = mask[e + 1];
+                // most of the terms, in most of the variables: row by row without the queue, every lane its own
+                if (__builtin_expect(__popcll(__ballot(__popc(mk) > IM_DENSE)) >= 32, 0)) {
+                    const T* __restrict__ at = Xt + i0 * n + j0;
+                    unsigned long long sum = 0;
+#pragma unroll 1
+                    for (int row = 0; row < IM_ROWS && i0 + row < i_end; row += 2) {
+                        T y[2];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) y[u] = dmmv_abs(at[(int64_t)(i0 + row + u < i_end ? row + u : row) * n + lc]);
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            const bool on = ((mk << (row + u)) & 0x80000000u) != 0;
+                            uint32_t term;
+                            const bool exact = alns_impact_term_fast((double)y[u], L.rate[wl][row + u][v], L.base[wl][row + u][v], L.exp2m, term);
+                            const unsigned long long odd = __ballot(on && !exact);      // (rare: by the queue, which knows how)
+                            if (odd != 0ull) {
+                                if (on && !exact)
+                                    L.queue[wl][waiting + __builtin_amdgcn_mbcnt_hi((uint32_t)(odd >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)odd, 0))] = (uint16_t)(lane | (v << 6) | ((row + u) << 8));
+                                waiting += __popcll(odd);
+                            }
+                            if (on && exact) sum += term;
+                        }
+                    }
+                    if (sum) atomicAdd(&L.sum[wl][v][lane], sum);
+                    continue;
+                }
                 // a variable with many terms (an outlier channel): all its rows at once, lane = row
                 unsigned long long many = __ballot(__popc(mk) > IM_FEW);
                 while (many) {                              // the same for the whole wavefront
