@@ -5,7 +5,7 @@
 // the best move known (Corollary 1 turns the same observation into a filter for swaps: a move
 // that does not fix the rows of largest |r| cannot improve).  Per iteration the workgroup
 //   1. picks S = 16 screening rows: of each lane's rows the one of largest |r|, and of these the four largest of each
-//      wavefront (the row of largest |r| overall is always one of them);
+//      wavefront (the row of largest |r| overall is always one of them; the wavefronts share the rows evenly);
 //   2. bounds candidates from below by lb(j, k) = max_{i in S} |fma(delta, X_ij, r_i)| - 16 rows instead
 //      of m - and keeps per variable its best candidate by (lb, k), found by walking outwards from
 //      the current level on the side that lowers the row of largest |r| until lb rises;
@@ -92,8 +92,10 @@ __device__ __forceinline__ double bp_entry(const __amdgpu_buffer_rsrc_t& rs, uin
 // AHEAD: the next block of variables' entries are requested before this one is walked.  With a single block (n <= 256) there
 // is none, and the registers it takes cost a wavefront per SIMD: 60 000 instances of 8 x 8, 30 moves, 1193 us with it
 // and 1043 without (fp64 1927 and 1527).
+// The wavefronts per SIMD asked for are what the kernel had before it kept a step table: one to nine registers more had cost one of
+// them (60 000 instances of 8 x 8 in fp64 1525 us, then 1558, 1237 with it back; 2000 of 64 x 64 1854, 2250, 1971).
 template <class T, class KI, bool AHEAD>
-__global__ __launch_bounds__(BP_BLOCK) void k_descent_batched_pruned(
+__global__ __launch_bounds__(BP_BLOCK, (sizeof(T) == 4 ? 5 : 3) + (AHEAD ? 0 : 1)) void k_descent_batched_pruned(
     int64_t m, int64_t n, int32_t nd, int64_t R, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Xt, const T* __restrict__ D, const T* __restrict__ scale,
     T* __restrict__ r, int32_t* __restrict__ kidx, InstState<T>* __restrict__ st, int32_t radius,
@@ -156,6 +158,10 @@ __global__ __launch_bounds__(BP_BLOCK) void k_descent_batched_pruned(
     bool dirty = false;
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void*)Xt, 0, (int)(uint32_t)(m * n * (int64_t)sizeof(T)), 0x00020000);
     const int32_t n32 = (int32_t)n, m32 = (int32_t)m;
+    // A lane's rows: every 256th.  Fewer than 256 are split into a quarter for each wavefront, or the first ones would hold them
+    // all and the others propose no screening rows: 2000 instances of 64 x 64, 16 levels, 1542 us with four rows, 168 with sixteen.
+    const int32_t quarter = (m32 + BP_WAVES - 1) / BP_WAVES;
+    const int32_t first_row = m32 >= BP_BLOCK ? tid : lane < quarter ? w * quarter + lane : m32;
     __syncthreads();
 
     for (int32_t step = 0; step < steps; ++step) {
@@ -165,7 +171,7 @@ __global__ __launch_bounds__(BP_BLOCK) void k_descent_batched_pruned(
             // which leaves the largest of all and rarely misses one of the others)
             T bv = (T)-1;
             int32_t bi = -1;
-            for (int32_t i = tid; i < m32; i += BP_BLOCK) {
+            for (int32_t i = first_row; i < m32; i += BP_BLOCK) {
                 const T a = dmmv_abs(sh_r[i]);
                 if (a > bv) { bv = a; bi = i; }
             }
