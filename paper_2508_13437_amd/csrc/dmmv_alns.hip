@@ -559,15 +559,18 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
                 uint32_t mk = j < n ? mask[0] : 0;          // highest bit = first row
 #pragma unroll
                 for (int e = 0; e + 1 < IM_Q; ++e) mask[e] = mask[e + 1];
+                unsigned long long many = __ballot(__popc(mk) > IM_FEW);
                 // most of the terms, in most of the variables: row by row without the queue, every lane its own
-                if (__builtin_expect(__popcll(__ballot(__popc(mk) > IM_DENSE)) >= 32, 0)) {
-                    const T* __restrict__ at = Xt + i0 * n + j0;
+                if (__builtin_expect(__popcll(many) >= 32, 0) && __popcll(__ballot(__popc(mk) > IM_DENSE)) >= 32) {
+                    int64_t nn = n;                         // (made opaque: nothing of this block is kept in registers for it)
+                    asm volatile("" : "+s"(nn));
+                    const T* __restrict__ at = Xt + i0 * nn + j0;
                     unsigned long long sum = 0;
 #pragma unroll 1
                     for (int row = 0; row < IM_ROWS && i0 + row < i_end; row += 2) {
                         T y[2];
 #pragma unroll
-                        for (int u = 0; u < 2; ++u) y[u] = dmmv_abs(at[(int64_t)(i0 + row + u < i_end ? row + u : row) * n + lc]);
+                        for (int u = 0; u < 2; ++u) y[u] = dmmv_abs(at[(int64_t)(i0 + row + u < i_end ? row + u : row) * nn + lc]);
 #pragma unroll
                         for (int u = 0; u < 2; ++u) {
                             const bool on = ((mk << (row + u)) & 0x80000000u) != 0;
@@ -586,7 +589,6 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
                     continue;
                 }
                 // a variable with many terms (an outlier channel): all its rows at once, lane = row
-                unsigned long long many = __ballot(__popc(mk) > IM_FEW);
                 while (many) {                              // the same for the whole wavefront
                     const int col = __ffsll(many) - 1;
                     many &= many - 1;
