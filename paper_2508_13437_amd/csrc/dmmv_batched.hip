@@ -37,76 +37,97 @@ static void launch_transpose(hipStream_t s, const T* in, int64_t rows, int64_t c
     hipLaunchKernelGGL(k_transpose<T>, grid, dim3(32, 8), 0, s, in, rows, cols, ld_in, out, ld_out);
 }
 
-// x values [R][n] <-> kidx [n][R], 32 x 32 at a time through LDS so that both are read and written along their rows (an
+// x values [R][n] <-> kidx [n][R], 1024 at a time through LDS so that both are read and written along their rows (an
 // element per thread in the order of one of them took 99 and 57 us for 4096 x 4096 and 19 and 14 for 500 x 4096; now 39 and
-// 27, 9 and 6).
-// Values are looked up in a copy of D in LDS where it fits.
-constexpr int XV_LEVELS = 1024;
-template <class T>
+// 27, 9 and 6).  A tile is 2^wsh variables x the instances that make it 1024: 32 x 32, or as narrow as the batch is
+// (100 000 instances of one variable left 31 of 32 lanes idle with 32 x 32: a dmmv_set_x 28 us in fp64, now 24, of which 22 are its wait for the host).
+// Values are looked up in a copy of D in LDS where it fits, four a thread at a time, so that their reads are in flight together.
+constexpr int XV_LEVELS = 1024, XV_TILE = 1024, XV_LDS = 1536;      // (2^wsh | 1) * (1024 >> wsh) at most
+template <class T, bool SQUARE>                             // (SQUARE: 32 x 32, the shifts as constants)
 __global__ __launch_bounds__(256) void k_values_to_index_batched(const T* __restrict__ x, const T* __restrict__ D,
-                                                                 int32_t nd, int64_t n, int64_t R,
+                                                                 int32_t nd, int64_t n, int64_t R, int32_t log_wide,
                                                                  int32_t* __restrict__ kidx, int32_t* flags) {
-    __shared__ int32_t tile[32][33];
+    __shared__ int32_t tile[XV_LDS];
     __shared__ T sh_d[XV_LEVELS];
-    const int64_t j0 = blockIdx.x * 32ll, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) * 32;
+    const int wsh = SQUARE ? 5 : log_wide, hsh = 10 - wsh, wide = 1 << wsh, pitch = wide | 1;
+    const int64_t j0 = (int64_t)blockIdx.x << wsh, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) << hsh;
     if (q0 >= R) return;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const bool in_lds = nd <= XV_LEVELS;
     T v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int64_t q = q0 + ty + 8 * u, j = j0 + tx;
+        const int e = threadIdx.x + 256 * u;
+        const int64_t q = q0 + (e >> wsh), j = j0 + (e & (wide - 1));
         v[u] = x[(q < R ? q : R - 1) * n + (j < n ? j : n - 1)];
     }
     for (int32_t k = threadIdx.x; in_lds && k < nd; k += 256) sh_d[k] = D[k];
     __syncthreads();
-    auto level = [&](int32_t k) -> T { return in_lds ? sh_d[k] : D[k]; };
     int32_t lo[4] = {0, 0, 0, 0}, hi[4] = {nd - 1, nd - 1, nd - 1, nd - 1};
-    for (int32_t span = nd - 1; span > 0; span >>= 1)       // (as many steps as the widest interval takes)
+    for (int32_t span = nd - 1; span > 0; span >>= 1) {     // (as many steps as the widest interval takes)
+        T d[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) d[u] = in_lds ? sh_d[(lo[u] + hi[u]) >> 1] : D[(lo[u] + hi[u]) >> 1];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int32_t mid = (lo[u] + hi[u]) >> 1;
-            if (lo[u] < hi[u]) { if (level(mid) < v[u]) lo[u] = mid + 1; else hi[u] = mid; }
+            const bool above = lo[u] < hi[u] && d[u] < v[u], below = lo[u] < hi[u] && !(d[u] < v[u]);
+            lo[u] = above ? mid + 1 : lo[u];
+            hi[u] = below ? mid : hi[u];
         }
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        if (!(level(lo[u]) == v[u])) { atomicOr(&flags[FLAG_ERROR], ERRBIT_X_NOT_IN_D); lo[u] = 0; }
-        tile[ty + 8 * u][tx] = lo[u];
+        const int e = threadIdx.x + 256 * u;
+        if (!((in_lds ? sh_d[lo[u]] : D[lo[u]]) == v[u])) { atomicOr(&flags[FLAG_ERROR], ERRBIT_X_NOT_IN_D); lo[u] = 0; }
+        tile[(e >> wsh) * pitch + (e & (wide - 1))] = lo[u];
     }
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int64_t j = j0 + ty + 8 * u, q = q0 + tx;
-        if (j < n && q < R) kidx[j * R + q] = tile[tx][ty + 8 * u];
+        const int e = threadIdx.x + 256 * u, tq = e & ((1 << hsh) - 1), tj = e >> hsh;
+        const int64_t j = j0 + tj, q = q0 + tq;
+        if (j < n && q < R) kidx[j * R + q] = tile[tq * pitch + tj];
     }
 }
 
-template <class T>
+template <class T, bool SQUARE>
 __global__ __launch_bounds__(256) void k_index_to_values_batched(const int32_t* __restrict__ kidx, const T* __restrict__ D,
-                                                                 int64_t n, int64_t R, T* __restrict__ x) {
-    __shared__ T tile[32][33];
-    const int64_t j0 = blockIdx.x * 32ll, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) * 32;
+                                                                 int64_t n, int64_t R, int32_t log_wide, T* __restrict__ x) {
+    __shared__ T tile[XV_LDS];
+    const int wsh = SQUARE ? 5 : log_wide, hsh = 10 - wsh, wide = 1 << wsh, pitch = wide | 1;
+    const int64_t j0 = (int64_t)blockIdx.x << wsh, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) << hsh;
     if (q0 >= R) return;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     int32_t k[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int64_t j = j0 + ty + 8 * u, q = q0 + tx;
+        const int e = threadIdx.x + 256 * u;
+        const int64_t j = j0 + (e >> hsh), q = q0 + (e & ((1 << hsh) - 1));
         k[u] = kidx[(j < n ? j : n - 1) * R + (q < R ? q : R - 1)];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) tile[ty + 8 * u][tx] = D[k[u]];
+    for (int u = 0; u < 4; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        tile[(e & ((1 << hsh) - 1)) * pitch + (e >> hsh)] = D[k[u]];
+    }
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int64_t q = q0 + ty + 8 * u, j = j0 + tx;
-        if (j < n && q < R) x[q * n + j] = tile[tx][ty + 8 * u];
+        const int e = threadIdx.x + 256 * u;
+        const int64_t q = q0 + (e >> wsh), j = j0 + (e & (wide - 1));
+        if (j < n && q < R) x[q * n + j] = tile[(e >> wsh) * pitch + (e & (wide - 1))];
     }
 }
 
+static int32_t values_wsh(int64_t n, int64_t R) {
+    int32_t a = 0, b = 0;                                   // whole powers of two from n and R on, 32 at most
+    while (a < 5 && 1ll << a < n) ++a;
+    while (b < 5 && 1ll << b < R) ++b;
+    return a < 5 ? a : 10 - b;
+}
 static dim3 values_grid(int64_t n, int64_t R) {
-    const int64_t gq = ceil_div(R, 32), gy = gq < 32768 ? gq : 32768;
-    return dim3((unsigned)ceil_div(n, 32), (unsigned)gy, (unsigned)ceil_div(gq, gy));
+    const int32_t wsh = values_wsh(n, R);
+    const int64_t gq = ceil_div(R, XV_TILE >> wsh), gy = gq < 32768 ? gq : 32768;
+    return dim3((unsigned)ceil_div(n, 1ll << wsh), (unsigned)gy, (unsigned)ceil_div(gq, gy));
 }
 
 // ---- residual -------------------------------------------------------------------------------
@@ -564,16 +585,18 @@ static dmmv_status apply_t(Ctx* c, bool t_from_score, int32_t iters, dmmv_move* 
 
 template <class T>
 static dmmv_status set_x_t(Ctx* c, const void* x) {
-    hipLaunchKernelGGL(k_values_to_index_batched<T>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
-                       (const T*)x, (const T*)c->D_dev, c->p.nd, c->p.n, c->p.R, c->kidx, c->flags);
+    const int32_t wsh = values_wsh(c->p.n, c->p.R);
+    hipLaunchKernelGGL((wsh == 5 ? k_values_to_index_batched<T, true> : k_values_to_index_batched<T, false>), values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
+                       (const T*)x, (const T*)c->D_dev, c->p.nd, c->p.n, c->p.R, wsh, c->kidx, c->flags);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
 }
 
 template <class T>
-static dmmv_status get_x_t(Ctx* c, void* x) {
-    hipLaunchKernelGGL(k_index_to_values_batched<T>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
-                       (const int32_t*)c->kidx, (const T*)c->D_dev, c->p.n, c->p.R, (T*)x);
+static dmmv_status get_x_t(Ctx* c, const int32_t* kidx, void* x) {
+    const int32_t wsh = values_wsh(c->p.n, c->p.R);
+    hipLaunchKernelGGL((wsh == 5 ? k_index_to_values_batched<T, true> : k_index_to_values_batched<T, false>), values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
+                       kidx, (const T*)c->D_dev, c->p.n, c->p.R, wsh, (T*)x);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
 }
@@ -722,18 +745,10 @@ dmmv_status batched_apply(Ctx* c, bool tf, int32_t iters, dmmv_move* trace, void
 }
 dmmv_status batched_set_x(Ctx* c, const void* x) { return c->p.dtype == DMMV_F64 ? set_x_t<double>(c, x) : set_x_t<float>(c, x); }
 dmmv_status batched_get_x_from(Ctx* c, const int32_t* kidx, void* x) {
-    const int64_t tot = c->p.n * c->p.R;
-    if (tot == 0) return DMMV_OK;
-    if (c->p.dtype == DMMV_F64)
-        hipLaunchKernelGGL(k_index_to_values_batched<double>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
-                           kidx, (const double*)c->D_dev, c->p.n, c->p.R, (double*)x);
-    else
-        hipLaunchKernelGGL(k_index_to_values_batched<float>, values_grid(c->p.n, c->p.R), dim3(256), 0, c->stream,
-                           kidx, (const float*)c->D_dev, c->p.n, c->p.R, (float*)x);
-    DMMV_LAUNCH_CHECK();
-    return DMMV_OK;
+    if (c->p.n * c->p.R == 0) return DMMV_OK;
+    return c->p.dtype == DMMV_F64 ? get_x_t<double>(c, kidx, x) : get_x_t<float>(c, kidx, x);
 }
-dmmv_status batched_get_x(Ctx* c, void* x) { return c->p.dtype == DMMV_F64 ? get_x_t<double>(c, x) : get_x_t<float>(c, x); }
+dmmv_status batched_get_x(Ctx* c, void* x) { return batched_get_x_from(c, c->kidx, x); }
 dmmv_status batched_set_r(Ctx* c, const void* r) {
     // caller layout [R][m] -> internal [m][R]
     if (c->p.dtype == DMMV_F64) launch_transpose<double>(c->stream, (const double*)r, c->p.R, c->p.m, c->p.m, (double*)c->r, c->p.R);
