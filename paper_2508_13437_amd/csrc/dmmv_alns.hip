@@ -430,7 +430,10 @@ __device__ __forceinline__ bool alns_impact_term_fast(double x, double rate, dou
     return usual && frac > 0x1p-15 && frac < 1.0 - 0x1p-15;
 }
 
-template <class T>
+// NARROW: at most 128 variables, whose one or two wavefronts' worth of columns leave the others rows of their own (with one of four
+// wavefronts busy 500 instances of 4096 x 16 took 188 us, 125 before the queue took its LDS, 98 so).  A form of its own: in the
+// other the divisors would cost scalar registers, and 1 % of the time.
+template <class T, bool NARROW>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_batched(int64_t m, int64_t n, int64_t R,
                                                              const T* __restrict__ Xt,
                                                              const T* __restrict__ scale_q,
@@ -453,8 +456,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
         L.scale[threadIdx.x] = alns_impact_scale((double)st[q].t);
     }
     __syncthreads();
-    const int64_t i_begin = blockIdx.z * chunk_rows;
+    const int beside = NARROW ? (n > 64 ? 2 : 1) : 4;       // wavefronts side by side
+    const int64_t i_begin = (blockIdx.z * (int64_t)(4 / beside) + (NARROW ? w / beside : 0)) * chunk_rows;
     const int64_t i_end = i_begin + chunk_rows < m ? i_begin + chunk_rows : m;
+    if (NARROW && i_begin >= m) return;
     // staging of r and of the limits: lane = (row, instance), two passes of 16 rows
     const int sv = lane & (IM_Q - 1), su = lane / IM_Q;
     const int64_t slot = s0 + sv, slot_c = slot < count ? slot : count - 1;
@@ -502,7 +507,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
         __builtin_amdgcn_wave_barrier();
         waiting = 0;
     };
-    for (int64_t j0 = (blockIdx.y * 4ll + w) * 64; j0 < n; j0 += 256ll * gridDim.y) {   // whole wavefronts; no barrier inside
+    for (int64_t j0 = (blockIdx.y * (int64_t)beside + (NARROW ? w % beside : w)) * 64; j0 < n; j0 += 64ll * beside * gridDim.y) {   // whole wavefronts; no barrier inside
         const int64_t j = j0 + lane;
         const uint32_t lc = (uint32_t)(j < n ? lane : n - 1 - j0);
 #pragma unroll
@@ -784,7 +789,8 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
                            (const int32_t*)c->cmp_orig, (const int32_t*)c->flags);
         // about half of the instances are on the list; the rows are split until some 8 wavefronts per SIMD
         // are there to hide the loads of each other, at least one pass of rows each
-        const int64_t col_groups = ceil_div(c->p.n, 256);
+        const int64_t beside = c->p.n > 128 ? 4 : c->p.n > 64 ? 2 : 1;     // (as in the kernel: the others take rows of their own)
+        const int64_t col_groups = ceil_div(c->p.n, 64 * beside);
         const int64_t waves = ceil_div(c->p.n, 64) * ceil_div(ceil_div(R, 2), IM_Q);
         int64_t chunks = ceil_div(8192, waves > 0 ? waves : 1);
         if (chunks > ceil_div(c->p.m, IM_ROWS)) chunks = ceil_div(c->p.m, IM_ROWS);
@@ -792,7 +798,7 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
         const int64_t chunk_rows = ceil_div(ceil_div(c->p.m, chunks), IM_ROWS) * IM_ROWS;
         chunks = ceil_div(c->p.m, chunk_rows > 0 ? chunk_rows : 1);
         if (chunks > 0)
-            hipLaunchKernelGGL(k_alns_impact_batched<T>, dim3((unsigned)ceil_div(R, IM_Q), (unsigned)(col_groups < 65535 ? col_groups : 65535), (unsigned)chunks),
+            hipLaunchKernelGGL((beside < 4 ? k_alns_impact_batched<T, true> : k_alns_impact_batched<T, false>), dim3((unsigned)ceil_div(R, IM_Q), (unsigned)(col_groups < 65535 ? col_groups : 65535), (unsigned)ceil_div(chunks, 4 / beside)),
                                dim3(256), 0, c->stream, c->p.m, c->p.n, R, (const T*)c->Xt, (const T*)c->scale_dev,
                                (const T*)c->r, (const T*)c->cmp_r, (const InstState<T>*)c->state, prm.alpha, c->alns_weight,
                                chunk_rows, (const int32_t*)c->cmp_orig, (const int32_t*)c->flags);
