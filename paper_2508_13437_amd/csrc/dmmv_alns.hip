@@ -554,19 +554,17 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
                 for (int v = 0; v < IM_Q; ++v) mask[v] = impact_test(mask[v], x[u], L.lim[wl][u][v]);
             }
             if (i0 + IM_ROWS < i_end) fetch(i0 + IM_ROWS);
-            // (the entries of X and r are replaced after the pass: the queue is emptied with its last instance)
-#pragma unroll 1
-            for (int v = 0;; ++v) {
-                if (waiting > IM_CAP - IM_MOST || v == IM_Q) {
-                    evaluate(i0, j0);
-                    if (v == IM_Q) break;
-                }
-                uint32_t mk = j < n ? mask[0] : 0;          // highest bit = first row
+            // most of the terms, in most of the variables: row by row without the queue, every lane its own
+            uint32_t terms = 0;
+            const uint32_t live = (uint32_t)(count - s0 < IM_Q ? count - s0 : IM_Q);      // instances of the four
 #pragma unroll
-                for (int e = 0; e + 1 < IM_Q; ++e) mask[e] = mask[e + 1];
-                unsigned long long many = __ballot(__popc(mk) > IM_FEW);
-                // most of the terms, in most of the variables: row by row without the queue, every lane its own
-                if (__builtin_expect(__popcll(many) >= 32, 0) && __popcll(__ballot(__popc(mk) > IM_DENSE)) >= 32) {
+            for (int v = 0; v < IM_Q; ++v) terms += __popc(mask[v]);
+            if (__builtin_expect(__popcll(__ballot(j < n && terms > live * IM_DENSE)) >= 32, 0)) {
+#pragma unroll 1
+                for (uint32_t v = 0; v < live; ++v) {
+                    const uint32_t mk = mask[0];
+#pragma unroll
+                    for (int e = 0; e + 1 < IM_Q; ++e) mask[e] = mask[e + 1];
                     int64_t nn = n;                         // (made opaque: nothing of this block is kept in registers for it)
                     asm volatile("" : "+s"(nn));
                     const T* __restrict__ at = Xt + i0 * nn + j0;
@@ -578,7 +576,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
                         for (int u = 0; u < 2; ++u) y[u] = dmmv_abs(at[(int64_t)(i0 + row + u < i_end ? row + u : row) * nn + lc]);
 #pragma unroll
                         for (int u = 0; u < 2; ++u) {
-                            const bool on = ((mk << (row + u)) & 0x80000000u) != 0;
+                            const bool on = j < n && ((mk << (row + u)) & 0x80000000u) != 0;
                             uint32_t term;
                             const bool exact = alns_impact_term_fast((double)y[u], L.rate[wl][row + u][v], L.base[wl][row + u][v], L.exp2m, term);
                             const unsigned long long odd = __ballot(on && !exact);      // (rare: by the queue, which knows how)
@@ -591,8 +589,22 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void k_alns_impact_bat
                         }
                     }
                     if (sum) atomicAdd(&L.sum[wl][v][lane], sum);
-                    continue;
+                    if (waiting > IM_CAP - IM_MOST) evaluate(i0, j0);
                 }
+                if (waiting > 0) evaluate(i0, j0);
+                continue;
+            }
+            // (the entries of X and r are replaced after the pass: the queue is emptied with its last instance)
+#pragma unroll 1
+            for (int v = 0;; ++v) {
+                if (waiting > IM_CAP - IM_MOST || v == IM_Q) {
+                    evaluate(i0, j0);
+                    if (v == IM_Q) break;
+                }
+                uint32_t mk = j < n ? mask[0] : 0;          // highest bit = first row
+#pragma unroll
+                for (int e = 0; e + 1 < IM_Q; ++e) mask[e] = mask[e + 1];
+                unsigned long long many = __ballot(__popc(mk) > IM_FEW);
                 // a variable with many terms (an outlier channel): all its rows at once, lane = row
                 while (many) {                              // the same for the whole wavefront
                     const int col = __ffsll(many) - 1;

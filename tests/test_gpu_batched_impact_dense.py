@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("m,n,R,alpha", [(31, 63, 3, 0.0), (33, 33, 5, 0.001), (97, 64, 6, 0.01), (130, 129, 9, 0.03), (64, 31, 4, 0.0),
-                                         (35, 200, 17, 0.1), (300, 20, 7, 0.02), (161, 100, 6, 0.3), (1000, 128, 3, 0.1)])
+                                         (35, 200, 17, 0.1), (300, 20, 7, 0.02), (161, 100, 6, 0.3), (1000, 128, 3, 0.1), (70, 150, 1, 0.0),
+                                         (70, 150, 2, 0.0)])
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_batched_impact_weights_of_most_terms(m, n, R, alpha, dtype):
     inst = random_batched(8500 + m, m, n, R, 6, dtype=dtype)
