@@ -47,7 +47,7 @@ template <class T, bool SQUARE>                             // (SQUARE: 32 x 32,
 __global__ __launch_bounds__(256) void k_values_to_index_batched(const T* __restrict__ x, const T* __restrict__ D,
                                                                  int32_t nd, int64_t n, int64_t R, int32_t log_wide,
                                                                  int32_t* __restrict__ kidx, int32_t* flags) {
-    __shared__ int32_t tile[XV_LDS];
+    __shared__ int32_t tile[SQUARE ? 32 * 33 : XV_LDS];
     __shared__ T sh_d[XV_LEVELS];
     const int wsh = SQUARE ? 5 : log_wide, hsh = 10 - wsh, wide = 1 << wsh, pitch = wide | 1;
     const int64_t j0 = (int64_t)blockIdx.x << wsh, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) << hsh;
@@ -62,18 +62,15 @@ __global__ __launch_bounds__(256) void k_values_to_index_batched(const T* __rest
     }
     for (int32_t k = threadIdx.x; in_lds && k < nd; k += 256) sh_d[k] = D[k];
     __syncthreads();
-    int32_t lo[4] = {0, 0, 0, 0}, hi[4] = {nd - 1, nd - 1, nd - 1, nd - 1};
-    for (int32_t span = nd - 1; span > 0; span >>= 1) {     // (as many steps as the widest interval takes)
+    int32_t lo[4] = {0, 0, 0, 0};                           // a value of D is among the `len` levels from here on
+    for (int32_t len = nd; len > 1;) {
+        const int32_t half = len >> 1;
         T d[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) d[u] = in_lds ? sh_d[(lo[u] + hi[u]) >> 1] : D[(lo[u] + hi[u]) >> 1];
+        for (int u = 0; u < 4; ++u) d[u] = in_lds ? sh_d[lo[u] + half - 1] : D[lo[u] + half - 1];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int32_t mid = (lo[u] + hi[u]) >> 1;
-            const bool above = lo[u] < hi[u] && d[u] < v[u], below = lo[u] < hi[u] && !(d[u] < v[u]);
-            lo[u] = above ? mid + 1 : lo[u];
-            hi[u] = below ? mid : hi[u];
-        }
+        for (int u = 0; u < 4; ++u) lo[u] += d[u] < v[u] ? half : 0;
+        len -= half;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -93,7 +90,7 @@ __global__ __launch_bounds__(256) void k_values_to_index_batched(const T* __rest
 template <class T, bool SQUARE>
 __global__ __launch_bounds__(256) void k_index_to_values_batched(const int32_t* __restrict__ kidx, const T* __restrict__ D,
                                                                  int64_t n, int64_t R, int32_t log_wide, T* __restrict__ x) {
-    __shared__ T tile[XV_LDS];
+    __shared__ T tile[SQUARE ? 32 * 33 : XV_LDS];
     const int wsh = SQUARE ? 5 : log_wide, hsh = 10 - wsh, wide = 1 << wsh, pitch = wide | 1;
     const int64_t j0 = (int64_t)blockIdx.x << wsh, q0 = (blockIdx.y + blockIdx.z * (int64_t)gridDim.y) << hsh;
     if (q0 >= R) return;
