@@ -29,6 +29,8 @@
 // The instance's r (m values) and x (n level indices) live in LDS for the whole
 // launch, so a launch can run any number of iterations without touching the other instances;
 // an instance stops by itself at a local optimum.
+#include <type_traits>
+
 #include "dmmv_common.h"
 
 namespace dmmv {
@@ -93,9 +95,11 @@ __device__ __forceinline__ double bp_entry(const __amdgpu_buffer_rsrc_t& rs, uin
 // is none, and the registers it takes cost a wavefront per SIMD: 60 000 instances of 8 x 8, 30 moves, 1193 us with it
 // and 1043 without (fp64 1927 and 1527).
 // The wavefronts per SIMD asked for are what the kernel had before it kept a step table: one to nine registers more had cost one of
-// them (60 000 instances of 8 x 8 in fp64 1525 us, then 1558, 1237 with it back; 2000 of 64 x 64 1854, 2250, 1971).
-template <class T, class KI, bool AHEAD>
-__global__ __launch_bounds__(BP_BLOCK, (sizeof(T) == 4 ? 5 : 3) + (AHEAD ? 0 : 1)) void k_descent_batched_pruned(
+// them (60 000 instances of 8 x 8 in fp64 1525 us, then 1558, 1237 with it back; 2000 of 64 x 64 1854, 2250, 1971).  Not so in fp32
+// with AHEAD, where the fifth wavefront is worth less than the register it spills (4096 of 2048 x 4096: 0.5 %).
+// FEW: an instance has fewer rows than the workgroup threads.
+template <class T, class KI, bool AHEAD, bool FEW>
+__global__ __launch_bounds__(BP_BLOCK, sizeof(T) == 4 ? (AHEAD ? 1 : 6) : (AHEAD ? 3 : 4)) void k_descent_batched_pruned(
     int64_t m, int64_t n, int32_t nd, int64_t R, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Xt, const T* __restrict__ D, const T* __restrict__ scale,
     T* __restrict__ r, int32_t* __restrict__ kidx, InstState<T>* __restrict__ st, int32_t radius,
@@ -158,10 +162,10 @@ __global__ __launch_bounds__(BP_BLOCK, (sizeof(T) == 4 ? 5 : 3) + (AHEAD ? 0 : 1
     bool dirty = false;
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void*)Xt, 0, (int)(uint32_t)(m * n * (int64_t)sizeof(T)), 0x00020000);
     const int32_t n32 = (int32_t)n, m32 = (int32_t)m;
-    // A lane's rows: every 256th.  Fewer than 256 are split into a quarter for each wavefront, or the first ones would hold them
+    // A lane's rows: every 256th.  FEW of them are split into a quarter for each wavefront, or the first ones would hold them
     // all and the others propose no screening rows: 2000 instances of 64 x 64, 16 levels, 1542 us with four rows, 168 with sixteen.
     const int32_t quarter = (m32 + BP_WAVES - 1) / BP_WAVES;
-    const int32_t first_row = m32 >= BP_BLOCK ? tid : lane < quarter ? w * quarter + lane : m32;
+    const int32_t first_row = !FEW ? tid : lane < quarter ? w * quarter + lane : m32;
     __syncthreads();
 
     for (int32_t step = 0; step < steps; ++step) {
@@ -457,9 +461,13 @@ dmmv_status descent_t(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, vo
     };
     // (512 threads per instance, which then screen 32 rows: 26.8 ms against 14.0 on 4096 instances of 2048 x 4096 and 8.0 against
     // 5.3 on 1024, but 2.6 against 3.9 on 100 and 2.3 against 3.6 on 20; not taken.  1024 threads: 237 and 66 ms, 16 on 100)
-    const bool ahead = n > BP_BLOCK;
-    if (c->p.nd > BP_DCAP) return ahead ? launch(k_descent_batched_pruned<T, uint16_t, true>) : launch(k_descent_batched_pruned<T, uint16_t, false>);
-    return ahead ? launch(k_descent_batched_pruned<T, uint8_t, true>) : launch(k_descent_batched_pruned<T, uint8_t, false>);
+    auto with = [&](auto ki, auto ahead) -> dmmv_status {
+        typedef decltype(ki) KI;
+        constexpr bool AHEAD = decltype(ahead)::value;
+        return m < BP_BLOCK ? launch(k_descent_batched_pruned<T, KI, AHEAD, true>) : launch(k_descent_batched_pruned<T, KI, AHEAD, false>);
+    };
+    if (c->p.nd > BP_DCAP) return n > BP_BLOCK ? with(uint16_t(), std::true_type()) : with(uint16_t(), std::false_type());
+    return n > BP_BLOCK ? with(uint8_t(), std::true_type()) : with(uint8_t(), std::false_type());
 }
 
 }  // namespace
