@@ -38,7 +38,7 @@ static void launch_transpose(hipStream_t s, const T* in, int64_t rows, int64_t c
 }
 
 // x values [R][n] <-> kidx [n][R], 1024 at a time through LDS so that both are read and written along their rows (an
-// element per thread in the order of one of them took 99 and 57 us for 4096 x 4096 and 19 and 14 for 500 x 4096; now 39 and
+// element per thread in the order of one of them took 99 and 57 us for 4096 x 4096 and 19 and 14 for 500 x 4096; now 37 and
 // 27, 9 and 6).  A tile is 2^wsh variables x the instances that make it 1024: 32 x 32, or as narrow as the batch is
 // (100 000 instances of one variable left 31 of 32 lanes idle with 32 x 32: a dmmv_set_x 28 us in fp64, now 24, of which 22 are its wait for the host).
 // Values are looked up in a copy of D in LDS where it fits, four a thread at a time, so that their reads are in flight together.

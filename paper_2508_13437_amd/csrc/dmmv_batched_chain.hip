@@ -18,8 +18,8 @@
 //
 // G_jq = acc with acc = fma(X_ij, r_iq, acc) for i ascending is the same product with the rows of X in the place
 // of its columns and r in that of V: the same loop, another end.  (A kernel of its own with 128 x 64 per wavefront only took
-// 0.78 ms on 4096 x 4096 with 1376 instances, whose 176 workgroups left a third of the chip idle; with the tile of
-// the rule below 0.43.)
+// 0.64 ms on 4096 x 4096 with 1376 instances, whose 176 workgroups left a third of the chip idle, and 0.59 on 2048 x 4096
+// with 4096; with the tile and the workgroups a compute unit of the rule below 0.38 and 0.54.)
 #include <type_traits>
 
 #include "dmmv_common.h"

@@ -105,7 +105,7 @@ __device__ __forceinline__ T l2_change(T delta, T csq, T g) {
 // go through LDS, read along the instances ([n][R]) and used along the table's rows, whose width * nd values of an instance are
 // contiguous.  The host sizes the tile by its values (table_t).
 // (One thread per variable and instance, its nd values written by itself: 242 us for 1376 tables of 4096 x 8, a
-// wavefront's stores 64 tables apart; now 49.)
+// wavefront's stores 64 tables apart; now 47.)
 constexpr int LTB_Q = 32, LTB_AREA = 64 * (LTB_Q + 1), LTB_J = 256, LTB_EACH = 8, LTB_D = 256;
 static constexpr int ltb_pitch(int32_t qsh) { return (1 << qsh) + (qsh > 0); }
 static constexpr int ltb_most(int32_t qsh) {                // variables: what the tile, a thread's registers and sh_c hold

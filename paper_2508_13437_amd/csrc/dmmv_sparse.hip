@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(RP_BLOCK) void k_alns_repair_gathered(
 // maximum over all of r, four rows an access, and put the new ones in: one workgroup issues one wavefront instruction per
 // clock at best, and this is a third of the instructions that maxima of chunks need (135 us for 82 picks of 8192 rows).
 // 8192 rows, 82 picks of some 190 entries: 30 us where the choices are random, 43 where they are greedy, the reservoir's
-// 9 us included, against 87 us on the average and two reservoirs of 18 us (outer iteration of that tomography 275 against 168 us,
+// 9 us included, against 87 us on the average and two reservoirs of 18 us (outer iteration of that tomography 168 against 275 us,
 // the faster local search included).
 constexpr int64_t RL_R_BYTES = 112 * 1024;   // largest r
 constexpr int RL_PICKS = 256;
