@@ -305,8 +305,9 @@ __global__ __launch_bounds__(SWE_BLOCK) void k_swap_eval(
 //     20 of them                               9.0 / 1.28     0.19 / 0.91      2048 x 8192, 2 levels             1.98 / 0.54     0.31 / 0.26
 //     64 of 4096 x 4096, 8 levels              29.1 / 2.52    0.33 / 1.51      100 000 x 512, 8 levels           11.9 / 0.122    0.69 / 0.068
 //     200 of 700 x 1000, 8 levels              2.12 / 0.90    0.20 / 0.49      256 x 64, 16 levels               0.070 / 0.041   0.040 / 0.037
-// Slower at a local optimum, in fp64: one of 2048 x 512, 2 levels, 0.054 and 0.065; a batch of four 2048 x 8192, 1.83 and 2.38
-// (two filter rows fit LDS) - with 1.92 and 0.5 at a rounded start.
+// Slower at a local optimum are most fp64 instances, whose tests cost twice and whose keys are 16 bytes (all pairs, this one; the same at a
+// rounded start): one of 2048 x 8192, 16 levels, 0.50 and 0.79 (1.42, 0.35), four 1.83 and 2.38 (1.92, 0.45); 16 000 x 300, 8 levels,
+// 0.060 and 0.090 (2.00, 0.16); 700 x 1000, 8 levels, 0.066 and 0.092 (0.40, 0.079); 2048 x 512, 2 levels, 0.054 and 0.065 (0.61, 0.067).
 template <class T> struct SwapKey;
 template <> struct SwapKey<float> {                        // level 8 bits | entry, as ordered bits, 32 | variable 16
     uint64_t k;
