@@ -270,7 +270,8 @@ dmmv_status dmmv_solve(dmmv_handle h, const void* x0, int32_t iters, void* x_out
  * runs on holds its own copy until the process ends); the handle lives on the stack.  Arguments as
  * for dmmv_create (problem, options, hip_stream) and dmmv_solve (the rest); x0 must not be NULL.
  * The device of hip_stream must be the current device.  Fails with DMMV_ERR_WORKSPACE, before any
- * GPU work, when dmmv_workspace_bytes(problem, options) exceeds DMMV_STATIC_SCRATCH_BYTES.
+ * GPU work, when dmmv_workspace_bytes(problem, options) exceeds DMMV_STATIC_SCRATCH_BYTES (with options.alns = 0;
+ * the tables of the outer loop that options.alns adds for a batch are not all counted: it is not run here).
  * Every call on a GPU uses that GPU's one array, so calls that overlap in time on one GPU race
  * (also from different streams or threads); what a call needs cleared it clears itself.  Waits for
  * the stream before returning. */

@@ -93,13 +93,14 @@ __global__ void k_alns_begin(AlnsState* S, int64_t R, uint64_t seed, int32_t it)
 // consecutive weights in registers, the wavefronts scan the threads' totals, and the total of a
 // tile of 1024 * SC_E weights is carried into the next.
 constexpr int SC_E = 8;
-__global__ __launch_bounds__(1024) void k_alns_scan(int64_t n, const uint64_t* __restrict__ weight_all,
+// clear: the weights are set to 0 for the next iteration, whose terms are added to them.
+__global__ __launch_bounds__(1024) void k_alns_scan(int64_t n, uint64_t* __restrict__ weight_all,
                                                     uint64_t* __restrict__ prefix_all, const AlnsState* S,
-                                                    int32_t raw_shift) {
+                                                    int32_t raw_shift, int32_t clear) {
     __shared__ uint64_t sh_w[16];
     const int64_t q = blockIdx.x;
     if (S[q].d_op != 1) return;
-    const uint64_t* __restrict__ weight = weight_all + q * n;
+    uint64_t* __restrict__ weight = weight_all + q * n;
     uint64_t* __restrict__ prefix = prefix_all + q * n;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint64_t carry = 0;                                     // the same in every thread
@@ -112,6 +113,11 @@ __global__ __launch_bounds__(1024) void k_alns_scan(int64_t n, const uint64_t* _
         for (int u = 0; u < SC_E; ++u) {
             if (raw_shift >= 0) v[u] = 1 + (v[u] >> raw_shift);
             v[u] = j0 + u < n ? v[u] : 0;
+        }
+        if (clear) {
+#pragma unroll
+            for (int u = 0; u < SC_E; ++u)
+                if (j0 + u < n) weight[j0 + u] = 0;
         }
 #pragma unroll
         for (int u = 1; u < SC_E; ++u) v[u] += v[u - 1];
@@ -251,10 +257,10 @@ __global__ void k_alns_copy(int64_t m, int64_t n, int64_t R, const AlnsState* S,
 
 template <class T>
 __global__ void k_alns_snapshot(int64_t m, int64_t n, int64_t R, const int32_t* kidx, int32_t* kidx_cur,
-                                int32_t* kidx_best, const T* r, T* r_cur, unsigned long long* first) {
+                                int32_t* kidx_best, const T* r, T* r_cur, unsigned long long* first, uint64_t* weight) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    for (int64_t e = t0; e < n * R; e += stride) { kidx_cur[e] = kidx[e]; kidx_best[e] = kidx[e]; first[e] = 0; }
+    for (int64_t e = t0; e < n * R; e += stride) { kidx_cur[e] = kidx[e]; kidx_best[e] = kidx[e]; first[e] = 0; weight[e] = 0; }
     for (int64_t e = t0; e < m * R; e += stride) r_cur[e] = r[e];
 }
 
@@ -326,6 +332,9 @@ __global__ __launch_bounds__(1024) void k_alns_worst_list(int64_t R, const AlnsS
 // i.e. when |x| is at least a limit that depends on the row and the instance alone.  The limits are
 // written first (k_alns_impact_limits, lowered by 1 % so that the roundings on both sides are covered: a term the
 // test drops is 0, the reverse need not hold), then a term costs one comparison.
+//
+// fp32 batches of 129 to 8192 variables take k_alns_impact_lists instead (dmmv_alns_impact.hip), which is 3.9 times as fast
+// on the layer named below; fp64, fewer and more variables are left to this one.
 //
 // k_alns_impact_batched: lane = variable, so a row of X is one coalesced load that IM_Q instances share
 // (with lane = instance and X through the scalar unit a small batch left most of the chip idle:
@@ -402,32 +411,6 @@ __global__ __launch_bounds__(256) void k_alns_impact_limits(int64_t m, int64_t n
         uint64_t* __restrict__ out = weight + (int64_t)list[s] * n;
         for (int64_t j = blockIdx.y * 64ll + lane; j < n; j += 64ll * gridDim.y) out[j] = 0;
     }
-}
-
-// The fixed-point term by a shorter route: y16 = 16 log2(e) alpha (t - sk) / (sc |x|) with the part of row and instance
-// given (rate) and a reciprocal with one Newton step instead of a division, 2^(-y16 / 16) from 2^(-f/16) and a polynomial
-// of degree 6.  Its relative error stays below 2^-40 (reciprocal 2^-46, rate 2^-50, times y < 20; polynomial 2^-50),
-// the term is below 2^24, so the integer part is that of alns_impact_term unless the
-// fraction is within 2^-15 of an integer; those (and everything out of the ordinary) are left to it: false.
-__device__ __forceinline__ bool alns_impact_term_fast(double x, double rate, double base, const double* exp2m, uint32_t& term) {
-    double rc = __builtin_amdgcn_rcp(x);
-    rc = __builtin_fma(rc, __builtin_fma(-x, rc, 1.0), rc);
-    const double y16 = rate * rc;
-    const bool usual = y16 < 20.0 * 16.0 * 0x1.71547652b82fep+0;      // false for NaN
-    const double kf = __builtin_rint(usual ? y16 : 0.0);
-    const double z = kf - y16;                                        // |z| <= 1/2: powers of (ln 2 / 16) z
-    constexpr double C = 0x1.62e42fefa39efp-5;
-    double p = __builtin_fma(z, C * C * C * C * C * C / 720.0, C * C * C * C * C / 120.0);
-    p = __builtin_fma(p, z, C * C * C * C / 24.0);
-    p = __builtin_fma(p, z, C * C * C / 6.0);
-    p = __builtin_fma(p, z, C * C / 2.0);
-    p = __builtin_fma(p, z, C);
-    p = __builtin_fma(p, z, 1.0);
-    const int k = (int)kf;
-    const double g = __builtin_ldexp(base * (p * exp2m[k & 15]), -(k >> 4));
-    const double whole = __builtin_floor(g), frac = g - whole;
-    term = (uint32_t)whole;
-    return usual && frac > 0x1p-15 && frac < 1.0 - 0x1p-15;
 }
 
 // NARROW: at most 128 variables, whose one or two wavefronts' worth of columns leave the others rows of their own (with one of four
@@ -774,7 +757,7 @@ static dmmv_status start_t(Ctx* c, bool l2_guard) {
                        l2_guard ? (const double*)c->alns_q2 : nullptr);
     hipLaunchKernelGGL(k_alns_snapshot<T>, dim3(1024), dim3(256), 0, c->stream, c->p.m, c->p.n, R,
                        (const int32_t*)c->kidx, c->alns_kidx_cur, c->alns_kidx_best, (const T*)c->r,
-                       (T*)c->alns_r_cur, (unsigned long long*)c->alns_first);
+                       (T*)c->alns_r_cur, (unsigned long long*)c->alns_first, c->alns_weight);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
 }
@@ -788,6 +771,8 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
         hipLaunchKernelGGL(k_alns_impact_dense<T>, dim3((unsigned)c->p.n), dim3(256), 0, c->stream, c->p.m,
                            c->p.n, (const T*)c->p.A_dense, c->p.lda, (const T*)c->r,
                            (const InstState<T>*)c->state, prm.alpha, c->alns_weight, (const AlnsState*)S);
+    } else if (c->kind == KIND_BATCHED && c->alns_lists) {
+        DMMV_TRY(alns_impact_lists(c, prm.alpha));
     } else if (c->kind == KIND_BATCHED) {
         // (the list shares the buffer of the descent's list of running instances, the limits that of its
         // packed residuals: never both at once)
@@ -824,7 +809,7 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
         if (raw_shift < 0) raw_shift = 0;
     }
     hipLaunchKernelGGL(k_alns_scan, dim3((unsigned)R), dim3(1024), 0, c->stream, c->p.n,
-                       (const uint64_t*)c->alns_weight, c->alns_prefix, (const AlnsState*)S, raw_shift);
+                       c->alns_weight, c->alns_prefix, (const AlnsState*)S, raw_shift, c->kind == KIND_BATCHED && c->alns_lists ? 1 : 0);
     hipLaunchKernelGGL(k_alns_sample, dim3((unsigned)R), dim3(R > 1 ? 256 : 1024), 0, c->stream, c->p.n, count,
                        (const uint64_t*)c->alns_prefix, (unsigned long long*)c->alns_first, c->alns_picked,
                        (const AlnsState*)S, prm.seed);

@@ -83,7 +83,7 @@ static void sparse_partitions(const dmmv_problem& p, const dmmv_options& o, int6
     *P_out = p.m > 0 ? ceil_div(p.m, mp) : 1;
 }
 
-size_t workspace_layout(const dmmv_problem& p, const dmmv_options& o, Ctx* c, char* base) {
+size_t workspace_layout(const dmmv_problem& p, const dmmv_options& o, Ctx* c, char* base, bool loops) {
     (void)o;
     Ctx dummy;
     if (!c) c = &dummy;
@@ -206,6 +206,12 @@ size_t workspace_layout(const dmmv_problem& p, const dmmv_options& o, Ctx* c, ch
                 b.take(&at, extra);
                 batched_lists_bytes(p, c->lists_late, &c->lists, at);
             }
+        }
+        // the sorted rows of the impact weights (dmmv_solve_static runs no outer loop and goes without)
+        c->alns_lists = o.alns && loops && alns_impact_lists_applicable(p);
+        if (c->alns_lists) {
+            b.take(&c->alns_row_inv, (size_t)p.m * p.n * sizeof(double));
+            b.take(&c->alns_row_col, (size_t)p.m * p.n * sizeof(uint16_t));
         }
     } else {
         c->n_partials = dense_num_partials(p);
@@ -921,9 +927,9 @@ static dmmv_status resolve_options(const dmmv_problem* problem, const dmmv_optio
 }
 
 // Fill *c for a validated problem and build the internal layouts in `workspace` (large enough,
-// 256-byte aligned).  Waits for the stream.
+// 256-byte aligned).  loops: calls other than dmmv_solve may follow.  Waits for the stream.
 static dmmv_status ctx_setup(dmmv_ctx* c, const dmmv_problem* problem, const dmmv_options& o, void* workspace,
-                             hipStream_t stream) {
+                             hipStream_t stream, bool loops) {
     c->p = *problem;
     c->o = o;
     c->stream = stream;
@@ -932,7 +938,7 @@ static dmmv_status ctx_setup(dmmv_ctx* c, const dmmv_problem* problem, const dmm
     c->kind = sparse ? KIND_CSC : ((problem->R > 1 || problem->scale) ? KIND_BATCHED : KIND_DENSE);
     c->x_set = c->r_valid = false;
     c->cmp_on = false;
-    workspace_layout(*problem, o, c, (char*)workspace);
+    workspace_layout(*problem, o, c, (char*)workspace, loops);
     c->p.D = nullptr;       // host arrays are copied below and not referenced afterwards
     c->p.scale = nullptr;
 
@@ -985,6 +991,7 @@ static dmmv_status ctx_setup(dmmv_ctx* c, const dmmv_problem* problem, const dmm
         }
     }
     if (c->kind == KIND_BATCHED) DMMV_TRY(batched_build(c));
+    if (c->kind == KIND_BATCHED && c->alns_lists) DMMV_TRY(alns_impact_lists_build(c));
     if (c->kind == KIND_DENSE && o.prune) DMMV_TRY(batched_build_xt(c));
     if (o.l2_rule) DMMV_TRY(l2_build(c));
     c->mfma_planes = 1;
@@ -1013,7 +1020,7 @@ const char* dmmv_version(void) { return "libdmmv 0.1 (gfx950)"; }
 size_t dmmv_workspace_bytes(const dmmv_problem* problem, const dmmv_options* options) {
     dmmv_options o{};
     if (resolve_options(problem, options, &o) != DMMV_OK) return 0;
-    return workspace_layout(*problem, o, nullptr, nullptr);
+    return workspace_layout(*problem, o, nullptr, nullptr, true);
 }
 
 dmmv_status dmmv_create(dmmv_handle* out, const dmmv_problem* problem, const dmmv_options* options,
@@ -1022,14 +1029,14 @@ dmmv_status dmmv_create(dmmv_handle* out, const dmmv_problem* problem, const dmm
     *out = nullptr;
     dmmv_options o{};
     DMMV_TRY(resolve_options(problem, options, &o));
-    const size_t need = workspace_layout(*problem, o, nullptr, nullptr);
+    const size_t need = workspace_layout(*problem, o, nullptr, nullptr, true);
     if (!workspace) return fail(DMMV_ERR_WORKSPACE, "workspace is NULL (%zu bytes needed)", need);
     if (((uintptr_t)workspace & 255) != 0) return fail(DMMV_ERR_WORKSPACE, "workspace must be 256-byte aligned");
     if (workspace_bytes < need) return fail(DMMV_ERR_WORKSPACE, "workspace too small: %zu bytes given, %zu needed", workspace_bytes, need);
 
     dmmv_ctx* c = new (std::nothrow) dmmv_ctx();
     if (!c) return fail(DMMV_ERR_STATE, "out of host memory");
-    const dmmv_status st = ctx_setup(c, problem, o, workspace, (hipStream_t)hip_stream);
+    const dmmv_status st = ctx_setup(c, problem, o, workspace, (hipStream_t)hip_stream, true);
     if (st != DMMV_OK) { delete c; return st; }
     *out = c;
     return DMMV_OK;
@@ -1069,14 +1076,14 @@ dmmv_status dmmv_solve_static(const dmmv_problem* problem, const dmmv_options* o
     dmmv_options o{};
     DMMV_TRY(resolve_options(problem, options, &o));
     if (!x0 && problem->n > 0) return fail(DMMV_ERR_NULL, "dmmv_solve_static: x0 is NULL");
-    const size_t need = workspace_layout(*problem, o, nullptr, nullptr);
+    const size_t need = workspace_layout(*problem, o, nullptr, nullptr, false);
     if (need > (size_t)DMMV_STATIC_SCRATCH_BYTES)
         return fail(DMMV_ERR_WORKSPACE, "dmmv_solve_static: this problem needs %zu bytes of workspace, the built-in scratch holds %zu "
                     "(use dmmv_create with a workspace of your own)", need, (size_t)DMMV_STATIC_SCRATCH_BYTES);
     void* ws = nullptr;
     DMMV_TRY(scratch_of_current_device(&ws));
     dmmv_ctx c{};                                          // on the stack: nothing is allocated
-    DMMV_TRY(ctx_setup(&c, problem, o, ws, (hipStream_t)hip_stream));
+    DMMV_TRY(ctx_setup(&c, problem, o, ws, (hipStream_t)hip_stream, false));
     const dmmv_status st = dmmv_solve(&c, x0, iters, x_out, max_violation_out, iters_done, trace, trace_t);
     if (st != DMMV_OK) (void)hipStreamSynchronize(c.stream);   // nothing of this call may still use the scratch
     return st;

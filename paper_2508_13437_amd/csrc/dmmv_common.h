@@ -158,6 +158,9 @@ struct Ctx {
     uint8_t* alns_touched;    // [m] sparse repair: rows of the column being reassigned
     int32_t* alns_g_row;      // sparse repair: entries of the picked columns, global row (-1: padding)
     void* alns_g_val;         //   and value, a fixed stride per picked column (2^20 entries in all)
+    bool alns_lists;          // batch: the impact weights come from the rows' sorted entries
+    double* alns_row_inv;     //   [m][n] 1 / |X_ij| of a row, by bins of descending |X_ij|
+    uint16_t* alns_row_col;   //   their j
     double* alns_q2;          // [R] squared l2 norm of the working residual (l2 guard)
     double* alns_q2_blocks;   // [ceil(m / 256)] single instance: block sums of the above
     // batched descent: virtual batch of the instances still running
@@ -202,7 +205,7 @@ namespace dmmv {
 
 // Lays the device buffers out in a workspace starting at `base` (may be NULL: size only).
 // Returns the bytes needed.  Fills the pointer fields of *c when c != NULL.
-size_t workspace_layout(const dmmv_problem& p, const dmmv_options& o, Ctx* c, char* base);
+size_t workspace_layout(const dmmv_problem& p, const dmmv_options& o, Ctx* c, char* base, bool loops);
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -226,6 +229,9 @@ dmmv_status alns_sumsq(Ctx* c);          // alns_q2 <- squared l2 norm of r, per
 dmmv_status alns_destroy_repair(Ctx* c, const dmmv_alns_params& prm, int32_t it, int32_t count);
 dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, bool last, int32_t* trace, void* trace_t);
 dmmv_status alns_export(Ctx* c, void* t_best_out);
+bool alns_impact_lists_applicable(const dmmv_problem& p);
+dmmv_status alns_impact_lists_build(Ctx* c);            // once per handle
+dmmv_status alns_impact_lists(Ctx* c, double alpha);    // alns_weight, all zero before
 dmmv_status csc_alns_impact(Ctx* c, double alpha);
 dmmv_status csc_alns_repair(Ctx* c, int32_t count, uint64_t seed);
 dmmv_status csc_alns_after_copy(Ctx* c);
