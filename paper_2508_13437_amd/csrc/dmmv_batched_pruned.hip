@@ -4,28 +4,32 @@
 // rows is a lower bound of it, and a move can only win if its lower bound is below the score of
 // the best move known (Corollary 1 turns the same observation into a filter for swaps: a move
 // that does not fix the rows of largest |r| cannot improve).  Per iteration the workgroup
-//   1. picks S = 16 screening rows: of each lane's rows the one of largest |r|, and of these the four largest of each
-//      wavefront (the row of largest |r| overall is always one of them; the wavefronts share the rows evenly);
+//   1. picks S = 16 screening rows: the rows with |r| above a bound are listed while the move before is applied, the 16
+//      largest of them by rank (the row of largest |r| overall is always the first); the bound follows the 22nd
+//      largest, which a single move hardly changes;
 //   2. bounds candidates from below by lb(j, k) = max_{i in S} |fma(delta, X_ij, r_i)| - 16 rows instead
 //      of m - and keeps per variable its best candidate by (lb, k), found by walking outwards from
 //      the current level on the side that lowers the row of largest |r| until lb rises;
 //   3. takes candidates in ascending order of (lb, c), c = j nd + k - each wavefront among the
-//      variables it screened, one per round - scores each one over all m rows (the same fma on
-//      the same operands as the full evaluation, so the same bits), and stops when no wavefront's
-//      next candidate has (lb, c) below the best (score, c) found: every candidate not scored
-//      then has score >= lb >= that best score, and loses the tie on c;
+//      variables it screened - scores each one over all m rows (the same fma on
+//      the same operands as the full evaluation, so the same bits); the wavefronts share the smallest score found so far
+//      and do not wait for each other until their next candidate cannot win against it: every candidate not scored
+//      then has score >= lb, above the best score found, or loses the tie on c;
 //   4. applies the move if its score is below t.
 // The result is the arg-min of the full table restricted to strictly improving moves, i.e. the
 // move the full evaluation + selection would apply - found with a few full scores instead of
 // n (nd - 1); a candidate's score is given up as soon as a row puts it above the best one.
-// On 2048 x 4096 with 16 levels an iteration spends 42 % of its time on step 2 (256 KiB of X each, most of it past the
-// L2), 47 % on step 3 (eleven scores in five and a half rounds of dependent loads) and 6 % on step 1.  The 4096
-// instances of that layer take 10.1 ms to their local optima, the residual's 0.5 ms included; 23.7 with all levels of every
-// variable screened and every score finished, and 14.5 before the first step came from a table and a buffer load, the
-// screening rows from one pass over r, and a lane kept the best of its variables instead of looking through them all in
-// every round.  Tried: the first step on eight rows and the survivors queued for the other eight, 64 at a time (a line of X
-// fetched per row and variable: 11.7 ms); a good move looked for first, to bound the others (12.2); eight more rows for the
-// variables that are left (4.8 rounds, but 10.6).
+// Many instances (4096 of 2048 x 4096, 16 levels, to their local optima: 8.3 ms, 9.9 before) are bound by the rows of X, 256 KiB an
+// iteration, three quarters of which the L2 does not hold (8.9 TB/s into the compute units, 6.8 past the L2; the vector unit 63 % busy, 12 200 instructions an
+// iteration); a fifth workgroup on a compute unit changes nothing.  Few instances are bound by latencies: on 2048 x 4096
+// with eight wavefronts 2000 cycles for step 1, 15 000 to 25 000 for step 2, 3000 a score, 3000 for step 4.
+// What gave most: rows picked exactly instead of four from every wavefront's share (6.4 scores an iteration instead of 9.3); no barrier between
+// scores (there were 5.5 rounds of one score a wavefront); requests ahead that are not under a condition, so that the
+// compiler waits for the block it needs only.
+// Tried and dropped: the first step on eight rows and the survivors queued for the other eight, 64 at a time (a line of X
+// fetched per row and variable); a good move looked for first, to bound the others; eight more rows for the
+// variables that are left; the candidates left after a wavefront's first score shared out by a queue (no gain: few are left, and
+// ties cost more); sixteen wavefronts an instance; bounds and levels in one word, for a fifth workgroup.
 // The instance's r (m values) and x (n level indices) live in LDS for the whole
 // launch, so a launch can run any number of iterations without touching the other instances;
 // an instance stops by itself at a local optimum.
@@ -37,23 +41,43 @@ namespace dmmv {
 
 namespace {
 
-constexpr int BP_BLOCK = 256;
-constexpr int BP_WAVES = BP_BLOCK / 64;
-constexpr int BP_TOPW = 4;                       // screening rows a wavefront contributes
-constexpr int BP_S = BP_WAVES * BP_TOPW;         // screening rows
+constexpr int BP_S = 16;                         // screening rows
+constexpr int BP_LIST = 64;                      // rows gathered to pick them from
+constexpr int BP_WANT = 22;                      //   aimed at
+constexpr int BP_FEWEST = 10;                    //   made do with
 constexpr int64_t BP_MAX_ROWS = 16384;
 constexpr int BP_DCAP = 256;                     // levels kept in LDS
 constexpr size_t BP_LDS_LIMIT = 96 * 1024;       // dynamic LDS a workgroup may ask for
-constexpr int BP_UNROLL = 8;                     // independent global loads a thread issues before it uses them
 
+// the best move a wavefront has found (c < 0: none)
 template <class T>
+struct alignas(16) BpFound {
+    T s;
+    int32_t c;
+};
+
+// a non-negative number as an integer of the same order
+__device__ __forceinline__ uint32_t bp_order(float v) { return __float_as_uint(v); }
+__device__ __forceinline__ unsigned long long bp_order(double v) { return (unsigned long long)__double_as_longlong(v); }
+__device__ __forceinline__ float bp_number(uint32_t v) { return __uint_as_float(v); }
+__device__ __forceinline__ double bp_number(unsigned long long v) { return __longlong_as_double((long long)v); }
+
+// max |f(u)| over the screening rows, three dependent steps
+template <class T, class F>
+__device__ __forceinline__ T bp_max(F f) {
+    auto three = [](T a, T b, T c) { return dmmv_max(dmmv_max(a, b), c); };
+    T p[5];
+#pragma unroll
+    for (int u = 0; u < 5; ++u) p[u] = three(dmmv_abs(f(3 * u)), dmmv_abs(f(3 * u + 1)), dmmv_abs(f(3 * u + 2)));
+    return dmmv_max(three(p[0], p[1], p[2]), three(p[3], p[4], dmmv_abs(f(15))));
+}
+
+template <class T, int W>
 struct BpShared {
-    T D[BP_DCAP];
-    T step[2][BP_DCAP];                          // from a level to the next lower and the next higher one
-    T top_r[BP_S];
-    int32_t top_row[BP_S];
-    T round_s[2][BP_WAVES];                      // score and candidate each wavefront scored in a round
-    int32_t round_c[2][BP_WAVES];                //   (-1: it had none left that could win)
+    BpFound<T> found[W];                         // by each wavefront
+    decltype(bp_order(T())) bound;               // smallest score found so far, t at first
+    int32_t list[BP_LIST];                       // rows of large |r|, the first one of largest
+    int32_t listed;                              // how many there were to put behind it
 };
 
 // A candidate (j, k) as one number, ordered like the flat index: j in the upper bits, k in the lower 8 or 16 (an instance
@@ -90,29 +114,38 @@ __device__ __forceinline__ double bp_entry(const __amdgpu_buffer_rsrc_t& rs, uin
     return __hiloint2double((int)v[1], (int)v[0]);
 }
 
+__device__ __forceinline__ unsigned long long bp_ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
+
+// v of the lane that names this one (0: none does)
+__device__ __forceinline__ float bp_permute(int to, float v) { return __int_as_float(__builtin_amdgcn_ds_permute(to, __float_as_int(v))); }
+__device__ __forceinline__ double bp_permute(int to, double v) {
+    return __hiloint2double(__builtin_amdgcn_ds_permute(to, __double2hiint(v)), __builtin_amdgcn_ds_permute(to, __double2loint(v)));
+}
+
 // KI: type of a level index in LDS (8 bits when nd <= 256, whose values then lie in LDS too).
-// AHEAD: the next block of variables' entries are requested before this one is walked.  With a single block (n <= 256) there
-// is none, and the registers it takes cost a wavefront per SIMD: 60 000 instances of 8 x 8, 30 moves, 1193 us with it
-// and 1043 without (fp64 1927 and 1527).
-// The wavefronts per SIMD asked for are what the kernel had before it kept a step table: one to nine registers more had cost one of
-// them (60 000 instances of 8 x 8 in fp64 1525 us, then 1558, 1237 with it back; 2000 of 64 x 64 1854, 2250, 1971).  Not so in fp32
-// with AHEAD, where the fifth wavefront is worth less than the register it spills (4096 of 2048 x 4096: 0.5 %).
-// FEW: an instance has fewer rows than the workgroup threads.
-template <class T, class KI, bool AHEAD, bool FEW>
-__global__ __launch_bounds__(BP_BLOCK, sizeof(T) == 4 ? (AHEAD ? 1 : 6) : (AHEAD ? 3 : 4)) void k_descent_batched_pruned(
+// W: wavefronts of the workgroup.
+// DEPTH: blocks of variables whose entries are requested ahead of the one that is walked.
+template <class T, class KI, int W, int DEPTH>
+__global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4 : 6) : (DEPTH ? 3 : 4)) void k_descent_batched_pruned(
     int64_t m, int64_t n, int32_t nd, int64_t R, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Xt, const T* __restrict__ D, const T* __restrict__ scale,
     T* __restrict__ r, int32_t* __restrict__ kidx, InstState<T>* __restrict__ st, int32_t radius,
     const uint8_t* __restrict__ var_mask, int32_t steps, int32_t iters,
     dmmv_move* __restrict__ trace, T* __restrict__ trace_t) {
+    constexpr int BP_BLOCK = 64 * W, BP_WAVES = W;
+    constexpr int BP_UNROLL = W <= 4 ? 8 : sizeof(T) == 4 ? 16 : 8;      // independent global loads a thread issues before it uses them
+    constexpr int AP_UNROLL = W <= 4 ? 8 : 4;               //   and where it applies a move
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ BpShared<T> F;
+    __shared__ BpShared<T, W> F;
     T* sh_r = reinterpret_cast<T*>(smem);                  // the instance's residual
-    T* sh_jmin = sh_r + m;                                 // per variable: bound of its next candidate
+    T* sh_D = sh_r + m;                                    // the levels, and the steps from each to the next lower and the next
+    T* sh_down = sh_D + (sizeof(KI) == 1 ? nd : 0);         //   higher one (where they are kept in LDS)
+    T* sh_up = sh_down + (sizeof(KI) == 1 ? nd : 0);
+    T* sh_jmin = sh_up + (sizeof(KI) == 1 ? nd : 0);        // per variable: bound of its next candidate
     KI* sh_k = reinterpret_cast<KI*>(sh_jmin + n);          // current level of every variable
     KI* sh_jarg = sh_k + n;                                // per variable: level of its next candidate
     // one bit per variable: it has a candidate (words of 32, after the others at a multiple of four bytes)
-    uint32_t* sh_has = reinterpret_cast<uint32_t*>(smem + (((m + n) * (int64_t)sizeof(T) + 2 * n * (int64_t)sizeof(KI) + 3) & ~3ll));
+    uint32_t* sh_has = reinterpret_cast<uint32_t*>(smem + ((((m + n + (sizeof(KI) == 1 ? 3 * nd : 0)) * (int64_t)sizeof(T) + 2 * n * (int64_t)sizeof(KI)) + 3) & ~3ll));
     constexpr int KSH = 8 * sizeof(KI);
 
     const int64_t q = blockIdx.x;
@@ -151,74 +184,92 @@ __global__ __launch_bounds__(BP_BLOCK, sizeof(T) == 4 ? (AHEAD ? 1 : 6) : (AHEAD
     const uint8_t* __restrict__ vm = var_mask ? var_mask + q * n : nullptr;
     if (sizeof(KI) == 1)
         for (int32_t k = tid; k < nd; k += BP_BLOCK) {
-            F.D[k] = D[k];
-            F.step[0][k] = step_of(D[k > 0 ? k - 1 : 0], D[k], sc);
-            F.step[1][k] = step_of(D[k < nd - 1 ? k + 1 : k], D[k], sc);
+            sh_D[k] = D[k];
+            sh_down[k] = step_of(D[k > 0 ? k - 1 : 0], D[k], sc);
+            sh_up[k] = step_of(D[k < nd - 1 ? k + 1 : k], D[k], sc);
         }
-    auto level = [&](int32_t k) -> T { return sizeof(KI) == 1 ? F.D[k] : D[k]; };
+    auto level = [&](int32_t k) -> T { return sizeof(KI) == 1 ? sh_D[k] : D[k]; };
     // levels a variable at level kc may take: klo(kc) .. khi(kc) without kc
     auto klo = [&](int32_t kc) -> int32_t { return radius > 0 && kc - radius > 0 ? kc - radius : 0; };
     auto khi = [&](int32_t kc) -> int32_t { return radius > 0 && kc < nd - 1 - radius ? kc + radius : nd - 1; };
     bool dirty = false;
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void*)Xt, 0, (int)(uint32_t)(m * n * (int64_t)sizeof(T)), 0x00020000);
     const int32_t n32 = (int32_t)n, m32 = (int32_t)m;
-    // A lane's rows: every 256th.  FEW of them are split into a quarter for each wavefront, or the first ones would hold them
-    // all and the others propose no screening rows: 2000 instances of 64 x 64, 16 levels, 1542 us with four rows, 168 with sixteen.
-    const int32_t quarter = (m32 + BP_WAVES - 1) / BP_WAVES;
-    const int32_t first_row = !FEW ? tid : lane < quarter ? w * quarter + lane : m32;
-    __syncthreads();
+    // Rows with |r| of at least `bound` are listed for the screening rows to be picked from.
+    const bool all_rows = m32 < BP_LIST;
+    T bound = all_rows ? (T)0 : (T)0.75 * z.t;
+    auto list_row = [&](int32_t i, T v, T largest) {
+        const T a = dmmv_abs(v);
+        if (a >= bound || a == largest) {
+            if (a == largest) F.list[0] = i;                // (any of them)
+            const int32_t at = 1 + atomicAdd(&F.listed, 1);
+            if (at < BP_LIST) F.list[at] = i;
+        }
+    };
+    auto list_all = [&]() {
+        if (tid == 0) { F.listed = 0; F.list[0] = -1; }
+        __syncthreads();
+        for (int32_t i = tid; i < m32; i += BP_BLOCK) list_row(i, sh_r[i], z.t);
+        __syncthreads();
+    };
+    list_all();
 
     for (int32_t step = 0; step < steps; ++step) {
         // ---- 1. screening rows -----------------------------------------------------------
-        {
-            // (the largest of every lane's rows, and of these the largest four: a lane's second row is not looked for,
-            // which leaves the largest of all and rarely misses one of the others)
-            T bv = (T)-1;
-            int32_t bi = -1;
-            for (int32_t i = first_row; i < m32; i += BP_BLOCK) {
-                const T a = dmmv_abs(sh_r[i]);
-                if (a > bv) { bv = a; bi = i; }
-            }
-            for (int round = 0; round < BP_TOPW; ++round) {
-                T s = -bv;                                  // largest |r| = smallest -|r|; ties: lowest row
-                int32_t c = bi;
-                bp_argmin(s, c);
-                if (lane == 0) {                            // the largest of every share first, then the second, ..
-                    F.top_row[round * BP_WAVES + w] = c;
-                    F.top_r[round * BP_WAVES + w] = c >= 0 ? sh_r[c] : (T)0;
-                }
-                if (bi == c) bi = -1;
-            }
-        }
-        __syncthreads();
-        // The row of largest |r| of all goes to entry 0 (row 0 belongs to wavefront 0, so there is one whenever m > 0); a
-        // share with fewer rows than BP_TOPW repeats it, which changes no maximum.
-        int32_t um = 0;
-#pragma unroll
-        for (int x = 1; x < BP_WAVES; ++x) if (F.top_row[x] >= 0 && dmmv_abs(F.top_r[x]) > dmmv_abs(F.top_r[um])) um = x;
-        const int32_t row0 = F.top_row[um], row_x = F.top_row[tid & (BP_S - 1)];
-        const T r0 = F.top_r[um], r_x = F.top_r[tid & (BP_S - 1)];
-        const int32_t row_0 = F.top_row[0];
-        const T r_0 = F.top_r[0];
-        __syncthreads();
-        if (tid < BP_S) {
-            const bool first = tid == 0, swapped = tid == um && um != 0;
-            const int32_t row = first ? row0 : swapped ? row_0 : row_x;
-            F.top_row[tid] = row < 0 ? row0 : row;
-            F.top_r[tid] = first || row < 0 ? r0 : swapped ? r_0 : r_x;
-        }
-        __syncthreads();
+        // The rows of largest |r| among those listed, by their ranks: every wavefront finds them for itself.
+        T tr[BP_S];
+        uint32_t row_off[BP_S];
+        const int32_t row0 = F.list[0];
         if (row0 < 0) {                                    // m == 0: every score is 0 = t, nothing improves
             z.done = 1;
             z.best_s = z.t;
             break;
         }
-        T tr[BP_S];
-        uint32_t row_off[BP_S];
+        for (int pass = 0;; ++pass) {
+            const int32_t listed = F.listed, behind = listed < BP_LIST - 1 ? listed : BP_LIST - 1;
+            const int32_t top = F.list[0], row = lane <= behind ? F.list[lane] : top;
+            const T v = sh_r[row];
+            // Ranks by |r| in 32 bits, the last six replaced by the lane: no two alike, and which of two rows that differ by
+            // less comes first is all the same.  (The row listed first is listed again further on: left out, as the places
+            // past the end.)
+            uint32_t key = (__float_as_uint((float)dmmv_abs(v)) & ~63u) | (uint32_t)(63 - lane);
+            if (lane > behind || (lane > 0 && row == top)) key = 0;
+            if (lane == 0) key = 0xFFFFFFFFu;
+            uint32_t rank = 0;
 #pragma unroll
-        for (int u = 0; u < BP_S; ++u) {
-            tr[u] = F.top_r[u];
-            row_off[u] = (uint32_t)__builtin_amdgcn_readfirstlane(F.top_row[u]) * (uint32_t)n * (uint32_t)sizeof(T);
+            for (int e = 0; e < 32; ++e) rank += (uint32_t)__builtin_amdgcn_readlane((int)key, e) > key ? 1u : 0u;
+            if (behind >= 32) {
+#pragma unroll
+                for (int e = 32; e < 64; ++e) rank += (uint32_t)__builtin_amdgcn_readlane((int)key, e) > key ? 1u : 0u;
+            }
+            // lane `rank` takes the row; lanes that none is for repeat the first, which changes no maximum
+            const int32_t to = key != 0 ? (int32_t)rank * 4 : 63 * 4;
+            const int32_t got = __builtin_amdgcn_ds_permute(to, lane < 63 || key != 0 ? row + 1 : 0);
+            const T r_got = bp_permute(to, v);
+            const int32_t row_by_rank = got > 0 ? got - 1 : top;
+            const T r_by_rank = got > 0 ? r_got : read_lane(v, 0);
+            const uint32_t off_by_rank = (uint32_t)row_by_rank * (uint32_t)n * (uint32_t)sizeof(T);
+#pragma unroll
+            for (int u = 0; u < BP_S; ++u) {
+                row_off[u] = (uint32_t)__builtin_amdgcn_readlane((int)off_by_rank, u);
+                tr[u] = read_lane(r_by_rank, u);
+            }
+            // The bound of the next iteration, whose r differs by one move: the value of rank BP_WANT (of as many of them as the
+            // list holds), or further down where there are fewer.
+            if (all_rows) break;
+            const T used = bound;
+            if (listed >= BP_WANT) {
+                const int32_t guess = BP_WANT * (BP_LIST - 1) / listed, at = listed < BP_LIST ? BP_WANT - 1 : guess > 2 ? guess : 2;
+                bound = dmmv_abs(read_lane(r_by_rank, at));
+            } else {
+                const T from = dmmv_min(bound, z.t), span = dmmv_max(z.t - from, (T)0.02 * z.t);
+                const T by = (T)(BP_WANT - listed) / (T)(listed > 0 ? listed : 1);
+                bound = dmmv_max(listed < BP_FEWEST ? z.t - (T)2 * span : from - (T)0.5 * span * dmmv_min(by, (T)1), (T)0);
+            }
+            // with too few or far too many listed, again (not where they are all alike: the bound stays)
+            if (pass == 6 || (listed >= BP_FEWEST && listed < 2 * BP_LIST) || bound == used) break;
+            __syncthreads();
+            list_all();
         }
 
         // ---- 2. per variable the best candidate by (lb, k) ----------------------------------
@@ -231,66 +282,70 @@ __global__ __launch_bounds__(BP_BLOCK, sizeof(T) == 4 ? (AHEAD ? 1 : 6) : (AHEAD
         // few variables left, and these walk on in place, 64 lanes or one.
         const T r_max = tr[0], t_now = dmmv_abs(r_max);
         for (int64_t i = tid; i < 2 * ((n + 63) / 64); i += BP_BLOCK) sh_has[i] = 0;
+        if (tid == 0) F.bound = bp_order(t_now);
         __syncthreads();
+        if (tid == 0) { F.listed = 0; F.list[0] = -1; }     // (every wavefront has its rows; a barrier follows before the next are listed)
         // the step to the next level up or down, 0 at the ends of D
         auto first_step = [&](int32_t kc, bool up) -> T {
-            if (sizeof(KI) == 1) return F.step[up ? 1 : 0][kc];
+            if (sizeof(KI) == 1) return sh_down[up ? nd + kc : kc];
             const int32_t k = up ? (kc < nd - 1 ? kc + 1 : kc) : (kc > 0 ? kc - 1 : 0);
             return step_of(level(k), level(kc), sc);
         };
-        T nx[BP_S];
-        auto fetch = [&](int32_t j0) {
-            const uint32_t at = (uint32_t)(j0 + lane < n32 ? j0 + lane : n32 - 1) * (uint32_t)sizeof(T);
+        T ahead[DEPTH + 1][BP_S];
+        int32_t ahead_k[DEPTH + 1];
+        const int32_t first = w * 64;
+        auto fetch = [&](int32_t j0, int to) {
+            const int32_t jc = j0 + lane < n32 ? j0 + lane : n32 - 1;
+            const uint32_t at = (uint32_t)jc * (uint32_t)sizeof(T);
+            ahead_k[to] = sh_k[jc];
 #pragma unroll
-            for (int u = 0; u < BP_S; ++u) nx[u] = bp_entry(rs_x, at, row_off[u], (T)0);
+            for (int u = 0; u < BP_S; ++u) ahead[to][u] = bp_entry(rs_x, at, row_off[u], (T)0);
         };
-        const int32_t first = tid - lane;
-        if (AHEAD && first < n32) fetch(first);
-        for (int32_t j0 = first; j0 < n32; j0 += BP_BLOCK) {        // whole wavefronts
+        auto screen = [&](int32_t j0, const T* xs, int32_t kc) {
             const int32_t j = j0 + lane;
-            const int32_t jc = j < n32 ? j : n32 - 1;
-            const int32_t kc = sh_k[jc];
-            if (!AHEAD) fetch(j0);
-            T xs[BP_S];
-#pragma unroll
-            for (int u = 0; u < BP_S; ++u) xs[u] = nx[u];
-            if (AHEAD && j0 + BP_BLOCK < n32) fetch(j0 + BP_BLOCK);
-            auto bound_of = [&](T delta) -> T {
-                T lb = (T)0;
-#pragma unroll
-                for (int u = 0; u < BP_S; ++u) lb = dmmv_max(lb, dmmv_abs(dmmv_fma(delta, xs[u], tr[u])));
-                return lb;
-            };
+            auto bound_of = [&](T delta) -> T { return bp_max<T>([&](int u) { return dmmv_fma(delta, xs[u], tr[u]); }); };
             const bool up = (xs[0] < (T)0) == (r_max > (T)0);
             T delta = first_step(kc, up);
             T lb = bound_of(delta);
             bool walk = !(lb > t_now) && xs[0] != (T)0 && j < n32;      // (an entry 0 in that row lowers nothing)
-            if (__ballot(walk) == 0ull) continue;
-            if (vm) walk = walk && vm[jc] != 0;
-            T prev = t_now, jbest = Limits<T>::inf();
+            if (bp_ballot(walk) == 0ull) return;
+            if (vm) walk = walk && vm[j < n32 ? j : n32 - 1] != 0;
             const int32_t end = up ? khi(kc) : klo(kc), dir = up ? 1 : -1;
             walk = walk && kc != end;
             const T dcur = level(kc);
-            int32_t k = kc, jk = 0;
-            while (__ballot(walk) != 0ull) {
-                if (walk) {
+            T prev = Limits<T>::inf();
+            int32_t k = kc, jk = kc;
+            while (bp_ballot(walk) != 0ull) {
+                if (walk) {                                 // a step on: its bound is no larger than the one before
                     k += dir;
-                    if (lb < jbest || !up) { jbest = lb; jk = k; }     // equal bounds: the lowest level stays
+                    jk = lb < prev || !up ? k : jk;         // equal bounds: the lowest level stays
                     prev = lb;
                 }
                 walk = walk && k != end;
-                if (__ballot(walk) == 0ull) break;
+                if (bp_ballot(walk) == 0ull) break;
                 delta = step_of(level(walk ? k + dir : k), dcur, sc);
                 lb = bound_of(delta);
                 walk = walk && !(lb > prev);
             }
-            const bool found = jbest < Limits<T>::inf();
-            const unsigned long long has = __ballot(found);
+            const bool found = jk != kc;
+            const unsigned long long has = bp_ballot(found);
             if (found) {
-                sh_jmin[j] = jbest;
+                sh_jmin[j] = prev;
                 sh_jarg[j] = (KI)jk;
             }
             if (lane < 2) sh_has[(j0 >> 5) + lane] = (uint32_t)(lane == 0 ? has : has >> 32);
+        };
+        // (requested unasked, the last variable's where there are no more: with the request under a condition the compiler waits
+        // for all that is in flight before the first of them is used)
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) fetch(first + u * BP_BLOCK, u);
+        for (int32_t j0 = first; j0 < n32; j0 += (DEPTH + 1) * BP_BLOCK) {      // whole wavefronts
+#pragma unroll
+            for (int u = 0; u <= DEPTH; ++u) {
+                const int32_t ju = j0 + u * BP_BLOCK;
+                fetch(ju + DEPTH * BP_BLOCK, (u + DEPTH) % (DEPTH + 1));
+                if (u == 0 || ju < n32) screen(ju, ahead[u], ahead_k[u]);
+            }
         }
 
         // ---- 3. candidates in ascending (lb, c) until none can beat the best score ---------
@@ -322,74 +377,82 @@ __global__ __launch_bounds__(BP_BLOCK, sizeof(T) == 4 ? (AHEAD ? 1 : 6) : (AHEAD
         look_through();                                    // (of what this wavefront has written itself)
         T best_s = z.t;                                    // only scores below t count
         int32_t best_c = -1;
-        for (int parity = 0;; parity ^= 1) {
+        auto shared_bound = [&]() -> T { return bp_number(__hip_atomic_load(&F.bound, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)); };
+        for (;;) {
             T s = mine_s;
             int32_t c = mine_c;
             bp_argmin(s, c);
-            const bool live = bp_better(s, c, best_s, best_c);   // the same for the whole wavefront
-            T sfull = (T)0;
-            if (live) {
-                const int32_t j = c >> KSH, k = c & ((1 << KSH) - 1);
-                const int32_t kc = sh_k[j];
-                const T dcur = level(kc);
-                const T delta = step_of(level(k), dcur, sc);
-                // (the entries of its next candidate's bounds go out with the first of the column's)
-                T xs[BP_S];
+            // (a bound equal to the best score another wavefront has found may still win by its number)
+            if (!bp_better(s, c, best_s, best_c) || s > shared_bound()) break;      // the same for the whole wavefront
+            const int32_t j = c >> KSH, k = c & ((1 << KSH) - 1);
+            const T* __restrict__ col = X + ldx * j;
+            // its score over all rows, BP_UNROLL loads in flight; a row past the end repeats row m - 1, which changes
+            // no maximum
+            T a[BP_UNROLL], xs[BP_S];
 #pragma unroll
-                for (int u = 0; u < BP_S; ++u) xs[u] = bp_entry(rs_x, (uint32_t)j * (uint32_t)sizeof(T), row_off[u], (T)0);
-                // its score over all rows, eight loads in flight; a row past the end repeats row m - 1, which changes
-                // no maximum
-                const T* __restrict__ col = X + ldx * j;
-                T acc = (T)0;
-                for (int32_t i0 = lane; i0 < m32; i0 += 64 * BP_UNROLL) {
-                    T a[BP_UNROLL];
+            for (int u = 0; u < BP_UNROLL; ++u) a[u] = col[lane + 64 * u < m32 ? lane + 64 * u : m32 - 1];
+            // (the entries of the variable's next candidate's bounds go out with them)
 #pragma unroll
-                    for (int u = 0; u < BP_UNROLL; ++u) {
-                        const int32_t i = i0 + 64 * u;
-                        a[u] = col[i < m32 ? i : m32 - 1];
-                    }
+            for (int u = 0; u < BP_S; ++u) xs[u] = bp_entry(rs_x, (uint32_t)j * (uint32_t)sizeof(T), row_off[u], (T)0);
+            const int32_t kc = sh_k[j];
+            const T dcur = level(kc);
+            const T delta = step_of(level(k), dcur, sc);
+            T acc = (T)0, least;
+            for (int32_t i0 = lane;;) {
 #pragma unroll
-                    for (int u = 0; u < BP_UNROLL; ++u) {
-                        const int32_t i = i0 + 64 * u;
-                        acc = dmmv_max(acc, dmmv_abs(dmmv_fma(delta, a[u], sh_r[i < m32 ? i : m32 - 1])));
-                    }
-                    if (__ballot(acc > best_s) != 0ull) break;        // it has lost already: the rest cannot matter
+                for (int u = 0; u < BP_UNROLL; ++u) {
+                    const int32_t i = i0 + 64 * u;
+                    acc = dmmv_max(acc, dmmv_abs(dmmv_fma(delta, a[u], sh_r[i < m32 ? i : m32 - 1])));
                 }
-                // this variable's next candidate: the smallest (lb, k) after (s, k); lanes take the levels
-                T bl = Limits<T>::inf();
-                int32_t bk = -1;
-                const int32_t kend = khi(kc);
-                for (int32_t k0 = klo(kc); k0 <= kend; k0 += 64) {
-                    const int32_t kk = k0 + lane;
-                    const bool ok = kk <= kend && kk != kc;
-                    const T dl = ok ? step_of(level(kk), dcur, sc) : (T)0;
-                    T lb = (T)0;
+                i0 += 64 * BP_UNROLL;
+                least = shared_bound();
+                if (i0 - lane >= m32 || bp_ballot(acc > least) != 0ull) break;        // it has lost already: the rest cannot matter
 #pragma unroll
-                    for (int u = 0; u < BP_S; ++u) lb = dmmv_max(lb, dmmv_abs(dmmv_fma(dl, xs[u], tr[u])));
-                    const bool after = ok && (lb > s || (lb == s && kk > k));
-                    if (after && lb < bl) { bl = lb; bk = kk; }       // kk ascends per lane: ties keep the lowest
+                for (int u = 0; u < BP_UNROLL; ++u) {
+                    const int32_t i = i0 + 64 * u;
+                    a[u] = col[i < m32 ? i : m32 - 1];
                 }
-                bp_argmin(bl, bk);
-                if (lane == (int)((((j >> 8) << 2) | ((j >> 4) & 3)) & 63)) {      // the lane that looks after it
-                    if (bk >= 0) { sh_jmin[j] = bl; sh_jarg[j] = (KI)bk; }
-                    else sh_has[j >> 5] &= ~(1u << (j & 31));
-                    look_through();
-                }
-                sfull = wave_max(acc);
             }
-            if (lane == 0) { F.round_s[parity][w] = sfull; F.round_c[parity][w] = live ? c : -1; }
-            __syncthreads();
-            bool any = false;
-#pragma unroll
-            for (int u = 0; u < BP_WAVES; ++u) {
-                const T us = F.round_s[parity][u];
-                const int32_t uc = F.round_c[parity][u];
-                any = any || uc >= 0;
-                if (bp_better(us, uc, best_s, best_c)) { best_s = us; best_c = uc; }
+            const T sfull = wave_max(acc);
+            if (!(sfull > least) && bp_better(sfull, c, best_s, best_c)) { best_s = sfull; best_c = c; }
+            if (sfull < least) {
+                if (lane == 0) atomicMin(&F.bound, bp_order(sfull));
+                least = sfull;
             }
-            if (!any) break;                               // the same for the whole workgroup
-            // the other pair of slots is written next: a wavefront gets there only after every
-            // wavefront has passed this round's barrier, i.e. has read the slots of the round before
+            // what is left of this wavefront's comes behind (s, c)
+            if (s > least) break;
+            // this variable's next candidate: the smallest (lb, k) after (s, k); lanes take the levels
+            T bl = Limits<T>::inf();
+            int32_t bk = -1;
+            const int32_t kend = khi(kc);
+            for (int32_t k0 = klo(kc); k0 <= kend; k0 += 64) {
+                const int32_t kk = k0 + lane;
+                const bool ok = kk <= kend && kk != kc;
+                const T dl = ok ? step_of(level(kk), dcur, sc) : (T)0;
+                const T lb = bp_max<T>([&](int u) { return dmmv_fma(dl, xs[u], tr[u]); });
+                const bool after = ok && (lb > s || (lb == s && kk > k));
+                if (after && lb < bl) { bl = lb; bk = kk; }       // kk ascends per lane: ties keep the lowest
+            }
+            bp_argmin(bl, bk);
+            if (lane == (int)((((j / BP_BLOCK) << 2) | ((j >> 4) & 3)) & 63)) {      // the lane that looks after it
+                if (bk >= 0) { sh_jmin[j] = bl; sh_jarg[j] = (KI)bk; }
+                else sh_has[j >> 5] &= ~(1u << (j & 31));
+                look_through();
+            }
+        }
+        if (lane == 0) {
+            BpFound<T> f;
+            f.s = best_s; f.c = best_c;
+            F.found[w] = f;
+        }
+        __syncthreads();
+        {
+            const BpFound<T> f = F.found[lane & (BP_WAVES - 1)];
+            best_s = f.s;
+            best_c = f.c;
+            bp_argmin(best_s, best_c);                     // -1: nothing below t
+            best_c = best_s < t_now ? best_c : -1;
+            if (best_c < 0) best_s = t_now;
         }
 
         // ---- 4. decide and apply ---------------------------------------------------------
@@ -400,17 +463,32 @@ __global__ __launch_bounds__(BP_BLOCK, sizeof(T) == 4 ? (AHEAD ? 1 : 6) : (AHEAD
             const int32_t k = best_c & ((1 << KSH) - 1);
             const T delta = step_of(level(k), level(sh_k[j]), sc);
             const T* __restrict__ col = X + ldx * j;
-            for (int64_t i0 = tid; i0 < m; i0 += BP_BLOCK * BP_UNROLL) {
-                T a[BP_UNROLL];
+            for (int64_t i0 = tid; i0 < m; i0 += BP_BLOCK * AP_UNROLL) {
+                T a[AP_UNROLL];
+                uint32_t large = 0;                        // which of these rows are listed
 #pragma unroll
-                for (int u = 0; u < BP_UNROLL; ++u) {
+                for (int u = 0; u < AP_UNROLL; ++u) {
                     const int64_t i = i0 + BP_BLOCK * u;
                     a[u] = col[i < m ? i : m - 1];
                 }
 #pragma unroll
-                for (int u = 0; u < BP_UNROLL; ++u) {
+                for (int u = 0; u < AP_UNROLL; ++u) {
                     const int64_t i = i0 + BP_BLOCK * u;
-                    if (i < m) sh_r[i] = dmmv_fma(delta, a[u], sh_r[i]);
+                    if (i < m) {
+                        a[u] = dmmv_fma(delta, a[u], sh_r[i]);
+                        sh_r[i] = a[u];
+                        large |= (dmmv_abs(a[u]) >= bound || dmmv_abs(a[u]) == best_s ? 1u : 0u) << u;
+                    }
+                }
+                if (large) {                               // (the applied move's score is the new max |r|, bit for bit)
+                    int32_t at = 1 + atomicAdd(&F.listed, __popc(large));
+#pragma unroll
+                    for (int u = 0; u < AP_UNROLL; ++u) {
+                        if (!((large >> u) & 1u)) continue;
+                        if (dmmv_abs(a[u]) == best_s) F.list[0] = (int32_t)i0 + BP_BLOCK * u;
+                        if (at < BP_LIST) F.list[at] = (int32_t)i0 + BP_BLOCK * u;
+                        ++at;
+                    }
                 }
             }
             __syncthreads();                               // everyone has read sh_k[j]
@@ -423,10 +501,9 @@ __global__ __launch_bounds__(BP_BLOCK, sizeof(T) == 4 ? (AHEAD ? 1 : 6) : (AHEAD
                     if (trace_t) trace_t[slot] = best_s;
                 }
             }
-            z.t = best_s;                                  // the applied move's score is the new max |r|, bit for bit
+            z.t = best_s;
             z.moves += 1;
-            dirty = true;
-            __syncthreads();
+            dirty = true;                                  // (sh_k is read again behind the next iteration's first barrier)
         }
     }
 
@@ -443,31 +520,35 @@ __global__ __launch_bounds__(BP_BLOCK, sizeof(T) == 4 ? (AHEAD ? 1 : 6) : (AHEAD
 static size_t bp_lds_bytes(int64_t m, int64_t n, int32_t nd, size_t esz) {
     return (size_t)(m + n) * esz + (size_t)n * 2 * (nd <= 256 ? 1 : 2);
 }
-static size_t bp_lds_bits(int64_t n) { return 4 + (size_t)ceil_div(n, 64) * 8; }      // the variables' bits, on top of these
-constexpr size_t BP_LDS_MOST = BP_LDS_LIMIT + 4096;
+// the variables' bits and the levels, on top of these
+static size_t bp_lds_more(int64_t n, int32_t nd, size_t esz) { return 4 + (size_t)ceil_div(n, 64) * 8 + (nd <= BP_DCAP ? 3 * (size_t)nd * esz : 0); }
+constexpr size_t BP_LDS_MOST = BP_LDS_LIMIT + 4096 + 3 * BP_DCAP * 8;
 
 template <class T>
 dmmv_status descent_t(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t) {
     const int64_t m = c->p.m, n = c->p.n, R = c->p.R;
-    const size_t lds = bp_lds_bytes(m, n, c->p.nd, sizeof(T)) + bp_lds_bits(n);
-    auto launch = [&](auto kernel) -> dmmv_status {
+    const size_t lds = bp_lds_bytes(m, n, c->p.nd, sizeof(T)) + bp_lds_more(n, c->p.nd, sizeof(T));
+    auto launch = [&](auto kernel, int waves) -> dmmv_status {
         DMMV_TRY(ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)BP_LDS_MOST));
-        hipLaunchKernelGGL(kernel, dim3((unsigned)R), dim3(BP_BLOCK), lds, c->stream, m, n, c->p.nd, R,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)R), dim3(64 * waves), lds, c->stream, m, n, c->p.nd, R,
                            (const T*)c->p.A_dense, c->p.lda, (const T*)c->Xt, (const T*)c->D_dev,
                            (const T*)c->scale_dev, (T*)c->r, c->kidx, (InstState<T>*)c->state, c->o.radius,
                            c->o.var_mask, steps, iters, trace, (T*)trace_t);
         DMMV_LAUNCH_CHECK();
         return DMMV_OK;
     };
-    // (512 threads per instance, which then screen 32 rows: 26.8 ms against 14.0 on 4096 instances of 2048 x 4096 and 8.0 against
-    // 5.3 on 1024, but 2.6 against 3.9 on 100 and 2.3 against 3.6 on 20; not taken.  1024 threads: 237 and 66 ms, 16 on 100)
-    auto with = [&](auto ki, auto ahead) -> dmmv_status {
+    // Eight wavefronts an instance as long as the compute units hold all instances two at a time (an instance's iteration is a
+    // chain of latencies then), four beyond, and for instances that do not fill more.  us to the local optima, four and eight (the
+    // kernel before, always four): 20 of 2048 x 4096 1949 and 1511 (2618), 250 2254 and 1776 (2850), 500 2307 and 1861 (2913),
+    // 1000 2783 and 3220 (3593); 600 of 1024 x 2048 1276 and 1295 (1587); 20 of 2048 x 768 551 and 479 (652); 30 of 256 x 128 296 and 300
+    // (325); 60 000 of 8 x 8 525 and 1462 (533).
+    const bool eight = R <= 512 && n > 128;
+    auto with = [&](auto ki) -> dmmv_status {
         typedef decltype(ki) KI;
-        constexpr bool AHEAD = decltype(ahead)::value;
-        return m < BP_BLOCK ? launch(k_descent_batched_pruned<T, KI, AHEAD, true>) : launch(k_descent_batched_pruned<T, KI, AHEAD, false>);
+        if (eight) return n > 1024 ? launch(k_descent_batched_pruned<T, KI, 8, 2>, 8) : n > 512 ? launch(k_descent_batched_pruned<T, KI, 8, 1>, 8) : launch(k_descent_batched_pruned<T, KI, 8, 0>, 8);
+        return n > 256 ? launch(k_descent_batched_pruned<T, KI, 4, 1>, 4) : launch(k_descent_batched_pruned<T, KI, 4, 0>, 4);
     };
-    if (c->p.nd > BP_DCAP) return n > BP_BLOCK ? with(uint16_t(), std::true_type()) : with(uint16_t(), std::false_type());
-    return n > BP_BLOCK ? with(uint8_t(), std::true_type()) : with(uint8_t(), std::false_type());
+    return c->p.nd > BP_DCAP ? with(uint16_t()) : with(uint8_t());
 }
 
 }  // namespace
