@@ -13,6 +13,8 @@
 //     sampling weight; exp is a fixed Horner polynomial after a fixed range reduction;
 //   - variables are drawn against integer prefix sums, a repeated draw is skipped.
 // This file holds what is independent of the matrix storage plus the dense kernels.
+#include <type_traits>
+
 #include "dmmv_alns_common.h"
 
 namespace dmmv {
@@ -65,21 +67,8 @@ __global__ __launch_bounds__(1024) void k_alns_sumsq_single(int64_t m, const T* 
     }
 }
 
-template <class T>
-__global__ void k_alns_init(AlnsState* S, const InstState<T>* st, int64_t R, const double* q2) {
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= R) return;
-    S[q].q2_cur = q2 ? q2[q] : 0.0;
-    for (int u = 0; u < 4; ++u) S[q].w[u] = 1.0;
-    S[q].t_cur = (double)st[q].t;
-    S[q].t_best = (double)st[q].t;
-    S[q].it = 0; S[q].d_op = 0; S[q].r_op = 0; S[q].accepted = 0; S[q].new_best = 0;
-}
-
-// operators of this outer iteration by roulette wheel
-__global__ void k_alns_begin(AlnsState* S, int64_t R, uint64_t seed, int32_t it) {
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= R) return;
+// operators of outer iteration `it` by roulette wheel
+__device__ __forceinline__ void alns_begin(AlnsState* S, int64_t q, uint64_t seed, int32_t it) {
     const double ud = alns_unit(alns_rnd(seed, (uint64_t)q, (uint64_t)it, 0, 0));
     const double ur = alns_unit(alns_rnd(seed, (uint64_t)q, (uint64_t)it, 0, 1));
     S[q].it = it;
@@ -87,24 +76,46 @@ __global__ void k_alns_begin(AlnsState* S, int64_t R, uint64_t seed, int32_t it)
     S[q].r_op = (ur * (S[q].w[2] + S[q].w[3]) < S[q].w[2]) ? 0 : 1;
 }
 
-// Inclusive prefix sums of the weights (one workgroup per instance); only for worst-remove.
+template <class T>
+__global__ void k_alns_init(AlnsState* S, const InstState<T>* st, int64_t R, const double* q2, uint64_t seed, int32_t* flags) {
+    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (q == 0) flags[FLAG_TURN] = 0;
+    if (q >= R) return;
+    S[q].q2_cur = q2 ? q2[q] : 0.0;
+    for (int u = 0; u < 4; ++u) S[q].w[u] = 1.0;
+    S[q].t_cur = (double)st[q].t;
+    S[q].t_best = (double)st[q].t;
+    S[q].accepted = 0; S[q].new_best = 0;
+    alns_begin(S, q, seed, 0);
+}
+
+// Destroy: the prefix sums of the weights where the operator is worst-remove, then the draws.  One workgroup of NT threads
+// per instance.
+constexpr int SC_E = 8;
+constexpr int SC_MARKS = 1024;                 // prefix sums kept in LDS, at every `stride` weights
+
+struct DestroyShared {
+    uint64_t mark[SC_MARKS];                   // sum of the weights ahead of weight e * stride
+    uint64_t wave[16];
+    int32_t cnt[16];
+    int32_t have;
+};
+
+__device__ __forceinline__ int64_t alns_mark_stride(int64_t n) { return (n + SC_MARKS * SC_E - 1) / (SC_MARKS * SC_E) * SC_E; }
+
+// Inclusive prefix sums of the weights.
 // raw_shift >= 0: what is stored are the sums of the impact terms, a weight is 1 + (sum >> raw_shift).
 // The weights are integers, so the sums are the same in any order: a thread sums SC_E
 // consecutive weights in registers, the wavefronts scan the threads' totals, and the total of a
-// tile of 1024 * SC_E weights is carried into the next.
-constexpr int SC_E = 8;
+// tile of NT * SC_E weights is carried into the next.
 // clear: the weights are set to 0 for the next iteration, whose terms are added to them.
-__global__ __launch_bounds__(1024) void k_alns_scan(int64_t n, uint64_t* __restrict__ weight_all,
-                                                    uint64_t* __restrict__ prefix_all, const AlnsState* S,
-                                                    int32_t raw_shift, int32_t clear) {
-    __shared__ uint64_t sh_w[16];
-    const int64_t q = blockIdx.x;
-    if (S[q].d_op != 1) return;
-    uint64_t* __restrict__ weight = weight_all + q * n;
-    uint64_t* __restrict__ prefix = prefix_all + q * n;
+template <int NT>
+__device__ __forceinline__ void alns_scan(int64_t n, uint64_t* weight, uint64_t* prefix, int32_t raw_shift, int32_t clear,
+                                          DestroyShared& L) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t stride = alns_mark_stride(n);
     uint64_t carry = 0;                                     // the same in every thread
-    for (int64_t base = 0; base < n; base += 1024 * SC_E) {
+    for (int64_t base = 0; base < n; base += NT * SC_E) {
         const int64_t j0 = base + (int64_t)threadIdx.x * SC_E;
         uint64_t v[SC_E];
 #pragma unroll
@@ -128,96 +139,241 @@ __global__ __launch_bounds__(1024) void k_alns_scan(int64_t n, uint64_t* __restr
             const uint64_t t = (uint64_t)__shfl_up((long long)inc, off, 64);
             if (lane >= off) inc += t;
         }
-        if (lane == 63) sh_w[w] = inc;
+        if (lane == 63) L.wave[w] = inc;
         __syncthreads();
         uint64_t before = 0, all = 0;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const uint64_t x = sh_w[k];
+        for (int k = 0; k < NT / 64; ++k) {
+            const uint64_t x = L.wave[k];
             if (k < w) before += x;
             all += x;
         }
         const uint64_t ex = carry + before + (inc - tot);   // everything ahead of this thread
+        if (j0 < n && j0 % stride == 0) L.mark[j0 / stride] = ex;
 #pragma unroll
         for (int u = 0; u < SC_E; ++u)
             if (j0 + u < n) prefix[j0 + u] = v[u] + ex;
         carry += all;
-        __syncthreads();                                    // sh_w is written again
+        __syncthreads();                                    // L.wave is written again, the sums are read
     }
 }
 
-// Draw `count` distinct variables (one workgroup per instance).  Draw c takes rnd(.., 1, c) mod
+// the first weight whose prefix sum exceeds v (below the total)
+__device__ __forceinline__ int64_t alns_find(int64_t n, const uint64_t* prefix, uint64_t v, const DestroyShared& L) {
+    const int64_t stride = alns_mark_stride(n);
+    int32_t lo = 0, hi = (int32_t)((n - 1) / stride);       // the last mark not above v: the sum ahead of it is not above v
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (L.mark[mid] > v) hi = mid - 1; else lo = mid;
+    }
+    int64_t j = lo * stride, end = j + stride < n ? j + stride : n;
+    while (end - j > SC_E) {
+        const int64_t mid = (j + end) / 2;
+        if (prefix[mid - 1] > v) end = mid; else j = mid;
+    }
+    uint64_t x[SC_E];                                       // (the rest at once)
+#pragma unroll
+    for (int u = 0; u < SC_E; ++u) x[u] = prefix[j + u < n ? j + u : n - 1];
+    int32_t more = 0;
+#pragma unroll
+    for (int u = 0; u < SC_E; ++u) more += j + u < end - 1 && !(x[u] > v) ? 1 : 0;
+    return j + more;
+}
+
+// Draw `count` distinct variables.  Draw c takes rnd(.., 1, c) mod
 // total and the first variable whose prefix sum exceeds it (all weights 1 for the random
-// operator); a variable drawn before is skipped.  blockDim.x draws are made at a time: a draw is
+// operator); a variable drawn before is skipped.  A few variables are drawn by one wavefront, which compares its lanes' draws;
+// otherwise (or if too many of the 64 were alike) NT draws are made at a time: a draw is
 // the first of its variable exactly if it holds the largest stamp (iteration, -c) that
 // variable has seen.
-__global__ __launch_bounds__(1024) void k_alns_sample(int64_t n, int32_t count,
-                                                      const uint64_t* __restrict__ prefix_all,
-                                                      unsigned long long* first_all,
-                                                      int32_t* __restrict__ picked_all, const AlnsState* S,
-                                                      uint64_t seed) {
-    __shared__ int32_t sh_cnt[16];
-    __shared__ int32_t sh_have;
-    const int64_t q = blockIdx.x;
-    const uint64_t* __restrict__ prefix = prefix_all + q * n;
-    unsigned long long* first = first_all + q * n;
-    int32_t* __restrict__ picked = picked_all + q * (int64_t)count;
-    const int32_t it = S[q].it;
-    const bool weighted = S[q].d_op == 1;
+constexpr int SAMPLE_FEW = 32;
+template <int NT>
+__device__ __forceinline__ void alns_sample(int64_t n, int32_t count, const uint64_t* prefix, unsigned long long* first,
+                                            int32_t* picked, int64_t q, int32_t it, bool weighted, uint64_t seed,
+                                            DestroyShared& L) {
     const uint64_t total = weighted ? prefix[n - 1] : (uint64_t)n;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if (threadIdx.x == 0) sh_have = 0;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = NT / 64;
+    auto draw = [&](uint64_t c) -> int64_t {
+        const uint64_t v = alns_rnd(seed, (uint64_t)q, (uint64_t)it, 1, c) % total;
+        return weighted ? alns_find(n, prefix, v, L) : (int64_t)v;
+    };
+    if (threadIdx.x == 0) L.have = 0;
     __syncthreads();
-    for (uint64_t base = 0;; base += blockDim.x) {
-        const int32_t have = sh_have;
+    if (count <= SAMPLE_FEW) {
+        if (w == 0) {
+            const int32_t j = (int32_t)draw((uint64_t)lane);
+            bool is_first = true;
+#pragma unroll
+            for (int e = 0; e < 63; ++e) is_first = is_first && !(e < lane && __builtin_amdgcn_readlane(j, e) == j);
+            const unsigned long long bal = __ballot(is_first);
+            if (__popcll(bal) >= count) {
+                const int32_t pos = __popcll(bal & ((1ull << lane) - 1ull));
+                if (is_first && pos < count) picked[pos] = j;
+                if (lane == 0) L.have = count;
+            }
+        }
+        __syncthreads();
+    }
+    for (uint64_t base = 0;; base += NT) {
+        const int32_t have = L.have;
         if (have >= count) break;
         const uint64_t c = base + threadIdx.x;
-        const uint64_t v = alns_rnd(seed, (uint64_t)q, (uint64_t)it, 1, c) % total;
-        int64_t j;
-        if (weighted) {
-            int64_t lo = 0, hi = n - 1;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) / 2;
-                if (prefix[mid] > v) hi = mid; else lo = mid + 1;
-            }
-            j = lo;
-        } else {
-            j = (int64_t)v;
-        }
+        const int64_t j = draw(c);
         const unsigned long long stamp = ((unsigned long long)(it + 1) << 32) | (0xFFFFFFFFull - (c & 0xFFFFFFFFull));
         atomicMax(&first[j], stamp);
         __syncthreads();
         const bool is_first = __hip_atomic_load(&first[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == stamp;
         const unsigned long long bal = __ballot(is_first);
-        if (lane == 0) sh_cnt[w] = __popcll(bal);
+        if (lane == 0) L.cnt[w] = __popcll(bal);
         __syncthreads();
         int32_t before = 0, all = 0;
-        for (int u = 0; u < nw; ++u) { if (u < w) before += sh_cnt[u]; all += sh_cnt[u]; }
+        for (int u = 0; u < nw; ++u) { if (u < w) before += L.cnt[u]; all += L.cnt[u]; }
         const int32_t pos = have + before + __popcll(bal & ((1ull << lane) - 1ull));
         if (is_first && pos < count) picked[pos] = (int32_t)j;
         __syncthreads();
-        if (threadIdx.x == 0) sh_have = have + all;
+        if (threadIdx.x == 0) L.have = have + all;
         __syncthreads();
     }
 }
 
-// acceptance, best solution, weights, trace (one thread per instance)
+template <int NT>
+__global__ __launch_bounds__(NT) void k_alns_destroy(int64_t n, int32_t count, uint64_t* weight_all, uint64_t* prefix_all,
+                                                     unsigned long long* first_all, int32_t* picked_all, const AlnsState* S,
+                                                     uint64_t seed, int32_t raw_shift, int32_t clear) {
+    __shared__ DestroyShared L;
+    const int64_t q = blockIdx.x;
+    const bool weighted = S[q].d_op == 1;
+    if (weighted) alns_scan<NT>(n, weight_all + q * n, prefix_all + q * n, raw_shift, clear, L);
+    alns_sample<NT>(n, count, prefix_all + q * n, first_all + q * n, picked_all + q * (int64_t)count, q, S[q].it, weighted, seed, L);
+}
+
+// Destroy and repair of a dense instance (single or of a batch) in one launch.  A thread keeps its rows tid, tid + NT, .. of r in
+// registers for all picks; the picks' levels, steps and random bits are looked up for up to RP_PICKS of them at once, the next
+// pick's column is requested before the present one is used, and a greedy choice costs one barrier (two columns' trips to
+// memory, a chain of three loads and four barriers a pick before).  Three launches and a fourth that cleared the exchange of
+// the one-launch descent: 26 us on 8016 x 251 (2 picks), now 15.5; 25 and 18 on 20 instances of 2048 x 768 (4 picks), 135 and 85 on 1024 of
+// 2048 x 4096 (21 picks).  What is left is a chain of latencies.
+constexpr int RP_PICKS = 256;
+template <class T, int NT, int RPT>
+__global__ __launch_bounds__(NT) void k_alns_destroy_repair(int64_t m, int64_t n, int64_t R, int32_t nd, int32_t count,
+                                                            uint64_t* weight_all, uint64_t* prefix_all,
+                                                            unsigned long long* first_all, int32_t* picked_all,
+                                                            const AlnsState* S, uint64_t seed, int32_t raw_shift, int32_t clear,
+                                                            const T* __restrict__ A, int64_t lda, const T* __restrict__ D,
+                                                            const T* __restrict__ scale_q, T* __restrict__ r, int32_t* kidx,
+                                                            InstState<T>* st, uint32_t* zero, int32_t zero_words) {
+    __shared__ DestroyShared L;
+    __shared__ int32_t sh_j[RP_PICKS];
+    __shared__ int32_t sh_k[RP_PICKS];                      // the level to take; with bit 30: this one or the one two below
+    __shared__ T sh_up[RP_PICKS], sh_down[RP_PICKS];        // the step to it, or both
+    __shared__ T sh_max[2][2][NT / 64];
+    const int64_t q = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int32_t it = S[q].it, m32 = (int32_t)m;
+    const bool greedy = S[q].r_op == 1, weighted = S[q].d_op == 1;
+    int32_t* picked = picked_all + q * (int64_t)count;
+    T rr[RPT], a[RPT], next[RPT];
+    if (m32 > 0) {
+#pragma unroll
+        for (int u = 0; u < RPT; ++u) rr[u] = r[(int64_t)(tid + NT * u < m32 ? tid + NT * u : m32 - 1) * R + q];
+    }
+    for (int32_t e = tid; e < zero_words; e += NT) zero[e] = 0;       // (the exchange of the descent that follows)
+    if (weighted) alns_scan<NT>(n, weight_all + q * n, prefix_all + q * n, raw_shift, clear, L);
+    alns_sample<NT>(n, count, prefix_all + q * n, first_all + q * n, picked, q, it, weighted, seed, L);
+    const T sc = scale_q[q];
+    int turn = 0;                                           // a greedy choice's half of sh_max: the other is read until the next barrier
+    for (int32_t p0 = 0; p0 < count; p0 += RP_PICKS) {
+        const int32_t here = count - p0 < RP_PICKS ? count - p0 : RP_PICKS;
+        if (p0 > 0) __syncthreads();                        // the tables are read no more
+        for (int32_t p = tid; p < here; p += NT) {
+            const int64_t j = picked[p0 + p];
+            const int32_t kc = kidx[j * R + q];
+            const bool has_lo = kc > 0, has_hi = kc < nd - 1;
+            bool up = !has_lo;
+            if (has_lo && has_hi && !greedy) up = (alns_rnd(seed, (uint64_t)q, (uint64_t)it, 2, (uint64_t)(p0 + p)) & 1) != 0;
+            const int32_t klo = has_lo ? kc - 1 : kc, khi = has_hi ? kc + 1 : kc;
+            sh_j[p] = (int32_t)j;
+            sh_k[p] = has_lo && has_hi && greedy ? (khi | (1 << 30)) : up ? khi : klo;
+            sh_up[p] = step_of(D[khi], D[kc], sc);
+            sh_down[p] = step_of(D[klo], D[kc], sc);
+            if (!(has_lo && has_hi && greedy) && !up) sh_up[p] = sh_down[p];
+        }
+        __syncthreads();
+        auto fetch = [&](int32_t p) {
+            const T* __restrict__ col = A + lda * sh_j[p < here ? p : here - 1];
+#pragma unroll
+            for (int u = 0; u < RPT; ++u) next[u] = col[tid + NT * u < m32 ? tid + NT * u : m32 - 1];
+        };
+        if (m32 > 0) fetch(0);
+        for (int32_t p = 0; p < here; ++p) {
+#pragma unroll
+            for (int u = 0; u < RPT; ++u) a[u] = next[u];
+            if (m32 > 0) fetch(p + 1);
+            const int32_t kk = sh_k[p];
+            T delta = sh_up[p];
+            int32_t k = kk & ~(1 << 30);
+            if (kk >> 30) {                                 // the same for the whole workgroup
+                const T dlo = sh_down[p];
+                T elo = (T)0, ehi = (T)0;
+                if (m32 > 0) {                              // (rows past the end repeat row m - 1, which changes no maximum)
+#pragma unroll
+                    for (int u = 0; u < RPT; ++u) {
+                        elo = dmmv_max(elo, dmmv_abs(dmmv_fma(dlo, a[u], rr[u])));
+                        ehi = dmmv_max(ehi, dmmv_abs(dmmv_fma(delta, a[u], rr[u])));
+                    }
+                }
+                elo = wave_max(elo);
+                ehi = wave_max(ehi);
+                if (lane == 0) { sh_max[turn][0][w] = elo; sh_max[turn][1][w] = ehi; }
+                __syncthreads();
+                for (int e = 0; e < NT / 64; ++e) {
+                    elo = dmmv_max(elo, sh_max[turn][0][e]);
+                    ehi = dmmv_max(ehi, sh_max[turn][1][e]);
+                }
+                turn ^= 1;
+                if (!(ehi < elo)) { delta = dlo; k -= 2; }
+            }
+#pragma unroll
+            for (int u = 0; u < RPT; ++u) rr[u] = dmmv_fma(delta, a[u], rr[u]);
+            if (tid == 0) kidx[(int64_t)sh_j[p] * R + q] = k;
+        }
+    }
+    T tmax = (T)0;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u)
+        if (tid + NT * u < m32) {
+            tmax = dmmv_max(tmax, dmmv_abs(rr[u]));
+            r[(int64_t)(tid + NT * u) * R + q] = rr[u];
+        }
+    tmax = block_max(tmax, &sh_max[0][0][0]);
+    if (tid == 0) { st[q].t = tmax; st[q].done = 0; st[q].moves = 0; }
+}
+
+// The end of an outer iteration and the start of the next one (unless it was the last).  Every thread takes the verdict
+// for the elements that it copies: accepted: current <- working (and best <- working for a new best); rejected: working
+// <- current.  The last workgroup to have done so (flags[FLAG_TURN] counts them) then updates the state: error, operator weights,
+// trace, the next iteration's operators.  One launch instead of three: 5.5 us instead of 13 on 8016 x 251, 8.3 instead of 14
+// on 20 instances of 2048 x 768, 37 instead of 43 on 1024 of 2048 x 4096.
 template <class T>
-__global__ void k_alns_end(AlnsState* S, InstState<T>* st, int64_t R, int32_t iters, double lambda,
-                           double sigma1, double sigma2, double sigma3, const double* q2, int32_t* trace,
-                           T* trace_t) {
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= R) return;
+__device__ __forceinline__ void alns_verdict(const AlnsState& s, const InstState<T>& z, const double* q2, int64_t q, bool& accepted, bool& best) {
+    const double t = (double)z.t;
+    // q2 != NULL: the l2 norm of the residual must not increase either
+    accepted = t <= s.t_cur && (!q2 || q2[q] <= s.q2_cur);
+    best = accepted && t < s.t_best;
+}
+
+template <class T>
+__device__ __forceinline__ void alns_end(AlnsState* S, InstState<T>* st, int64_t q, int32_t iters, double lambda, double sigma1,
+                                         double sigma2, double sigma3, const double* q2, int32_t* trace, T* trace_t) {
     const double t = (double)st[q].t;
     const int32_t it = S[q].it;
-    // q2 != NULL: the l2 norm of the residual must not increase either
-    const int accepted = t <= S[q].t_cur && (!q2 || q2[q] <= S[q].q2_cur);
-    int new_best = 0;
+    bool accepted, new_best;
+    alns_verdict(S[q], st[q], q2, q, accepted, new_best);
     if (accepted) {
         if (q2) S[q].q2_cur = q2[q];
         double psi = sigma3;
         if (t < S[q].t_cur) psi = sigma2;
-        if (t < S[q].t_best) { psi = sigma1; S[q].t_best = t; new_best = 1; }
+        if (new_best) { psi = sigma1; S[q].t_best = t; }
         S[q].t_cur = t;
         const double keep = 1.0 - lambda;
         S[q].w[S[q].d_op] = keep * S[q].w[S[q].d_op] + lambda * psi;
@@ -231,28 +387,51 @@ __global__ void k_alns_end(AlnsState* S, InstState<T>* st, int64_t R, int32_t it
         trace[slot * 4 + 2] = st[q].moves; trace[slot * 4 + 3] = accepted;
     }
     if (trace_t) { trace_t[slot * 2 + 0] = st[q].t; trace_t[slot * 2 + 1] = (T)S[q].t_best; }
-    if (!accepted) st[q].t = (T)S[q].t_cur;          // the copy kernel restores x and r
+    if (!accepted) st[q].t = (T)S[q].t_cur;          // (x and r have been restored)
 }
 
-// accepted: current <- working (and best <- working for a new best); rejected: working <- current
+// grid: a strip of 256 instances (or 256 elements of the only one) x some of the rows and variables
 template <class T>
-__global__ void k_alns_copy(int64_t m, int64_t n, int64_t R, const AlnsState* S, int32_t* kidx,
-                            int32_t* kidx_cur, int32_t* kidx_best, T* r, T* r_cur) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    for (int64_t e = t0; e < n * R; e += stride) {
-        const AlnsState& s = S[e % R];
-        if (s.accepted) {
-            const int32_t k = kidx[e];
-            kidx_cur[e] = k;
-            if (s.new_best) kidx_best[e] = k;
-        } else {
-            kidx[e] = kidx_cur[e];
-        }
+__global__ __launch_bounds__(256) void k_alns_turn(int64_t m, int64_t n, int64_t R, AlnsState* S, InstState<T>* st, int32_t* kidx,
+                                                   int32_t* kidx_cur, int32_t* kidx_best, T* r, T* r_cur, int32_t iters,
+                                                   double lambda, double sigma1, double sigma2, double sigma3, const double* q2,
+                                                   int32_t* trace, T* trace_t, uint64_t seed, int32_t next, int32_t* flags) {
+    __shared__ bool last;
+    const int64_t at = blockIdx.x * 256ll + threadIdx.x;
+    // an instance of its own for every thread, rows over the workgroups; or one instance, rows over the threads too
+    const int64_t q = R > 1 ? at : 0, e0 = R > 1 ? blockIdx.y : at, step = R > 1 ? gridDim.y : gridDim.x * 256ll;
+    if (q < R) {
+        bool accepted, best;
+        alns_verdict(S[q], st[q], q2, q, accepted, best);
+        // (eight elements in flight in a thread)
+        auto copy = [&](int64_t rows, auto* work, auto* cur, auto* most) {
+            for (int64_t j0 = e0; j0 < rows; j0 += 8 * step) {
+                std::remove_reference_t<decltype(*work)> v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) { const int64_t j = j0 + u * step; v[u] = (accepted ? work : cur)[(j < rows ? j : rows - 1) * R + q]; }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int64_t j = j0 + u * step;
+                    if (j >= rows) break;
+                    (accepted ? cur : work)[j * R + q] = v[u];
+                    if (most && best) most[j * R + q] = v[u];
+                }
+            }
+        };
+        copy(n, kidx, kidx_cur, kidx_best);
+        copy(m, r, r_cur, (T*)nullptr);
     }
-    for (int64_t e = t0; e < m * R; e += stride) {
-        if (S[e % R].accepted) r_cur[e] = r[e]; else r[e] = r_cur[e];
+    __syncthreads();                                  // (nobody here reads the state any more)
+    if (threadIdx.x == 0) {                           // (a count only: no fence, which would write the caches back)
+        last = atomicAdd(&flags[FLAG_TURN], 1) == (int32_t)(gridDim.x * gridDim.y) - 1;
     }
+    __syncthreads();
+    if (!last) return;
+    for (int64_t p = threadIdx.x; p < R; p += 256) {
+        alns_end(S, st, p, iters, lambda, sigma1, sigma2, sigma3, q2, trace, trace_t);
+        if (next >= 0) alns_begin(S, p, seed, next);
+    }
+    if (threadIdx.x == 0) flags[FLAG_TURN] = 0;
 }
 
 template <class T>
@@ -749,12 +928,12 @@ static dmmv_status sumsq_t(Ctx* c) {
 }
 
 template <class T>
-static dmmv_status start_t(Ctx* c, bool l2_guard) {
+static dmmv_status start_t(Ctx* c, bool l2_guard, uint64_t seed) {
     const int64_t R = c->p.R;
     if (l2_guard) DMMV_TRY(sumsq_t<T>(c));
     hipLaunchKernelGGL(k_alns_init<T>, dim3(blocks_for(R, 256)), dim3(256), 0, c->stream,
                        (AlnsState*)c->alns_state, (const InstState<T>*)c->state, R,
-                       l2_guard ? (const double*)c->alns_q2 : nullptr);
+                       l2_guard ? (const double*)c->alns_q2 : nullptr, seed, c->flags);
     hipLaunchKernelGGL(k_alns_snapshot<T>, dim3(1024), dim3(256), 0, c->stream, c->p.m, c->p.n, R,
                        (const int32_t*)c->kidx, c->alns_kidx_cur, c->alns_kidx_best, (const T*)c->r,
                        (T*)c->alns_r_cur, (unsigned long long*)c->alns_first, c->alns_weight);
@@ -763,10 +942,9 @@ static dmmv_status start_t(Ctx* c, bool l2_guard) {
 }
 
 template <class T>
-static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t it, int32_t count) {
+static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t count) {
     AlnsState* S = (AlnsState*)c->alns_state;
     const int64_t R = c->p.R;
-    hipLaunchKernelGGL(k_alns_begin, dim3(blocks_for(R, 256)), dim3(256), 0, c->stream, S, R, prm.seed, it);
     if (c->kind == KIND_DENSE) {
         hipLaunchKernelGGL(k_alns_impact_dense<T>, dim3((unsigned)c->p.n), dim3(256), 0, c->stream, c->p.m,
                            c->p.n, (const T*)c->p.A_dense, c->p.lda, (const T*)c->r,
@@ -808,11 +986,26 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
         raw_shift = bits(c->p.m) + 24 + bits(c->p.n) - 62;
         if (raw_shift < 0) raw_shift = 0;
     }
-    hipLaunchKernelGGL(k_alns_scan, dim3((unsigned)R), dim3(1024), 0, c->stream, c->p.n,
-                       c->alns_weight, c->alns_prefix, (const AlnsState*)S, raw_shift, c->kind == KIND_BATCHED && c->alns_lists ? 1 : 0);
-    hipLaunchKernelGGL(k_alns_sample, dim3((unsigned)R), dim3(R > 1 ? 256 : 1024), 0, c->stream, c->p.n, count,
-                       (const uint64_t*)c->alns_prefix, (unsigned long long*)c->alns_first, c->alns_picked,
-                       (const AlnsState*)S, prm.seed);
+    const int32_t clear = c->kind == KIND_BATCHED && c->alns_lists ? 1 : 0;
+    c->exchange_clear = false;
+    // Up to 8 rows a thread in one launch (16 where many instances share the chip).
+    const bool many = R > 512;
+    if (c->kind != KIND_CSC && c->p.m <= (many ? 256 * 16 : 1024 * 8)) {
+        auto both = [&](auto kernel, int threads) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)R), dim3(threads), 0, c->stream, c->p.m, c->p.n, R, c->p.nd, count,
+                               c->alns_weight, c->alns_prefix, (unsigned long long*)c->alns_first, c->alns_picked,
+                               (const AlnsState*)S, prm.seed, raw_shift, clear, (const T*)c->p.A_dense, c->p.lda,
+                               (const T*)c->D_dev, (const T*)c->scale_dev, (T*)c->r, c->kidx, (InstState<T>*)c->state,
+                               (uint32_t*)c->persist_exchange, c->kind == KIND_DENSE ? (int32_t)(dense_persistent_exchange_bytes() / 4) : 0);
+        };
+        if (many) { if (c->p.m <= 2048) both(k_alns_destroy_repair<T, 256, 8>, 256); else both(k_alns_destroy_repair<T, 256, 16>, 256); }
+        else { if (c->p.m <= 2048) both(k_alns_destroy_repair<T, 1024, 2>, 1024); else both(k_alns_destroy_repair<T, 1024, 8>, 1024); }
+        DMMV_LAUNCH_CHECK();
+        c->exchange_clear = c->kind == KIND_DENSE;
+        return DMMV_OK;
+    }
+    hipLaunchKernelGGL(k_alns_destroy<1024>, dim3((unsigned)R), dim3(1024), 0, c->stream, c->p.n, count, c->alns_weight,
+                       c->alns_prefix, (unsigned long long*)c->alns_first, c->alns_picked, (const AlnsState*)S, prm.seed, raw_shift, clear);
     if (c->kind == KIND_CSC) {
         DMMV_TRY(csc_alns_repair(c, count, prm.seed));
     } else {
@@ -829,19 +1022,22 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
 }
 
 template <class T>
-static dmmv_status finish_iteration_t(Ctx* c, const dmmv_alns_params& prm, bool last, int32_t* trace, void* trace_t) {
-    AlnsState* S = (AlnsState*)c->alns_state;
-    const int64_t R = c->p.R;
+static dmmv_status finish_iteration_t(Ctx* c, const dmmv_alns_params& prm, int32_t next, int32_t* trace, void* trace_t) {
+    const int64_t R = c->p.R, m = c->p.m, n = c->p.n;
     if (prm.l2_guard) DMMV_TRY(sumsq_t<T>(c));
-    hipLaunchKernelGGL(k_alns_end<T>, dim3(blocks_for(R, 256)), dim3(256), 0, c->stream, S,
-                       (InstState<T>*)c->state, R, prm.iters, prm.lambda, prm.sigma1, prm.sigma2, prm.sigma3,
-                       prm.l2_guard ? (const double*)c->alns_q2 : nullptr, trace, (T*)trace_t);
-    hipLaunchKernelGGL(k_alns_copy<T>, dim3(1024), dim3(256), 0, c->stream, c->p.m, c->p.n, R,
-                       (const AlnsState*)S, c->kidx, c->alns_kidx_cur, c->alns_kidx_best, (T*)c->r,
-                       (T*)c->alns_r_cur);
+    // some sixteen elements a thread, more where that takes over 512 workgroups (each adds to the one counter: 1024 instances of
+    // 2048 x 4096 take 43 us with 2048 of them, 40 with 1024, 37 with 512, 38 with 256)
+    constexpr int64_t cap = 512;
+    int64_t strips = ceil_div(R > 1 ? R : ceil_div(m + n, 4), 256), rows = R > 1 ? ceil_div(m + n, 16) : 1;
+    if (R == 1 && strips > 1024) strips = 1024;
+    if (rows > ceil_div(cap, strips)) rows = ceil_div(cap, strips);
+    hipLaunchKernelGGL(k_alns_turn<T>, dim3((unsigned)strips, (unsigned)rows), dim3(256), 0, c->stream, m, n, R,
+                       (AlnsState*)c->alns_state, (InstState<T>*)c->state, c->kidx, c->alns_kidx_cur, c->alns_kidx_best, (T*)c->r,
+                       (T*)c->alns_r_cur, prm.iters, prm.lambda, prm.sigma1, prm.sigma2, prm.sigma3,
+                       prm.l2_guard ? (const double*)c->alns_q2 : nullptr, trace, (T*)trace_t, prm.seed, next, c->flags);
     DMMV_LAUNCH_CHECK();
     // (before another iteration, its repair gives what it leaves a reservoir of its own)
-    if (c->kind == KIND_CSC && last) DMMV_TRY(csc_alns_after_copy(c));
+    if (c->kind == KIND_CSC && next < 0) DMMV_TRY(csc_alns_after_copy(c));
     return DMMV_OK;
 }
 
@@ -853,17 +1049,16 @@ static dmmv_status export_t(Ctx* c, void* t_best_out) {
     return DMMV_OK;
 }
 
-dmmv_status alns_start(Ctx* c, bool l2_guard) {
-    return c->p.dtype == DMMV_F64 ? start_t<double>(c, l2_guard) : start_t<float>(c, l2_guard);
+dmmv_status alns_start(Ctx* c, bool l2_guard, uint64_t seed) {
+    return c->p.dtype == DMMV_F64 ? start_t<double>(c, l2_guard, seed) : start_t<float>(c, l2_guard, seed);
 }
 dmmv_status alns_sumsq(Ctx* c) { return c->p.dtype == DMMV_F64 ? sumsq_t<double>(c) : sumsq_t<float>(c); }
-dmmv_status alns_destroy_repair(Ctx* c, const dmmv_alns_params& prm, int32_t it, int32_t count) {
-    return c->p.dtype == DMMV_F64 ? destroy_repair_t<double>(c, prm, it, count)
-                                  : destroy_repair_t<float>(c, prm, it, count);
+dmmv_status alns_destroy_repair(Ctx* c, const dmmv_alns_params& prm, int32_t count) {
+    return c->p.dtype == DMMV_F64 ? destroy_repair_t<double>(c, prm, count) : destroy_repair_t<float>(c, prm, count);
 }
-dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, bool last, int32_t* trace, void* trace_t) {
-    return c->p.dtype == DMMV_F64 ? finish_iteration_t<double>(c, prm, last, trace, trace_t)
-                                  : finish_iteration_t<float>(c, prm, last, trace, trace_t);
+dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, int32_t next, int32_t* trace, void* trace_t) {
+    return c->p.dtype == DMMV_F64 ? finish_iteration_t<double>(c, prm, next, trace, trace_t)
+                                  : finish_iteration_t<float>(c, prm, next, trace, trace_t);
 }
 dmmv_status alns_export(Ctx* c, void* t_best_out) {
     return c->p.dtype == DMMV_F64 ? export_t<double>(c, t_best_out) : export_t<float>(c, t_best_out);

@@ -787,7 +787,7 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
     if (!c->x_set) return fail(DMMV_ERR_STATE, "dmmv_alns: no starting point (x0 is NULL and dmmv_set_x was never called)");
     DMMV_TRY(residual_any(c));
     if (c->p.n == 0) {
-        DMMV_TRY(alns_start(c, false));
+        DMMV_TRY(alns_start(c, false, prm.seed));
         DMMV_TRY(alns_export(c, t_best_out));
         DMMV_HIP_CHECK(hipStreamSynchronize(c->stream));
         return DMMV_OK;
@@ -801,10 +801,10 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
     c->o.keep_going = 0;
     int32_t raw = 0;                                        // error bits found at a polling point of a one-launch run
     auto run = [&](bool one_launch) -> dmmv_status {
-        DMMV_TRY(alns_start(c, prm.l2_guard != 0));
+        DMMV_TRY(alns_start(c, prm.l2_guard != 0, prm.seed));
         int32_t poll_at = ALNS_POLL;
         for (int32_t it = 0; it < prm.iters; ++it) {
-            DMMV_TRY(alns_destroy_repair(c, prm, it, (int32_t)count));
+            DMMV_TRY(alns_destroy_repair(c, prm, (int32_t)count));
             if (batched_pruned_applicable(c)) {
                 DMMV_TRY(batched_descent_pruned(c, prm.ls_moves, prm.ls_moves, nullptr, nullptr));
             } else if (one_launch) {
@@ -817,7 +817,7 @@ static dmmv_status alns_run(dmmv_ctx* c, const void* x0, const dmmv_alns_params&
                 for (int32_t sw = 0; sw < prm.ls_swaps; ++sw)
                     DMMV_TRY(swap_move(c, prm.k_eps, 1, true, nullptr, nullptr));
             }
-            DMMV_TRY(alns_finish_iteration(c, prm, it + 1 == prm.iters, trace, trace_t));
+            DMMV_TRY(alns_finish_iteration(c, prm, it + 1 < prm.iters ? it + 1 : -1, trace, trace_t));
             if (one_launch && it + 1 == poll_at && it + 1 < prm.iters) {
                 DMMV_TRY(check_device_errors(c, &raw));
                 poll_at = poll_at < INT32_MAX / 4 ? 4 * poll_at : INT32_MAX;

@@ -80,7 +80,7 @@ struct alignas(16) Partial {
 
 // device flag slots
 enum { FLAG_ERROR = 0, FLAG_ACTIVE = 1, FLAG_PLANES = 2, FLAG_MAXROW = 3, FLAG_MAXCOL = 4, FLAG_WORST = 5,
-       FLAG_SWAP_BEST = 6 /* and 7, one 8-byte word */, FLAG_COUNT = 8 };
+       FLAG_SWAP_BEST = 6 /* and 7, one 8-byte word */, FLAG_TURN = 8, FLAG_COUNT = 9 };
 // error bits set by kernels
 enum { ERRBIT_X_NOT_IN_D = 1, ERRBIT_CSR_RANGE = 2, ERRBIT_CSR_DUP = 4, ERRBIT_MOVE_RANGE = 8, ERRBIT_WAIT_LIMIT = 16 };
 
@@ -113,6 +113,7 @@ struct Ctx {
     int64_t n_partials;
     int32_t* flags;       // [FLAG_COUNT]
     void* persist_exchange; // dense single instance: arg-min records and arrival words of the one-launch descent
+    bool exchange_clear;    //   the kernel enqueued last has cleared them
     void* red;            // T[red_elems] partial maxima of the max-|r| reduction
     int64_t red_elems;
 
@@ -224,10 +225,11 @@ constexpr int CSC_MAX_PARTITIONS = 1024;
 // ----------------------------------------------------------------------------------------
 // per-path entry points (all enqueue on c->stream)
 // ----------------------------------------------------------------------------------------
-dmmv_status alns_start(Ctx* c, bool l2_guard);
+dmmv_status alns_start(Ctx* c, bool l2_guard, uint64_t seed);       // chooses the first iteration's operators too
 dmmv_status alns_sumsq(Ctx* c);          // alns_q2 <- squared l2 norm of r, per instance
-dmmv_status alns_destroy_repair(Ctx* c, const dmmv_alns_params& prm, int32_t it, int32_t count);
-dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, bool last, int32_t* trace, void* trace_t);
+dmmv_status alns_destroy_repair(Ctx* c, const dmmv_alns_params& prm, int32_t count);
+// next: number of the outer iteration that follows, -1 = none
+dmmv_status alns_finish_iteration(Ctx* c, const dmmv_alns_params& prm, int32_t next, int32_t* trace, void* trace_t);
 dmmv_status alns_export(Ctx* c, void* t_best_out);
 bool alns_impact_lists_applicable(const dmmv_problem& p);
 dmmv_status alns_impact_lists_build(Ctx* c);            // once per handle

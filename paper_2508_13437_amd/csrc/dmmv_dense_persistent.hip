@@ -715,7 +715,9 @@ dmmv_status run_t(Ctx* c, const Plan& pl, int32_t steps, int32_t iters, dmmv_mov
     // iteration numbers start at 1: cleared records name no iteration
     uint64_t* rec = (uint64_t*)c->persist_exchange;
     const int words = 2 * DP_MAX_G * DP_REC_WORDS * 2;       // as 32-bit words
-    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)ceil_div(words, 256)), dim3(256), 0, c->stream, (uint32_t*)rec, words);
+    if (!c->exchange_clear)
+        hipLaunchKernelGGL(k_zero_words, dim3((unsigned)ceil_div(words, 256)), dim3(256), 0, c->stream, (uint32_t*)rec, words);
+    c->exchange_clear = false;
     const int32_t wait_limit = c->o.wait_limit > 0 ? c->o.wait_limit : DP_WAIT_DEFAULT;
     auto kernel = pl.waves == 8 ? k_descent_dense_persistent<T, 8> : k_descent_dense_persistent<T, 4>;
     DMMV_TRY(ensure_dynamic_lds((const void*)kernel, (int)DP_LDS_LIMIT));
@@ -732,7 +734,9 @@ template <class T>
 dmmv_status run_interval_t(Ctx* c, const PlanI& pl, int32_t steps, int32_t iters, dmmv_move* trace, void* trace_t) {
     uint64_t* rec = (uint64_t*)c->persist_exchange;
     const int words = 2 * DP_MAX_G * DP_REC_WORDS * 2;
-    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)ceil_div(words, 256)), dim3(256), 0, c->stream, (uint32_t*)rec, words);
+    if (!c->exchange_clear)
+        hipLaunchKernelGGL(k_zero_words, dim3((unsigned)ceil_div(words, 256)), dim3(256), 0, c->stream, (uint32_t*)rec, words);
+    c->exchange_clear = false;
     const int32_t wait_limit = c->o.wait_limit > 0 ? c->o.wait_limit : DP_WAIT_DEFAULT;
     auto launch = [&](auto kernel) -> dmmv_status {
         DMMV_TRY(ensure_dynamic_lds((const void*)kernel, (int)DP_LDS_LIMIT));
