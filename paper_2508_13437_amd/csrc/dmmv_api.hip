@@ -278,20 +278,25 @@ __global__ void k_zero_flags(int32_t* flags) {
     if (threadIdx.x < FLAG_COUNT) flags[threadIdx.x] = 0;
 }
 
-// x values -> index into D (binary search, exact match required), single instance
+// the level of a value (binary search; it must be one of D)
 template <class T>
-__global__ void k_values_to_index(const T* __restrict__ x, const T* __restrict__ D, int32_t nd,
-                                  int64_t n, int32_t* __restrict__ kidx, int32_t* flags) {
-    int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    T v = x[j];
+__device__ __forceinline__ int32_t level_of(T v, const T* __restrict__ D, int32_t nd, int32_t* flags) {
     int32_t lo = 0, hi = nd - 1;
     while (lo < hi) {
         int32_t mid = (lo + hi) >> 1;
         if (D[mid] < v) lo = mid + 1; else hi = mid;
     }
     if (!(D[lo] == v)) { atomicOr(&flags[FLAG_ERROR], ERRBIT_X_NOT_IN_D); lo = 0; }
-    kidx[j] = lo;
+    return lo;
+}
+
+// x values -> index into D, single instance
+template <class T>
+__global__ void k_values_to_index(const T* __restrict__ x, const T* __restrict__ D, int32_t nd,
+                                  int64_t n, int32_t* __restrict__ kidx, int32_t* flags) {
+    int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (j >= n) return;
+    kidx[j] = level_of(x[j], D, nd, flags);
 }
 
 template <class T>
@@ -515,6 +520,8 @@ __global__ void k_stage_moves(const dmmv_move* __restrict__ moves, int64_t R, in
     st[q] = z;
 }
 
+__global__ void k_zero_active(int32_t* flags) { flags[FLAG_ACTIVE] = 0; }
+
 template <class T>
 __global__ void k_count_active(const InstState<T>* __restrict__ st, int64_t R, int32_t* flags) {
     int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -528,24 +535,26 @@ __global__ void k_clear_done(InstState<T>* st, int64_t R) {
     if (q < R) st[q].done = 0;
 }
 
+// What a descent needs before its residual, in one launch: the loop's state, a trace without moves, and (x != NULL, single
+// instance) the levels of the starting point.
 template <class T>
-__global__ void k_reset_loop(InstState<T>* st, int64_t R) {
-    int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+__global__ void k_start_loop(InstState<T>* st, int64_t R, dmmv_move* trace, T* trace_t, int64_t count, const T* __restrict__ x,
+                             const T* __restrict__ D, int32_t nd, int64_t n, int32_t* __restrict__ kidx, int32_t* flags) {
+    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (q < R) { st[q].done = 0; st[q].moves = 0; st[q].apply_j = -1; }
+    if (q < count) {
+        if (trace) { trace[q].j = -1; trace[q].k = -1; }
+        if (trace_t) trace_t[q] = (T)0;
+    }
+    if (x && q < n) kidx[q] = level_of(x[q], D, nd, flags);
 }
 
-template <class T>
-__global__ void k_fill_trace(dmmv_move* trace, T* trace_t, int64_t count) {
-    int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= count) return;
-    if (trace) { trace[q].j = -1; trace[q].k = -1; }
-    if (trace_t) trace_t[q] = (T)0;
-}
-
+// (x != NULL: a single instance's values too)
 template <class T>
 __global__ void k_export_state(const InstState<T>* __restrict__ st, int64_t R, T* t_out,
-                               int32_t* moves_out) {
+                               int32_t* moves_out, T* x, const int32_t* __restrict__ kidx, const T* __restrict__ D, int64_t n) {
     int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (x && q < n) x[q] = D[kidx[q]];
     if (q >= R) return;
     if (t_out) t_out[q] = st[q].t;
     if (moves_out) moves_out[q] = st[q].moves;
@@ -666,7 +675,13 @@ static dmmv_status loop_step(Ctx* c, int32_t iters, dmmv_move* trace, void* trac
 
 static dmmv_status residual_any(Ctx* c) {
     switch (c->kind) {
-        case KIND_DENSE: DMMV_TRY(dense_residual(c)); break;
+        case KIND_DENSE:
+            DMMV_TRY(dense_residual(c));
+            if (dense_residual_sets_t(c->p)) {
+                c->r_valid = true;
+                return DMMV_OK;
+            }
+            break;
         case KIND_CSC: DMMV_TRY(csc_residual(c)); break;
         default:
             if (c->o.residual_mfma) DMMV_TRY(batched_mfma_residual(c));
@@ -714,13 +729,29 @@ static dmmv_status set_x_single(Ctx* c, const void* x) {
 template <class T>
 static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_out, void* t_out,
                            int32_t* iters_done, dmmv_move* trace, void* trace_t) {
-    const int64_t R = c->p.R;
-    if (x0 || c->p.n == 0) DMMV_TRY(dmmv_set_x(c, x0));
-    if (!c->x_set) return fail(DMMV_ERR_STATE, "dmmv_solve: no starting point (x0 is NULL and dmmv_set_x was never called)");
-    hipLaunchKernelGGL(k_reset_loop<T>, grid1(R, 256), dim3(256), 0, c->stream, (InstState<T>*)c->state, R);
+    const int64_t R = c->p.R, n = c->p.n;
+    const bool single = c->kind != KIND_BATCHED;
+    if (!x0 && n > 0 && !c->x_set) return fail(DMMV_ERR_STATE, "dmmv_solve: no starting point (x0 is NULL and dmmv_set_x was never called)");
+    // (a value of x0 outside D is taken for the first level, and reported when the stream is waited for)
+    const int64_t count = iters > 0 && (trace || trace_t) ? R * (int64_t)iters : 0, most = count > R ? count : R;
+    hipLaunchKernelGGL(k_start_loop<T>, grid1(single && x0 && n > most ? n : most, 256), dim3(256), 0, c->stream, (InstState<T>*)c->state, R,
+                       trace, (T*)trace_t, count, single && n > 0 ? (const T*)x0 : nullptr, (const T*)c->D_dev, c->p.nd, n, c->kidx, c->flags);
+    DMMV_LAUNCH_CHECK();
+    if (x0 && n > 0 && !single) DMMV_TRY(batched_set_x(c, x0));
+    c->x_set = true;
     DMMV_TRY(residual_any(c));
-    if (iters > 0 && (trace || trace_t))
-        hipLaunchKernelGGL(k_fill_trace<T>, grid1(R * (int64_t)iters, 256), dim3(256), 0, c->stream, trace, (T*)trace_t, R * (int64_t)iters);
+    // what comes out, and the wait for it
+    auto finish = [&](int32_t* raw) -> dmmv_status {
+        hipLaunchKernelGGL(k_export_state<T>, grid1(single && x_out && n > R ? n : R, 256), dim3(256), 0, c->stream, (const InstState<T>*)c->state, R, (T*)t_out, iters_done,
+                           single ? (T*)x_out : nullptr, (const int32_t*)c->kidx, (const T*)c->D_dev, n);
+        DMMV_LAUNCH_CHECK();
+        if (x_out && !single) DMMV_TRY(dmmv_get_state(c, x_out, nullptr, nullptr));
+        int32_t bits = 0;
+        const dmmv_status st = check_device_errors(c, &bits);
+        if (bits & ERRBIT_X_NOT_IN_D) c->x_set = c->r_valid = false;
+        if (raw) *raw = bits;
+        return st;
+    };
     int32_t poll = c->o.keep_going ? 0 : c->o.poll_every;
     // a batch drops its stopped instances at the polling points (their wavefronts would
     // otherwise keep running for the sake of a few neighbours), so it polls more often
@@ -728,26 +759,29 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
     const bool l2_on = c->o.l2_rule == 1 || c->o.l2_rule == 2;
     const bool compacting = c->kind == KIND_BATCHED && poll > 0 && !c->o.var_mask && !pruned_batch && !l2_on;
     if (compacting && poll > 8) poll = 8;
-    dmmv_status loop_st = [&]() -> dmmv_status {
-        // a pruned batch runs all its iterations in one launch; every instance stops by itself
-        if (pruned_batch) return batched_descent_pruned(c, iters, iters, trace, trace_t);
-        // a small dense instance too; the wait between its workgroups is bounded and reports here
-        // (others of the process that leave it no room for long: the loop of launches)
+    // a small dense instance runs all its iterations in one launch; the wait between its workgroups is bounded and reports here
+    // (others of the process that leave it no room for long: the loop of launches)
+    if (!pruned_batch) {
         OneLaunchClaim claim;
         const int32_t workgroups = iters > 0 ? dense_persistent_workgroups(c) : 0;
         if (workgroups > 0 && claim.take(c, workgroups, iters)) {
             int32_t raw = 0;
             dmmv_status one = dense_descent_persistent(c, iters, iters, trace, trace_t);
-            if (one == DMMV_OK) one = check_device_errors(c, &raw);
+            if (one == DMMV_OK) one = finish(&raw);
             else (void)hipStreamSynchronize(c->stream);
             claim.release();
             // An automatic choice must not add a way to fail: if the workgroups could not all be
             // resident (the device is shared), the attempt has left x, r and the loop state alone,
             // and the loop of launches below does the same descent.
             if (!(one != DMMV_OK && raw == ERRBIT_WAIT_LIMIT && c->o.dense_loop == 0)) return one;
-            if (trace || trace_t)
-                hipLaunchKernelGGL(k_fill_trace<T>, grid1(R * (int64_t)iters, 256), dim3(256), 0, c->stream, trace, (T*)trace_t, R * (int64_t)iters);
+            if (count > 0)
+                hipLaunchKernelGGL(k_start_loop<T>, grid1(most, 256), dim3(256), 0, c->stream, (InstState<T>*)c->state, R, trace, (T*)trace_t,
+                                   count, (const T*)nullptr, (const T*)c->D_dev, c->p.nd, n, c->kidx, c->flags);
         }
+    }
+    dmmv_status loop_st = [&]() -> dmmv_status {
+        // a pruned batch runs all its iterations in one launch; every instance stops by itself
+        if (pruned_batch) return batched_descent_pruned(c, iters, iters, trace, trace_t);
         for (int32_t it = 0; it < iters; ++it) {
             DMMV_TRY(loop_step(c, iters, trace, trace_t));
             if (poll > 0 && (it + 1) % poll == 0 && it + 1 < iters) {
@@ -755,10 +789,13 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
                 if (compacting) {
                     DMMV_TRY(batched_compact(c, &active));
                 } else {
-                    hipLaunchKernelGGL(k_zero_flags, dim3(1), dim3(64), 0, c->stream, c->flags);
+                    int32_t seen[2];                        // error bits and number of running instances
+                    static_assert(FLAG_ERROR == 0 && FLAG_ACTIVE == 1, "read together");
+                    hipLaunchKernelGGL(k_zero_active, dim3(1), dim3(1), 0, c->stream, c->flags);
                     hipLaunchKernelGGL(k_count_active<T>, grid1(R, 256), dim3(256), 0, c->stream, (const InstState<T>*)c->state, R, c->flags);
-                    DMMV_HIP_CHECK(hipMemcpyAsync(&active, &c->flags[FLAG_ACTIVE], sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+                    DMMV_HIP_CHECK(hipMemcpyAsync(seen, c->flags, sizeof(seen), hipMemcpyDeviceToHost, c->stream));
                     DMMV_HIP_CHECK(hipStreamSynchronize(c->stream));
+                    active = seen[0] ? 0 : seen[1];
                 }
                 if (active == 0) break;
             }
@@ -769,12 +806,11 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
         const dmmv_status back = batched_compact_end(c);
         if (loop_st == DMMV_OK) loop_st = back;
     }
-    DMMV_TRY(loop_st);
-    hipLaunchKernelGGL(k_export_state<T>, grid1(R, 256), dim3(256), 0, c->stream, (const InstState<T>*)c->state, R, (T*)t_out, iters_done);
-    DMMV_LAUNCH_CHECK();
-    if (x_out) DMMV_TRY(dmmv_get_state(c, x_out, nullptr, nullptr));
-    DMMV_HIP_CHECK(hipStreamSynchronize(c->stream));
-    return DMMV_OK;
+    if (loop_st != DMMV_OK) {
+        const dmmv_status seen = finish(nullptr);           // (an x0 outside D is the first thing to report)
+        return seen == DMMV_ERR_DOMAIN ? seen : loop_st;
+    }
+    return finish(nullptr);
 }
 
 // ---- ALNS outer loop (Algorithm 1): destroy + repair, local search, accept ---------------
@@ -1227,9 +1263,9 @@ dmmv_status dmmv_get_state(dmmv_handle h, void* x_values, void* r, void* max_vio
     if (max_violation) {
         if (!h->r_valid) return fail(DMMV_ERR_STATE, "dmmv_get_state: no residual yet");
         if (h->p.dtype == DMMV_F64)
-            hipLaunchKernelGGL(k_export_state<double>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<double>*)h->state, R, (double*)max_violation, (int32_t*)nullptr);
+            hipLaunchKernelGGL(k_export_state<double>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<double>*)h->state, R, (double*)max_violation, (int32_t*)nullptr, (double*)nullptr, (const int32_t*)nullptr, (const double*)nullptr, (int64_t)0);
         else
-            hipLaunchKernelGGL(k_export_state<float>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<float>*)h->state, R, (float*)max_violation, (int32_t*)nullptr);
+            hipLaunchKernelGGL(k_export_state<float>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<float>*)h->state, R, (float*)max_violation, (int32_t*)nullptr, (float*)nullptr, (const int32_t*)nullptr, (const float*)nullptr, (int64_t)0);
     }
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;

@@ -241,6 +241,7 @@ int64_t mfma_ldk(int64_t n);
 dmmv_status batched_mfma_build(Ctx* c);
 dmmv_status batched_mfma_residual(Ctx* c);
 dmmv_status dense_residual(Ctx* c);
+bool dense_residual_sets_t(const dmmv_problem& p);    // ... and t = max |r| with it
 int64_t dense_num_partials(const dmmv_problem& p);    // arg-min records one evaluation writes
 dmmv_status dense_eval(Ctx* c, void* scores_out, bool want_partials, bool honor_done);
 bool dense_has_fused_select_apply(const Ctx* c);

@@ -28,7 +28,8 @@ constexpr int DR_TILE = 1024;             // levels staged at a time
 template <class T>
 __global__ __launch_bounds__(64) void k_residual_dense(int64_t m, int64_t n, const T* __restrict__ A, int64_t lda,
                                                        const T* __restrict__ D, const int32_t* __restrict__ kidx,
-                                                       const T* __restrict__ b, T* __restrict__ r) {
+                                                       const T* __restrict__ b, T* __restrict__ r, T* red, InstState<T>* st,
+                                                       int32_t* flags) {
     __shared__ T sh_d[DR_TILE];
     const int64_t i = blockIdx.x * 64ll + threadIdx.x;
     const int64_t ic = i < m ? i : m - 1;
@@ -56,7 +57,27 @@ __global__ __launch_bounds__(64) void k_residual_dense(int64_t m, int64_t n, con
                 if (u + e < tn) acc = dmmv_fma(v[e], sh_d[u + e], acc);
         }
     }
-    if (i < m) r[i] = dmmv_fma(acc, (T)1, -b[i]);
+    const T ri = dmmv_fma(acc, (T)1, -b[ic]);
+    if (i < m) r[i] = ri;
+    // red != NULL: t = max |r| too.  Every workgroup leaves its maximum; the last one to have done so (flags[FLAG_TURN]
+    // counts them) takes the largest.  (The maxima are written and read past the caches, so no fence is needed that would
+    // write them back; a launch of its own takes 2 to 3 us.)
+    if (!red) return;
+    const T most = wave_max(dmmv_max((T)0, dmmv_abs(ri)));          // (rows past the end repeat row m - 1)
+    int32_t ticket = 0;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&red[blockIdx.x], most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        ticket = atomicAdd(&flags[FLAG_TURN], 1);
+    }
+    if (__builtin_amdgcn_readfirstlane(ticket) != (int32_t)gridDim.x - 1) return;
+    T t = (T)0;
+    for (uint32_t e = threadIdx.x; e < gridDim.x; e += 64) t = dmmv_max(t, __hip_atomic_load(&red[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    t = wave_max(t);
+    if (threadIdx.x == 0) {
+        st[0].t = t;
+        flags[FLAG_TURN] = 0;
+    }
 }
 
 // ---- evaluation ---------------------------------------------------------------------------
@@ -255,12 +276,16 @@ int64_t dense_num_partials(const dmmv_problem& p) {
     return p.n * ceil_div(tiles, dense_wavefronts(tiles));
 }
 
+// one maximum for every 64 rows in the buffer of partial maxima
+bool dense_residual_sets_t(const dmmv_problem& p) { return p.m > 0 && p.m <= 64 * 1024; }
+
 template <class T>
 static dmmv_status residual_t(Ctx* c) {
     if (c->p.m == 0) return DMMV_OK;
     hipLaunchKernelGGL(k_residual_dense<T>, dim3((unsigned)ceil_div(c->p.m, 64)), dim3(64), 0,
                        c->stream, c->p.m, c->p.n, (const T*)c->p.A_dense, c->p.lda,
-                       (const T*)c->D_dev, (const int32_t*)c->kidx, (const T*)c->p.b, (T*)c->r);
+                       (const T*)c->D_dev, (const int32_t*)c->kidx, (const T*)c->p.b, (T*)c->r,
+                       dense_residual_sets_t(c->p) ? (T*)c->red : nullptr, (InstState<T>*)c->state, c->flags);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
 }
