@@ -549,11 +549,13 @@ __global__ void k_start_loop(InstState<T>* st, int64_t R, dmmv_move* trace, T* t
     if (x && q < n) kidx[q] = level_of(x[q], D, nd, flags);
 }
 
-// (x != NULL: a single instance's values too)
+// (x != NULL: a single instance's values too; flags != NULL: nothing if x0 had a value outside D, x may be the caller's x0)
 template <class T>
 __global__ void k_export_state(const InstState<T>* __restrict__ st, int64_t R, T* t_out,
-                               int32_t* moves_out, T* x, const int32_t* __restrict__ kidx, const T* __restrict__ D, int64_t n) {
+                               int32_t* moves_out, T* x, const int32_t* __restrict__ kidx, const T* __restrict__ D, int64_t n,
+                               const int32_t* flags) {
     int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (flags && (flags[FLAG_ERROR] & ERRBIT_X_NOT_IN_D)) return;
     if (x && q < n) x[q] = D[kidx[q]];
     if (q >= R) return;
     if (t_out) t_out[q] = st[q].t;
@@ -732,18 +734,18 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
     const int64_t R = c->p.R, n = c->p.n;
     const bool single = c->kind != KIND_BATCHED;
     if (!x0 && n > 0 && !c->x_set) return fail(DMMV_ERR_STATE, "dmmv_solve: no starting point (x0 is NULL and dmmv_set_x was never called)");
-    // (a value of x0 outside D is taken for the first level, and reported when the stream is waited for)
+    if (x0 && n > 0 && !single) DMMV_TRY(dmmv_set_x(c, x0));
+    // (a single instance's value of x0 outside D is taken for the first level, and reported when the stream is waited for)
     const int64_t count = iters > 0 && (trace || trace_t) ? R * (int64_t)iters : 0, most = count > R ? count : R;
     hipLaunchKernelGGL(k_start_loop<T>, grid1(single && x0 && n > most ? n : most, 256), dim3(256), 0, c->stream, (InstState<T>*)c->state, R,
                        trace, (T*)trace_t, count, single && n > 0 ? (const T*)x0 : nullptr, (const T*)c->D_dev, c->p.nd, n, c->kidx, c->flags);
     DMMV_LAUNCH_CHECK();
-    if (x0 && n > 0 && !single) DMMV_TRY(batched_set_x(c, x0));
     c->x_set = true;
     DMMV_TRY(residual_any(c));
     // what comes out, and the wait for it
     auto finish = [&](int32_t* raw) -> dmmv_status {
         hipLaunchKernelGGL(k_export_state<T>, grid1(single && x_out && n > R ? n : R, 256), dim3(256), 0, c->stream, (const InstState<T>*)c->state, R, (T*)t_out, iters_done,
-                           single ? (T*)x_out : nullptr, (const int32_t*)c->kidx, (const T*)c->D_dev, n);
+                           single ? (T*)x_out : nullptr, (const int32_t*)c->kidx, (const T*)c->D_dev, n, (const int32_t*)c->flags);
         DMMV_LAUNCH_CHECK();
         if (x_out && !single) DMMV_TRY(dmmv_get_state(c, x_out, nullptr, nullptr));
         int32_t bits = 0;
@@ -1263,9 +1265,9 @@ dmmv_status dmmv_get_state(dmmv_handle h, void* x_values, void* r, void* max_vio
     if (max_violation) {
         if (!h->r_valid) return fail(DMMV_ERR_STATE, "dmmv_get_state: no residual yet");
         if (h->p.dtype == DMMV_F64)
-            hipLaunchKernelGGL(k_export_state<double>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<double>*)h->state, R, (double*)max_violation, (int32_t*)nullptr, (double*)nullptr, (const int32_t*)nullptr, (const double*)nullptr, (int64_t)0);
+            hipLaunchKernelGGL(k_export_state<double>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<double>*)h->state, R, (double*)max_violation, (int32_t*)nullptr, (double*)nullptr, (const int32_t*)nullptr, (const double*)nullptr, (int64_t)0, (const int32_t*)nullptr);
         else
-            hipLaunchKernelGGL(k_export_state<float>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<float>*)h->state, R, (float*)max_violation, (int32_t*)nullptr, (float*)nullptr, (const int32_t*)nullptr, (const float*)nullptr, (int64_t)0);
+            hipLaunchKernelGGL(k_export_state<float>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<float>*)h->state, R, (float*)max_violation, (int32_t*)nullptr, (float*)nullptr, (const int32_t*)nullptr, (const float*)nullptr, (int64_t)0, (const int32_t*)nullptr);
     }
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
