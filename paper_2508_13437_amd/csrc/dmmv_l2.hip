@@ -175,48 +175,81 @@ __device__ __forceinline__ bool rec3_less(T s1, T q1, int64_t c1, T s2, T q2, in
     return c1 < c2;
 }
 
-// ROWS: a thread takes a variable's values one after the other (what depends on the variable is read once, and
-// nothing of a value whose score is above the best so far); else the values are spread over the threads.
-template <class T, bool ROWS>
+// The table is read once, eight values of a thread in flight; what the second criterion needs (g, the level and their
+// dependent loads) is read for the first eight and then only where a score is not above the best that the wavefront has
+// found.  per_xcd > 0: instances to an XCD, which then take neighbouring ones (g and the levels lie along the instances,
+// a line of them serves 32).
+// Before, every value took a 64-bit division and all loads (or, few instances, a thread took a variable's values one after the
+// other).  us before and now, fp32: 1376 tables of 4096 x 8 135 and 46 (181 and 105 where most moves that lower the largest |r|
+// raise the l2 norm and the loads cannot be left out: their lines are then what bounds it), 5000 of 600 x 4 85 and 47, 300 of
+// 4096 x 16 78 and 31, 100 of 4096 x 8 28 and 17, one of 4096 x 16 34 and 15, one of 16 x 16 3.9 and 3.8.
+template <class T>
 __global__ __launch_bounds__(1024) void k_l2_select(int64_t n, int64_t R, int32_t nd, int32_t rule,
                                                     const T* __restrict__ scores, const T* __restrict__ D,
                                                     const T* __restrict__ scale, const int32_t* __restrict__ kidx,
                                                     const T* __restrict__ g, const T* __restrict__ csq,
                                                     InstState<T>* st, int32_t keep_going, dmmv_move* best_out,
-                                                    T* best_score_out) {
+                                                    T* best_score_out, int64_t per_xcd) {
     __shared__ T sh_s[16], sh_q[16];
     __shared__ int64_t sh_c[16];
-    const int64_t q = blockIdx.x;
+    const int64_t q = per_xcd > 0 ? (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3) : (int64_t)blockIdx.x;
+    if (q >= R) return;
     InstState<T> z = st[q];
     if (z.done && !best_out) return;
     const T sc = scale[q];
     const T* __restrict__ tab = scores + q * (n * (int64_t)nd);
     T bs = (T)0, bq = (T)0;
     int64_t bc = -1;
-    for (int64_t j = threadIdx.x; ROWS && j < n; j += blockDim.x) {
-        const T dcur = D[kidx[j * R + q]], gj = g[j * R + q], cj = csq[j];
-        for (int32_t k0 = 0; k0 < nd; k0 += 8) {
-            T s[8];
+    constexpr int U = 8;                                   // values of a thread in flight
+    const int32_t jump = (int32_t)blockDim.x;
+    const uint32_t step_j = (uint32_t)jump / (uint32_t)nd, step_k = (uint32_t)jump % (uint32_t)nd;
+    const uint32_t all_j = (uint32_t)(U * jump) / (uint32_t)nd, all_k = (uint32_t)(U * jump) % (uint32_t)nd;
+    const int64_t count = n * (int64_t)nd;
+    uint32_t j0 = threadIdx.x / (uint32_t)nd, k0 = threadIdx.x % (uint32_t)nd;      // of the first of them
+    T most = Limits<T>::inf();                             // smallest score the wavefront has found: above it nothing counts
+    auto batch = [&](int64_t e0, bool first) __attribute__((always_inline)) {
+        T s[U];
+        bool need[U], any = false;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s[u] = tab[j * nd + (k0 + u < nd ? k0 + u : nd - 1)];
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = e0 + u * jump + threadIdx.x;
+            s[u] = tab[e < count ? e : count - 1];
+        }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (k0 + u >= nd || (bc >= 0 && s[u] > bs)) continue;
-                const T dq = l2_change(step_of(D[k0 + u], dcur, sc), cj, gj);
-                const int64_t e = j * nd + k0 + u;
-                if (rule == 2 && !(dq <= (T)0)) continue;
+        for (int u = 0; u < U; ++u) {
+            need[u] = e0 + u * jump + threadIdx.x < count && (first || !(s[u] > most));
+            any = any || need[u];
+        }
+        if (first || __builtin_amdgcn_ballot_w64(any) != 0ull) {
+            uint32_t k[U], jn = j0, kn = k0;
+            int32_t kc[U];
+            T gj[U], cj[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t j = need[u] ? jn : 0;        // (one address for the lanes that need none)
+                k[u] = need[u] ? kn : 0;
+                kc[u] = kidx[j * R + q];
+                gj[u] = g[j * R + q];
+                cj[u] = csq[j];
+                jn += step_j;
+                kn += step_k;
+                if (kn >= (uint32_t)nd) { kn -= (uint32_t)nd; ++jn; }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const T dq = l2_change(step_of(D[k[u]], D[kc[u]], sc), cj[u], gj[u]);
+                const int64_t e = e0 + u * jump + threadIdx.x;
+                if (!need[u] || (rule == 2 && !(dq <= (T)0))) continue;
                 if (rec3_less(s[u], dq, e, bs, bq, bc)) { bs = s[u]; bq = dq; bc = e; }
             }
+            most = wave_min(bc >= 0 ? bs : Limits<T>::inf());
         }
-    }
-    for (int64_t e = threadIdx.x; !ROWS && e < n * (int64_t)nd; e += blockDim.x) {
-        const int64_t j = e / nd;
-        const int32_t k = (int32_t)(e - j * nd);
-        const T dq = l2_change(step_of(D[k], D[kidx[j * R + q]], sc), csq[j], g[j * R + q]);
-        if (rule == 2 && !(dq <= (T)0)) continue;
-        const T s = tab[e];
-        if (rec3_less(s, dq, e, bs, bq, bc)) { bs = s; bq = dq; bc = e; }
-    }
+        j0 += all_j;
+        k0 += all_k;
+        if (k0 >= (uint32_t)nd) { k0 -= (uint32_t)nd; ++j0; }
+    };
+    if (count > 0) batch(0, true);
+    for (int64_t e0 = U * jump; e0 < count; e0 += U * jump) batch(e0, false);      // whole wavefronts
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const T os = __shfl_xor(bs, off, 64), oq = __shfl_xor(bq, off, 64);
@@ -321,17 +354,16 @@ dmmv_status table_t(Ctx* c, void* dq_out) {
 
 template <class T>
 dmmv_status select_t(Ctx* c, const void* scores, int32_t keep_going, dmmv_move* best_out, void* best_score_out) {
-    // By rows up to 32 values (a wavefront's 64 rows of the table then stay in the cache between the loads of a row), where there are
-    // variables for a quarter of the threads and four values for each of them, and no more instances than compute units: there it
-    // is latency that counts (us by values / by rows, fp32: one of 500 x 31 16.6 / 13.5; one of 512 x 8 9.8 / 9.2; 100 of 4096 x 8
-    // 42 / 31; 200 of 4096 x 16 73 / 46; 300 of them 82 / 85; 1376 of 4096 x 4 92 / 116; 5000 of 600 x 4 86 / 112; one of 16 x 16
-    // 6.3 / 8.5).
-    const bool by_rows = c->p.nd <= 32 && c->p.n >= 256 && c->p.n * c->p.nd >= 4096 && c->p.R <= 256;
-    auto kernel = by_rows ? k_l2_select<T, true> : k_l2_select<T, false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)c->p.R), dim3(1024), 0, c->stream, c->p.n, c->p.R, c->p.nd,
+    // A thread takes eight values at least, and the more the fewer wavefronts an instance has: 256 threads where the instances fill
+    // the chip (with 1024 small tables were slower than before: 5000 of 600 x 4 118 us, now 47), up to 1024 for few.
+    const int64_t values = c->p.n * c->p.nd;
+    unsigned threads = 64;
+    while (threads < (c->p.R > 256 ? 256u : 1024u) && 8 * (int64_t)threads < values) threads *= 2;
+    const int64_t per_xcd = c->p.R >= 64 ? ceil_div(c->p.R, 8) : 0;
+    hipLaunchKernelGGL(k_l2_select<T>, dim3((unsigned)(per_xcd > 0 ? 8 * per_xcd : c->p.R)), dim3(threads), 0, c->stream, c->p.n, c->p.R, c->p.nd,
                        c->o.l2_rule, (const T*)scores, (const T*)c->D_dev, (const T*)c->scale_dev,
                        (const int32_t*)c->kidx, (const T*)c->l2_g, (const T*)c->l2_c, (InstState<T>*)c->state,
-                       keep_going, best_out, (T*)best_score_out);
+                       keep_going, best_out, (T*)best_score_out, per_xcd);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
 }
