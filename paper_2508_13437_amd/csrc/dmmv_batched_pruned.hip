@@ -542,7 +542,10 @@ dmmv_status descent_t(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, vo
     // kernel before, always four): 20 of 2048 x 4096 1949 and 1511 (2618), 250 2254 and 1776 (2850), 500 2307 and 1861 (2913),
     // 1000 2783 and 3220 (3593); 600 of 1024 x 2048 1276 and 1295 (1587); 20 of 2048 x 768 551 and 479 (652); 30 of 256 x 128 296 and 300
     // (325); 60 000 of 8 x 8 525 and 1462 (533).
-    const bool eight = R <= 512 && n > 128;
+    // Up to 256 variables four wavefronts screen all of them at once, and eight gain by their full scores only: on whole calls of 2048 x
+    // 158 405 and 325 (20), 499 and 367 (191), 561 and 503 (500); but from 270 to 512 rows from 5 % faster to 14 % slower, alike on
+    // the average (191 of 270 x 250 353 and 354, 300 of 512 x 140 387 and 443), so four there.
+    const bool eight = R <= 512 && n > 128 && (n > 256 || m > 512);
     auto with = [&](auto ki) -> dmmv_status {
         typedef decltype(ki) KI;
         if (eight) return n > 1024 ? launch(k_descent_batched_pruned<T, KI, 8, 2>, 8) : n > 512 ? launch(k_descent_batched_pruned<T, KI, 8, 1>, 8) : launch(k_descent_batched_pruned<T, KI, 8, 0>, 8);

@@ -21,7 +21,7 @@ def _with_residual(inst, r):
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("m,n,R,nd", [(10, 20, 4, 5), (22, 130, 3, 4), (62, 40, 3, 8), (63, 129, 5, 4), (64, 128, 5, 4), (65, 30, 6, 7), (66, 200, 2, 16),
                                       (129, 511, 2, 3), (128, 513, 2, 3), (70, 1023, 2, 3), (70, 1025, 2, 3), (70, 1537, 2, 2),
-                                      (40, 140, 512, 3), (40, 140, 513, 3), (2050, 9, 3, 5)])
+                                      (40, 140, 512, 3), (40, 140, 513, 3), (512, 129, 3, 3), (513, 129, 3, 3), (513, 256, 3, 3), (40, 257, 5, 3), (40, 257, 512, 3), (40, 257, 513, 3), (2050, 9, 3, 5)])
 def test_rows_variables_and_instances_around_the_edges(m, n, R, nd, dtype):
     batched_check(random_batched(11000 + m + n, m, n, R, nd, dtype=dtype), 8, prune=True)
 
