@@ -327,7 +327,7 @@ __global__ void k_maxabs_partial(const T* __restrict__ r, int64_t m, T* __restri
 // both stages in one workgroup, for vectors that a single one reads as fast as two launches take
 constexpr int64_t MAXABS_ONE_ROWS = 32768;      // 32 rows per thread
 template <class T>
-__global__ __launch_bounds__(1024) void k_maxabs_one(const T* __restrict__ r, int64_t m, InstState<T>* st) {
+__global__ __launch_bounds__(1024) void k_maxabs_one(const T* __restrict__ r, int64_t m, InstState<T>* st, const int32_t* flags) {
     __shared__ T sh[16];
     T v = (T)0;
     for (int64_t i0 = threadIdx.x; i0 < m; i0 += 8 * 1024) {
@@ -342,12 +342,12 @@ __global__ __launch_bounds__(1024) void k_maxabs_one(const T* __restrict__ r, in
     __syncthreads();
     if (threadIdx.x < 64) {
         v = wave_max(sh[threadIdx.x & 15]);
-        if (threadIdx.x == 0) st[0].t = v;
+        if (threadIdx.x == 0) state_set_t(st, v, flags);
     }
 }
 
 template <class T>
-__global__ void k_maxabs_final(const T* __restrict__ red, int nred, InstState<T>* st) {
+__global__ void k_maxabs_final(const T* __restrict__ red, int nred, InstState<T>* st, const int32_t* flags) {
     T v = (T)0;
     for (int q = threadIdx.x; q < nred; q += blockDim.x) v = dmmv_max(v, red[q]);
     v = wave_max(v);
@@ -357,7 +357,7 @@ __global__ void k_maxabs_final(const T* __restrict__ red, int nred, InstState<T>
     if (threadIdx.x == 0) {
         T w = (T)0;
         for (int q = 0; q < (int)(blockDim.x >> 6); ++q) w = dmmv_max(w, sh[q]);
-        st[0].t = w;
+        state_set_t(st, w, flags);
     }
 }
 
@@ -535,31 +535,43 @@ __global__ void k_clear_done(InstState<T>* st, int64_t R) {
     if (q < R) st[q].done = 0;
 }
 
-// What a descent needs before its residual, in one launch: the loop's state, a trace without moves, and (x != NULL, single
-// instance) the levels of the starting point.
+// What a descent needs before its residual, in one launch: the loop's state and (x != NULL, single instance) the levels of the
+// starting point.  (A value outside D raises the error bit; what writes t next then marks the instance as stopped.)
 template <class T>
-__global__ void k_start_loop(InstState<T>* st, int64_t R, dmmv_move* trace, T* trace_t, int64_t count, const T* __restrict__ x,
-                             const T* __restrict__ D, int32_t nd, int64_t n, int32_t* __restrict__ kidx, int32_t* flags) {
+__global__ void k_start_loop(InstState<T>* st, int64_t R, const T* __restrict__ x, const T* __restrict__ D, int32_t nd, int64_t n,
+                             int32_t* __restrict__ kidx, int32_t* flags) {
     const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (q < R) { st[q].done = 0; st[q].moves = 0; st[q].apply_j = -1; }
-    if (q < count) {
-        if (trace) { trace[q].j = -1; trace[q].k = -1; }
-        if (trace_t) trace_t[q] = (T)0;
-    }
     if (x && q < n) kidx[q] = level_of(x[q], D, nd, flags);
 }
 
-// (x != NULL: a single instance's values too; flags != NULL: nothing if x0 had a value outside D, x may be the caller's x0)
+// What comes out of a descent, in one launch: the trace past the moves taken, t, the count and (x != NULL, single instance) the
+// values.  Nothing if x0 had a value outside D (x may be the caller's x0); the trace alone after any other error.
 template <class T>
-__global__ void k_export_state(const InstState<T>* __restrict__ st, int64_t R, T* t_out,
-                               int32_t* moves_out, T* x, const int32_t* __restrict__ kidx, const T* __restrict__ D, int64_t n,
-                               const int32_t* flags) {
-    int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (flags && (flags[FLAG_ERROR] & ERRBIT_X_NOT_IN_D)) return;
+__global__ void k_end_loop(const InstState<T>* __restrict__ st, int64_t R, int32_t iters, dmmv_move* trace, T* trace_t,
+                           int64_t count, T* t_out, int32_t* moves_out, T* x, const int32_t* __restrict__ kidx,
+                           const T* __restrict__ D, int64_t n, const int32_t* __restrict__ flags) {
+    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int32_t bits = flags[FLAG_ERROR];
+    if (bits & ERRBIT_X_NOT_IN_D) return;
+    if (q < count) {
+        const int64_t p = R > 1 ? q / iters : 0;
+        if (q - p * iters >= st[p].moves) {
+            if (trace) { trace[q].j = -1; trace[q].k = -1; }
+            if (trace_t) trace_t[q] = (T)0;
+        }
+    }
+    if (bits) return;
     if (x && q < n) x[q] = D[kidx[q]];
     if (q >= R) return;
     if (t_out) t_out[q] = st[q].t;
     if (moves_out) moves_out[q] = st[q].moves;
+}
+
+template <class T>
+__global__ void k_export_state(const InstState<T>* __restrict__ st, int64_t R, T* t_out) {
+    int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (q < R) t_out[q] = st[q].t;
 }
 
 static inline dim3 grid1(int64_t n, int block) { return dim3((unsigned)(n > 0 ? ceil_div(n, block) : 1)); }
@@ -567,13 +579,13 @@ static inline dim3 grid1(int64_t n, int block) { return dim3((unsigned)(n > 0 ? 
 template <class T>
 static dmmv_status maxabs_single(Ctx* c) {
     if (c->p.m <= MAXABS_ONE_ROWS) {
-        hipLaunchKernelGGL(k_maxabs_one<T>, dim3(1), dim3(1024), 0, c->stream, (const T*)c->r, c->p.m, (InstState<T>*)c->state);
+        hipLaunchKernelGGL(k_maxabs_one<T>, dim3(1), dim3(1024), 0, c->stream, (const T*)c->r, c->p.m, (InstState<T>*)c->state, (const int32_t*)c->flags);
         DMMV_LAUNCH_CHECK();
         return DMMV_OK;
     }
     const int nblk = (int)(c->p.m > 0 ? (ceil_div(c->p.m, 1024) < c->red_elems ? ceil_div(c->p.m, 1024) : c->red_elems) : 1);
     hipLaunchKernelGGL(k_maxabs_partial<T>, dim3(nblk), dim3(256), 0, c->stream, (const T*)c->r, c->p.m, (T*)c->red);
-    hipLaunchKernelGGL(k_maxabs_final<T>, dim3(1), dim3(256), 0, c->stream, (const T*)c->red, nblk, (InstState<T>*)c->state);
+    hipLaunchKernelGGL(k_maxabs_final<T>, dim3(1), dim3(256), 0, c->stream, (const T*)c->red, nblk, (InstState<T>*)c->state, (const int32_t*)c->flags);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
 }
@@ -735,24 +747,29 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
     const bool single = c->kind != KIND_BATCHED;
     if (!x0 && n > 0 && !c->x_set) return fail(DMMV_ERR_STATE, "dmmv_solve: no starting point (x0 is NULL and dmmv_set_x was never called)");
     if (x0 && n > 0 && !single) DMMV_TRY(dmmv_set_x(c, x0));
-    // (a single instance's value of x0 outside D is taken for the first level, and reported when the stream is waited for)
-    const int64_t count = iters > 0 && (trace || trace_t) ? R * (int64_t)iters : 0, most = count > R ? count : R;
-    hipLaunchKernelGGL(k_start_loop<T>, grid1(single && x0 && n > most ? n : most, 256), dim3(256), 0, c->stream, (InstState<T>*)c->state, R,
-                       trace, (T*)trace_t, count, single && n > 0 ? (const T*)x0 : nullptr, (const T*)c->D_dev, c->p.nd, n, c->kidx, c->flags);
+    // (a single instance's value of x0 outside D stops the loops below before their first move, and is reported when the stream
+    // is waited for)
+    hipLaunchKernelGGL(k_start_loop<T>, grid1(single && x0 && n > R ? n : R, 256), dim3(256), 0, c->stream, (InstState<T>*)c->state, R,
+                       single && n > 0 ? (const T*)x0 : nullptr, (const T*)c->D_dev, c->p.nd, n, c->kidx, c->flags);
     DMMV_LAUNCH_CHECK();
     c->x_set = true;
     DMMV_TRY(residual_any(c));
-    // what comes out, and the wait for it
-    auto finish = [&](int32_t* raw) -> dmmv_status {
-        hipLaunchKernelGGL(k_export_state<T>, grid1(single && x_out && n > R ? n : R, 256), dim3(256), 0, c->stream, (const InstState<T>*)c->state, R, (T*)t_out, iters_done,
-                           single ? (T*)x_out : nullptr, (const int32_t*)c->kidx, (const T*)c->D_dev, n, (const int32_t*)c->flags);
-        DMMV_LAUNCH_CHECK();
-        if (x_out && !single) DMMV_TRY(dmmv_get_state(c, x_out, nullptr, nullptr));
+    auto errors = [&](int32_t* raw) -> dmmv_status {
         int32_t bits = 0;
         const dmmv_status st = check_device_errors(c, &bits);
         if (bits & ERRBIT_X_NOT_IN_D) c->x_set = c->r_valid = false;
         if (raw) *raw = bits;
         return st;
+    };
+    // what comes out, and the wait for it
+    auto finish = [&](int32_t* raw) -> dmmv_status {
+        const int64_t count = iters > 0 && (trace || trace_t) ? R * (int64_t)iters : 0, most = count > R ? count : R;
+        hipLaunchKernelGGL(k_end_loop<T>, grid1(single && x_out && n > most ? n : most, 256), dim3(256), 0, c->stream, (const InstState<T>*)c->state, R, iters,
+                           trace, (T*)trace_t, count, (T*)t_out, iters_done, single ? (T*)x_out : nullptr, (const int32_t*)c->kidx, (const T*)c->D_dev, n,
+                           (const int32_t*)c->flags);
+        DMMV_LAUNCH_CHECK();
+        if (x_out && !single) DMMV_TRY(dmmv_get_state(c, x_out, nullptr, nullptr));
+        return errors(raw);
     };
     int32_t poll = c->o.keep_going ? 0 : c->o.poll_every;
     // a batch drops its stopped instances at the polling points (their wavefronts would
@@ -776,14 +793,12 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
             // resident (the device is shared), the attempt has left x, r and the loop state alone,
             // and the loop of launches below does the same descent.
             if (!(one != DMMV_OK && raw == ERRBIT_WAIT_LIMIT && c->o.dense_loop == 0)) return one;
-            if (count > 0)
-                hipLaunchKernelGGL(k_start_loop<T>, grid1(most, 256), dim3(256), 0, c->stream, (InstState<T>*)c->state, R, trace, (T*)trace_t,
-                                   count, (const T*)nullptr, (const T*)c->D_dev, c->p.nd, n, c->kidx, c->flags);
         }
     }
     dmmv_status loop_st = [&]() -> dmmv_status {
         // a pruned batch runs all its iterations in one launch; every instance stops by itself
         if (pruned_batch) return batched_descent_pruned(c, iters, iters, trace, trace_t);
+        if (single && x0 && poll == 0) DMMV_TRY(errors(nullptr));     // (no look on the way)
         for (int32_t it = 0; it < iters; ++it) {
             DMMV_TRY(loop_step(c, iters, trace, trace_t));
             if (poll > 0 && (it + 1) % poll == 0 && it + 1 < iters) {
@@ -809,7 +824,7 @@ static dmmv_status solve_t(dmmv_ctx* c, const void* x0, int32_t iters, void* x_o
         if (loop_st == DMMV_OK) loop_st = back;
     }
     if (loop_st != DMMV_OK) {
-        const dmmv_status seen = finish(nullptr);           // (an x0 outside D is the first thing to report)
+        const dmmv_status seen = errors(nullptr);           // (an x0 outside D is the first thing to report)
         return seen == DMMV_ERR_DOMAIN ? seen : loop_st;
     }
     return finish(nullptr);
@@ -1265,9 +1280,9 @@ dmmv_status dmmv_get_state(dmmv_handle h, void* x_values, void* r, void* max_vio
     if (max_violation) {
         if (!h->r_valid) return fail(DMMV_ERR_STATE, "dmmv_get_state: no residual yet");
         if (h->p.dtype == DMMV_F64)
-            hipLaunchKernelGGL(k_export_state<double>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<double>*)h->state, R, (double*)max_violation, (int32_t*)nullptr, (double*)nullptr, (const int32_t*)nullptr, (const double*)nullptr, (int64_t)0, (const int32_t*)nullptr);
+            hipLaunchKernelGGL(k_export_state<double>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<double>*)h->state, R, (double*)max_violation);
         else
-            hipLaunchKernelGGL(k_export_state<float>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<float>*)h->state, R, (float*)max_violation, (int32_t*)nullptr, (float*)nullptr, (const int32_t*)nullptr, (const float*)nullptr, (int64_t)0, (const int32_t*)nullptr);
+            hipLaunchKernelGGL(k_export_state<float>, grid1(R, 256), dim3(256), 0, h->stream, (const InstState<float>*)h->state, R, (float*)max_violation);
     }
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;

@@ -337,6 +337,14 @@ dmmv_status batched_descent_pruned(Ctx* c, int32_t steps, int32_t iters, dmmv_mo
 // ----------------------------------------------------------------------------------------
 #ifdef __HIPCC__
 
+// t of a single instance, from a residual just made.  A descent whose x0 has a value outside D, which nobody has waited to hear of,
+// is marked as stopped: its loop takes no move.
+template <class T>
+__device__ __forceinline__ void state_set_t(InstState<T>* st, T t, const int32_t* flags) {
+    st[0].t = t;
+    if (flags[FLAG_ERROR] & ERRBIT_X_NOT_IN_D) st[0].done = 1;
+}
+
 template <class T> struct Limits;
 template <> struct Limits<float> {
     __device__ static float inf() { return __builtin_huge_valf(); }

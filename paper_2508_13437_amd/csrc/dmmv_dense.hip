@@ -75,7 +75,7 @@ __global__ __launch_bounds__(64) void k_residual_dense(int64_t m, int64_t n, con
     for (uint32_t e = threadIdx.x; e < gridDim.x; e += 64) t = dmmv_max(t, __hip_atomic_load(&red[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     t = wave_max(t);
     if (threadIdx.x == 0) {
-        st[0].t = t;
+        state_set_t(st, t, flags);
         flags[FLAG_TURN] = 0;
     }
 }

@@ -434,11 +434,12 @@ __device__ void reservoir_rebuild(ResLds<T>& L, int64_t m, const T* r, T* res_va
 template <class T>
 __global__ __launch_bounds__(1024) void k_reservoir_build(int64_t m, const T* r,
                                                           T* res_val, int32_t* res_row,
-                                                          int32_t* meta, T* floor_val, InstState<T>* st) {
+                                                          int32_t* meta, T* floor_val, InstState<T>* st,
+                                                          const int32_t* flags) {
     __shared__ ResLds<T> L;
     reservoir_rebuild(L, m, r, res_val, res_row, meta, floor_val);
     // the first row of the reservoir is the row of largest |r| (the caller wants t: no scan of its own)
-    if (st && threadIdx.x == 0) st[0].t = m > 0 ? L.ov[0] : (T)0;
+    if (st && threadIdx.x == 0) state_set_t(st, m > 0 ? L.ov[0] : (T)0, flags);
 }
 
 // =========================================================================================
@@ -667,7 +668,7 @@ template <class T>
 static dmmv_status reservoir_t(Ctx* c, bool set_t) {
     hipLaunchKernelGGL(k_reservoir_build<T>, dim3(1), dim3(1024), 0, c->stream, c->p.m, (const T*)c->r,
                        (T*)c->res_val, c->res_row, c->res_meta, (T*)c->res_floor,
-                       set_t ? (InstState<T>*)c->state : (InstState<T>*)nullptr);
+                       set_t ? (InstState<T>*)c->state : (InstState<T>*)nullptr, (const int32_t*)c->flags);
     DMMV_LAUNCH_CHECK();
     return DMMV_OK;
 }
