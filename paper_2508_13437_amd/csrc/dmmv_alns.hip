@@ -77,15 +77,14 @@ __device__ __forceinline__ void alns_begin(AlnsState* S, int64_t q, uint64_t see
 }
 
 template <class T>
-__global__ void k_alns_init(AlnsState* S, const InstState<T>* st, int64_t R, const double* q2, uint64_t seed, int32_t* flags) {
+__global__ void k_alns_init(AlnsState* S, const InstState<T>* st, int64_t R, const double* q2, uint64_t seed) {
     const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q == 0) flags[FLAG_TURN] = 0;
     if (q >= R) return;
     S[q].q2_cur = q2 ? q2[q] : 0.0;
     for (int u = 0; u < 4; ++u) S[q].w[u] = 1.0;
     S[q].t_cur = (double)st[q].t;
     S[q].t_best = (double)st[q].t;
-    S[q].accepted = 0; S[q].new_best = 0;
+    S[q].accepted = 0; S[q].turn = 0;
     alns_begin(S, q, seed, 0);
 }
 
@@ -351,9 +350,10 @@ __global__ __launch_bounds__(NT) void k_alns_destroy_repair(int64_t m, int64_t n
 
 // The end of an outer iteration and the start of the next one (unless it was the last).  Every thread takes the verdict
 // for the elements that it copies: accepted: current <- working (and best <- working for a new best); rejected: working
-// <- current.  The last workgroup to have done so (flags[FLAG_TURN] counts them) then updates the state: error, operator weights,
-// trace, the next iteration's operators.  One launch instead of three: 5.5 us instead of 13 on 8016 x 251, 8.3 instead of 14
-// on 20 instances of 2048 x 768, 37 instead of 43 on 1024 of 2048 x 4096.
+// <- current.  The last workgroup to have done so with a strip of instances (the strip counts them) then updates their state: error,
+// operator weights, trace, the next iteration's operators.  One launch instead of three (us): 5.5 instead of 13 on 8016 x 251, 8.4 instead
+// of 11 on 20 instances of 2048 x 768, 28 instead of 42 on 1024 of 2048 x 4096, 91 instead of 170 on 11 008 of 2048 x 256, 11 instead of 25
+// on 60 000 of 8 x 8.  (With one workgroup that updated the states of all instances: 36, 211 and 696 on the last three.)
 template <class T>
 __device__ __forceinline__ void alns_verdict(const AlnsState& s, const InstState<T>& z, const double* q2, int64_t q, bool& accepted, bool& best) {
     const double t = (double)z.t;
@@ -380,7 +380,6 @@ __device__ __forceinline__ void alns_end(AlnsState* S, InstState<T>* st, int64_t
         S[q].w[2 + S[q].r_op] = keep * S[q].w[2 + S[q].r_op] + lambda * psi;
     }
     S[q].accepted = accepted;
-    S[q].new_best = new_best;
     const int64_t slot = q * (int64_t)iters + it;
     if (trace) {
         trace[slot * 4 + 0] = S[q].d_op; trace[slot * 4 + 1] = S[q].r_op;
@@ -395,7 +394,7 @@ template <class T>
 __global__ __launch_bounds__(256) void k_alns_turn(int64_t m, int64_t n, int64_t R, AlnsState* S, InstState<T>* st, int32_t* kidx,
                                                    int32_t* kidx_cur, int32_t* kidx_best, T* r, T* r_cur, int32_t iters,
                                                    double lambda, double sigma1, double sigma2, double sigma3, const double* q2,
-                                                   int32_t* trace, T* trace_t, uint64_t seed, int32_t next, int32_t* flags) {
+                                                   int32_t* trace, T* trace_t, uint64_t seed, int32_t next) {
     __shared__ bool last;
     const int64_t at = blockIdx.x * 256ll + threadIdx.x;
     // an instance of its own for every thread, rows over the workgroups; or one instance, rows over the threads too
@@ -422,16 +421,16 @@ __global__ __launch_bounds__(256) void k_alns_turn(int64_t m, int64_t n, int64_t
         copy(m, r, r_cur, (T*)nullptr);
     }
     __syncthreads();                                  // (nobody here reads the state any more)
-    if (threadIdx.x == 0) {                           // (a count only: no fence, which would write the caches back)
-        last = atomicAdd(&flags[FLAG_TURN], 1) == (int32_t)(gridDim.x * gridDim.y) - 1;
-    }
+    int32_t* turn = &S[R > 1 ? blockIdx.x * 256ll : 0].turn;
+    if (threadIdx.x == 0)                             // (a count only: no fence, which would write the caches back)
+        last = atomicAdd(turn, 1) == (int32_t)(R > 1 ? gridDim.y : gridDim.x) - 1;
     __syncthreads();
     if (!last) return;
-    for (int64_t p = threadIdx.x; p < R; p += 256) {
-        alns_end(S, st, p, iters, lambda, sigma1, sigma2, sigma3, q2, trace, trace_t);
-        if (next >= 0) alns_begin(S, p, seed, next);
+    if (R > 1 ? q < R : threadIdx.x == 0) {
+        alns_end(S, st, q, iters, lambda, sigma1, sigma2, sigma3, q2, trace, trace_t);
+        if (next >= 0) alns_begin(S, q, seed, next);
     }
-    if (threadIdx.x == 0) flags[FLAG_TURN] = 0;
+    if (threadIdx.x == 0) *turn = 0;
 }
 
 template <class T>
@@ -933,7 +932,7 @@ static dmmv_status start_t(Ctx* c, bool l2_guard, uint64_t seed) {
     if (l2_guard) DMMV_TRY(sumsq_t<T>(c));
     hipLaunchKernelGGL(k_alns_init<T>, dim3(blocks_for(R, 256)), dim3(256), 0, c->stream,
                        (AlnsState*)c->alns_state, (const InstState<T>*)c->state, R,
-                       l2_guard ? (const double*)c->alns_q2 : nullptr, seed, c->flags);
+                       l2_guard ? (const double*)c->alns_q2 : nullptr, seed);
     hipLaunchKernelGGL(k_alns_snapshot<T>, dim3(1024), dim3(256), 0, c->stream, c->p.m, c->p.n, R,
                        (const int32_t*)c->kidx, c->alns_kidx_cur, c->alns_kidx_best, (const T*)c->r,
                        (T*)c->alns_r_cur, (unsigned long long*)c->alns_first, c->alns_weight);
@@ -1025,16 +1024,16 @@ template <class T>
 static dmmv_status finish_iteration_t(Ctx* c, const dmmv_alns_params& prm, int32_t next, int32_t* trace, void* trace_t) {
     const int64_t R = c->p.R, m = c->p.m, n = c->p.n;
     if (prm.l2_guard) DMMV_TRY(sumsq_t<T>(c));
-    // some sixteen elements a thread, more where that takes over 512 workgroups (each adds to the one counter: 1024 instances of
-    // 2048 x 4096 take 43 us with 2048 of them, 40 with 1024, 37 with 512, 38 with 256)
-    constexpr int64_t cap = 512;
+    // some sixteen elements a thread, more where that takes over 1024 workgroups (us with 512, 1024, 2048 of them: 1024 instances of
+    // 2048 x 4096 27.6, 27.8, 28.9; 11 008 of 2048 x 256 97.7, 90.7, 91.3)
+    constexpr int64_t cap = 1024;
     int64_t strips = ceil_div(R > 1 ? R : ceil_div(m + n, 4), 256), rows = R > 1 ? ceil_div(m + n, 16) : 1;
     if (R == 1 && strips > 1024) strips = 1024;
     if (rows > ceil_div(cap, strips)) rows = ceil_div(cap, strips);
     hipLaunchKernelGGL(k_alns_turn<T>, dim3((unsigned)strips, (unsigned)rows), dim3(256), 0, c->stream, m, n, R,
                        (AlnsState*)c->alns_state, (InstState<T>*)c->state, c->kidx, c->alns_kidx_cur, c->alns_kidx_best, (T*)c->r,
                        (T*)c->alns_r_cur, prm.iters, prm.lambda, prm.sigma1, prm.sigma2, prm.sigma3,
-                       prm.l2_guard ? (const double*)c->alns_q2 : nullptr, trace, (T*)trace_t, prm.seed, next, c->flags);
+                       prm.l2_guard ? (const double*)c->alns_q2 : nullptr, trace, (T*)trace_t, prm.seed, next);
     DMMV_LAUNCH_CHECK();
     // (before another iteration, its repair gives what it leaves a reservoir of its own)
     if (c->kind == KIND_CSC && next < 0) DMMV_TRY(csc_alns_after_copy(c));

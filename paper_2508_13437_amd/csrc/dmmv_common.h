@@ -68,7 +68,7 @@ struct alignas(16) AlnsState {
     int32_t it;         // outer iteration in progress
     int32_t d_op, r_op; // operators chosen for it
     int32_t accepted;   // verdict of the iteration just finished
-    int32_t new_best;
+    int32_t turn;       // first instance of a strip of 256: workgroups that are done with the strip's end of an iteration
 };
 
 // One partial arg-min record: score and flat candidate index (c < 0: empty).

@@ -28,3 +28,9 @@ def test_batch(m, n, R, nd, count):
 def test_integer_ties_and_the_l2_guard():
     alns_check(random_dense(12200, 50, 40, 4, dtype=np.float32, integer=True), 30, ls_moves=2, destroy_count=6, seed=1, l2_guard=1)
     batched_alns_check(random_batched(12201, 40, 30, 300, 5, integer=True), 12, ls_moves=2, destroy_count=4, seed=2, l2_guard=1)
+
+
+@pytest.mark.parametrize("m,n,R", [(5, 4, 256), (5, 4, 257), (40, 33, 1300), (700, 9, 600), (3, 2, 4097)])
+def test_batch_of_several_strips(m, n, R):
+    """The state of an instance turns with its strip of 256: the last of the workgroups that copy the strip's elements does it."""
+    batched_alns_check(random_batched(12300 + R, m, n, R, 4), 7, ls_moves=1, destroy_count=max(1, n // 4), seed=R, l2_guard=R % 2)
