@@ -6,7 +6,8 @@
 // that does not fix the rows of largest |r| cannot improve).  Per iteration the workgroup
 //   1. picks S = 16 screening rows: the rows with |r| above a bound are listed while the move before is applied, the 16
 //      largest of them by rank (the row of largest |r| overall is always the first); the bound follows the 22nd
-//      largest, which a single move hardly changes;
+//      largest, which a single move hardly changes.  At the start, and where a move has left fewer than 10 or more than the list
+//      holds, they are listed from all rows, with a bound that 22 rows or a few more reach;
 //   2. bounds candidates from below by lb(j, k) = max_{i in S} |fma(delta, X_ij, r_i)| - 16 rows instead
 //      of m - and keeps per variable its best candidate by (lb, k), found by walking outwards from
 //      the current level on the side that lowers the row of largest |r| until lb rises;
@@ -26,6 +27,9 @@
 // What gave most: rows picked exactly instead of four from every wavefront's share (6.4 scores an iteration instead of 9.3); no barrier between
 // scores (there were 5.5 rounds of one score a wavefront); requests ahead that are not under a condition, so that the
 // compiler waits for the block it needs only.
+// The listing from all rows found its bound by trial before (from 3/4 of the largest |r| on, up to seven times, then all rows): where |r| has
+// a heavy tail that ended with arbitrary rows and thousands of scores for one move.  1000 instances of 500 x 1000 with 256 levels
+// 3863 us, now 2263; 100 of 9000 x 100 under the outer loop 2888 and 2462, 2000 of 300 x 100 554 and 415.
 // Tried and dropped: the first step on eight rows and the survivors queued for the other eight, 64 at a time (a line of X
 // fetched per row and variable); a good move looked for first, to bound the others; eight more rows for the
 // variables that are left; the candidates left after a wavefront's first score shared out by a queue (no gain: few are left, and
@@ -76,6 +80,7 @@ template <class T, int W>
 struct BpShared {
     BpFound<T> found[W];                         // by each wavefront
     decltype(bp_order(T())) bound;               // smallest score found so far, t at first
+    uint32_t peak[64 * W];                       // upper 32 bits of the largest |r| of every thread's rows
     int32_t list[BP_LIST];                       // rows of large |r|, the first one of largest
     int32_t listed;                              // how many there were to put behind it
 };
@@ -126,7 +131,7 @@ __device__ __forceinline__ double bp_permute(int to, double v) {
 // W: wavefronts of the workgroup.
 // DEPTH: blocks of variables whose entries are requested ahead of the one that is walked.
 template <class T, class KI, int W, int DEPTH>
-__global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4 : 6) : (DEPTH ? 3 : 4)) void k_descent_batched_pruned(
+__global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4 : 6) : 4) void k_descent_batched_pruned(
     int64_t m, int64_t n, int32_t nd, int64_t R, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Xt, const T* __restrict__ D, const T* __restrict__ scale,
     T* __restrict__ r, int32_t* __restrict__ kidx, InstState<T>* __restrict__ st, int32_t radius,
@@ -195,21 +200,65 @@ __global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4
     bool dirty = false;
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void*)Xt, 0, (int)(uint32_t)(m * n * (int64_t)sizeof(T)), 0x00020000);
     const int32_t n32 = (int32_t)n, m32 = (int32_t)m;
+    // how many of the wavefront's keys are larger
+    auto rank_of = [&](uint32_t key, bool upper) -> uint32_t {
+        uint32_t rank = 0;
+#pragma unroll
+        for (int e = 0; e < 32; ++e) rank += (uint32_t)__builtin_amdgcn_readlane((int)key, e) > key ? 1u : 0u;
+        if (upper) {
+#pragma unroll
+            for (int e = 32; e < 64; ++e) rank += (uint32_t)__builtin_amdgcn_readlane((int)key, e) > key ? 1u : 0u;
+        }
+        return rank;
+    };
     // Rows with |r| of at least `bound` are listed for the screening rows to be picked from.
     const bool all_rows = m32 < BP_LIST;
-    T bound = all_rows ? (T)0 : (T)0.75 * z.t;
-    auto list_row = [&](int32_t i, T v, T largest) {
-        const T a = dmmv_abs(v);
-        if (a >= bound || a == largest) {
-            if (a == largest) F.list[0] = i;                // (any of them)
-            const int32_t at = 1 + atomicAdd(&F.listed, 1);
-            if (at < BP_LIST) F.list[at] = i;
+    T bound = (T)0;
+    // (by a whole wavefront: bit u of `large` lists row i0 + u * BP_BLOCK, of |r| a(u), as the first one where that is `largest`)
+    auto list_rows = [&](uint32_t large, int32_t i0, T largest, auto count, auto a) {
+        constexpr int N = decltype(count)::value;
+        int32_t all = 0, at = 0;
+#pragma unroll
+        for (int u = 0; u < N; ++u) all += __popcll(bp_ballot((large >> u) & 1u));
+        if (all == 0) return;
+        if (lane == 0) at = 1 + atomicAdd(&F.listed, all);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const unsigned long long rows = bp_ballot((large >> u) & 1u);
+            if (rows == 0ull) continue;
+            if ((large >> u) & 1u) {
+                const int32_t to = at + __popcll(rows & ((1ull << lane) - 1ull));
+                if (a(u) == largest) F.list[0] = i0 + u * BP_BLOCK;
+                if (to < BP_LIST) F.list[to] = i0 + u * BP_BLOCK;
+            }
+            at += __popcll(rows);
         }
     };
+    // From all rows (a thread reads its own).  The bound is the BP_WANT-th largest of 64 maxima, each over the rows that are alike
+    // modulo 64: as many rows reach it, and the few that a larger one of their share hides.
     auto list_all = [&]() {
+        if (!all_rows) {
+            T most = (T)0;
+            for (int32_t i = tid; i < m32; i += BP_BLOCK) most = dmmv_max(most, dmmv_abs(sh_r[i]));
+            F.peak[tid] = (uint32_t)(bp_order(most) >> (8 * sizeof(T) - 32));
+        }
         if (tid == 0) { F.listed = 0; F.list[0] = -1; }
         __syncthreads();
-        for (int32_t i = tid; i < m32; i += BP_BLOCK) list_row(i, sh_r[i], z.t);
+        if (!all_rows) {
+            uint32_t key = 0;
+#pragma unroll
+            for (int u = 0; u < BP_WAVES; ++u) key = max(key, F.peak[lane + 64 * u]);
+            key = (key & ~63u) | (uint32_t)(63 - lane);     // (no two alike)
+            const unsigned long long at = bp_ballot(rank_of(key, true) == BP_WANT - 1);
+            const uint32_t of = (uint32_t)__builtin_amdgcn_readlane((int)key, __builtin_ctzll(at)) & ~63u;
+            bound = bp_number((decltype(bp_order(T())))of << (8 * sizeof(T) - 32));
+        }
+        for (int32_t i0 = w * 64; i0 < m32; i0 += BP_BLOCK) {      // whole wavefronts
+            const int32_t i = i0 + lane;
+            const T a = dmmv_abs(sh_r[i < m32 ? i : m32 - 1]);
+            list_rows(i < m32 && (a >= bound || a == z.t) ? 1u : 0u, i, z.t, std::integral_constant<int, 1>(), [&](int) { return a; });
+        }
         __syncthreads();
     };
     list_all();
@@ -225,7 +274,7 @@ __global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4
             z.best_s = z.t;
             break;
         }
-        for (int pass = 0;; ++pass) {
+        for (bool again = false;; again = true) {
             const int32_t listed = F.listed, behind = listed < BP_LIST - 1 ? listed : BP_LIST - 1;
             const int32_t top = F.list[0], row = lane <= behind ? F.list[lane] : top;
             const T v = sh_r[row];
@@ -235,13 +284,7 @@ __global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4
             uint32_t key = (__float_as_uint((float)dmmv_abs(v)) & ~63u) | (uint32_t)(63 - lane);
             if (lane > behind || (lane > 0 && row == top)) key = 0;
             if (lane == 0) key = 0xFFFFFFFFu;
-            uint32_t rank = 0;
-#pragma unroll
-            for (int e = 0; e < 32; ++e) rank += (uint32_t)__builtin_amdgcn_readlane((int)key, e) > key ? 1u : 0u;
-            if (behind >= 32) {
-#pragma unroll
-                for (int e = 32; e < 64; ++e) rank += (uint32_t)__builtin_amdgcn_readlane((int)key, e) > key ? 1u : 0u;
-            }
+            const uint32_t rank = rank_of(key, behind >= 32);
             // lane `rank` takes the row; lanes that none is for repeat the first, which changes no maximum
             const int32_t to = key != 0 ? (int32_t)rank * 4 : 63 * 4;
             const int32_t got = __builtin_amdgcn_ds_permute(to, lane < 63 || key != 0 ? row + 1 : 0);
@@ -254,22 +297,23 @@ __global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4
                 row_off[u] = (uint32_t)__builtin_amdgcn_readlane((int)off_by_rank, u);
                 tr[u] = read_lane(r_by_rank, u);
             }
+            if (all_rows) break;
+            if (!again && (listed < BP_FEWEST || listed >= BP_LIST)) {      // too few to choose from, or more than were kept
+                __syncthreads();
+                list_all();
+                continue;
+            }
             // The bound of the next iteration, whose r differs by one move: the value of rank BP_WANT (of as many of them as the
             // list holds), or further down where there are fewer.
-            if (all_rows) break;
-            const T used = bound;
             if (listed >= BP_WANT) {
                 const int32_t guess = BP_WANT * (BP_LIST - 1) / listed, at = listed < BP_LIST ? BP_WANT - 1 : guess > 2 ? guess : 2;
                 bound = dmmv_abs(read_lane(r_by_rank, at));
             } else {
                 const T from = dmmv_min(bound, z.t), span = dmmv_max(z.t - from, (T)0.02 * z.t);
                 const T by = (T)(BP_WANT - listed) / (T)(listed > 0 ? listed : 1);
-                bound = dmmv_max(listed < BP_FEWEST ? z.t - (T)2 * span : from - (T)0.5 * span * dmmv_min(by, (T)1), (T)0);
+                bound = dmmv_max(from - (T)0.5 * span * dmmv_min(by, (T)1), (T)0);
             }
-            // with too few or far too many listed, again (not where they are all alike: the bound stays)
-            if (pass == 6 || (listed >= BP_FEWEST && listed < 2 * BP_LIST) || bound == used) break;
-            __syncthreads();
-            list_all();
+            break;
         }
 
         // ---- 2. per variable the best candidate by (lb, k) ----------------------------------
@@ -463,33 +507,25 @@ __global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4
             const int32_t k = best_c & ((1 << KSH) - 1);
             const T delta = step_of(level(k), level(sh_k[j]), sc);
             const T* __restrict__ col = X + ldx * j;
-            for (int64_t i0 = tid; i0 < m; i0 += BP_BLOCK * AP_UNROLL) {
+            for (int32_t i0 = w * 64; i0 < m32; i0 += BP_BLOCK * AP_UNROLL) {      // whole wavefronts
                 T a[AP_UNROLL];
                 uint32_t large = 0;                        // which of these rows are listed
 #pragma unroll
                 for (int u = 0; u < AP_UNROLL; ++u) {
-                    const int64_t i = i0 + BP_BLOCK * u;
-                    a[u] = col[i < m ? i : m - 1];
+                    const int32_t i = i0 + lane + BP_BLOCK * u;
+                    a[u] = col[i < m32 ? i : m32 - 1];
                 }
 #pragma unroll
                 for (int u = 0; u < AP_UNROLL; ++u) {
-                    const int64_t i = i0 + BP_BLOCK * u;
-                    if (i < m) {
+                    const int32_t i = i0 + lane + BP_BLOCK * u;
+                    if (i < m32) {
                         a[u] = dmmv_fma(delta, a[u], sh_r[i]);
                         sh_r[i] = a[u];
                         large |= (dmmv_abs(a[u]) >= bound || dmmv_abs(a[u]) == best_s ? 1u : 0u) << u;
                     }
                 }
-                if (large) {                               // (the applied move's score is the new max |r|, bit for bit)
-                    int32_t at = 1 + atomicAdd(&F.listed, __popc(large));
-#pragma unroll
-                    for (int u = 0; u < AP_UNROLL; ++u) {
-                        if (!((large >> u) & 1u)) continue;
-                        if (dmmv_abs(a[u]) == best_s) F.list[0] = (int32_t)i0 + BP_BLOCK * u;
-                        if (at < BP_LIST) F.list[at] = (int32_t)i0 + BP_BLOCK * u;
-                        ++at;
-                    }
-                }
+                // (the applied move's score is the new max |r|, bit for bit)
+                list_rows(large, i0 + lane, best_s, std::integral_constant<int, AP_UNROLL>(), [&](int u) { return dmmv_abs(a[u]); });
             }
             __syncthreads();                               // everyone has read sh_k[j]
             if (tid == 0) {
