@@ -130,8 +130,9 @@ __device__ __forceinline__ double bp_permute(int to, double v) {
 // KI: type of a level index in LDS (8 bits when nd <= 256, whose values then lie in LDS too).
 // W: wavefronts of the workgroup.
 // DEPTH: blocks of variables whose entries are requested ahead of the one that is walked.
-template <class T, class KI, int W, int DEPTH>
-__global__ __launch_bounds__(64 * W, W > 4 ? W / 4 : sizeof(T) == 4 ? (DEPTH ? 4 : 6) : 4) void k_descent_batched_pruned(
+// SIMD: wavefronts per SIMD that the registers must allow.
+template <class T, class KI, int W, int DEPTH, int SIMD>
+__global__ __launch_bounds__(64 * W, SIMD) void k_descent_batched_pruned(
     int64_t m, int64_t n, int32_t nd, int64_t R, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Xt, const T* __restrict__ D, const T* __restrict__ scale,
     T* __restrict__ r, int32_t* __restrict__ kidx, InstState<T>* __restrict__ st, int32_t radius,
@@ -573,19 +574,29 @@ dmmv_status descent_t(Ctx* c, int32_t steps, int32_t iters, dmmv_move* trace, vo
         DMMV_LAUNCH_CHECK();
         return DMMV_OK;
     };
-    // Eight wavefronts an instance as long as the compute units hold all instances two at a time (an instance's iteration is a
-    // chain of latencies then), four beyond, and for instances that do not fill more.  us to the local optima, four and eight (the
-    // kernel before, always four): 20 of 2048 x 4096 1949 and 1511 (2618), 250 2254 and 1776 (2850), 500 2307 and 1861 (2913),
-    // 1000 2783 and 3220 (3593); 600 of 1024 x 2048 1276 and 1295 (1587); 20 of 2048 x 768 551 and 479 (652); 30 of 256 x 128 296 and 300
-    // (325); 60 000 of 8 x 8 525 and 1462 (533).
-    // Up to 256 variables four wavefronts screen all of them at once, and eight gain by their full scores only: on whole calls of 2048 x
-    // 158 405 and 325 (20), 499 and 367 (191), 561 and 503 (500); but from 270 to 512 rows from 5 % faster to 14 % slower, alike on
-    // the average (191 of 270 x 250 353 and 354, 300 of 512 x 140 387 and 443), so four there.
-    const bool eight = R <= 512 && n > 128 && (n > 256 || m > 512);
+    constexpr int64_t CU_LDS = 160 * 1024, CUS = 256;
+    const int64_t by_lds = CU_LDS / (int64_t)(lds + sizeof(BpShared<T, 4>)), by_number = ceil_div(R, CUS);
+    const int64_t on_cu = by_lds < by_number ? by_lds : by_number;         // instances that a compute unit holds at a time
+    // Eight wavefronts an instance where these are no more than two (an instance's iteration is a chain of latencies then), four
+    // beyond, for instances that do not fill more, and where it is LDS alone that keeps others away and the screening (n) is what takes
+    // longest.  us of whole calls to the local optima, four and eight (always four, by another choice of screening rows, in brackets):
+    // 20 of 2048 x 4096 1931 and 1413 (2445), 250 2088 and 1657 (3280), 500 2300 and 1947 (3377), 600 2384 and 2346 (3423), 1000 2838 and
+    // 3308 (3654); 20 of 2048 x 768 608 and 517 (921); 400 of 300 x 300 359 and 344 (423); 100 of 9000 x 100 984 and 690 (1741), 500 of
+    // 600 x 100 358 and 339 (411), one of 8000 x 30 in fp64 2344 and 1815 (2145); 1000 of 16 000 x 2000 6794 and 5790 (9492); but 400 of
+    // 300 x 200 309 and 303 (379), 60 000 of 8 x 8 525 and 1462 (533; the kernel alone), 1000 of 4000 x 4000 in fp64 12 599 and 12 714.
+    const bool eight = (by_number <= 2 || (by_lds <= 2 && m > n)) && (n > 256 || m > 512);
+    // Of four, one block of variables is requested ahead where no more than five share a compute unit anyway, and where there are many
+    // blocks; else the registers that it takes cost more.  us without and with (in brackets with registers for six): 4096 of 2048 x 4096
+    // 9029 and 8718 (8805), 1000 of 1024 x 2048 1466 and 1400 (1437), 600 of 2048 x 100 472 and 445 (464), 2000 of 1024 x 2048 2209 and 2170
+    // (2141), 4000 3398 and 3451 (3329); but 2000 of 300 x 1000 1191 and 1263 (1222), 10 000 of 300 x 300 1420 and 1611 (1513).  Of eight
+    // none: with none, one and two blocks ahead 20 of 2048 x 768 517, 534, 547; 500 of 2048 x 4096 1947, 1960, 2075 (20 of them 1413, 1399,
+    // 1459); in fp64 500 of 2048 x 4000 4623, 4641, 5447.
+    constexpr int MORE = sizeof(T) == 4 ? 6 : 4;
     auto with = [&](auto ki) -> dmmv_status {
         typedef decltype(ki) KI;
-        if (eight) return n > 1024 ? launch(k_descent_batched_pruned<T, KI, 8, 2>, 8) : n > 512 ? launch(k_descent_batched_pruned<T, KI, 8, 1>, 8) : launch(k_descent_batched_pruned<T, KI, 8, 0>, 8);
-        return n > 256 ? launch(k_descent_batched_pruned<T, KI, 4, 1>, 4) : launch(k_descent_batched_pruned<T, KI, 4, 0>, 4);
+        if (eight) return launch(k_descent_batched_pruned<T, KI, 8, 0, 2>, 8);
+        if (on_cu <= 5) return launch(k_descent_batched_pruned<T, KI, 4, 1, 4>, 4);
+        return n > 1024 ? launch(k_descent_batched_pruned<T, KI, 4, 1, MORE>, 4) : launch(k_descent_batched_pruned<T, KI, 4, 0, MORE>, 4);
     };
     return c->p.nd > BP_DCAP ? with(uint16_t()) : with(uint8_t());
 }

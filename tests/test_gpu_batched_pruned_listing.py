@@ -1,5 +1,6 @@
 """options.prune on a batch, bitwise against the oracle: the screening rows listed anew from all rows, where |r| has a heavy tail, is
-alike in more rows than the list holds or falls by a move; rows around the maxima of a workgroup's threads."""
+alike in more rows than the list holds or falls by a move; rows around the maxima of a workgroup's threads; and the forms of
+the kernel by what a compute unit holds - instances around twice and five times the compute units, LDS for two of them."""
 import numpy as np
 import pytest
 
@@ -27,3 +28,9 @@ def test_rows_alike(alike, dtype):
     rng = np.random.default_rng(alike)
     r = np.stack([rng.permutation(np.where(np.arange(m) < alike, 9.0, 2.0)) for _ in range(R)]) * rng.choice([-1.0, 1.0], size=(R, m))
     batched_check(_with_residual(inst, r), 12, prune=True)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("m,n,R,nd", [(70, 20, 512, 3), (70, 20, 513, 3), (10, 300, 1281, 3), (5, 1024, 1281, 2), (5, 1025, 1280, 2), (5, 1025, 1281, 2), (513, 6, 512, 3), (13500, 7, 513, 3)])
+def test_forms_of_the_kernel(m, n, R, nd, dtype):
+    batched_check(random_batched(13300 + m + n + R, m, n, R, nd, dtype=dtype), 3, prune=True)
