@@ -987,9 +987,11 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
     }
     const int32_t clear = c->kind == KIND_BATCHED && c->alns_lists ? 1 : 0;
     c->exchange_clear = false;
-    // Up to 8 rows a thread in one launch (16 where many instances share the chip).
-    const bool many = R > 512;
-    if (c->kind != KIND_CSC && c->p.m <= (many ? 256 * 16 : 1024 * 8)) {
+    // One launch for up to 4096 rows, or 8192 where the instances do not fill the chip.  256 threads as long as these hold the rows: more of
+    // them wait for each other longer, and keep other instances out.  us of whole calls with 256 and 1024 threads (three launches, in
+    // brackets): 400 instances of 64 x 64, 30 iterations 2668 and 3037 (2887), 400 of 1000 x 200, 20, 2523 and 2747 (3567), 20 of 2000 x 768,
+    // 20, 1488 and 1527 (1904), 300 of 2500 x 200 in fp64, 10, 2954 and 3114 (2971), one of 2000 x 500, 20, 834 and 871 (1086).
+    if (c->kind != KIND_CSC && c->p.m <= (R > 512 ? 256 * 16 : 1024 * 8)) {
         auto both = [&](auto kernel, int threads) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)R), dim3(threads), 0, c->stream, c->p.m, c->p.n, R, c->p.nd, count,
                                c->alns_weight, c->alns_prefix, (unsigned long long*)c->alns_first, c->alns_picked,
@@ -997,14 +999,16 @@ static dmmv_status destroy_repair_t(Ctx* c, const dmmv_alns_params& prm, int32_t
                                (const T*)c->D_dev, (const T*)c->scale_dev, (T*)c->r, c->kidx, (InstState<T>*)c->state,
                                (uint32_t*)c->persist_exchange, c->kind == KIND_DENSE ? (int32_t)(dense_persistent_exchange_bytes() / 4) : 0);
         };
-        if (many) { if (c->p.m <= 2048) both(k_alns_destroy_repair<T, 256, 8>, 256); else both(k_alns_destroy_repair<T, 256, 16>, 256); }
-        else { if (c->p.m <= 2048) both(k_alns_destroy_repair<T, 1024, 2>, 1024); else both(k_alns_destroy_repair<T, 1024, 8>, 1024); }
+        if (c->p.m <= 256 * 8) both(k_alns_destroy_repair<T, 256, 8>, 256);
+        else if (c->p.m <= 256 * 16) both(k_alns_destroy_repair<T, 256, 16>, 256);
+        else both(k_alns_destroy_repair<T, 1024, 8>, 1024);
         DMMV_LAUNCH_CHECK();
         c->exchange_clear = c->kind == KIND_DENSE;
         return DMMV_OK;
     }
-    hipLaunchKernelGGL(k_alns_destroy<1024>, dim3((unsigned)R), dim3(1024), 0, c->stream, c->p.n, count, c->alns_weight,
-                       c->alns_prefix, (unsigned long long*)c->alns_first, c->alns_picked, (const AlnsState*)S, prm.seed, raw_shift, clear);
+    const bool alone = R == 1;
+    hipLaunchKernelGGL((alone ? k_alns_destroy<1024> : k_alns_destroy<256>), dim3((unsigned)R), dim3(alone ? 1024 : 256), 0, c->stream, c->p.n,
+                       count, c->alns_weight, c->alns_prefix, (unsigned long long*)c->alns_first, c->alns_picked, (const AlnsState*)S, prm.seed, raw_shift, clear);
     if (c->kind == KIND_CSC) {
         DMMV_TRY(csc_alns_repair(c, count, prm.seed));
     } else {

@@ -34,3 +34,10 @@ def test_integer_ties_and_the_l2_guard():
 def test_batch_of_several_strips(m, n, R):
     """The state of an instance turns with its strip of 256: the last of the workgroups that copy the strip's elements does it."""
     batched_alns_check(random_batched(12300 + R, m, n, R, 4), 7, ls_moves=1, destroy_count=max(1, n // 4), seed=R, l2_guard=R % 2)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("m,n,R", [(2048, 7, 512), (2049, 7, 4), (4096, 7, 4), (4097, 7, 4), (8193, 2049, 2), (4097, 40, 513)])
+def test_threads_of_an_instance(m, n, R, dtype):
+    """Rows around those that 256 threads hold, and prefix sums around a tile of theirs where the launches are apart."""
+    batched_alns_check(random_batched(12400 + m + n, m, n, R, 3, dtype=dtype), 3, ls_moves=0, destroy_count=2, seed=m)
