@@ -12,10 +12,14 @@
 // before these are evaluated.  The integers are added with LDS atomics, so neither their order nor the split of the rows
 // over workgroups changes a weight.
 // Listed half of 1024 instances of 2048 x 4096, 347 terms a row on the average: 1780 us by k_alns_impact_batched and the
-// two launches it needs, now 456; of 20 instances of 2048 x 768, 66 and 27.  33 vector instructions per 64 terms; the scalar unit
+// two launches it needs, now 456; of 20 instances of 2048 x 768, 66 and 27.  Where most terms count (a small alpha) a row costs its n terms,
+// by the short route as well: 512 of 2048 x 4096, 3 iterations, 7.9 ms with alpha = 0.01 (12.5 by k_alns_impact_batched), 14.2 with
+// 0 (21.5; 28.8 with such rows left to the exact evaluation).  33 vector instructions per 64 terms; the scalar unit
 // (addresses and a row's constants: 53 instructions before two loads of 64 entries shared them, 820 us), the vector unit
 // and the LDS (table and sums, conflicts included) are each busy half of the time or less, the rest is the latency of the
 // loads and the uneven length of the instances' lists.
+#include <type_traits>
+
 #include "dmmv_alns_common.h"
 
 namespace dmmv {
@@ -102,19 +106,22 @@ __global__ __launch_bounds__(IL_THREADS, 8) void k_alns_impact_lists(
         const int32_t i = i0 + lane;
         const bool row_on = lane < lanes && i < i_end;
         const double sk = __builtin_fabs((double)r[(int64_t)(row_on ? i : i0) * R + q]), v = sk * scale;
-        const double rate = (t - sk) * rate_q;
+        double rate = (t - sk) * rate_q;
         const uint32_t first = (uint32_t)(row_on ? i : i0) * (uint32_t)n;      // entry of the lists
         int32_t len = 0;                                    // terms of the row that may reach 1
-        bool slow = false;                                  //   all of them left to the exact evaluation
+        bool whole = false;                                 //   the whole row, not a prefix that the limit ends
         if (row_on && v >= 0.999) {
             // (the limit lowered by 1 %, which covers the roundings on both sides: a term left out is 0)
             const float lim = (float)((t - sk) * alpha / (sc * ((log(v) + 0.01) * 1.01)));
             const double* __restrict__ row = inv + first;
             const uint32_t edge = __float_as_uint(lim) >> IL_BIN_SHIFT, top = __float_as_uint((float)(1.0 / row[0])) >> IL_BIN_SHIFT;
             int32_t hi = n;
-            if (!(rate > -1e300) || (edge <= top && top - edge >= IL_BINS - 1)) {
+            if (!(rate > -1e300)) {
                 len = lim < Limits<float>::inf() ? n : 0;
-                slow = true;
+                rate = __builtin_nan("");                   // (leaves every term to the exact evaluation)
+            } else if (edge <= top && top - edge >= IL_BINS - 1) {      // the limit lies in the bin of all that is small
+                len = n;
+                whole = true;
             } else {
                 const double most = 1.0 / (double)__uint_as_float(edge << IL_BIN_SHIFT);
                 while (len < hi) {
@@ -123,7 +130,7 @@ __global__ __launch_bounds__(IL_THREADS, 8) void k_alns_impact_lists(
                 }
             }
         }
-        const unsigned long long all_slow = __ballot(slow);
+        const unsigned long long all_whole = __ballot(whole);
         unsigned long long todo = __ballot(len > 0);
         if (todo == 0ull) continue;
         int rr = __builtin_ctzll(todo), p = 0;              // row and first place of the 128 entries at hand
@@ -154,7 +161,9 @@ __global__ __launch_bounds__(IL_THREADS, 8) void k_alns_impact_lists(
                 // the term: base 2^(y / 256) with y = rate / |x| <= 0, by a table of 2^(f / 256) and a polynomial of degree
                 // 3.  Relative error below 2^-41 (polynomial 2^-42.7; y, below 25 octaves, 2^-46) and the term below 2^24,
                 // so the integer part is that of alns_impact_term unless the fraction is within 2^-15 of an integer.
-                auto evaluate = [&](int u) {
+                // (WHOLE: entries far below the limit too, whose terms, below 2^24 2^-26, are 0.)
+                auto evaluate = [&](int u, auto whole_row) {
+                    constexpr bool WHOLE = decltype(whole_row)::value;
                     const double y = row_rate * x[u];
                     const double kf = __builtin_rint(y), z = y - kf;
                     constexpr double C = 0x1.62e42fefa39efp-1 / IL_TABLE;
@@ -163,16 +172,22 @@ __global__ __launch_bounds__(IL_THREADS, 8) void k_alns_impact_lists(
                     e = __builtin_fma(e, z, 1.0);
                     const int k = (int)kf;
                     const double g = __builtin_ldexp(e * (row_base * exp2t[k & (IL_TABLE - 1)]), k >> 8);
-                    const double whole = __builtin_floor(g);
-                    uint32_t term = (uint32_t)whole;
-                    const bool ok = __builtin_fabs((g - whole) - 0.5) < 0.5 - 0x1p-15 && !((all_slow >> rr) & 1);
+                    const double down = __builtin_floor(g);
+                    uint32_t term = (uint32_t)down;
+                    bool ok = __builtin_fabs((g - down) - 0.5) < 0.5 - 0x1p-15;
+                    if (WHOLE && y < -26.0 * IL_TABLE) { term = 0; ok = true; }
                     if (p + 64 * u + lane < have) {
                         if (!ok) term = (uint32_t)alns_impact_term(__builtin_fabs(sc * (double)(float)(1.0 / x[u])), read_lane(sk, rr), t, alpha, scale);
                         if (term) atomicAdd(&sums[j[u]], (unsigned long long)term);
                     }
                 };
-                evaluate(0);
-                if (p + 64 < have) evaluate(1);
+                if ((all_whole >> rr) & 1) {
+                    evaluate(0, std::true_type());
+                    if (p + 64 < have) evaluate(1, std::true_type());
+                } else {
+                    evaluate(0, std::false_type());
+                    if (p + 64 < have) evaluate(1, std::false_type());
+                }
             }
             rr = next_rr;
         }

@@ -26,3 +26,14 @@ def test_batched_impact_weights_over_sorted_rows(m, n, R, alpha):
 def test_batched_impact_weights_of_equal_entries(m, n, R, alpha):
     inst = random_batched(9900 + m, m, n, R, 5, integer=True)
     batched_alns_check(inst, 6, ls_moves=1, destroy_count=n // 8, seed=m, alpha=alpha)
+
+
+@pytest.mark.parametrize("alpha", [0.0, 1e-15, 1e-11, 1e-7])
+@pytest.mark.parametrize("m,n,R", [(40, 150, 5), (70, 300, 3)])
+def test_batched_impact_weights_where_the_limit_is_far_below_a_row(m, n, R, alpha):
+    """Entries over 120 octaves, zeros among them: rows taken whole, most of whose terms are 0."""
+    inst = random_batched(9950 + m, m, n, R, 4)
+    rng = np.random.default_rng(m)
+    inst.A[:] *= np.exp2(-np.round(120.0 * rng.random(inst.A.shape) ** 3)).astype(inst.A.dtype)
+    inst.A[rng.random(inst.A.shape) < 0.1] = 0.0
+    batched_alns_check(inst, 8, ls_moves=1, destroy_count=n // 10, seed=m, alpha=alpha)
