@@ -214,10 +214,12 @@ dmmv_status alns_impact_lists_build(Ctx* c) {
 dmmv_status alns_impact_lists(Ctx* c, double alpha) {
     const int64_t m = c->p.m, R = c->p.R, about = ceil_div(R, 2) * m;      // rows of all instances: about half are listed
     // Rows a wavefront takes at a time: a search needs as many dependent loads for one row as for 64, but a small batch is
-    // spread over more wavefronts (20 instances of 2048 x 768: 8 rows 27 us, 4 28, 16 60; 1024 of 2048 x 4096: 32 rows
-    // 456, 64 484, 16 473).  Eight times as many a workgroup (sixteen: 33 us with 4 rows, 479 with 32).
-    int32_t lanes = 8;
-    while (lanes < 32 && about > 4096 * (int64_t)lanes) lanes *= 2;
+    // spread over more wavefronts (the kernel, us: 20 instances of 2048 x 768: 8 rows 27, 4 28, 16 60; 1024 of 2048 x 4096: 32 rows
+    // 456, 64 484, 16 473; whole calls of 20 iterations with 1, 2, 4 and 8 rows: 3 of 64 x 2000 1293, 1378, 1514, 1777; 20 of 300 x 1000 1249,
+    // 1265, 1300, 1444; 4 of 2048 x 768 1274, 1217, 1197, 1249; of 10: 20 of 1000 x 1000 845, 758, 744, 767).  Eight times as many a workgroup
+    // (sixteen: 33 us with 4 rows, 479 with 32).
+    int32_t lanes = 1;
+    while (lanes < 32 && about >= 4096 * (int64_t)lanes) lanes *= 2;
     const int32_t chunk_rows = IL_WAVES * lanes;
     hipLaunchKernelGGL(k_alns_impact_lists, dim3((unsigned)R, (unsigned)ceil_div(m, chunk_rows)), dim3(IL_THREADS),
                        (size_t)c->p.n * sizeof(uint64_t), c->stream, m, (int32_t)c->p.n, R, c->alns_row_inv, c->alns_row_col,

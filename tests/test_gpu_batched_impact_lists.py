@@ -1,6 +1,6 @@
 """Impact weights of a batch over the sorted rows of X: the outer loop, bitwise against the oracle, at the edges of the
-kernel - variables around a wavefront's 64 list entries, around the smallest and the largest number that takes it and around
-a power of two (the sort); rows around the 16, 32 and 64 of a wavefront and around a workgroup's; prefixes that are empty,
+kernel - variables around a wavefront's 64 list entries, around the smallest and the largest number that takes it; rows around a
+workgroup's 8 and their multiples, for every number of rows (1, 2, 4, .. 32) that a wavefront takes at a time; prefixes that are empty,
 whole, and ended by equal entries; zero columns."""
 import numpy as np
 import pytest
@@ -37,3 +37,10 @@ def test_batched_impact_weights_where_the_limit_is_far_below_a_row(m, n, R, alph
     inst.A[:] *= np.exp2(-np.round(120.0 * rng.random(inst.A.shape) ** 3)).astype(inst.A.dtype)
     inst.A[rng.random(inst.A.shape) < 0.1] = 0.0
     batched_alns_check(inst, 8, ls_moves=1, destroy_count=n // 10, seed=m, alpha=alpha)
+
+
+# rows of the instances that are listed, about half of them, around 4096, 8192, .. 65536 in all
+@pytest.mark.parametrize("m,n,R", [(63, 129, 130), (64, 129, 128), (129, 130, 65), (127, 130, 128), (128, 130, 128), (257, 131, 64), (255, 130, 128),
+                                   (257, 130, 128), (255, 130, 256), (257, 130, 255), (255, 130, 512), (257, 131, 514)])
+def test_batched_impact_weights_by_rows_a_wavefront_takes(m, n, R):
+    batched_alns_check(random_batched(9970 + m + R, m, n, R, 4), 4, ls_moves=1, destroy_count=9, seed=m + R, alpha=0.3)
