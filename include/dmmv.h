@@ -134,7 +134,9 @@ typedef struct {
                                 dmmv_eval_moves and dmmv_argmin_move always score all             */
     int32_t alns;            /* batched problems: 1 = reserve the workspace dmmv_alns needs (current
                                 and best solution, sampling weights and draws per instance, about
-                                R*(36 n + m w) bytes).  Single-instance handles always have it    */
+                                R*(36 n + m w) bytes; fp32 with 129 to 8192 variables 10 m n more,
+                                2.5 times the matrix, for the rows' entries by magnitude, which
+                                dmmv_create makes).  Single-instance handles always have it       */
     int32_t value_search;    /* dense matrices: 1 = the descent (dmmv_solve without keep_going, the
                                 local search of dmmv_alns) finds the best value of each variable
                                 by bisection over D instead of scoring all nd values: the score of
