@@ -82,32 +82,6 @@ __device__ __forceinline__ double alns_impact_scale(double t) {
     return ldexp(1.0, 24 - e);
 }
 
-// The fixed-point term by a shorter route: y16 = 16 log2(e) alpha (t - sk) / (sc |x|) with the part of row and instance
-// given (rate) and a reciprocal with one Newton step instead of a division, 2^(-y16 / 16) from 2^(-f/16) and a polynomial
-// of degree 6.  Its relative error stays below 2^-40 (reciprocal 2^-46, rate 2^-50, times y < 20; polynomial 2^-50),
-// the term is below 2^24, so the integer part is that of alns_impact_term unless the
-// fraction is within 2^-15 of an integer; those (and everything out of the ordinary) are left to it: false.
-__device__ __forceinline__ bool alns_impact_term_fast(double x, double rate, double base, const double* exp2m, uint32_t& term) {
-    double rc = __builtin_amdgcn_rcp(x);
-    rc = __builtin_fma(rc, __builtin_fma(-x, rc, 1.0), rc);
-    const double y16 = rate * rc;
-    const bool usual = y16 < 20.0 * 16.0 * 0x1.71547652b82fep+0;      // false for NaN
-    const double kf = __builtin_rint(usual ? y16 : 0.0);
-    const double z = kf - y16;                                        // |z| <= 1/2: powers of (ln 2 / 16) z
-    constexpr double C = 0x1.62e42fefa39efp-5;
-    double p = __builtin_fma(z, C * C * C * C * C * C / 720.0, C * C * C * C * C / 120.0);
-    p = __builtin_fma(p, z, C * C * C * C / 24.0);
-    p = __builtin_fma(p, z, C * C * C / 6.0);
-    p = __builtin_fma(p, z, C * C / 2.0);
-    p = __builtin_fma(p, z, C);
-    p = __builtin_fma(p, z, 1.0);
-    const int k = (int)kf;
-    const double g = __builtin_ldexp(base * (p * exp2m[k & 15]), -(k >> 4));
-    const double whole = __builtin_floor(g), frac = g - whole;
-    term = (uint32_t)whole;
-    return usual && frac > 0x1p-15 && frac < 1.0 - 0x1p-15;
-}
-
 __device__ __forceinline__ uint64_t block_sum_u64(uint64_t v, uint64_t* sh /* blockDim/64 */) {
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) v += (uint64_t)__shfl_xor((long long)v, off, 64);
