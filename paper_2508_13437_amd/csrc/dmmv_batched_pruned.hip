@@ -395,10 +395,11 @@ __global__ __launch_bounds__(64 * W, SIMD) void k_descent_batched_pruned(
 
         // ---- 3. candidates in ascending (lb, c) until none can beat the best score ---------
         // Every wavefront walks the candidates of ITS variables (those its threads screened) in
-        // ascending (lb, c) and scores one per round, as long as that candidate can still beat the
-        // best (score, c) the workgroup knew when the round began; the rounds end when no
-        // wavefront had such a candidate.  Then every candidate not scored has
-        // (lb, c) >= (best score, its c), hence score >= lb >= best score, and loses the tie on c.
+        // ascending (lb, c) and scores them one after the other, without waiting for the others.  It stops at a candidate that
+        // loses to its own best (score, c), or whose lb is above the smallest score found by any wavefront: only above,
+        // as that score comes without its c, and a candidate of the same score may have a smaller one.  For the same reason a
+        // score equal to the shared one is kept, and the arg-min over F.found decides by c.  Then every candidate not scored
+        // has score >= lb, which is above the best score, or the same with a larger c.
         // A lane keeps the best of the variables it looks after (16 at a time of the wavefront's blocks), and looks
         // them through again only when one of them has been scored.
         const int32_t groups = 4 * ((n32 - first + BP_BLOCK - 1) / BP_BLOCK);      // of 16, of this wavefront
