@@ -182,7 +182,9 @@ __device__ __forceinline__ bool rec3_less(T s1, T q1, int64_t c1, T s2, T q2, in
 // Before, every value took a 64-bit division and all loads (or, few instances, a thread took a variable's values one after the
 // other).  us before and now, fp32: 1376 tables of 4096 x 8 135 and 46 (181 and 105 where most moves that lower the largest |r|
 // raise the l2 norm and the loads cannot be left out: their lines are then what bounds it), 5000 of 600 x 4 85 and 47, 300 of
-// 4096 x 16 78 and 31, 100 of 4096 x 8 28 and 17, one of 4096 x 16 34 and 15, one of 16 x 16 3.9 and 3.8.
+// 4096 x 16 78 and 31, 100 of 4096 x 8 28 and 17, one of 4096 x 16 34 and 15, one of 16 x 16 3.9 and 3.8.  Slower, by what the second of
+// two dependent rounds takes, is one instance of some ten thousand values in fp64: 500 x 31 14.1 and 15.5 (with the next round's
+// values requested ahead 16.1, and 5000 x 16 a fifth slower).
 template <class T>
 __global__ __launch_bounds__(1024) void k_l2_select(int64_t n, int64_t R, int32_t nd, int32_t rule,
                                                     const T* __restrict__ scores, const T* __restrict__ D,
