@@ -21,9 +21,9 @@
 // move the full evaluation + selection would apply - found with a few full scores instead of
 // n (nd - 1); a candidate's score is given up as soon as a row puts it above the best one.
 // Many instances (4096 of 2048 x 4096, 16 levels, to their local optima: 8.3 ms, 9.9 before) are bound by the rows of X, 256 KiB an
-// iteration, three quarters of which the L2 does not hold (8.9 TB/s into the compute units, 6.8 past the L2; the vector unit 63 % busy, 12 200 instructions an
-// iteration); a fifth workgroup on a compute unit changes nothing.  Few instances are bound by latencies: on 2048 x 4096
-// with eight wavefronts 2000 cycles for step 1, 15 000 to 25 000 for step 2, 3000 a score, 3000 for step 4.
+// iteration, three quarters of which the L2 does not hold (8.9 TB/s into the compute units, 6.8 past the L2; the vector unit 64 % busy, 12 100 instructions an
+// iteration; cycles for the four steps 2300, 35 300, 26 200, 5800); a fifth workgroup on a compute unit changes nothing.  Few instances
+// are bound by latencies: 20 of 2048 x 4096 with eight wavefronts 1600, 13 700, 16 300 and 3300.
 // What gave most: rows picked exactly instead of four from every wavefront's share (6.4 scores an iteration instead of 9.3); no barrier between
 // scores (there were 5.5 rounds of one score a wavefront); requests ahead that are not under a condition, so that the
 // compiler waits for the block it needs only.
