@@ -220,6 +220,8 @@ __device__ __forceinline__ void alns_sample(int64_t n, int32_t count, const uint
         const int64_t j = draw(c);
         const unsigned long long stamp = ((unsigned long long)(it + 1) << 32) | (0xFFFFFFFFull - (c & 0xFFFFFFFFull));
         atomicMax(&first[j], stamp);
+        // (other wavefronts read it behind the barrier, which by itself waits for no atomic that returns nothing)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         const bool is_first = __hip_atomic_load(&first[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == stamp;
         const unsigned long long bal = __ballot(is_first);
